@@ -81,7 +81,7 @@ def kernel_source_hash() -> str:
     return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
 
 
-PAIR_KERNEL = {0: "k_pair_mfma", 1: "k_pair_valu", 2: "k_pair_mfma16", 3: "k_pair_mfma16", 4: "k_pair_mfma32"}
+PAIR_KERNEL = {0: "k_pair_mfma", 1: "k_pair_valu", 2: "k_pair_mfma16", 3: "k_pair_mfma16", 4: "k_pair_bf3"}
 PAIR_ARITHMETIC = {
     0: "fp32: pair products on FP32 MFMA 16x16x4, FP32 exponentials",
     1: "fp32: pair products as FP32 vector FMAs, FP32 exponentials",
@@ -89,7 +89,8 @@ PAIR_ARITHMETIC = {
        "factors, FP32 accumulation",
     3: "fp16 hi/lo split (~22-bit): both pair products on FP16 MFMA with every factor split into high and low "
        "halves, FP32 accumulation and exponentials",
-    4: "fp32: distances on FP32 MFMA 32x32x2, kernel-weighted sums on FP32 MFMA 4x4x1, FP32 exponentials",
+    4: "fp32: every factor as three BF16 parts (24 bits, FP32 exponent range), both pair products on BF16 MFMA "
+       "16x16x32 with FP32 accumulation, FP32 exponentials",
 }
 # v_exp_f32 issues 8 lanes per cycle per SIMD (measured: 8 cycles per wave64 instruction)
 EXP_PER_S = 256 * 4 * 8 * 2.4e9
@@ -98,10 +99,10 @@ PEAK_FP16_TFLOPS = 2500.0
 
 def issued_mfma_flop_per_pair(impl: int, D: int) -> float:
     """FLOP the matrix cores issue per pair-eval (padding included)."""
-    if impl == 4:
-        kp = (D + 2) & ~1
-        ng = (D + 4) // 4
-        return 2.0 * kp + 2.0 * 4 * ng
+    if impl == 4:  # per 16 x 32 pairs: distances of two blocks, two cuts of both, the three parts' tiles
+        slices = (6 * D + 6 + 31) // 32
+        tiles = sum((k * (D + 1) + 15) // 16 for k in (1, 2, 3))
+        return (2 * slices + 4 + tiles) * 2.0 * 16 * 16 * 32 / 512
     if impl == 0:
         kk = (D + 2 + 3) // 4
         return 2.0 * 4 * kk + 2.0 * 16
@@ -118,8 +119,8 @@ def secondary_ceilings(impl: int, D: int, pairs_per_s: float):
     out = {"exp_unit": {"pair_evals_per_s": EXP_PER_S, "frac": pairs_per_s / EXP_PER_S}}
     f = issued_mfma_flop_per_pair(impl, D)
     if f:
-        peak = PEAK_FP16_TFLOPS if impl in (2, 3) else PEAK_FP32_TFLOPS
-        out["issued_mfma"] = {"dtype": "fp16" if impl in (2, 3) else "fp32", "flop_per_pair": f,
+        peak = PEAK_FP16_TFLOPS if impl in (2, 3, 4) else PEAK_FP32_TFLOPS
+        out["issued_mfma"] = {"dtype": {2: "fp16", 3: "fp16", 4: "bf16"}.get(impl, "fp32"), "flop_per_pair": f,
                               "tflops": pairs_per_s * f / 1e12, "frac": pairs_per_s * f / (peak * 1e12)}
     return out
 

@@ -51,10 +51,10 @@ typedef enum vds_status {
 enum { VDS_HOOKEAN = 0, VDS_FENE = 1 };
 enum { VDS_EXPLICIT = 0, VDS_IMPLICIT = 1 };
 /* Pair-kernel implementations (all compute the same sums):
- *   VDS_PAIR_MFMA32     FP32 throughout (the default): distances on FP32 32x32x2 matrix
- *                       instructions over augmented vectors with both squared norms in the
- *                       contraction, kernel-weighted sums on FP32 4x4x1 matrix instructions
- *                       (outputs in groups of four), FP32 exponentials;
+ *   VDS_PAIR_MFMA32     FP32 (the default): every factor of both products as the sum of three
+ *                       BF16 numbers (24 bits, FP32's exponent range) on BF16 16x16x32 matrix
+ *                       instructions, products of parts below 2^-24 of the whole left out,
+ *                       FP32 accumulation, FP32 exponentials;
  *   VDS_PAIR_MFMA       FP32 matrix cores for both products on 16x16x4 tiles;
  *   VDS_PAIR_VALU       FP32 vector FMAs;
  *   VDS_PAIR_MFMA_F16X2 FP32 matrix cores for the distances, the kernel-weighted sums on FP16
@@ -110,17 +110,18 @@ typedef struct vds_diag {
 } vds_diag;
 
 /* Pair-kernel launch shape (chosen by vds_autotune or set by hand; a new
- * context starts with VDS_PAIR_MFMA32, 2 row blocks per wave, 4 workgroups per
- * compute unit).  The FP16-split forms are opt-in: they keep about 22 bits, not
+ * context starts with VDS_PAIR_MFMA32, 2 row blocks per wave, col_splits 4: two
+ * workgroups per compute unit).  The FP16-split forms are opt-in: they keep about 22 bits, not
  * FP32's 24. */
 typedef struct vds_tuning {
   int32_t impl;          /* one of the VDS_PAIR_* implementations */
   int32_t rows_per_wave; /* MFMA forms: row blocks per wavefront (16 rows each: 1, 2 or 4;
-                          * VDS_PAIR_MFMA32: 32 rows each, 1 or 2) */
+                          * VDS_PAIR_MFMA32: 1 or 2; 2 counts as 1 from D = 12 on) */
   int32_t col_splits;    /* 1..32.  Column ranges summed separately, then reduced; for
-                          * VDS_PAIR_MFMA32 the workgroups per compute unit of its balanced
-                          * grid, whose workgroups take equal runs of (row group, column
-                          * chunk) work and leave one partial sum per row group they cover */
+                          * VDS_PAIR_MFMA32 twice the workgroups (of eight waves) per compute
+                          * unit of its balanced grid, whose workgroups take equal runs of
+                          * (row group, column chunk) work and leave one partial sum per row
+                          * group they cover */
   int32_t reserved;
 } vds_tuning;
 

@@ -45,7 +45,7 @@ int64_t vds_batch_state_offset(vds_batch b, int32_t e);
 
 /* Pair-pass implementation (VDS_PAIR_MFMA32, VDS_PAIR_MFMA, VDS_PAIR_MFMA_F16X2
  * or VDS_PAIR_MFMA_F16X2_ALL; see vds.h) and launch shape: row blocks per
- * wavefront (1, 2, 4; 1 or 2 for VDS_PAIR_MFMA32, whose blocks hold 32 rows)
+ * wavefront (1, 2, 4; 1 or 2 for VDS_PAIR_MFMA32)
  * and persistent grid size (workgroups, >= 1);
  * use_graph = 0 launches each step eagerly.  Changing the implementation
  * synchronises (the ensemble table is re-uploaded). */

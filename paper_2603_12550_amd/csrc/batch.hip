@@ -65,6 +65,9 @@ vds_status bhip(vds_batch b, hipError_t e, const char *what) {
 
 int64_t pad(int64_t P) { return round_up(P, kRowAlign); }
 
+// Floats per particle of the V operands.
+int v_width(int D) { return std::max(16, 8 * bf3_tiles(D)); }
+
 BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   const int D = 3 * nb, KK = (D + 2 + 3) / 4;
   int64_t Ptot = 0;
@@ -86,8 +89,9 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   L.items = take(sizeof(int2) * items_max);
   L.QB = take(sizeof(float) * Ptot * KK * 4);
   L.KA = take(sizeof(float) * Ptot * KK * 4);
-  L.VA = take(sizeof(float) * Ptot * 16);
-  L.VB = take(sizeof(float) * Ptot * 16);
+  L.VA = take(sizeof(float) * Ptot * v_width(D));
+  L.VB = take(sizeof(float) * Ptot * v_width(D));
+  // (K3 of VDS_PAIR_MFMA32 takes QH and KH together)
   L.QH = take(sizeof(uint16_t) * Ptot * 32 * f16_slices(D));
   L.KH = take(sizeof(uint16_t) * Ptot * 32 * f16_slices(D));
   L.RN = take(sizeof(float) * Ptot);
@@ -104,16 +108,15 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
 }
 
 // (ensemble, row tile) items, costliest ensembles first.  A row tile is the
-// 4 rb 16-row blocks of the 16x16 forms, or the 4 rb 32-row blocks of
-// VDS_PAIR_MFMA32.
+// rows a workgroup of the pair implementation takes.
 std::vector<int2> make_items(const vds_batch b, int rb) {
-  const int64_t rows_per_block = b->impl == VDS_PAIR_MFMA32 ? 32 : 16;
+  const int64_t rows = pair_tile_rows(b->impl, rb, b->D);
   std::vector<int> order(b->nens);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return b->P[x] > b->P[y]; });
   std::vector<int2> items;
   for (int e : order) {
-    const int64_t tiles = (pad(b->P[e]) / rows_per_block + 4 * rb - 1) / (4 * rb);
+    const int64_t tiles = (pad(b->P[e]) + rows - 1) / rows;
     for (int64_t t = 0; t < tiles; ++t) items.push_back(make_int2(e, (int)t));
   }
   return items;
@@ -137,6 +140,7 @@ BatchView view(vds_batch b) {
   v.nblk256 = (int)(b->Ptot_pad / 256);
   v.D = b->D;
   v.KK = b->KK;
+  v.vw = v_width(b->D);
   v.f16 = b->f16;
   return v;
 }
@@ -146,7 +150,7 @@ void set_formats(vds_batch b) {
   for (EnsDesc &d : b->ens) {
     d.p.vhalf = (b->impl == VDS_PAIR_MFMA_F16X2 || b->impl == VDS_PAIR_MFMA_F16X2_ALL) ? 1 : 0;
     d.p.qhalf = b->impl == VDS_PAIR_MFMA_F16X2_ALL ? 1 : 0;
-    d.p.f32x = b->impl == VDS_PAIR_MFMA32 ? 1 : 0;  // its per-chunk operand layout
+    d.p.bf3 = b->impl == VDS_PAIR_MFMA32 ? 1 : 0;  // its BF16-thirds operands
   }
 }
 

@@ -77,11 +77,40 @@ __device__ inline void store_v(const EvalParams &p, float *V, int64_t J, int n, 
     const int64_t i = vh_index(J, n);
     h[i] = hi;
     h[i + p.Ppad * 16] = (_Float16)(v - (float)hi);
-  } else if (p.f32x) {
-    V[vc_index(J, n)] = v;
   } else {
     V[v_index(J, n)] = v;
   }
+}
+
+// The three BF16 parts of an FP64 number, each rounded to nearest (the third
+// leaves 2^-27 of it); bit patterns.
+struct Bf3 {
+  uint16_t h, m, l;
+};
+__device__ inline uint16_t bf16_bits(double v) {
+  return __builtin_bit_cast(uint16_t, (__bf16)(float)v);
+}
+__device__ inline double bf16_value(uint16_t u) { return (double)__uint_as_float((uint32_t)u << 16); }
+__device__ inline Bf3 split_bf3(double v) {
+  Bf3 s;
+  s.h = bf16_bits(v);
+  v -= bf16_value(s.h);
+  s.m = bf16_bits(v);
+  v -= bf16_value(s.m);
+  s.l = bf16_bits(v);
+  return s;
+}
+// Lane n of particle J writes element n of V_J = (wx, w) (0 past the
+// particles) in the format of the pair implementation; w_x is this lane's
+// weighted coordinate or weight.
+__device__ inline void store_v3(const EvalParams &p, float *V, int64_t J, int n, double v) {
+  if (n > p.D) return;
+  uint16_t *V3 = reinterpret_cast<uint16_t *>(V);
+  const int NT = bf3_tiles(p.D);
+  const Bf3 s = split_bf3(v);
+  V3[v3_index(J, n, NT)] = s.h;
+  V3[v3_index(J, p.D + 1 + n, NT)] = s.m;
+  V3[v3_index(J, 2 * (p.D + 1) + n, NT)] = s.l;
 }
 
 // Partial sums of w_I x_I (FP64) per block, for the weighted centring.
@@ -200,6 +229,32 @@ __device__ bool picard_converged(const PicardCheck &chk, const float *__restrict
   return conv != 0;
 }
 
+// Column operand K3 of particle I from its centred coordinate x (lane n;
+// zeros past the particles): see vds_internal.h.
+__device__ inline void store_k3(const EvalParams &p, uint32_t *__restrict__ K3, int64_t I, int n, float x) {
+  const int NQ = bf3_slices(p.D);
+  const bool real = I < p.P;
+  const Bf3 y = split_bf3(n < p.D ? p.cs * (double)x : 0.0);
+  const double ys = bf16_value(y.h) + bf16_value(y.m) + bf16_value(y.l);
+  double nrm = ys * ys;
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 16);
+  // lane n holds dwords 3n .. 3n + 2: component n, the norm (n = D) or zeros
+  uint32_t d[3] = {0u, 0u, 0u};
+  if (real && n < p.D) {
+    d[0] = d[1] = (uint32_t)y.h | ((uint32_t)y.m << 16);
+    d[2] = (uint32_t)y.h | ((uint32_t)y.l << 16);
+  } else if (real && n == p.D) {
+    const Bf3 r = split_bf3(-0.5 * nrm);
+    d[0] = (uint32_t)r.h | ((uint32_t)r.m << 16);
+    d[1] = (uint32_t)r.l | 0x3f800000u;
+    d[2] = 0x3f803f80u;
+  }
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (3 * n + j < 16 * NQ) K3[bf3_index(I, 3 * n + j, NQ)] = d[j];
+}
+
 // Centre, pack Q/K operands and the pass-A V operand (weights w; over their
 // maximum, which goes to *wscale, when V is written in FP16 halves).
 // Lane n of particle I's raw coordinate (0 past the particles or D).
@@ -218,7 +273,7 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
   if (n < p.D) xc[I * p.D + n] = x;
   // the FP32 distance operands are read only by the FP32-distance pair forms
   // (KP can exceed the sixteen lanes: slots k = n, n + 16)
-  for (int k = n; k < (p.f32x ? p.KP : 0); k += 16) {
+  for (int k = n; k < (p.bf3 ? p.KP : 0); k += 16) {
     float ka = 0.f;
     if (real) {
       if (k < p.D) ka = 2.f * p.kappa * x;  // k < D <= 15 only for k == n
@@ -227,7 +282,8 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
     }
     KA[kc_index(I, k, p.KP)] = ka;
   }
-  for (int k = n; k < ((p.qhalf || p.f32x) ? 0 : 4 * p.KK); k += 16) {
+  if (p.bf3) store_k3(p, reinterpret_cast<uint32_t *>(f16.QH), I, n, x);
+  for (int k = n; k < ((p.qhalf || p.bf3) ? 0 : 4 * p.KK); k += 16) {
     float qa = 0.f, ka = 0.f;
     if (real) {
       if (k < p.D) {
@@ -261,6 +317,10 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
       kh[di] = (uint32_t)__builtin_bit_cast(uint16_t, c0) | ((uint32_t)__builtin_bit_cast(uint16_t, c1) << 16);
     }
     if (n == 0) f16.RN[I] = nt;
+  }
+  if (p.bf3) {
+    store_v3(p, VA, I, n, n < p.D ? (double)wi * (double)x : (double)wi);
+    return;
   }
   const float wn = p.vhalf ? (real ? wi / mean_sh[15] : 0.f) : wi;
   float v = 0.f;
@@ -324,7 +384,8 @@ __device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__
   const int n = group_lane();
   if (I >= p.Ppad) return;
   if (I >= p.P) {  // padding columns carry zero weight in pass B too
-    store_v(p, VB, I, n, 0.f);
+    if (p.bf3) store_v3(p, VB, I, n, 0.0);
+    else store_v(p, VB, I, n, 0.f);
     return;
   }
   const double o = n <= p.D ? sum_splits(p, partial, splits, I, n) : 0.0;
@@ -338,6 +399,11 @@ __device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__
   } else if (n == p.D) {
     S[I] = (float)Si;
     v = wb;
+  }
+  if (p.bf3) {
+    const double wd = wI / Si;
+    store_v3(p, VB, I, n, n < p.D ? wd * (double)xc[I * p.D + n] : wd);
+    return;
   }
   store_v(p, VB, I, n, v);  // wb <= 1, so the FP16 form needs no normalisation
 }
@@ -665,10 +731,6 @@ __global__ __launch_bounds__(kRedBlock) void k_density_rows(EvalParams p, const 
     x[a] = I < ny ? y[I * p.D + a] - mean_sh[a] : 0.f;
     nrm = fmaf(x[a], x[a], nrm);
   }
-  if (p.f32x) {  // plain centred coordinates, read by VDS_PAIR_MFMA32
-    for (int a = 0; a < p.D; ++a) QB[I * p.D + a] = x[a];
-    return;
-  }
   for (int k = 0; k < 4 * p.KK; ++k) {
     float qa = 0.f;
     if (I < ny) {
@@ -690,36 +752,18 @@ __global__ __launch_bounds__(kRedBlock) void k_density_rows(EvalParams p, const 
   }
 }
 
-// QB/KA in the 16-row FP32 layout (qk_index) from the centred coordinates,
-// one thread per particle (padding rows: zeros).
-__global__ __launch_bounds__(kRedBlock) void k_pack_qk(EvalParams p, const float *__restrict__ xc,
-                                                       float *__restrict__ QB, float *__restrict__ KA) {
-  const int64_t I = (int64_t)blockIdx.x * kRedBlock + threadIdx.x;
-  if (I >= p.Ppad) return;
-  const bool real = I < p.P;
-  float x[kMaxD];
-  float nrm = 0.f;
-  for (int a = 0; a < p.D; ++a) {
-    x[a] = real ? xc[I * p.D + a] : 0.f;
-    nrm = fmaf(x[a], x[a], nrm);
-  }
-  for (int k = 0; k < 4 * p.KK; ++k) {
-    float qa = 0.f, ka = 0.f;
-    if (real) {
-      if (k < p.D) {
-        qa = x[k];
-        ka = 2.f * p.kappa * x[k];
-      } else if (k == p.D) {
-        qa = -p.kappa * nrm;
-        ka = 1.f;
-      } else if (k == p.D + 1) {
-        qa = 1.f;
-        ka = -p.kappa * nrm;
-      }
-    }
-    QB[qk_index(I, k, p.KK)] = qa;
-    KA[qk_index(I, k, p.KK)] = ka;
-  }
+// The same for VDS_PAIR_MFMA32: the rows in K3's layout, sixteen lanes per row.
+__global__ __launch_bounds__(kRedBlock) void k_density_rows_bf3(EvalParams p, const float *__restrict__ y, int64_t ny,
+                                                                const double *__restrict__ meanp, int nmeanp,
+                                                                uint32_t *__restrict__ R3, int64_t nrows_pad) {
+  __shared__ float mean_sh[16];
+  load_mean(p, meanp, nmeanp, mean_sh);
+  const int64_t I = group_particle(blockIdx.x);
+  const int n = group_lane();
+  if (I >= nrows_pad) return;
+  EvalParams pr = p;
+  pr.P = ny;  // rows past ny are zeros
+  store_k3(pr, R3, I, n, I < ny && n < p.D ? y[I * p.D + n] - mean_sh[n] : 0.f);
 }
 
 __global__ __launch_bounds__(kRedBlock) void k_density_out(const float *__restrict__ partial, SplitMap splits,
@@ -738,8 +782,11 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_mean(BatchView b, const flo
   mean_partials_body(d.p, blockIdx.x - d.blk256, q + d.q_off, nullptr, meanp + (int64_t)d.blk256 * 16);
 }
 
-// Ensemble d's slice of the concatenated FP16 distance operands.
+// Ensemble d's slice of the concatenated FP16 distance operands, or of K3 in
+// their place.
 __device__ inline F16Operands batch_f16(const BatchView &b, const EnsDesc &d) {
+  if (d.p.bf3)
+    return F16Operands{reinterpret_cast<uint32_t *>(b.f16.QH) + d.pad_off * 16 * bf3_slices(d.p.D), nullptr, nullptr};
   if (!d.p.qhalf) return F16Operands{nullptr, nullptr, nullptr};
   const int64_t halves = d.pad_off * 32 * d.p.KQ;
   return F16Operands{reinterpret_cast<_Float16 *>(b.f16.QH) + halves, reinterpret_cast<_Float16 *>(b.f16.KH) + halves,
@@ -753,7 +800,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_prep(BatchView b, const flo
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   prep_body(d.p, blockIdx.x - d.blk16, q + d.q_off, nullptr, meanp + (int64_t)d.blk256 * 16,
-            (int)(d.p.Ppad / kRedBlock), xc + o * b.D, wv + o, QB + o * b.KK * 4, KA + o * b.KK * 4, VA + o * 16,
+            (int)(d.p.Ppad / kRedBlock), xc + o * b.D, wv + o, QB + o * b.KK * 4, KA + o * b.KK * 4, VA + o * b.vw,
             nullptr, batch_f16(b, d));
 }
 
@@ -764,7 +811,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_finalize_a(BatchView b, con
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   finalize_a_body(d.p, blockIdx.x - d.blk16, partial + o * 16, SplitMap{}, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
-                  VB + o * 16);
+                  VB + o * b.vw);
 }
 
 __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const float *__restrict__ partial,
@@ -842,10 +889,12 @@ void launch_density_rows(const EvalParams &p, const float *y, int64_t ny, const 
   const F16Operands ops = f16 != nullptr ? *f16 : F16Operands{nullptr, nullptr, nullptr};
   // rows are padded to a multiple of 256 within the Ppad-row operand buffer
   const int64_t nrows_pad = round_up(ny, kRowAlign);
+  if (p.bf3) {
+    k_density_rows_bf3<<<nblocks(nrows_pad * 16), kRedBlock, 0, s>>>(p, y, ny, meanp, nmeanp,
+                                                                     reinterpret_cast<uint32_t *>(QB), nrows_pad);
+    return;
+  }
   k_density_rows<<<nblocks(nrows_pad), kRedBlock, 0, s>>>(p, y, ny, meanp, nmeanp, QB, ops, nrows_pad);
-}
-void launch_pack_qk(const EvalParams &p, const float *xc, float *QB, float *KA, hipStream_t s) {
-  k_pack_qk<<<nblocks(p.Ppad), kRedBlock, 0, s>>>(p, xc, QB, KA);
 }
 void launch_density_out(const EvalParams &p, const float *partial, const SplitMap &splits, int64_t ny, float norm, float *f,
                         hipStream_t s) {

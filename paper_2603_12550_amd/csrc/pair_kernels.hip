@@ -175,293 +175,323 @@ __global__ __launch_bounds__(256) void k_pair_mfma(const float *__restrict__ QB,
                     partial + (int64_t)blockIdx.y * part_stride_rows * 16, rb0);
 }
 
-// ---- FP32, 32x32 distance tiles and 4x4 sum blocks --------------------------
+// ---- FP32 by three BF16 parts ------------------------------------------------
 //
-// On gfx950 the FP32 matrix instructions and the exponentials do not overlap
-// (the VALU work of one wave and the MFMAs of another share the SIMD's issue),
-// so a pass costs its MFMA cycles plus its exponential cycles and the MFMA
-// work per pair-eval is what to cut.  This form issues, per 1024 pairs (a
-// 32-row by 32-column tile):
-//  * distances: ceil((D+2)/2) v_mfma_f32_32x32x2f32 over the augmented
-//    vectors K_J = (2 kappa x_J, -kappa |x_J|^2, 1) and Q_I = (x_I, 1,
-//    -kappa |x_I|^2) (D = 9: 6 instead of 12 16x16x4 steps; the row norm in a
-//    K slot costs one 32x32x2 step, what setting every accumulator to it would
-//    cost in moves, and no registers);
-//  * kernel-weighted sums: 16 * ceil((D+1)/4) v_mfma_f32_4x4x1f32, whose 4x4
-//    blocks need only ceil((D+1)/4) groups of four outputs (D = 9: 12 output
-//    slots instead of the 16 of a 16x16 tile).
-// Lane l of the distance product holds t[J][I] for I = l % 32 and the sixteen
-// columns J = 8 (v / 4) + 4 (l / 32) + v % 4 of its registers v.  Taken as the
-// A operand of a 4x4x1 product, register v gives block b = l / 4 the rows
-// I = 4 (b % 8) + i and the single column J(b, v), which is the layout the
-// sums need: block b accumulates O[I][4 g + j] over the columns of lane half
-// b / 8, and the two halves are added at every FP64 flush (a permlane32 swap
-// that leaves lane half h with rows i = h and i = 2 + h).
-// The four waves of a workgroup take the same column chunks, which are staged
-// once per workgroup in LDS, double buffered with one barrier per chunk.
-// Accumulation: FP32 within groups of kFlush32 chunks (each lane half sums 128
-// columns), then FP64, and the difference sums are formed in FP64 as for the
-// other forms.
+// The default form (VDS_PAIR_MFMA32).  On gfx950 an FP32 matrix instruction
+// runs at a sixteenth of the BF16 rate and lets no vector instruction issue
+// beside it, a BF16 one does.  An FP32 number is the exact sum of three BF16
+// numbers (8 bits each), so both products are taken on
+// v_mfma_f32_16x16x32_bf16, whose products are exact in FP32, from operands
+// that hold all 24 bits:
+//  * distances: with y = sqrt(2 kappa) x = yh + ym + yl, six products per
+//    component (hh, mm, hm, mh, hl, lh; the dropped ml, lm, ll are below
+//    2^-26 |y_I y_J|) and both norms -|y|^2 / 2 in three parts each give
+//    t_IJ = y_I.y_J - |y_I|^2/2 - |y_J|^2/2 in 6 D + 6 slots of the
+//    contraction (D = 9: two instructions per 16 x 16 pairs).  y and the norms
+//    are split from FP64, and the norm is that of the parts, so t is the
+//    distance of two slightly displaced points to within the accumulation's
+//    rounding;
+//  * kernel-weighted sums: e = 2^t is cut into three parts in registers: the
+//    upper halves of the values are a BF16 operand as they stand, and what
+//    they leave comes from a product with minus the identity (exact), which
+//    takes it off the vector units.  The parts meet those of V, which sit side
+//    by side as columns of B (D = 9: 30 of 32).
+// The distance product leaves lane l with the row I = l % 16 and the columns
+// J = 4 (l / 16) + v of two 16-column blocks: eight values, which are the
+// A operand of the sums' instruction (row l % 16, k = 8 (l / 16) + i) when V is
+// stored with its columns in the order J = 16 (i / 4) + 4 (l / 16) + i % 4.
+// Eight waves of a workgroup take the same 32-column chunks, staged in LDS
+// straight from memory (no registers), kStage3 chunks per barrier, double
+// buffered.  Accumulation: FP32 within groups of kFlush3 chunks, then the
+// three parts of a sum are added and go to FP64, and the difference sums are
+// formed in FP64 as for the other forms.
+//
+// Bound: the matrix pipe and vector issue together, and the board's power (the
+// clock falls from 2.39 to about 2.1 GHz).  Per 1024 pairs at D = 9: 26 matrix
+// instructions (416 cycles), 16 exponentials and 24 packs (224), about 690
+// cycles in all.  Measured, P = 20000, D = 9: 128 us per pass against 170 with
+// FP32 instructions (32x32x2 distances, 4x4x1 sums); D = 15, P = 50000: 1.02
+// against 1.57 ms; 32 batched ensembles (4.3e9 pairs) 1.35 against 1.87 ms.
+// With dot products (v_dot2_f32_bf16) forming what a cut leaves, the pass took
+// 157 us: they hold the matrix pipe; with and/subtract pairs, 153.
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kFlush32 = 8;  // 32-column chunks per FP32 accumulation group (128 columns per lane half)
-constexpr int kStage32 = 2;  // 32-column chunks staged in LDS per barrier (divides kFlush32)
+constexpr int kWaves3 = 8;   // waves per workgroup
+constexpr int kStage3 = 2;   // 32-column chunks staged in LDS per barrier
+constexpr int kFlush3 = 8;   // chunks per FP32 accumulation group (a multiple of kStage3)
 
-// v_permlane32_swap: exchanges lanes 32..63 of `a` with lanes 0..31 of `b`.
-// Inline asm because __builtin_amdgcn_permlane32_swap is mistranslated by this
-// compiler when its operands come from MFMA results (both results become the
-// first operand).  The compiler does not account for the wait an MFMA result
-// needs before a VALU instruction may read it when the reader is inline asm,
-// so the asm waits 8 cycles itself (a 4x4x1 result needs fewer).
-__device__ inline void permlane32_swap(float &a, float &b) {
-  asm volatile("s_nop 7\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
+// Row blocks of 16 per wave: rows_per_wave of the tuning, 1 or 2.  From D = 12
+// on, two would not leave four waves a SIMD's registers (D = 15, P = 30000: 368
+// against 538 us per pass), so one is taken.
+constexpr int kMaxRB3 = 2;
+constexpr int bf3_rb(int D, int rows_per_wave) { return D >= 12 ? 1 : rows_per_wave; }
 
 template <int D>
-struct Mfma32Shape {
-  static constexpr int KP = mfma32_kslots(D);  // K slots: D coordinates and the two norm terms, even
-  static constexpr int NK = KP / 2;             // 32x32x2 steps of the distance product
-  static constexpr int NG = (D + 4) / 4;        // four-wide output groups covering the D + 1 sums
-  static constexpr int KF4 = KP * 8;            // float4s of a chunk's K operand (KP x 32 floats)
-  static constexpr int VS = 5;                  // LDS float4 stride of one column's V (16 floats + 4 padding)
-  static constexpr int LF4 = KF4 + 32 * VS;     // LDS float4s of one chunk buffer
-  static constexpr int GF4 = KF4 + 128;         // float4s of one chunk in global memory
+struct Bf3Shape {
+  static constexpr int NQ = bf3_slices(D);   // instructions of a 16x16 distance tile
+  static constexpr int NT = bf3_tiles(D);    // 16-column tiles of the three parts of the D + 1 sums
+  static constexpr int PC = 2 * NQ + NT;     // 1 KiB pieces (64 lanes x 16 bytes) of one 32-column chunk
 };
 
-// Largest row-norm term kappa |x_I|^2 that a row block may fold out of the
-// exponent (see mfma32_segment): e' <= 2^100, and a group of 128 products
-// e' V stays far below the FP32 range.
-constexpr float kFoldMax = 100.f;
-
-// LDS of one workgroup of the FP32 32x32 form: staged chunks (double buffered)
-// and the FP64 running sums of its four waves (one slot per lane and value;
-// only its own lane touches a slot, so plain read-add-write keeps the
-// summation order; held in LDS, they leave the registers to the arithmetic).
-template <int D, int RB>
-struct Mfma32Lds {
-  float4 sb[2][kStage32 * Mfma32Shape<D>::LF4];
-  double stot[4][RB][Mfma32Shape<D>::NG][2][64];
+// LDS of one workgroup: staged chunks (double buffered) and the FP64 running
+// sums of its waves (one slot per lane and value, touched by its own lane only;
+// held here they leave the registers to the arithmetic, so that four waves
+// share a SIMD: 128 instead of 147 us per pass at D = 9, P = 20000).
+template <int D>
+struct Bf3Lds {
+  uint4 buf[2][kStage3 * Bf3Shape<D>::PC * 64];
+  double tot[kWaves3][4 * kMaxRB3][64];
 };
 
-// Waves per SIMD the FP32 32x32 kernels are compiled for: four (128 VGPRs)
-// where the workgroup's LDS lets four workgroups share a compute unit.
-template <int D, int RB>
-constexpr int mfma32_waves() {
-  return sizeof(Mfma32Lds<D, RB>) <= 40960 ? 4 : 3;
+__device__ inline bf16x8 as_bf8(uint4 u) {
+  bf16x8 r;
+  __builtin_memcpy(&r, &u, sizeof(r));
+  return r;
+}
+__device__ inline bf16x2 as_bf2(uint32_t u) {
+  bf16x2 r;
+  __builtin_memcpy(&r, &u, sizeof(r));
+  return r;
 }
 
-// One segment of the FP32 32x32 form: the workgroup's four waves take row
-// group rg (wave w: 32-row blocks (4 rg + w) RB ..), the columns of chunks
-// [c0, c1), and write partial sums for their rows to out[row][W] (W >= D + 1).
-// Every thread of the workgroup calls it with the same arguments (it holds
-// barriers).  With run_len > 0 the segment is part of a run of run_len chunk
-// units of which done0 came before it, and every stage sets the waves' issue
-// priority by the share of the run still to do (see k_pair_mfma32).
-template <int D, int RB, int W>
-__device__ __forceinline__ void mfma32_segment(const float *__restrict__ xr, int nrb32, const float4 *__restrict__ KC,
-                               const float4 *__restrict__ VC, int rg, int c0, int c1, int exclude_self, float kappa,
-                               float *__restrict__ out, Mfma32Lds<D, RB> &lds, int64_t done0 = 0,
-                               int64_t run_len = 0) {
-  using S = Mfma32Shape<D>;
-  // odd D: the last distance step holds only the row-norm slot and padding
-  constexpr bool kFold = (D % 2) == 1;
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int h = lane >> 5;   // lane half
-  const int li = lane & 31;  // row of the 32x32 tile (distance product) / column slot of the K operand
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  auto &sb = lds.sb;
-  double(*tot)[S::NG][2][64] = lds.stot[wave];
-  constexpr int NST = (S::GF4 + 255) / 256;
-  auto stage_dst = [&](int u) { return u < S::KF4 ? u : S::KF4 + ((u - S::KF4) >> 2) * S::VS + ((u - S::KF4) & 3); };
-  auto chunk_src = [&](int c, int u) -> float4 {
-    return u < S::KF4 ? KC[(int64_t)c * S::KF4 + u] : VC[(int64_t)c * 128 + (u - S::KF4)];
-  };
-  const int rb0 = (rg * 4 + wave) * RB;  // first 32-row block of this wave
+// The upper halves of eight values, a BF16 operand (truncation: what is left of
+// a value after two such cuts is again a BF16 number).
+__device__ __forceinline__ bf16x8 upper_halves(const floatx4 &a, const floatx4 &b) {
+  uint32_t u[4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    u[j] = __builtin_amdgcn_perm(__float_as_uint(a[2 * j + 1]), __float_as_uint(a[2 * j]), 0x07060302u);
+    u[2 + j] = __builtin_amdgcn_perm(__float_as_uint(b[2 * j + 1]), __float_as_uint(b[2 * j]), 0x07060302u);
+  }
+  return as_bf8(uint4{u[0], u[1], u[2], u[3]});
+}
 
-  // row operands: slot 2 kk + h of row I is x_I[k] (k < D), 1 (k == D), the
-  // row norm term -kappa |x_I|^2 (k == D + 1), 0 beyond.  With kFold, a wave
-  // whose row-norm terms all lie within kFoldMax leaves out the last step (the
-  // row-norm slot): its exponents are t + kappa |x_I|^2, and the factor
-  // 2^(-kappa |x_I|^2) of each row is applied to its sums in FP64 at the end
-  float qv[RB][S::NK];
-  bool in_range = true;
+// Lane i of each row of 16 gets lane (i + R) % 16 of its row.
+template <int R>
+__device__ __forceinline__ float row_rotate(float v) {
+  if constexpr (R % 16 == 0) return v;
+  else
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + (16 - R % 16), 0xf, 0xf, true));
+}
+
+// Row operand of the 16-row block rb from its column operand (layout at
+// bf3_index): the slots of a component swap within a dword, the norm's dwords
+// change places (see there).
+template <int D>
+__device__ __forceinline__ void bf3_row_operand(const uint4 *__restrict__ K3, int64_t rb, int lane,
+                                                bf16x8 (&q)[Bf3Shape<D>::NQ]) {
+  constexpr int NQ = Bf3Shape<D>::NQ;
+  constexpr int dA = 3 * D, dB = dA + 1, dC = dA + 2;
+  const int g = lane >> 4;
+  uint32_t k[NQ][4];
+#pragma unroll
+  for (int m = 0; m < NQ; ++m) {
+    const uint4 u = K3[(rb * NQ + m) * 64 + lane];
+    k[m][0] = u.x, k[m][1] = u.y, k[m][2] = u.z, k[m][3] = u.w;
+  }
+  const uint32_t nA = __shfl(k[dA / 16][dA % 4], (lane & 15) + 16 * (dA % 16 / 4));
+#pragma unroll
+  for (int m = 0; m < NQ; ++m) {
+    uint32_t o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int dd = 16 * m + 4 * g + j;
+      const uint32_t v = k[m][j], sw = (v >> 16) | (v << 16);
+      o[j] = (dd % 3 != 0 && dd < dA) || dd == dB ? sw : v;
+      if (dd == dA) o[j] = 0x3f803f80u;
+      if (dd == dC) o[j] = nA;
+    }
+    q[m] = as_bf8(uint4{o[0], o[1], o[2], o[3]});
+  }
+}
+
+// One segment: wave w of the workgroup takes the 16-row blocks
+// (kWaves3 rg + w) RB .. + RB - 1 against the columns of chunks [c0, c1) and
+// writes partial sums for its rows to out[row][W] (W >= D + 1).  R3 holds the
+// rows in the column-operand layout (K3 itself when the rows are the
+// particles).  Every thread of the workgroup calls it with the same arguments
+// (it holds barriers).  With run_len > 0 the segment is part of a run of
+// run_len chunk units of which done0 came before it, and every stage sets the
+// waves' issue priority by the share of the run still to do (see k_pair_bf3).
+template <int D, int RB, int W>
+__device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const uint4 *__restrict__ K3,
+                                            const uint4 *__restrict__ V3, const float *__restrict__ xr, int rg, int c0,
+                                            int c1, int exclude_self, float *__restrict__ out, Bf3Lds<D> &lds,
+                                            int64_t done0 = 0, int64_t run_len = 0) {
+  using S = Bf3Shape<D>;
+  constexpr int NQ = S::NQ, NT = S::NT, PC = S::PC;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb0 = (rg * kWaves3 + wave) * RB;
+  // position of the self pair inside a diagonal 16x16 block, per element i
+  const int diag_i = (lane & 15) - 4 * (lane >> 4);
+  // minus the identity: row m of block b picks the slot that holds column
+  // J = m of that block, k = 8 (m / 4) + 4 b + m % 4
+  bf16x8 neg[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) neg[b][i] = (diag_i >= 0 && diag_i < 4 && i == 4 * b + diag_i) ? (__bf16)-1.f : (__bf16)0.f;
+
+  // wave w brings in the pieces w, w + 8, ... of the stage that starts at
+  // chunk c (chunk by chunk: distance operands, then V)
+  auto stage = [&](int c, int buf) {
+#pragma unroll
+    for (int i = 0; i < (kStage3 * PC + kWaves3 - 1) / kWaves3; ++i) {
+      const int pc = wave + kWaves3 * i;
+      const int cc = pc / PC, w = pc % PC;
+      if (pc < kStage3 * PC && c + cc < c1) {  // scalar
+        const uint4 *src = w < 2 * NQ ? K3 + ((int64_t)(c + cc) * 2 * NQ + w) * 64
+                                      : V3 + ((int64_t)(c + cc) * NT + (w - 2 * NQ)) * 64;
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)(src + lane),
+            (__attribute__((address_space(3))) void *)(&lds.buf[buf][pc * 64]), 16, 0, 0);
+      }
+    }
+  };
+  stage(c0, 0);
+
+  bf16x8 q[RB][NQ];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) bf3_row_operand<D>(R3, rb0 + r, lane, q[r]);
+  double (*tl)[64] = lds.tot[wave];
+  floatx4 acc[RB][NT];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    const int rb = rb0 + r < nrb32 ? rb0 + r : 0;  // waves past the rows compute on row block 0, unwritten
-    const float *x = xr + ((int64_t)rb * 32 + li) * D;
-    float nrm = 0.f;
 #pragma unroll
-    for (int a = 0; a < D; ++a) nrm = __builtin_fmaf(x[a], x[a], nrm);
-    const float rn = -kappa * nrm;
+    for (int i = 0; i < 4; ++i) tl[4 * r + i][lane] = 0.0;
 #pragma unroll
-    for (int kk = 0; kk < S::NK; ++kk) {
-      const int k = 2 * kk + h;
-      qv[r][kk] = k < D ? x[k < D ? k : 0] : (k == D ? 1.f : (k == D + 1 ? rn : 0.f));
-    }
-    in_range = in_range && rn >= -kFoldMax;
+    for (int T = 0; T < NT; ++T) acc[r][T] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  const int fold = kFold ? __builtin_amdgcn_readfirstlane(__all(in_range ? 1 : 0) ? 1 : 0) : 0;
-
-  // thread t stages float4s t, t + 256, ... of a chunk: the K operand first,
-  // then V into rows of VS float4s; a stage is kStage32 consecutive chunks,
-  // one barrier each
+  // the three parts of every sum (columns p (D + 1) + n of the tiles) added up
+  // in lane n of each row of 16, into FP64
+  auto flush = [&] {
 #pragma unroll
-  for (int cc = 0; cc < kStage32; ++cc) {
-    if (c0 + cc < c1) {
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
-      for (int i = 0; i < NST; ++i) {
-        const int v = t + 256 * i;
-        if (v < S::GF4) sb[0][cc * S::LF4 + stage_dst(v)] = chunk_src(c0 + cc, v);
+      for (int i = 0; i < 4; ++i) {
+        float v = 0.f;
+        auto part = [&](auto pc) {
+          constexpr int s = decltype(pc)::value * (D + 1);
+          float u = row_rotate<s % 16>(acc[r][s / 16][i]);
+          if constexpr (s % 16 + D + 1 > 16) {
+            const float u2 = row_rotate<s % 16>(acc[r][s / 16 + 1][i]);
+            u = (lane & 15) < 16 - s % 16 ? u : u2;
+          }
+          v += u;
+        };
+        part(std::integral_constant<int, 2>{});
+        part(std::integral_constant<int, 1>{});
+        part(std::integral_constant<int, 0>{});
+        tl[4 * r + i][lane] += (double)v;
       }
-    }
-  }
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
+    for (int r = 0; r < RB; ++r)
 #pragma unroll
-    for (int g = 0; g < S::NG; ++g) tot[r][g][0][lane] = tot[r][g][1][lane] = 0.0;
-  __syncthreads();
-
-  floatx4 acc[RB][S::NG];
-  // one chunk of 32 columns from its LDS buffer; NKS distance steps
-  auto chunk = [&](int c, const float4 *cb, auto nks) {
-    constexpr int NKS = decltype(nks)::value;
-    // per-lane bases; every read below is at a constant offset from them
-    const float *sK = reinterpret_cast<const float *>(cb) + h * 32 + li;
-    const float4 *sV = cb + S::KF4 + 4 * h * S::VS + (lane & 3);
-    float ka[S::NK];
+      for (int T = 0; T < NT; ++T) acc[r][T] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  // one chunk of 32 columns; kDiag: it holds the wave's self pairs
+  auto chunk = [&](int c, const uint4 *cb, auto diag) {
+    constexpr bool kDiag = decltype(diag)::value;
+    bf16x8 ka[2][NQ], va[NT];
 #pragma unroll
-    for (int kk = 0; kk < S::NK; ++kk) ka[kk] = sK[kk * 64];
-    floatx16 e[RB];
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
+      for (int m = 0; m < NQ; ++m) ka[b][m] = as_bf8(cb[(b * NQ + m) * 64 + lane]);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) e[r][v] = 0.f;
+    for (int T = 0; T < NT; ++T) va[T] = as_bf8(cb[(2 * NQ + T) * 64 + lane]);
+    floatx4 e[RB][2];
 #pragma unroll
-      for (int kk = 0; kk < NKS; ++kk)
-        e[r] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[kk], qv[r][kk], e[r], 0, 0, 0);
-      // no clamp: the expanded squared distance exceeds zero only by its rounding
-#pragma unroll
-      for (int v = 0; v < 16; ++v) e[r][v] = __builtin_amdgcn_exp2f(e[r][v]);
-      if (exclude_self && c == rb0 + r) {  // scalar branch: the diagonal tile
-        // an empty volatile asm keeps this a branch: if-converted into selects
-        // it would cost sixteen VALU instructions on every tile
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int v = 0; v < 16; ++v) e[r][v] = (8 * (v >> 2) + 4 * h + (v & 3)) == li ? 0.f : e[r][v];
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float4 vv = sV[(8 * (v >> 2) + (v & 3)) * S::VS];
-      const float vg[4] = {vv.x, vv.y, vv.z, vv.w};
+    for (int m = 0; m < NQ; ++m)
 #pragma unroll
       for (int r = 0; r < RB; ++r)
 #pragma unroll
-        for (int g = 0; g < S::NG; ++g)
-          acc[r][g] = __builtin_amdgcn_mfma_f32_4x4x1f32(e[r][v], vg[g], acc[r][g], 0, 0, 0);
-    }
-  };
-
-  // the chunk loop, in two copies (all steps, or the folded wave's NK - 1);
-  // both pass the same barriers
-  auto chunks = [&](auto nks) {
-  for (int c = c0; c < c1;) {
-    // groups start kFlush32 (a multiple of kStage32) chunks apart, so a stage
-    // never crosses a group boundary
-    const int gend = min(c1, c + kFlush32);
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-      for (int g = 0; g < S::NG; ++g) acc[r][g] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (; c < gend; c += kStage32) {
-      if (run_len > 0) {  // scalar: priority 3 while more than half the run is left, then 2, 1, 0 below 20 %, 5 %
-        const int64_t rem = run_len - (done0 + (c - c0));
-        if (20 * rem > 10 * run_len) __builtin_amdgcn_s_setprio(3);
-        else if (20 * rem > 4 * run_len) __builtin_amdgcn_s_setprio(2);
-        else if (20 * rem > run_len) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-      }
-      const int buf = ((c - c0) / kStage32) & 1;
-      const int cn = c + kStage32;  // first chunk of the next stage
-      float4 pre[kStage32][NST];    // the next stage, stored after this one's arithmetic
-#pragma unroll
-      for (int cc = 0; cc < kStage32; ++cc)
-#pragma unroll
-        for (int i = 0; i < NST; ++i) {
-          const int v = t + 256 * i;
-          pre[cc][i] = (cn + cc < c1 && v < S::GF4) ? chunk_src(cn + cc, v) : float4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 2; ++b) {
+          if (m == 0) e[r][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+          e[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[b][m], q[r][m], e[r][b], 0, 0, 0);
         }
 #pragma unroll
-      for (int cc = 0; cc < kStage32; ++cc)
-        if (c + cc < gend) chunk(c + cc, sb[buf] + cc * S::LF4, nks);
-      if (cn < c1) {
-#pragma unroll
-        for (int cc = 0; cc < kStage32; ++cc)
-#pragma unroll
-          for (int i = 0; i < NST; ++i) {
-            const int v = t + 256 * i;
-            if (cn + cc < c1 && v < S::GF4) sb[buf ^ 1][cc * S::LF4 + stage_dst(v)] = pre[cc][i];
-          }
-      }
-      // every stage ends at a barrier, the segment's last one too: the next
-      // segment may overwrite either buffer
-      __syncthreads();
-    }
-    // the two lane halves hold the same outputs over different columns: after a
-    // swap of rows (0, 1) and one of rows (2, 3), each sum of the pair leaves
-    // half h with the full row h and the full row 2 + h
-#pragma unroll
     for (int r = 0; r < RB; ++r)
 #pragma unroll
-      for (int g = 0; g < S::NG; ++g) {
-        float a0 = acc[r][g][0], a1 = acc[r][g][1], a2 = acc[r][g][2], a3 = acc[r][g][3];
-        permlane32_swap(a0, a1);
-        permlane32_swap(a2, a3);
-        tot[r][g][0][lane] += (double)(a0 + a1);
-        tot[r][g][1][lane] += (double)(a2 + a3);
+      for (int b = 0; b < 2; ++b) {
+        // no clamp: t exceeds zero only by its rounding
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[r][b][i] = __builtin_amdgcn_exp2f(e[r][b][i]);
+        if constexpr (kDiag)
+          if (2 * c + b == rb0 + r) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[r][b][i] = diag_i == i ? 0.f : e[r][b][i];
+          }
       }
-  }
-  };
-  if (fold)  // scalar branch
-    chunks(std::integral_constant<int, S::NK - 1>{});
-  else
-    chunks(std::integral_constant<int, S::NK>{});
-
-  // lane l holds rows 4 ((l % 32) / 4) + h + 2 s (s = 0, 1) and outputs n = 4 g + l % 4;
-  // the weighted kernel sum O[.][D] sits in the lane of the same quad with l % 4 = D % 4
-  const int src = (lane & ~3) | (D & 3);
+    // e = e_0 + e_1 + e_2 in BF16; part p meets the columns of the parts
+    // q <= 2 - p of V (the others are below 2^-24 of the product), rounded up
+    // to whole tiles.  What a cut leaves is formed on the matrix cores.
 #pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    if (rb0 + r >= nrb32) break;
+    for (int p = 0; p < 3; ++p) {
+      const int nt = ((3 - p) * (D + 1) + 15) / 16;
 #pragma unroll
-    for (int sidx = 0; sidx < 2; ++sidx) {
-      const int64_t row = (int64_t)(rb0 + r) * 32 + 4 * (li >> 2) + h + 2 * sidx;
-      double f = 1.0;  // the factor a folded wave's sums still carry
-      if (fold) {
-        float nrm = 0.f;
+      for (int r = 0; r < RB; ++r) {
+        const bf16x8 ep = upper_halves(e[r][0], e[r][1]);
+        if (p < 2) {
 #pragma unroll
-        for (int a = 0; a < D; ++a) nrm = __builtin_fmaf(xr[row * D + a], xr[row * D + a], nrm);
-        f = exp2((double)(-kappa * nrm));
-      }
-      const double sv = f * tot[r][D / 4][sidx][src];
+          for (int b = 0; b < 2; ++b) e[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(neg[b], ep, e[r][b], 0, 0, 0);
+        }
 #pragma unroll
-      for (int g = 0; g < S::NG; ++g) {
-        const int n = 4 * g + (lane & 3);
-        if (n < D) out[row * W + n] = (float)((double)xr[row * D + n] * sv - f * tot[r][g][sidx][lane]);
-        else if (n == D) out[row * W + n] = (float)sv;
+        for (int T = 0; T < nt; ++T) acc[r][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep, va[T], acc[r][T], 0, 0, 0);
       }
     }
+  };
+
+  for (int c = c0; c < c1; c += kStage3) {
+    if (run_len > 0) {  // scalar: priority 3 while more than half the run is left, then 2, 1, 0 below 20 %, 5 %
+      const int64_t rem = run_len - (done0 + (c - c0));
+      if (20 * rem > 10 * run_len) __builtin_amdgcn_s_setprio(3);
+      else if (20 * rem > 4 * run_len) __builtin_amdgcn_s_setprio(2);
+      else if (20 * rem > run_len) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
+    }
+    const int buf = ((c - c0) / kStage3) & 1;
+    // this stage's pieces are in LDS once every wave has waited for its own
+    // and met the barrier, which also ends the reads of the buffer that the
+    // next stage's pieces go to
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (c + kStage3 < c1) stage(c + kStage3, buf ^ 1);
+    const uint4 *cb = lds.buf[buf];
+    for (int cc = 0; cc < kStage3 && c + cc < c1; ++cc) {
+      if (exclude_self && c + cc == rb0 >> 1)  // scalar branch
+        chunk(c + cc, cb + cc * PC * 64, std::true_type{});
+      else
+        chunk(c + cc, cb + cc * PC * 64, std::false_type{});
+    }
+    if (((c - c0) / kStage3 + 1) % (kFlush3 / kStage3) == 0) flush();
   }
+  flush();
+  __syncthreads();  // the next segment may overwrite either buffer
+
+  // lane holds O[row 4 (lane / 16) + i][n = lane % 16]; the weighted kernel sum
+  // O[.][D] sits in lane (lane & 48) + D
+  const int n = lane & 15;
+  const int src = (lane & 48) + D;
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double s = tl[4 * r + i][src];
+      const int64_t row = (int64_t)(rb0 + r) * 16 + 4 * (lane >> 4) + i;
+      if (n < D) out[row * W + n] = (float)((double)xr[row * D + n] * s - tl[4 * r + i][lane]);
+      else if (n == D) out[row * W + n] = (float)s;
+    }
 }
 
 template <int D, int RB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mfma32_waves<D, RB>()))) void k_pair_mfma32(
-    const float *__restrict__ xr, int nrb32, const float4 *__restrict__ KC, const float4 *__restrict__ VC,
-    SplitMap map, int exclude_self, float kappa, float *__restrict__ partial, int64_t part_stride_rows,
-    const int *__restrict__ done) {
-  __shared__ Mfma32Lds<D, RB> lds;
+__global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_pair_bf3(
+    const uint4 *__restrict__ R3, const uint4 *__restrict__ K3, const uint4 *__restrict__ V3,
+    const float *__restrict__ xr, SplitMap map, int exclude_self, float *__restrict__ partial,
+    int64_t part_stride_rows, const int *__restrict__ done) {
+  __shared__ Bf3Lds<D> lds;
   if (done != nullptr && *done) return;  // the whole grid returns: no barrier is left waiting
   // workgroups go to the 8 XCDs round robin by linear id, and each XCD has its
   // own L2: with a multiple of 8 runs, XCD x takes the consecutive runs
@@ -470,14 +500,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mfma32_wave
   const int L = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   const int64_t nch = map.nch;
   const int64_t u_beg = map.run_start(L), u_end = map.run_start(L + 1);
-  // Four workgroups share a compute unit, and its SIMDs issue for the oldest
-  // ready wave first: left alone, the first workgroup placed runs ahead and
-  // the four finish one after another (at about 60, 75, 90 and 100 % of the
-  // pass), the last with one wave per SIMD to hide latency.  Each workgroup
-  // therefore lowers its waves' priority as its run progresses
-  // (mfma32_segment), so that the laggards are issued first and the four
-  // finish together.
-  // one segment per row group this run covers: chunks [c0, c1) of row group rg
+  // The workgroups of a compute unit share its SIMDs, which issue for the
+  // oldest ready wave first: left alone, the first one placed runs ahead and
+  // the last finishes with few waves to hide latency.  Each workgroup
+  // therefore lowers its waves' priority as its run progresses, so that the
+  // laggards are issued first and all finish together.
+  // One segment per row group this run covers: chunks [c0, c1) of row group rg.
   for (int64_t u = u_beg; u < u_end;) {
     const int64_t rg = u / nch;
     const int c0 = (int)(u - rg * nch);
@@ -485,34 +513,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mfma32_wave
     const int slot = (int)(L - map.run_of(rg * nch));
     u = rg * nch + c1;
     // slots in the compact layout: D + 1 floats per row
-    mfma32_segment<D, RB, D + 1>(xr, nrb32, KC, VC, (int)rg, c0, c1, exclude_self, kappa,
-                                 partial + (int64_t)slot * part_stride_rows * (D + 1), lds,
-                                 rg * nch + c0 - u_beg, u_end - u_beg);
+    bf3_segment<D, RB, D + 1>(R3, K3, V3, xr, (int)rg, c0, c1, exclude_self,
+                              partial + (int64_t)slot * part_stride_rows * (D + 1), lds, rg * nch + c0 - u_beg,
+                              u_end - u_beg);
   }
 }
 
 // Batched form: a persistent grid walks the (ensemble, row group) items; each
 // item takes all columns of its ensemble (one slot of partial sums).
 template <int D, int RB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mfma32_waves<D, RB>()))) void k_batch_pair32(
+__global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_pair_bf3(
     const int2 *__restrict__ items, int nitems, const EnsDesc *__restrict__ ens, const float *__restrict__ xc,
-    const float *__restrict__ KC, const float *__restrict__ VC, int KK, float *__restrict__ partial) {
-  __shared__ Mfma32Lds<D, RB> lds;
+    const uint4 *__restrict__ K3, const uint4 *__restrict__ V3, float *__restrict__ partial) {
+  using S = Bf3Shape<D>;
+  __shared__ Bf3Lds<D> lds;
   // this workgroup's chunks over all its items, for the issue priority by
-  // progress (see k_pair_mfma32)
+  // progress (see k_pair_bf3)
   int64_t total = 0;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) total += (ens[items[it].x].p.P + 31) / 32;
   int64_t done = 0;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const int64_t off = ens[item.x].pad_off;
-    const int64_t P = ens[item.x].p.P;
-    const int nrb32 = (int)(ens[item.x].p.Ppad / 32);
-    const float kappa = ens[item.x].p.kappa;
-    const int nc = (int)((P + 31) / 32);
-    mfma32_segment<D, RB, 16>(xc + off * D, nrb32, reinterpret_cast<const float4 *>(KC + off * KK * 4),
-                          reinterpret_cast<const float4 *>(VC + off * 16), item.y, 0, nc, 1, kappa,
-                          partial + off * 16, lds, done, total);
+    const int nc = (int)((ens[item.x].p.P + 31) / 32);
+    const uint4 *k3 = K3 + off / 16 * S::NQ * 64;
+    bf3_segment<D, RB, 16>(k3, k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y, 0, nc, 1, partial + off * 16, lds,
+                           done, total);
     done += nc;
   }
 }
@@ -884,12 +910,13 @@ static void launch_batch_kk(int rb, int grid, const int2 *items, int nitems, con
 }
 
 template <int D>
-static void launch_batch32_d(int rb, int grid, const int2 *items, int nitems, const EnsDesc *ens, const float *xc,
-                             const float *KC, const float *VC, int KK, float *partial, hipStream_t s) {
-  if (rb == 1)
-    k_batch_pair32<D, 1><<<grid, 256, 0, s>>>(items, nitems, ens, xc, KC, VC, KK, partial);
+static void launch_batch_bf3_d(int rb, int grid, const int2 *items, int nitems, const EnsDesc *ens, const float *xc,
+                               const void *K3, const float *V3, float *partial, hipStream_t s) {
+  const uint4 *k3 = reinterpret_cast<const uint4 *>(K3), *v3 = reinterpret_cast<const uint4 *>(V3);
+  if (bf3_rb(D, rb) == 1)
+    k_batch_pair_bf3<D, 1><<<grid, kWaves3 * 64, 0, s>>>(items, nitems, ens, xc, k3, v3, partial);
   else
-    k_batch_pair32<D, 2><<<grid, 256, 0, s>>>(items, nitems, ens, xc, KC, VC, KK, partial);
+    k_batch_pair_bf3<D, bf3_rb(D, 2)><<<grid, kWaves3 * 64, 0, s>>>(items, nitems, ens, xc, k3, v3, partial);
 }
 
 void launch_batch_pair(int impl, int rb, int grid, int KK, int D, const int2 *items, int nitems, const EnsDesc *ens,
@@ -897,11 +924,11 @@ void launch_batch_pair(int impl, int rb, int grid, int KK, int D, const int2 *it
                        const float *xc, float *partial, hipStream_t s) {
   if (impl == VDS_PAIR_MFMA32) {
     switch (D) {
-      case 3: launch_batch32_d<3>(rb, grid, items, nitems, ens, xc, KA, VB, KK, partial, s); break;
-      case 6: launch_batch32_d<6>(rb, grid, items, nitems, ens, xc, KA, VB, KK, partial, s); break;
-      case 9: launch_batch32_d<9>(rb, grid, items, nitems, ens, xc, KA, VB, KK, partial, s); break;
-      case 12: launch_batch32_d<12>(rb, grid, items, nitems, ens, xc, KA, VB, KK, partial, s); break;
-      default: launch_batch32_d<15>(rb, grid, items, nitems, ens, xc, KA, VB, KK, partial, s); break;
+      case 3: launch_batch_bf3_d<3>(rb, grid, items, nitems, ens, xc, f16.QH, VB, partial, s); break;
+      case 6: launch_batch_bf3_d<6>(rb, grid, items, nitems, ens, xc, f16.QH, VB, partial, s); break;
+      case 9: launch_batch_bf3_d<9>(rb, grid, items, nitems, ens, xc, f16.QH, VB, partial, s); break;
+      case 12: launch_batch_bf3_d<12>(rb, grid, items, nitems, ens, xc, f16.QH, VB, partial, s); break;
+      default: launch_batch_bf3_d<15>(rb, grid, items, nitems, ens, xc, f16.QH, VB, partial, s); break;
     }
     return;
   }
@@ -928,6 +955,10 @@ void launch_batch_pair(int impl, int rb, int grid, int KK, int D, const int2 *it
     case 4: launch_batch_kk<4>(rb, grid, items, nitems, ens, QB, KA, VB, xc, D, partial, s); break;
     default: launch_batch_kk<5>(rb, grid, items, nitems, ens, QB, KA, VB, xc, D, partial, s); break;
   }
+}
+
+int pair_tile_rows(int impl, int rb, int D) {
+  return impl == VDS_PAIR_MFMA32 ? kWaves3 * bf3_rb(D, rb) * 16 : 4 * rb * 16;
 }
 
 bool pair_shape_ok(const vds_tuning &t, int D) {
@@ -963,14 +994,15 @@ static void launch_mfma16_k(int rb, dim3 grid, const PairF16Ops &ops, int nrb, i
 }
 
 template <int D>
-static void launch_mfma32_d(int rb, const float *xr, int nrb32, const float *KC, const float *VC, const SplitMap &map,
-                            int ex, float kappa, float *partial, int64_t stride, const int *done, hipStream_t s) {
-  const float4 *kc = reinterpret_cast<const float4 *>(KC), *vc = reinterpret_cast<const float4 *>(VC);
-  const dim3 grid((unsigned)map.G);
-  if (rb == 1)
-    k_pair_mfma32<D, 1><<<grid, 256, 0, s>>>(xr, nrb32, kc, vc, map, ex, kappa, partial, stride, done);
+static void launch_bf3_d(int rb, const void *R3, const void *K3, const float *V3, const float *xr, const SplitMap &map,
+                         int ex, float *partial, int64_t stride, const int *done, hipStream_t s) {
+  const uint4 *r3 = reinterpret_cast<const uint4 *>(R3), *k3 = reinterpret_cast<const uint4 *>(K3),
+              *v3 = reinterpret_cast<const uint4 *>(V3);
+  const dim3 grid((unsigned)map.G), block(kWaves3 * 64);
+  if (bf3_rb(D, rb) == 1)
+    k_pair_bf3<D, 1><<<grid, block, 0, s>>>(r3, k3, v3, xr, map, ex, partial, stride, done);
   else
-    k_pair_mfma32<D, 2><<<grid, 256, 0, s>>>(xr, nrb32, kc, vc, map, ex, kappa, partial, stride, done);
+    k_pair_bf3<D, bf3_rb(D, 2)><<<grid, block, 0, s>>>(r3, k3, v3, xr, map, ex, partial, stride, done);
 }
 
 // Compute units of the current device (256 on MI355X), looked up once per
@@ -995,18 +1027,18 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
     return m;
   }
   m.width = D + 1;  // the compact layout
-  // rows in blocks of 32, four waves of RB blocks per row group; columns in chunks of 32
-  const int rb = t.rows_per_wave;
-  const int64_t nrb32 = nrow_blocks / 2;
-  m.rows_per_group = 4 * rb * 32;
-  m.n_rg = (nrb32 + 4 * rb - 1) / (4 * rb);
+  // kWaves3 waves of RB 16-row blocks per row group (whole groups: the rows are
+  // a multiple of 256); columns in chunks of 32
+  const int rb = bf3_rb(D, t.rows_per_wave);
+  m.rows_per_group = kWaves3 * rb * 16;
+  m.n_rg = (nrow_blocks + kWaves3 * rb - 1) / (kWaves3 * rb);
   m.nch = (ncol_chunks + 1) / 2;
   m.splits = kMaxSplits;
-  // col_splits workgroups per compute unit; runs of at least qmin units, so
-  // that at most kMaxSplits runs meet in one row group
+  // col_splits / 2 workgroups of eight waves per compute unit; runs of at least
+  // qmin units, so that at most kMaxSplits runs meet in one row group
   const int64_t U = m.units();
   const int64_t qmin = (m.nch + kMaxSplits - 2) / (kMaxSplits - 1);
-  int64_t G = std::min<int64_t>((int64_t)t.col_splits * device_cu_count(), U / qmin);
+  int64_t G = std::min<int64_t>(std::max<int64_t>(1, (int64_t)t.col_splits * device_cu_count() / 2), U / qmin);
   if (G >= 8) G -= G % 8;
   m.G = (int)std::max<int64_t>(G, 1);
   return m;
@@ -1015,23 +1047,22 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
 void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64_t nrow_blocks, const float *KA,
                       const float *VB, int64_t ncol_chunks, int64_t ncol_pad, const float *xc, bool exclude_self,
                       const float *wscale, const F16Operands &f16, float *partial, int64_t part_stride_rows,
-                      const int *done, hipStream_t s, float kappa) {
+                      const int *done, hipStream_t s, const void *rows3) {
   const int ex = exclude_self ? 1 : 0;
   const int splits = t.col_splits;
   const int64_t cps = (ncol_chunks + splits - 1) / splits;
   if (t.impl == VDS_PAIR_MFMA32) {
-    // rows in blocks of 32 (nrow_blocks counts 16-row blocks of a multiple of 256 rows, so
-    // every row group of 4 waves x RB blocks is whole); columns in chunks of 32, the last
-    // inside the padding (ncol_pad is a multiple of 256 columns), whose weights are zero
+    // whole row groups (nrow_blocks counts 16-row blocks of a multiple of 256 rows); columns
+    // in chunks of 32, the last inside the padding (ncol_pad is a multiple of 256 columns),
+    // whose weights are zero
     const SplitMap map = pair_split_map(t, D, nrow_blocks, ncol_chunks);
     const int rb = t.rows_per_wave;
-    const int nrb32 = (int)(nrow_blocks / 2);
     switch (D) {
-      case 3: launch_mfma32_d<3>(rb, QB, nrb32, KA, VB, map, ex, kappa, partial, part_stride_rows, done, s); break;
-      case 6: launch_mfma32_d<6>(rb, QB, nrb32, KA, VB, map, ex, kappa, partial, part_stride_rows, done, s); break;
-      case 9: launch_mfma32_d<9>(rb, QB, nrb32, KA, VB, map, ex, kappa, partial, part_stride_rows, done, s); break;
-      case 12: launch_mfma32_d<12>(rb, QB, nrb32, KA, VB, map, ex, kappa, partial, part_stride_rows, done, s); break;
-      default: launch_mfma32_d<15>(rb, QB, nrb32, KA, VB, map, ex, kappa, partial, part_stride_rows, done, s); break;
+      case 3: launch_bf3_d<3>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
+      case 6: launch_bf3_d<6>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
+      case 9: launch_bf3_d<9>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
+      case 12: launch_bf3_d<12>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
+      default: launch_bf3_d<15>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
     }
     return;
   }

@@ -1074,7 +1074,7 @@ vds_status freeze(vds_rom r, const float *p) {
         default: k_kernel_gemm16<5><<<grid, 256, 0, s>>>(c->QB, c->KA, nrb, ncc, bh, lo_off, L.NB16, 3 * R, s0, s1, 1.f, r->Y, L.ldy); break;
       }
     });
-  } else if (c->ep.f32x) {
+  } else if (c->ep.bf3) {
     // the 32x32 form reads the pair kernel's operands as the passes left them;
     // column blocks per workgroup and runs were fixed when the model was laid
     // out (its slots hold G tiles of that width)

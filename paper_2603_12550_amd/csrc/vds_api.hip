@@ -87,9 +87,8 @@ void pair_pass(vds_ctx c, const float *V, const float *wscale, const int *done) 
   const int64_t nrb = c->ep.Ppad / 16;
   const double pairs = (double)c->prob.P * (double)c->prob.P;
   timed(c, VDS_TIMER_PAIR, pairs, [&] {
-    // VDS_PAIR_MFMA32 takes its rows straight from the centred coordinates
-    launch_pair_pass(c->tune, c->ep.KK, c->ep.D, c->ep.f32x ? c->xc : c->QB, nrb, c->KA, V, ncol_chunks(c),
-                     c->ep.Ppad, c->xc, true, wscale, c->f16, c->part, c->ep.Ppad, done, c->stream, c->ep.kappa);
+    launch_pair_pass(c->tune, c->ep.KK, c->ep.D, c->QB, nrb, c->KA, V, ncol_chunks(c), c->ep.Ppad, c->xc, true,
+                     wscale, c->f16, c->part, c->ep.Ppad, done, c->stream, c->f16.QH);
   });
 }
 
@@ -100,7 +99,7 @@ void apply_tuning(vds_ctx c, const vds_tuning &t) {
   c->smap = pair_split_map(t, c->ep.D, c->ep.Ppad / 16, ncol_chunks(c));
   c->ep.vhalf = (t.impl == VDS_PAIR_MFMA_F16X2 || t.impl == VDS_PAIR_MFMA_F16X2_ALL) ? 1 : 0;
   c->ep.qhalf = t.impl == VDS_PAIR_MFMA_F16X2_ALL ? 1 : 0;
-  c->ep.f32x = t.impl == VDS_PAIR_MFMA32 ? 1 : 0;
+  c->ep.bf3 = t.impl == VDS_PAIR_MFMA32 ? 1 : 0;
 }
 
 void eval_pass_a(vds_ctx c, const float *q, const float *w, const int *done, bool centre) {
@@ -158,10 +157,12 @@ Layout make_layout(const vds_problem &p) {
     off += round_up((int64_t)bytes, 256);
     return o;
   };
+  const int64_t vw = std::max(16, 8 * bf3_tiles(D));  // floats per particle of V
+  L.VA = take(sizeof(float) * Ppad * vw);
+  // (density rows of VDS_PAIR_MFMA32 take QB, KA and VB together)
   L.QB = take(sizeof(float) * Ppad * KK * 4);
   L.KA = take(sizeof(float) * Ppad * KK * 4);
-  L.VA = take(sizeof(float) * Ppad * 16);
-  L.VB = take(sizeof(float) * Ppad * 16);
+  L.VB = take(sizeof(float) * Ppad * vw);
   L.part = take(sizeof(float) * (size_t)kMaxSplits * Ppad * 16);
   L.xc = take(sizeof(float) * Ppad * D);
   L.t1 = take(sizeof(float) * Ppad * D);
@@ -174,6 +175,7 @@ Layout make_layout(const vds_problem &p) {
   L.blockmax = take(sizeof(float) * 2 * nblk);
   L.wscale = take(sizeof(float) * 4);
   L.cmean = take(sizeof(float) * 16);
+  // (K3 of VDS_PAIR_MFMA32 takes QH and KH together)
   L.QH = take(sizeof(uint16_t) * Ppad * 32 * f16_slices(D));
   L.KH = take(sizeof(uint16_t) * Ppad * 32 * f16_slices(D));
   L.RN = take(sizeof(float) * Ppad);
@@ -711,7 +713,7 @@ vds_status vds_density_at(vds_ctx c, const float *q, const float *w, const float
     const int64_t nrb = round_up(nr, kRowAlign) / 16;
     timed(c, VDS_TIMER_PAIR, (double)nr * (double)c->prob.P, [&] {
       launch_pair_pass(c->tune, e.KK, e.D, c->QB, nrb, c->KA, c->VA, ncol_chunks(c), e.Ppad, c->xc, false,
-                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream, e.kappa);
+                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream, c->QB);
     });
     launch_density_out(e, c->part, pair_split_map(c->tune, e.D, nrb, ncol_chunks(c)), nr, norm, f + r0, c->stream);
   }
@@ -764,11 +766,11 @@ vds_status vds_autotune(vds_ctx c, const float *q, const float *w) {
   for (const vds_tuning &t : cands) {
     if (!pair_shape_ok(t, c->ep.D)) continue;
     apply_tuning(c, t);
-    if (c->ep.vhalf + 2 * c->ep.qhalf + 4 * c->ep.f32x != prepared) {  // operand formats follow the implementation
+    if (c->ep.vhalf + 2 * c->ep.qhalf + 4 * c->ep.bf3 != prepared) {  // operand formats follow the implementation
       launch_mean_partials(c->ep, q, w, c->meanp, nullptr, nullptr, c->stream);
       launch_prep(c->ep, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, nullptr,
                   c->stream);
-      prepared = c->ep.vhalf + 2 * c->ep.qhalf + 4 * c->ep.f32x;
+      prepared = c->ep.vhalf + 2 * c->ep.qhalf + 4 * c->ep.bf3;
     }
     // each candidate is timed with the finalisation that sums its column splits
     auto pass = [&] {

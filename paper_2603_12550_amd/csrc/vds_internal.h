@@ -63,20 +63,39 @@ struct EvalParams {
   int qhalf;          // FP16 distance operands QH/KH and row norms RN written too (VDS_PAIR_MFMA_F16X2_ALL)
   int KQ;             // FP16 distance slices of 32 products: f16_slices(D)
   float cs;           // sqrt(2 kappa): the distance operands are cs x
-  int f32x;           // FP32 operands in the per-chunk layout of VDS_PAIR_MFMA32 (KC in the KA buffer,
-                      // V in VA/VB at vc_index); QB/KA in the 16-row layout are then not written
-  int KP;             // K slots of that kernel's distance product: D + 2 rounded up to even
+  int bf3;            // operands of VDS_PAIR_MFMA32: BF16 thirds K3 and V3 (see bf3_index, v3_index) and KC;
+                      // QB/KA in the 16-row layout are then not written
+  int KP;             // K slots of KC (the kernel-GEMM's distance product): D + 2 rounded up to even
 };
 
-// FP32 operands of VDS_PAIR_MFMA32, per chunk of 32 columns (see pair_kernels.hip):
-//   KC: slot k < KP of column J at [((J / 32) * KP + k) * 32 + J % 32], slot k < D holding
-//       2 kappa x_J[k], slot D the column norm term -kappa |x_J|^2, slot D + 1 one (the row
-//       side holds x_I, 1 and the row norm term there), zero beyond;
-//   V:  element n < 16 of V_J at [J * 16 + (n % 4) * 4 + n / 4], so that the float4 at
-//       J * 4 + j holds elements j, 4 + j, 8 + j, 12 + j.
+// Operands of VDS_PAIR_MFMA32 (see pair_kernels.hip), every number as three
+// BF16 parts h + m + l:
+//   K3: 32 bf3_slices(D) slots per particle, two per dword, for the distance
+//       product.  Dwords 3k .. 3k + 2 of component k hold (h, m), (h, m), (h, l)
+//       of y = sqrt(2 kappa) x_k; dwords 3D .. 3D + 2 hold (nh, nm), (nl, 1),
+//       (1, 1) with n = -|y|^2 / 2; zero beyond.  Dword dd of particle J sits at
+//       bf3_index.  The row side of the product is the same with the slots of
+//       dwords 3k + 1, 3k + 2 and 3D + 1 exchanged and (1, 1) and (nh, nm) in
+//       dwords 3D and 3D + 2, so the six products of a component are hh, mm,
+//       hm, mh, hl, lh.  Ppad * bf3_slices(D) * 64 bytes, in the QH and KH
+//       buffers (contiguous, and exactly as large or larger).
+//   V3: part p of element n <= D of V_J in column c = p (D + 1) + n of
+//       bf3_tiles(D) tiles of 16 columns, 32 rows J each, at v3_index (in 16-bit
+//       units).  Ppad * bf3_tiles(D) * 32 bytes, in VA or VB and, for D >= 12,
+//       the first part of the buffer behind (QB or KA).
+//   KC: slot k < KP of column J at [((J / 32) * KP + k) * 32 + J % 32], FP32 (the
+//       kernel-GEMM of the reduced model): slot k < D holds 2 kappa x_J[k], slot
+//       D the column norm term -kappa |x_J|^2, slot D + 1 one, zero beyond.
+__host__ __device__ constexpr int bf3_slices(int D) { return (6 * D + 6 + 31) / 32; }
+__host__ __device__ constexpr int bf3_tiles(int D) { return (3 * (D + 1) + 15) / 16; }
+__host__ __device__ inline int64_t bf3_index(int64_t J, int dd, int NQ) {
+  return (((J >> 4) * NQ + (dd >> 4)) * 64 + (J & 15) + 16 * ((dd & 15) >> 2)) * 4 + (dd & 3);
+}
+__host__ __device__ inline int64_t v3_index(int64_t J, int c, int NT) {
+  return (((J >> 5) * NT + (c >> 4)) * 64 + (c & 15) + 16 * ((J & 15) >> 2)) * 8 + 4 * ((J >> 4) & 1) + (J & 3);
+}
 __host__ __device__ constexpr int mfma32_kslots(int D) { return (D + 3) & ~1; }
 __host__ __device__ inline int64_t kc_index(int64_t J, int k, int KP) { return ((J >> 5) * KP + k) * 32 + (J & 31); }
-__host__ __device__ inline int64_t vc_index(int64_t J, int n) { return J * 16 + (n & 3) * 4 + (n >> 2); }
 
 // FP16 MFMA slices (32 products each) of the split distance product: three
 // per configuration component and two for the column norm.
@@ -186,14 +205,16 @@ enum CombineMode { MODE_TERMS = 0, MODE_VELOCITY = 1, MODE_EXPLICIT = 2, MODE_PI
 // the padded column count the V operand was written for.  With the FP16-split
 // implementation the V weights were divided by *wscale (NULL: by one), which
 // the pass multiplies back.
-// VDS_PAIR_MFMA32 reads its rows from QB as plain coordinates [nrow_blocks * 16][D] (the
-// centred particles, or centred foreign rows), KC from KA and V from VB in the per-chunk
-// layout above; kappa = log2(e) / 2h^2.
+// VDS_PAIR_MFMA32 reads K3 from f16.QH, V3 from VB and its rows from rows3, in K3's layout
+// (K3 itself when the rows are the particles).
 void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64_t nrow_blocks,
                       const float *KA, const float *VB, int64_t ncol_chunks, int64_t ncol_pad, const float *xc,
                       bool exclude_self, const float *wscale, const F16Operands &f16, float *partial,
-                      int64_t part_stride_rows, const int *done, hipStream_t s, float kappa = 0.f);
+                      int64_t part_stride_rows, const int *done, hipStream_t s, const void *rows3 = nullptr);
 bool pair_shape_ok(const vds_tuning &t, int D);
+// Rows a workgroup of the matrix-core implementation impl takes (rb as rows_per_wave of
+// vds_tuning).
+int pair_tile_rows(int impl, int rb, int D);
 // Compute units of the current device (256 on MI355X; 256 if the query fails).
 int device_cu_count();
 // The slots a pass of tuning t over nrow_blocks 16-row blocks and ncol_chunks
@@ -250,12 +271,9 @@ void launch_step_end(const EvalParams &p, Ctrl *ctrl, const PicardCheck &chk, co
 // packing combine; host-driven iterations).
 void launch_picard_check(const PicardCheck &chk, const float *blockmax, int nblk_chk, hipStream_t s);
 void launch_stress(const EvalParams &p, const float *q, const float *w, double *redp, hipStream_t s);
-// With p.f32x the centred rows go to QB as plain coordinates [rows][D] (VDS_PAIR_MFMA32).
+// With p.bf3 the centred rows go to QB in K3's layout (VDS_PAIR_MFMA32).
 void launch_density_rows(const EvalParams &p, const float *y, int64_t ny, const double *meanp, int nmeanp,
                          float *QB, const F16Operands *f16, hipStream_t s);
-// QB/KA in the 16-row FP32 layout from the centred coordinates xc (the FP32 kernel GEMM of
-// the reduced model reads them; under p.f32x the prep kernels write the per-chunk layout).
-void launch_pack_qk(const EvalParams &p, const float *xc, float *QB, float *KA, hipStream_t s);
 void launch_density_out(const EvalParams &p, const float *partial, const SplitMap &splits, int64_t ny, float norm,
                         float *f, hipStream_t s);
 void launch_copy(const float *src, float *dst, int64_t n, const int *done_flag_or_null, hipStream_t s);
@@ -270,6 +288,7 @@ struct BatchView {
   const int *blk256_ens;
   int nblk16, nblk256;  // total blocks over all ensembles (padded particles)
   int D, KK;
+  int vw;               // floats per particle of the V operands
   F16Operands f16;      // concatenated FP16 distance operands (used when the ensembles' qhalf is set)
 };
 void launch_batch_mean(const BatchView &b, const float *q, double *meanp, hipStream_t s);

@@ -1,0 +1,50 @@
+"""GPU parity of the kernels that take FP32 products from three BF16 parts, at
+the edges of their tiles, against the FP64 oracle.
+
+Tolerances: as in the particle tests, 1e-5 of the 2-norm and 1e-4 per row (the
+parts hold FP32's 24 bits; what rounds is the FP32 accumulation, over fewer
+terms at a time than in the forms those bounds were set for).
+"""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import vds as ovds
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    import paper_2603_12550_amd as pkg
+    return pkg
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(wl.to_f32(a)).cuda()
+
+
+def _check_rows(b, b_o, S, S_o, label):
+    num = np.sqrt(((b - b_o) ** 2).sum((0, 2)))
+    den = np.sqrt((b_o ** 2).sum((0, 2)))
+    print(label, "max row rel", (num / den).max(), "S", np.abs(S / S_o - 1).max(), flush=True)
+    assert (num <= 1e-4 * den).all()
+    assert np.linalg.norm(num) <= 1e-5 * np.linalg.norm(den)
+    assert np.abs(S / S_o - 1).max() <= 1e-5
+
+
+# chunk (32 columns), stage (64), accumulation group (256) and row group (128, 256) edges
+@pytest.mark.parametrize("P", [31, 32, 33, 65, 255, 257, 513, 1025])
+@pytest.mark.parametrize("nb,rb", [(1, 2), (2, 1), (2, 2), (3, 1), (3, 2), (4, 2), (5, 2)])
+def test_pair_sums_tile_edges(lib, P, nb, rb):
+    q = wl.f32_as_f64(wl.to_f32(wl.gaussian_bonds(300 + P, nb, P, 0.5)))
+    w = wl.f32_as_f64(wl.to_f32(wl.random_weights(9 + P, P)))
+    S_o, t1_o, t2_o = ovds.brownian_terms(ovds.particle_major(q), w, 0.6)
+    ctx = lib.Context(nb, P, 0.6, poison=True, scheme="explicit")
+    for sp in (1, 4, 8):
+        ctx.set_tuning(rows_per_wave=rb, col_splits=sp)
+        S, t1, t2 = (t.cpu().numpy().astype(np.float64) for t in ctx.pair_sums(_dev(q), _dev(w)))
+        _check_rows(t1 + t2, ovds.bond_major(t1_o + t2_o, nb), S, S_o, f"P={P} nb={nb} rb={rb} sp={sp}")
