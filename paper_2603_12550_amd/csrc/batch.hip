@@ -65,8 +65,8 @@ vds_status bhip(vds_batch b, hipError_t e, const char *what) {
 
 int64_t pad(int64_t P) { return round_up(P, kRowAlign); }
 
-// Floats per particle of the V operands.
-int v_width(int D) { return std::max(16, 8 * bf3_tiles(D)); }
+// Floats per particle of the V operands in the implementation's format.
+int v_width(int impl, int D) { return impl == VDS_PAIR_MFMA32 ? 8 * bf3_tiles(D) : 16; }
 
 BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   const int D = 3 * nb, KK = (D + 2 + 3) / 4;
@@ -87,10 +87,11 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   L.blk16 = take(sizeof(int) * (Ptot / 16));
   L.blk256 = take(sizeof(int) * (Ptot / 256));
   L.items = take(sizeof(int2) * items_max);
+  // (V of VDS_PAIR_MFMA32 runs from VA on into QB, and from VB on into KA, for D >= 12)
+  L.VA = take(sizeof(float) * Ptot * 16);
   L.QB = take(sizeof(float) * Ptot * KK * 4);
+  L.VB = take(sizeof(float) * Ptot * 16);
   L.KA = take(sizeof(float) * Ptot * KK * 4);
-  L.VA = take(sizeof(float) * Ptot * v_width(D));
-  L.VB = take(sizeof(float) * Ptot * v_width(D));
   // (K3 of VDS_PAIR_MFMA32 takes QH and KH together)
   L.QH = take(sizeof(uint16_t) * Ptot * 32 * f16_slices(D));
   L.KH = take(sizeof(uint16_t) * Ptot * 32 * f16_slices(D));
@@ -140,7 +141,7 @@ BatchView view(vds_batch b) {
   v.nblk256 = (int)(b->Ptot_pad / 256);
   v.D = b->D;
   v.KK = b->KK;
-  v.vw = v_width(b->D);
+  v.vw = v_width(b->impl, b->D);
   v.f16 = b->f16;
   return v;
 }
@@ -273,7 +274,6 @@ vds_status vds_batch_create(int32_t nens, const int64_t *P, const double *h, con
     p.log_norm = (float)(0.5 * b->D * std::log(2.0 * M_PI * h[e] * h[e]));
     p.KQ = f16_slices(b->D);
     p.cs = (float)std::sqrt(2.0 * 1.4426950408889634 / (2.0 * h[e] * h[e]));
-    p.KP = mfma32_kslots(b->D);
     d.pad_off = pad_off;
     d.q_off = q_off;
     d.blk16 = (int)(pad_off / 16);

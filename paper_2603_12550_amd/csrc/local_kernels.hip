@@ -4,6 +4,7 @@
 // control, the FENE domain flag, and FP64 reductions of stress, energy,
 // dissipation and work.  All reductions are two-stage (per-block partials in
 // a fixed tree, then a fixed-order sum), so results are bitwise reproducible.
+#include "bf3.h"
 #include "vds_internal.h"
 
 namespace vds {
@@ -82,24 +83,6 @@ __device__ inline void store_v(const EvalParams &p, float *V, int64_t J, int n, 
   }
 }
 
-// The three BF16 parts of an FP64 number, each rounded to nearest (the third
-// leaves 2^-27 of it); bit patterns.
-struct Bf3 {
-  uint16_t h, m, l;
-};
-__device__ inline uint16_t bf16_bits(double v) {
-  return __builtin_bit_cast(uint16_t, (__bf16)(float)v);
-}
-__device__ inline double bf16_value(uint16_t u) { return (double)__uint_as_float((uint32_t)u << 16); }
-__device__ inline Bf3 split_bf3(double v) {
-  Bf3 s;
-  s.h = bf16_bits(v);
-  v -= bf16_value(s.h);
-  s.m = bf16_bits(v);
-  v -= bf16_value(s.m);
-  s.l = bf16_bits(v);
-  return s;
-}
 // Lane n of particle J writes element n of V_J = (wx, w) (0 past the
 // particles) in the format of the pair implementation; w_x is this lane's
 // weighted coordinate or weight.
@@ -272,16 +255,6 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
   if (n == 0) wv[I] = wi;
   if (n < p.D) xc[I * p.D + n] = x;
   // the FP32 distance operands are read only by the FP32-distance pair forms
-  // (KP can exceed the sixteen lanes: slots k = n, n + 16)
-  for (int k = n; k < (p.bf3 ? p.KP : 0); k += 16) {
-    float ka = 0.f;
-    if (real) {
-      if (k < p.D) ka = 2.f * p.kappa * x;  // k < D <= 15 only for k == n
-      else if (k == p.D) ka = -p.kappa * nrm;
-      else if (k == p.D + 1) ka = 1.f;
-    }
-    KA[kc_index(I, k, p.KP)] = ka;
-  }
   if (p.bf3) store_k3(p, reinterpret_cast<uint32_t *>(f16.QH), I, n, x);
   for (int k = n; k < ((p.qhalf || p.bf3) ? 0 : 4 * p.KK); k += 16) {
     float qa = 0.f, ka = 0.f;

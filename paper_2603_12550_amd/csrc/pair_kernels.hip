@@ -54,11 +54,10 @@
 #include <atomic>
 #include <type_traits>
 
+#include "bf3.h"
 #include "vds_internal.h"
 
 namespace vds {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kFlush = 8;  // chunks per FP32 accumulation group
 
@@ -215,9 +214,6 @@ __global__ __launch_bounds__(256) void k_pair_mfma(const float *__restrict__ QB,
 // With dot products (v_dot2_f32_bf16) forming what a cut leaves, the pass took
 // 157 us: they hold the matrix pipe; with and/subtract pairs, 153.
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kWaves3 = 8;   // waves per workgroup
 constexpr int kStage3 = 2;   // 32-column chunks staged in LDS per barrier
 constexpr int kFlush3 = 8;   // chunks per FP32 accumulation group (a multiple of kStage3)
@@ -245,66 +241,12 @@ struct Bf3Lds {
   double tot[kWaves3][4 * kMaxRB3][64];
 };
 
-__device__ inline bf16x8 as_bf8(uint4 u) {
-  bf16x8 r;
-  __builtin_memcpy(&r, &u, sizeof(r));
-  return r;
-}
-__device__ inline bf16x2 as_bf2(uint32_t u) {
-  bf16x2 r;
-  __builtin_memcpy(&r, &u, sizeof(r));
-  return r;
-}
-
-// The upper halves of eight values, a BF16 operand (truncation: what is left of
-// a value after two such cuts is again a BF16 number).
-__device__ __forceinline__ bf16x8 upper_halves(const floatx4 &a, const floatx4 &b) {
-  uint32_t u[4];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    u[j] = __builtin_amdgcn_perm(__float_as_uint(a[2 * j + 1]), __float_as_uint(a[2 * j]), 0x07060302u);
-    u[2 + j] = __builtin_amdgcn_perm(__float_as_uint(b[2 * j + 1]), __float_as_uint(b[2 * j]), 0x07060302u);
-  }
-  return as_bf8(uint4{u[0], u[1], u[2], u[3]});
-}
-
 // Lane i of each row of 16 gets lane (i + R) % 16 of its row.
 template <int R>
 __device__ __forceinline__ float row_rotate(float v) {
   if constexpr (R % 16 == 0) return v;
   else
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + (16 - R % 16), 0xf, 0xf, true));
-}
-
-// Row operand of the 16-row block rb from its column operand (layout at
-// bf3_index): the slots of a component swap within a dword, the norm's dwords
-// change places (see there).
-template <int D>
-__device__ __forceinline__ void bf3_row_operand(const uint4 *__restrict__ K3, int64_t rb, int lane,
-                                                bf16x8 (&q)[Bf3Shape<D>::NQ]) {
-  constexpr int NQ = Bf3Shape<D>::NQ;
-  constexpr int dA = 3 * D, dB = dA + 1, dC = dA + 2;
-  const int g = lane >> 4;
-  uint32_t k[NQ][4];
-#pragma unroll
-  for (int m = 0; m < NQ; ++m) {
-    const uint4 u = K3[(rb * NQ + m) * 64 + lane];
-    k[m][0] = u.x, k[m][1] = u.y, k[m][2] = u.z, k[m][3] = u.w;
-  }
-  const uint32_t nA = __shfl(k[dA / 16][dA % 4], (lane & 15) + 16 * (dA % 16 / 4));
-#pragma unroll
-  for (int m = 0; m < NQ; ++m) {
-    uint32_t o[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int dd = 16 * m + 4 * g + j;
-      const uint32_t v = k[m][j], sw = (v >> 16) | (v << 16);
-      o[j] = (dd % 3 != 0 && dd < dA) || dd == dB ? sw : v;
-      if (dd == dA) o[j] = 0x3f803f80u;
-      if (dd == dC) o[j] = nA;
-    }
-    q[m] = as_bf8(uint4{o[0], o[1], o[2], o[3]});
-  }
 }
 
 // One segment: wave w of the workgroup takes the 16-row blocks
@@ -327,13 +269,8 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
   const int rb0 = (rg * kWaves3 + wave) * RB;
   // position of the self pair inside a diagonal 16x16 block, per element i
   const int diag_i = (lane & 15) - 4 * (lane >> 4);
-  // minus the identity: row m of block b picks the slot that holds column
-  // J = m of that block, k = 8 (m / 4) + 4 b + m % 4
   bf16x8 neg[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) neg[b][i] = (diag_i >= 0 && diag_i < 4 && i == 4 * b + diag_i) ? (__bf16)-1.f : (__bf16)0.f;
+  minus_identity(lane, neg);
 
   // wave w brings in the pieces w, w + 8, ... of the stage that starts at
   // chunk c (chunk by chunk: distance operands, then V)
@@ -345,9 +282,7 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
       if (pc < kStage3 * PC && c + cc < c1) {  // scalar
         const uint4 *src = w < 2 * NQ ? K3 + ((int64_t)(c + cc) * 2 * NQ + w) * 64
                                       : V3 + ((int64_t)(c + cc) * NT + (w - 2 * NQ)) * 64;
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(src + lane),
-            (__attribute__((address_space(3))) void *)(&lds.buf[buf][pc * 64]), 16, 0, 0);
+        piece_to_lds(src, &lds.buf[buf][pc * 64], lane);
       }
     }
   };

@@ -13,6 +13,7 @@
 
 #include <rocblas/rocblas.h>
 
+#include "bf3.h"
 #include "vds_ctx.h"
 #include "vds_linalg.h"
 #include "vds_pod.h"
@@ -21,58 +22,58 @@ using namespace vds;
 
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kMaxR = 1024;
 constexpr int kNBG = 8;       // 16-column output blocks per workgroup of the kernel-GEMM
 constexpr int kKgFlush = 8;   // chunks per FP32 accumulation group
-constexpr int kK32Waves = 8;  // waves (32-row blocks) per workgroup of the FP32 32x32 kernel-GEMM
-constexpr int kK32MaxNB = 4;  // its column blocks of 32 per workgroup: 1 to 4 (B holds 4 slots per lane and row)
-// floats of one (row group, column group) output tile with nb column blocks
-constexpr int kgemm32_tile(int nb) { return kK32Waves * 32 * 32 * nb; }
+constexpr int kKgWaves = 8;   // waves of a workgroup of the default kernel-GEMM
+constexpr int kKgRows = 256;  // its rows: two 16-row blocks per wave
+// floats of one (row group, column group) output tile with NB column tiles of 16
+constexpr int kgemm_tile(int NB) { return kKgRows * 16 * NB; }
 
-// (row group, column group) items of the FP32 kernel-GEMM with nb column blocks
-int64_t kgemm32_items(int64_t Ppad, int ncols, int nb) {
-  return (Ppad / 32 + kK32Waves - 1) / kK32Waves * ((ncols + 32 * nb - 1) / (32 * nb));
-}
+// The balanced grid of the default kernel-GEMM: the (column group, row group)
+// items, column-group major, times the nch 32-column chunks of Z, cut into G
+// equal runs, one workgroup each.
+struct KgMap {
+  int NB;       // column tiles of 16 per item: 4, 8 or 12
+  int NCG, n_rg, nch, G;
+  __host__ __device__ int64_t items() const { return (int64_t)NCG * n_rg; }
+  __host__ __device__ int64_t units() const { return items() * nch; }
+  __host__ __device__ int64_t run_start(int64_t L) const { return L * units() / G; }
+};
 
-// Runs (workgroups) of the FP32 kernel-GEMM's balanced grid for Ppad rows and
-// ncols output columns: two per compute unit (one round), at most one per
-// (row group, column group) item, so that no item spans more than two runs;
-// a multiple of 8 from 8 on (consecutive runs share an XCD).
-int kgemm32_runs(int64_t Ppad, int ncols, int nb) {
-  int64_t G = std::min<int64_t>(2 * (int64_t)device_cu_count(), kgemm32_items(Ppad, ncols, nb));
-  if (G >= 8) G -= G % 8;
-  return (int)std::max<int64_t>(G, 1);
-}
-
-// Column blocks per workgroup: the count whose issue cycles per run are fewest.
-// Per chunk of an item, the distance product and the exponentials cost
-// 64 NK + 128 cycles and each column block 16 x 64; columns past ncols in the
-// last group are computed too.  Wide groups amortise the distances (at
-// P = 20000, R = 180: four blocks); where the items are fewer than the runs a
-// full round would hold (small P), narrow groups give more, shorter runs.
-int kgemm32_nb(int64_t Ppad, int ncols, int D) {
-  const double ko = 64.0 * (mfma32_kslots(D) / 2) + 128.0;
-  int best = kK32MaxNB;
-  double best_cost = 0.0;
-  for (int nb = kK32MaxNB; nb >= 1; --nb) {
-    const double items = (double)kgemm32_items(Ppad, ncols, nb);
-    const double cost = items * (ko + 1024.0 * nb) / kgemm32_runs(Ppad, ncols, nb);
-    if (nb == kK32MaxNB || cost < best_cost) {
-      best = nb;
-      best_cost = cost;
+// One workgroup per compute unit (its eight waves take a SIMD's registers two
+// at a time), each with at least two chunks.  Column tiles per item by the
+// matrix instructions a chunk costs: 12 per tile, and 16 for its part of Z; the
+// padding of the last group counts (R = 180: 3 x 12 tiles for 34; R = 40: 8).
+KgMap kgemm_map(int64_t P, int ncols) {
+  KgMap m{};
+  const int tiles = (ncols + 15) / 16;
+  double best = 0.0;
+  for (int nb : {12, 8, 4}) {
+    const int g = (tiles + nb - 1) / nb;
+    const double cost = (double)g * (12.0 * nb + 16.0);
+    if (m.NB == 0 || cost < best) {
+      m.NB = nb;
+      m.NCG = g;
+      best = cost;
     }
   }
-  return best;
+  m.n_rg = (int)(round_up(P, kRowAlign) / kKgRows);
+  m.nch = (int)((P + 31) / 32);
+  int64_t G = std::min<int64_t>(device_cu_count(), m.units() / 2);
+  if (G >= 8) G -= G % 8;
+  m.G = (int)std::max<int64_t>(G, 1);
+  return m;
 }
+
+// Row length of Y of the default kernel-GEMM.
+int64_t rom_ldy3(int R) { return (3 * (int64_t)R + 15) / 16 * 16; }
 
 struct RomLayout {
   size_t Ude, Mbig, XH, I1, XB1, XB2, XB, Bsw, Y, qt, T, invS, part, red, psave, pprev, total;
   int NB16;
   int64_t ldy;
-  int kg_nb;    // column blocks per workgroup of the FP32 kernel-GEMM
-  int kg_runs;  // runs of its balanced grid (its continuation slots are sized for them)
+  KgMap kg;     // grid of the default kernel-GEMM (its continuation slots are sized for its runs)
 };
 
 RomLayout rom_layout(const vds_problem &p, int R) {
@@ -94,21 +95,22 @@ RomLayout rom_layout(const vds_problem &p, int R) {
   L.XB1 = take(sizeof(float) * R * R);
   L.XB2 = take(sizeof(float) * R * R);
   L.XB = take(sizeof(float) * R * R);
-  // B of the kernel-GEMM: the 16-column swizzled layout, or that of the 32x32 form
-  L.kg_nb = kgemm32_nb(Ppad, ncols, 3 * p.nb);
-  const int64_t ncg32 = (ncols + 32 * L.kg_nb - 1) / (32 * L.kg_nb);
-  L.Bsw = take(sizeof(float) * (size_t)Ppad * std::max<int64_t>(L.ldy, ncg32 * 128));
-  L.Y = take(sizeof(float) * (size_t)Ppad * L.ldy);
+  // B of the kernel-GEMM: the 16-column swizzled layout of 6 R columns, or the
+  // BF16 thirds of 3 R columns (6 bytes each)
+  L.kg = kgemm_map(P, 3 * R);
+  L.Bsw = take(std::max(sizeof(float) * (size_t)Ppad * L.ldy,
+                        sizeof(uint16_t) * 3 * (size_t)Ppad * 16 * L.kg.NB * L.kg.NCG));
+  // Y of 6 R columns, or of 3 R (then W, R x R, sits behind it)
+  L.Y = take(sizeof(float) * std::max((size_t)Ppad * L.ldy, (size_t)Ppad * rom_ldy3(R) + (size_t)R * R));
   L.qt = take(sizeof(float) * (size_t)p.nb * P * 3);
   L.T = take(sizeof(float) * Ppad);
   L.invS = take(sizeof(float) * Ppad);
   const int64_t m = 3 * P;
   // (the GEMMs' split partials, or the kernel-GEMM's continuation tiles: one per run)
-  L.kg_runs = kgemm32_runs(Ppad, ncols, L.kg_nb);
   const size_t part = std::max({sizeof(float) * (size_t)gemm_splits(3 * R, 3 * R, P) * 9 * R * R,
                                 sizeof(float) * (size_t)gemm_splits(R, R, P) * R * R,
                                 sizeof(float) * (size_t)m * p.nb,
-                                sizeof(float) * (size_t)L.kg_runs * kgemm32_tile(L.kg_nb)});
+                                sizeof(float) * (size_t)L.kg.G * kgemm_tile(L.kg.NB)});
   L.part = take(part);
   L.red = take(sizeof(double) * 16);
   L.psave = take(sizeof(float) * (size_t)p.nb * R);
@@ -258,73 +260,77 @@ __global__ __launch_bounds__(256) void k_kernel_gemm(const float *__restrict__ Q
   }
 }
 
-// ---- FP32 kernel-GEMM on 32x32 tiles (the operands of VDS_PAIR_MFMA32) -----
+// ---- FP32 kernel-GEMM by three BF16 parts (the operands of VDS_PAIR_MFMA32) --
 //
-// Y[I][col] = sum_J Z_IJ B[J][col] with a workgroup of kK32Waves waves owning
-// kK32Waves 32-row blocks (256 rows) and NB column blocks of 32 (32 NB
-// columns; NB from 1 to 4 by the problem's size).  Per chunk of 32 columns of
-// Z it stages the chunk's B block and the K operand of its distance product
-// (the pair kernel's per-chunk KC layout) in LDS once, double buffered with one
-// barrier.  Each wave forms its
-// 32x32 piece of Z on v_mfma_f32_32x32x2_f32 from the centred row coordinates
-// (Z_II = 1 set exactly) and multiplies it by the staged B block on the same
-// instruction: the distance product leaves lane l with row I = l % 32 and, in
-// register v, column J = 8 (v / 4) + 4 (l / 32) + v % 4, which is the A-operand
-// layout of step v of the product over J.  B of step v for column block nb
-// sits in lane l at row J(v, l / 32), column 32 nb + l % 32.  FP32
-// accumulation over all columns of Z (as the FP16-split form: ~1e-6 of the
-// sums).
-// B of the FP32 32x32 kernel-GEMM, one block of 32 rows J x 32 NB columns per
-// (chunk c, column group cg): element (jj, col = 32 NB cg + 32 nb + l) at
-// [((c NCG + cg) 32 + jj) 128 + 4 l + nb], one float4 per lane and row
-// (slots nb >= NB are zero).
-__global__ void k_rom_b32(const float *__restrict__ Ude, const float *__restrict__ wv, const float *__restrict__ invS,
-                          int64_t P, int64_t Ppad, int R, int NCG, int NB, float *__restrict__ Bk) {
+// Y[I][col] = sum_J Z_IJ U_a[t][J], col = a R + t < 3 R.  With the reduced
+// model's uniform weights and Z symmetric, W = sum_a U_a^T diag(1/S) Y_a holds
+// both operators' kernel terms: X^B1 needs w W, X^B2 needs
+// w sum_a U_a^T Z diag(1/S) U_a = w W^T.  So B is the basis alone: half the
+// columns of the weighted pair (w U_a, (w/S) U_a), and laid out once.
+//
+// A workgroup of eight waves owns 256 rows (32 per wave) and NB column tiles
+// of 16.  Per 32-column chunk of Z each wave forms its 32 x 32 piece as the
+// pair kernel does (pair_kernels.hip; Z_II = 1 set exactly), cut into three
+// BF16 parts that are A operands as they stand, and multiplies them with the
+// chunk's B parts from LDS: the six products hh, hm, mh, mm, hl, lh (the others
+// are below 2^-24 of the product), FP32 accumulation over all of Z.  The piece
+// of the next chunk is formed between this chunk's products.
+//
+// Bound: matrix pipe (144 of 160 instructions per chunk are the product's six
+// parts) and the board's power.  P = 20000, R = 180: 8.2e11 FLOP of FP32 work
+// were 7.1 ms on FP32 instructions (77 % of that peak) with both weighted
+// column sets.
+//
+// B of (chunk c, column group cg): pieces (tile T, part p) of 64 lanes x 8
+// values, value i of lane l being part p of U column 16 (NB cg + T) + l % 16
+// at row J = 32 c + 16 (i / 4) + 4 (l / 16) + i % 4.
+
+__global__ __launch_bounds__(256) void k_rom_b3(const float *__restrict__ Ude, int64_t P, int nch, int ncols, int tiles,
+                                                uint4 *__restrict__ Bk) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= Ppad * NCG * 128) return;
-  const int e = (int)(t & 127);
-  const int64_t blk = t >> 7;  // (c NCG + cg) 32 + jj
-  const int jj = (int)(blk & 31);
-  const int64_t cb = blk >> 5;
-  const int cg = (int)(cb % NCG);
-  const int64_t J = (cb / NCG) * 32 + jj;
-  const int l = e >> 2, nb = e & 3;
-  const int col = cg * 32 * NB + 32 * nb + l;
-  const int dR = 3 * R;
-  float v = 0.f;
-  if (nb < NB && J < P && col < 2 * dR) {
-    const int h = col / dR, rem = col % dR, a = rem / R, tt = rem % R;
-    const float wgt = h == 0 ? wv[J] : wv[J] * invS[J];
-    v = wgt * Ude[((int64_t)a * R + tt) * P + J];
+  const int lane = (int)(t & 63);
+  const int64_t ct = t >> 6;  // c tiles + T
+  if (ct >= (int64_t)nch * tiles) return;
+  const int64_t c = ct / tiles;
+  const int col = (int)(ct % tiles) * 16 + (lane & 15);
+  uint32_t o[3][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    Bf3 v[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = 2 * j + k;
+      const int64_t J = 32 * c + 16 * (i >> 2) + 4 * (lane >> 4) + (i & 3);
+      v[k] = split_bf3(J < P && col < ncols ? (double)Ude[(int64_t)col * P + J] : 0.0);
+    }
+    o[0][j] = (uint32_t)v[0].h | ((uint32_t)v[1].h << 16);
+    o[1][j] = (uint32_t)v[0].m | ((uint32_t)v[1].m << 16);
+    o[2][j] = (uint32_t)v[0].l | ((uint32_t)v[1].l << 16);
   }
-  Bk[t] = v;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) Bk[(ct * 3 + p) * 64 + lane] = uint4{o[p][0], o[p][1], o[p][2], o[p][3]};
 }
 
-// Balanced grid: the (column group, row group) items, column-group major,
-// times their nch chunks, cut into G equal runs (one workgroup each; at most
-// one run per item, so an item meets at most two runs).  A run's segment that
-// starts an item writes the item's output tile to Y; a run whose first segment
-// continues an item begun by the previous run writes that part to its slot,
-// slots[L] (kgemm32_tile(NB) floats: 256 rows x 32 NB columns), which
-// k_kgemm32_fixup then adds to Y.  Consecutive runs share an XCD (and its L2's
-// B blocks).
+// A run's segment that starts an item writes the item's output tile to Y; one
+// that continues an item (its run's first) writes to the run's slot,
+// kgemm_tile(NB) floats, which k_kgemm_fixup adds to Y.  Consecutive runs share
+// an XCD (and its L2's B blocks).
 template <int D, int NB>
-__global__ __launch_bounds__(kK32Waves * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_kernel_gemm32(
-    const float *__restrict__ xr, int nrb32, const float4 *__restrict__ KC, int nch, const float4 *__restrict__ Bk,
-    int NCG, int ncols, float kappa, float *__restrict__ Y, int64_t ldy, float *__restrict__ slots) {
-  constexpr int KP = mfma32_kslots(D), NK = KP / 2;
-  constexpr int KF4 = KP * 8;             // float4s of a chunk's K operand
-  constexpr int BF4 = 32 * 128 / 4;       // float4s of a chunk's B block
-  constexpr int SF4 = KF4 + BF4;          // float4s staged per chunk
-  constexpr int NST = (SF4 + kK32Waves * 64 - 1) / (kK32Waves * 64);
-  __shared__ float4 sb[2][SF4];
-  const int t = threadIdx.x, lane = t & 63, h = lane >> 5, li = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int n_rg = (nrb32 + kK32Waves - 1) / kK32Waves;
-  const int64_t U = (int64_t)NCG * n_rg * nch;
+__global__ __launch_bounds__(kKgWaves * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_kernel_gemm_bf3(
+    const uint4 *__restrict__ K3, const uint4 *__restrict__ Bk, KgMap map, int ncols, float *__restrict__ Y,
+    int64_t ldy, float *__restrict__ slots) {
+  constexpr int NQ = bf3_slices(D);
+  constexpr int KP = 2 * NQ, BP = 3 * NB, PC = KP + BP;  // pieces: K of the next chunk, B of this one
+  __shared__ uint4 buf[2][PC * 64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int G = (int)gridDim.x;
   const int L = G % 8 == 0 ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
-  const int64_t u_beg = (int64_t)L * U / G, u_end = (int64_t)(L + 1) * U / G;
+  const int64_t nch = map.nch;
+  const int64_t u_beg = map.run_start(L), u_end = map.run_start(L + 1);
+  const int diag_i = (lane & 15) - 4 * (lane >> 4);
+  bf16x8 neg[2];
+  minus_identity(lane, neg);
   // the segments that start an item first (every run's first segment then
   // starts at chunk 0, so the runs of a column group read its B blocks nearly
   // in step through their XCD's L2), a continued item's part last
@@ -332,164 +338,167 @@ __global__ __launch_bounds__(kK32Waves * 64) __attribute__((amdgpu_waves_per_eu(
   const bool continued = u_beg > i_first * nch;
   const int64_t i_lo = continued ? i_first + 1 : i_first;
   const int64_t n_seg = (u_end - 1) / nch - i_lo + 1 + (continued ? 1 : 0);
-  const int64_t run_len = u_end - u_beg;
-  int64_t seg_done = 0;  // units of the run in the segments before this one
   for (int64_t sgi = 0; sgi < n_seg; ++sgi) {
     const int64_t item = continued && sgi == n_seg - 1 ? i_first : i_lo + sgi;
     const int c0 = (int)(max(u_beg, item * nch) - item * nch);
     const int c1 = (int)(min(u_end, (item + 1) * nch) - item * nch);
-    const int cg = (int)(item / n_rg);
-    const int rb = (int)(item % n_rg) * kK32Waves + wave;  // this wave's 32-row block
-    // row operands: slot 2 kk + h of row I is x_I[k] (k < D), 1 (k == D), the
-    // row norm term (k == D + 1), 0 beyond
-    float qv[NK];
-    {
-      const int rr = rb < nrb32 ? rb : 0;  // waves past the rows compute on block 0, unwritten
-      const float *x = xr + ((int64_t)rr * 32 + li) * D;
-      float nrm = 0.f;
+    const int cg = (int)(item / map.n_rg);
+    const int rb0 = (int)(item % map.n_rg) * (kKgWaves * 2) + wave * 2;  // this wave's two 16-row blocks
+    auto stage = [&](int c, int b) {  // K of chunk c + 1 and B of chunk c
 #pragma unroll
-      for (int a = 0; a < D; ++a) nrm = __builtin_fmaf(x[a], x[a], nrm);
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) {
-        const int k = 2 * kk + h;
-        qv[kk] = k < D ? x[k < D ? k : 0] : (k == D ? 1.f : (k == D + 1 ? -kappa * nrm : 0.f));
-      }
-    }
-    auto src = [&](int c, int uu) -> float4 {
-      return uu < KF4 ? KC[(int64_t)c * KF4 + uu] : Bk[((int64_t)c * NCG + cg) * BF4 + (uu - KF4)];
-    };
-    float4 pre[NST];
-#pragma unroll
-    for (int i = 0; i < NST; ++i) {
-      const int uu = t + kK32Waves * 64 * i;
-      if (uu < SF4) sb[0][uu] = src(c0, uu);
-    }
-    __syncthreads();
-    floatx16 acc[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
-    for (int c = c0; c < c1; ++c) {
-      {  // scalar: issue priority by the share of the run still to do, so that the
-         // two workgroups of a CU finish together (the SIMDs issue for the oldest
-         // ready wave first): 3 above half, then 2, 1, 0 below 20 %, 5 %
-        const int64_t rem = run_len - (seg_done + (c - c0));
-        if (20 * rem > 10 * run_len) __builtin_amdgcn_s_setprio(3);
-        else if (20 * rem > 4 * run_len) __builtin_amdgcn_s_setprio(2);
-        else if (20 * rem > run_len) __builtin_amdgcn_s_setprio(1);
-        else __builtin_amdgcn_s_setprio(0);
-      }
-      const int buf = (c - c0) & 1;
-      if (c + 1 < c1) {
-#pragma unroll
-        for (int i = 0; i < NST; ++i) {
-          const int uu = t + kK32Waves * 64 * i;
-          pre[i] = uu < SF4 ? src(c + 1, uu) : float4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < (PC + kKgWaves - 1) / kKgWaves; ++i) {
+        const int pc = wave + kKgWaves * i;
+        if (pc < PC && (pc >= KP || c + 1 < c1)) {  // scalar
+          const uint4 *src = pc < KP ? K3 + ((int64_t)(c + 1) * KP + pc) * 64
+                                     : Bk + (((int64_t)c * map.NCG + cg) * BP + (pc - KP)) * 64;
+          piece_to_lds(src, &buf[b][pc * 64], lane);
         }
       }
-      const float *sK = reinterpret_cast<const float *>(sb[buf]) + h * 32 + li;
-      const float4 *sB = sb[buf] + KF4 + h * 128 + li;  // row J(v, h) = 8 (v / 4) + 4 h + v % 4
-      floatx16 z;
+    };
+    stage(c0, 0);
+    bf16x8 q[2][NQ];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) z[v] = 0.f;
+    for (int r = 0; r < 2; ++r) bf3_row_operand<D>(K3, rb0 + r, lane, q[r]);
+    floatx4 e[2][2];
+    bf16x8 ep[2][3];  // the parts of this chunk's piece of Z
+    auto distances = [&](const uint4 *kb) {
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk) z = __builtin_amdgcn_mfma_f32_32x32x2f32(sK[kk * 64], qv[kk], z, 0, 0, 0);
+      for (int m = 0; m < NQ; ++m)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) z[v] = __builtin_amdgcn_exp2f(z[v]);
-      if (c == rb) {  // scalar branch: the self pair has Z_II = K_h(0) = 1 exactly
+        for (int b = 0; b < 2; ++b) {
+          const bf16x8 ka = as_bf8(kb[(b * NQ + m) * 64 + lane]);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            if (m == 0) e[r][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+            e[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, q[r][m], e[r][b], 0, 0, 0);
+          }
+        }
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) e[r][b][i] = __builtin_amdgcn_exp2f(e[r][b][i]);
+    };
+    auto self_pairs = [&](int c) {
+      if (c == rb0 >> 1) {  // scalar branch: Z_II = K_h(0) = 1 exactly
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int v = 0; v < 16; ++v) z[v] = (8 * (v >> 2) + 4 * h + (v & 3)) == li ? 1.f : z[v];
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) e[r][r][i] = diag_i == i ? 1.f : e[r][r][i];
       }
+    };
+    auto cut = [&](bf16x8 (&o)[2][3]) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float4 b = sB[(8 * (v >> 2) + (v & 3)) * 32];
-        const float bv[4] = {b.x, b.y, b.z, b.w};
+      for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(z[v], bv[nb], acc[nb], 0, 0, 0);
-      }
-      if (c + 1 < c1) {
+        for (int r = 0; r < 2; ++r) {
+          o[r][p] = upper_halves(e[r][0], e[r][1]);
+          if (p < 2) {
 #pragma unroll
-        for (int i = 0; i < NST; ++i) {
-          const int uu = t + kK32Waves * 64 * i;
-          if (uu < SF4) sb[buf ^ 1][uu] = pre[i];
+            for (int b = 0; b < 2; ++b)
+              e[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(neg[b], o[r][p], e[r][b], 0, 0, 0);
+          }
         }
-      }
-      // every chunk ends at a barrier, the segment's last one too: the next
-      // segment's first stage overwrites buffer 0
+    };
+    floatx4 acc[2][NB];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int T = 0; T < NB; ++T) acc[r][T] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto products = [&](const uint4 *bb, int T) {
+      bf16x8 bv[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) bv[p] = as_bf8(bb[(T * 3 + p) * 64 + lane]);
+      constexpr int pe[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int x = 0; x < 6; ++x)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          acc[r][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep[r][pe[x]], bv[pb[x]], acc[r][T], 0, 0, 0);
+    };
+    distances(K3 + (int64_t)c0 * KP * 64);
+    self_pairs(c0);
+    cut(ep);
+    for (int c = c0; c < c1; ++c) {
+      const int b = (c - c0) & 1;
+      // each wave waits for its own pieces and the barrier publishes them; it
+      // also ends the reads of the buffer the next stage goes to
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
+      if (c + 1 < c1) stage(c + 1, b ^ 1);
+      const uint4 *bb = buf[b] + KP * 64;
+      distances(buf[b]);  // of chunk c + 1 (past the last chunk: not used)
+#pragma unroll
+      for (int T = 0; T < NB / 2; ++T) products(bb, T);
+      self_pairs(c + 1);
+      bf16x8 en[2][3];
+      cut(en);
+#pragma unroll
+      for (int T = NB / 2; T < NB; ++T) products(bb, T);
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) ep[r][p] = en[r][p];
     }
-    // output lane l, register v: row 32 rb + 8 (v / 4) + 4 h + v % 4, column 32 NB cg + 32 nb + li.
-    // The output addresses are formed here: formed ahead of the chunk loop
-    // (they do not depend on it) they stay live across it and spill.
-    float *ybase = Y, *sbase = slots;
-    int64_t ld = ldy;
-    int el = lane;
-    asm volatile("" : "+s"(ybase), "+s"(sbase), "+s"(ld), "+v"(el));
-    const int eh = el >> 5, eli = el & 31;
-    if (c0 > 0) {  // a continued item: the whole tile to this run's slot
-      float *o = sbase + (int64_t)L * kgemm32_tile(NB) + (wave * 32 + 4 * eh) * (32 * NB) + eli;
+    __syncthreads();  // the next segment may overwrite either buffer
+    // lane holds row 4 (lane / 16) + i of each block, column 16 T + lane % 16
+    const bool first = c0 == 0;
+    float *o = first ? Y + (int64_t)rb0 * 16 * ldy + (int64_t)cg * 16 * NB
+                     : slots + (int64_t)L * kgemm_tile(NB) + (wave * 32) * (16 * NB);
+    const int64_t ld = first ? ldy : 16 * NB;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+    for (int T = 0; T < NB; ++T) {
+      if (first && cg * 16 * NB + 16 * T + (lane & 15) >= ncols) continue;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[(8 * (v >> 2) + (v & 3)) * (32 * NB) + 32 * nb] = acc[nb][v];
-    } else if (rb < nrb32) {
-      float *o = ybase + ((int64_t)rb * 32 + 4 * eh) * ld + cg * 32 * NB + eli;
+      for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if (cg * 32 * NB + 32 * nb + eli >= ncols) break;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[(8 * (v >> 2) + (v & 3)) * ld + 32 * nb] = acc[nb][v];
-      }
+        for (int i = 0; i < 4; ++i) o[(16 * r + 4 * (lane >> 4) + i) * ld + 16 * T + (lane & 15)] = acc[r][T][i];
     }
-    seg_done += c1 - c0;
   }
 }
 
-// Y += the slot of every run whose first segment continued an item (block
-// (x, L): elements x 256 .. of run L's tile).  An item meets at most two runs,
-// so no two slots add to the same tile.
-__global__ void k_kgemm32_fixup(const float *__restrict__ slots, int nrb32, int nch, int NCG, int NB, int ncols,
-                                float *__restrict__ Y, int64_t ldy) {
-  const int L = (int)blockIdx.y, G = (int)gridDim.y;
-  const int n_rg = (nrb32 + kK32Waves - 1) / kK32Waves;
-  const int64_t U = (int64_t)NCG * n_rg * nch;
-  const int64_t u0 = (int64_t)L * U / G;
-  const int64_t item = u0 / nch;
-  if (u0 == item * nch) return;  // the run starts its first item
-  const int cg = (int)(item / n_rg), rg = (int)(item % n_rg);
+// Y += the slots of the runs that continue item blockIdx.y, in run order
+// (block x: elements x 256 .. of its tile).
+__global__ __launch_bounds__(256) void k_kgemm_fixup(const float *__restrict__ slots, KgMap map, int ncols,
+                                                     float *__restrict__ Y, int64_t ldy) {
+  const int64_t item = blockIdx.y;
+  const int64_t u0 = item * map.nch, u1 = u0 + map.nch;
+  int64_t L = (u0 * map.G) / map.units();  // a run that starts at or before u0
+  while (L < map.G && map.run_start(L) <= u0) ++L;
+  if (L >= map.G || map.run_start(L) >= u1) return;
   const int e = (int)blockIdx.x * 256 + threadIdx.x;
-  const int tile = kgemm32_tile(NB);
-  if (e >= tile) return;
-  const int r = e / (32 * NB), cc = e % (32 * NB);
-  const int64_t row = (int64_t)rg * 32 * kK32Waves + r;
-  const int col = cg * 32 * NB + cc;
-  if (row < (int64_t)nrb32 * 32 && col < ncols) Y[row * ldy + col] += slots[(int64_t)L * tile + e];
+  const int W = 16 * map.NB, r = e / W, cc = e % W;
+  const int col = (int)(item / map.n_rg) * W + cc;
+  if (col >= ncols) return;
+  float *y = Y + ((item % map.n_rg) * kKgRows + r) * ldy + col;
+  float v = *y;
+  for (; L < map.G && map.run_start(L) < u1; ++L) v += slots[L * kgemm_tile(map.NB) + e];
+  *y = v;
 }
-
-struct KGemm32Args {
-  const float *xr;
-  int nrb32;
-  const float4 *KC;
-  int nch;
-  const float4 *Bk;
-  int NCG, ncols;
-  float kappa;
-  float *Y;
-  int64_t ldy;
-  float *slots;
-};
 
 template <int D>
-void launch_kgemm32(int NB, int G, const KGemm32Args &a, hipStream_t s) {
-  const dim3 grid((unsigned)G), block(kK32Waves * 64);
-  switch (NB) {
-    case 1: k_kernel_gemm32<D, 1><<<grid, block, 0, s>>>(a.xr, a.nrb32, a.KC, a.nch, a.Bk, a.NCG, a.ncols, a.kappa, a.Y, a.ldy, a.slots); break;
-    case 2: k_kernel_gemm32<D, 2><<<grid, block, 0, s>>>(a.xr, a.nrb32, a.KC, a.nch, a.Bk, a.NCG, a.ncols, a.kappa, a.Y, a.ldy, a.slots); break;
-    case 3: k_kernel_gemm32<D, 3><<<grid, block, 0, s>>>(a.xr, a.nrb32, a.KC, a.nch, a.Bk, a.NCG, a.ncols, a.kappa, a.Y, a.ldy, a.slots); break;
-    default: k_kernel_gemm32<D, 4><<<grid, block, 0, s>>>(a.xr, a.nrb32, a.KC, a.nch, a.Bk, a.NCG, a.ncols, a.kappa, a.Y, a.ldy, a.slots); break;
+void launch_kgemm_bf3(const KgMap &m, const uint4 *K3, const uint4 *Bk, int ncols, float *Y, int64_t ldy, float *slots,
+                      hipStream_t s) {
+  const dim3 grid((unsigned)m.G), block(kKgWaves * 64);
+  switch (m.NB) {
+    case 4: k_kernel_gemm_bf3<D, 4><<<grid, block, 0, s>>>(K3, Bk, m, ncols, Y, ldy, slots); break;
+    case 8: k_kernel_gemm_bf3<D, 8><<<grid, block, 0, s>>>(K3, Bk, m, ncols, Y, ldy, slots); break;
+    default: k_kernel_gemm_bf3<D, 12><<<grid, block, 0, s>>>(K3, Bk, m, ncols, Y, ldy, slots); break;
   }
+}
+
+// X^B1 = (w W - I1) / h^2, X^B2 = (w W^T - G2) / h^2 (XB2 holds G2 on entry), X^B their sum.
+__global__ void k_rom_assemble(const float *__restrict__ W, const float *__restrict__ I1, int R, float w, float ih2,
+                               float *__restrict__ XB1, float *__restrict__ XB2, float *__restrict__ XB) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (int64_t)R * R) return;
+  const int i = (int)(t / R), j = (int)(t % R);
+  const float a = ih2 * (w * W[t] - I1[t]), b = ih2 * (w * W[(int64_t)j * R + i] - XB2[t]);
+  XB1[t] = a;
+  XB2[t] = b;
+  XB[t] = a + b;
 }
 
 // ---- FP16-split kernel-GEMM (used with the FP16-split pair kernels) ---------
@@ -1010,6 +1019,7 @@ struct vds_rom_s {
   int R = 0;
   RomLayout L{};
   char *ws = nullptr;
+  bool b3_ready = false;  // Bsw holds the basis as the default kernel-GEMM reads it
   float *Ude, *Mbig, *XH, *I1, *XB1, *XB2, *XB, *Bsw, *Y, *qt, *T, *invS, *part, *psave, *pprev;
   double *red;
 };
@@ -1030,6 +1040,68 @@ void reconstruct_qt(vds_rom r, const float *p) {
         [&] { launch_pod_reconstruct(r->U, m, r->R, c->prob.nb, p, r->qt, c->stream); });
 }
 
+// The basis as the B operand of the default kernel-GEMM, laid out once.
+void prepare_b3(vds_rom r) {
+  const vds_ctx c = r->ctx;
+  const KgMap &m = r->L.kg;
+  const int tiles = m.NB * m.NCG;
+  k_rom_b3<<<nblk256((int64_t)m.nch * tiles * 64), 256, 0, c->stream>>>(r->Ude, c->prob.P, m.nch, 3 * r->R, tiles,
+                                                                        reinterpret_cast<uint4 *>(r->Bsw));
+  r->b3_ready = true;
+}
+
+// X^B1, X^B2 and X^B from the pair operands, S and T at q~ with the default
+// kernel-GEMM (uniform weights: see there).
+vds_status operators_bf3(vds_rom r) {
+  vds_ctx c = r->ctx;
+  const int R = r->R;
+  const int64_t P = c->prob.P, RR = (int64_t)R * R;
+  const RomLayout &L = r->L;
+  hipStream_t s = c->stream;
+  if (!r->b3_ready) prepare_b3(r);
+  const int ncols = 3 * R;
+  const int64_t ldy = rom_ldy3(R);
+  float *W = r->Y + c->ep.Ppad * ldy;
+  timed(c, VDS_TIMER_KGEMM, 2.0 * (double)P * P * ncols, [&] {
+    const uint4 *k3 = static_cast<const uint4 *>(c->f16.QH), *bk = reinterpret_cast<const uint4 *>(r->Bsw);
+    switch (c->ep.D) {
+      case 3: launch_kgemm_bf3<3>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
+      case 6: launch_kgemm_bf3<6>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
+      case 9: launch_kgemm_bf3<9>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
+      case 12: launch_kgemm_bf3<12>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
+      default: launch_kgemm_bf3<15>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
+    }
+    k_kgemm_fixup<<<dim3((unsigned)(kgemm_tile(L.kg.NB) / 256), (unsigned)L.kg.items()), 256, 0, s>>>(
+        r->part, L.kg, ncols, r->Y, ldy);
+  });
+  GemmShape g;
+  g.M = R;
+  g.N = R;
+  g.K = P;
+  g.nbatch = 3;
+  g.A = r->Ude;
+  g.lda = P;
+  g.sA = (int64_t)R * P;
+  g.B = r->Y;  // W = sum_a U_a^T diag(1/S) Y_a
+  g.ldb = ldy;
+  g.sB = R;
+  g.b_mn = true;
+  g.scale = r->invS;
+  g.C = W;
+  g.ldc = R;
+  g.splits = gemm_splits(R, R, P);
+  rom_gemm(r, g, 2.0 * 3 * RR * P);
+  g.B = r->Ude;  // G2 = sum_a U_a^T diag(T) U_a
+  g.ldb = P;
+  g.sB = (int64_t)R * P;
+  g.b_mn = false;
+  g.scale = r->T;
+  g.C = r->XB2;
+  rom_gemm(r, g, 2.0 * 3 * RR * P);
+  k_rom_assemble<<<nblk256(RR), 256, 0, s>>>(W, r->I1, R, c->ep.uniform_w, c->ep.inv_h2, r->XB1, r->XB2, r->XB);
+  return hip_check(c, hipGetLastError(), "reduced operators");
+}
+
 vds_status freeze(vds_rom r, const float *p) {
   vds_ctx c = r->ctx;
   const int R = r->R;
@@ -1042,6 +1114,8 @@ vds_status freeze(vds_rom r, const float *p) {
   eval_pass_b(c, nullptr);
   k_rom_scalars<<<nblk256(Ppad), 256, 0, s>>>(c->part, c->smap, Ppad, P, c->ep.D, c->S, c->wv, r->T,
                                               r->invS);
+  if (c->ep.bf3) return operators_bf3(r);
+  r->b3_ready = false;  // the forms below lay their weighted columns out in Bsw
   // Y = Z B, in the FP16-split form when the context's pair kernels use it
   if (c->ep.vhalf) {
     const float wmax = c->ep.uniform_w;  // the reduced model runs with uniform weights
@@ -1073,30 +1147,6 @@ vds_status freeze(vds_rom r, const float *p) {
         case 4: k_kernel_gemm16<4><<<grid, 256, 0, s>>>(c->QB, c->KA, nrb, ncc, bh, lo_off, L.NB16, 3 * R, s0, s1, 1.f, r->Y, L.ldy); break;
         default: k_kernel_gemm16<5><<<grid, 256, 0, s>>>(c->QB, c->KA, nrb, ncc, bh, lo_off, L.NB16, 3 * R, s0, s1, 1.f, r->Y, L.ldy); break;
       }
-    });
-  } else if (c->ep.bf3) {
-    // the 32x32 form reads the pair kernel's operands as the passes left them;
-    // column blocks per workgroup and runs were fixed when the model was laid
-    // out (its slots hold G tiles of that width)
-    const int NB = L.kg_nb, G = L.kg_runs;
-    const int NCG = (int)((2 * 3 * R + 32 * NB - 1) / (32 * NB));
-    k_rom_b32<<<nblk256(Ppad * NCG * 128), 256, 0, s>>>(r->Ude, c->wv, r->invS, P, Ppad, R, NCG, NB, r->Bsw);
-    const int nrb32 = (int)(Ppad / 32), nch = (int)((P + 31) / 32);
-    const int ncols = 2 * 3 * R;
-    const float4 *kc = reinterpret_cast<const float4 *>(c->KA), *bk = reinterpret_cast<const float4 *>(r->Bsw);
-    const double flops = 2.0 * (double)P * P * 2 * 3 * R;
-    float *slots = reinterpret_cast<float *>(r->part);
-    timed(c, VDS_TIMER_KGEMM, flops, [&] {
-      const KGemm32Args a{c->xc, nrb32, kc, nch, bk, NCG, ncols, c->ep.kappa, r->Y, L.ldy, slots};
-      switch (c->ep.D) {
-        case 3: launch_kgemm32<3>(NB, G, a, s); break;
-        case 6: launch_kgemm32<6>(NB, G, a, s); break;
-        case 9: launch_kgemm32<9>(NB, G, a, s); break;
-        case 12: launch_kgemm32<12>(NB, G, a, s); break;
-        default: launch_kgemm32<15>(NB, G, a, s); break;
-      }
-      k_kgemm32_fixup<<<dim3((unsigned)((kgemm32_tile(NB) + 255) / 256), (unsigned)G), 256, 0, s>>>(
-          slots, nrb32, nch, NCG, NB, ncols, r->Y, L.ldy);
     });
   } else {
     // the 16x16 FP32 forms (VDS_PAIR_MFMA, VDS_PAIR_VALU) read the 16-row operand layout
@@ -1229,6 +1279,7 @@ vds_status vds_rom_create(vds_ctx c, const float *U, int32_t R, void *ws, size_t
   g.splits = gemm_splits(3 * R, 3 * R, P);
   rom_gemm(r, g, 2.0 * 9.0 * R * R * P);
   k_hydro<<<nblk256((int64_t)R * R), 256, 0, s>>>(r->Mbig, R, c->ep, r->XH, r->I1);
+  if (c->ep.bf3) prepare_b3(r);
   st = hip_check(c, hipGetLastError(), "reduced model setup");
   if (st != VDS_OK) {
     delete r;

@@ -157,15 +157,17 @@ Layout make_layout(const vds_problem &p) {
     off += round_up((int64_t)bytes, 256);
     return o;
   };
-  const int64_t vw = std::max(16, 8 * bf3_tiles(D));  // floats per particle of V
-  L.VA = take(sizeof(float) * Ppad * vw);
-  // (density rows of VDS_PAIR_MFMA32 take QB, KA and VB together)
+  // VDS_PAIR_MFMA32 does not use QB and KA: its V operands run from VA on into
+  // QB and from VB on into KA where they need more than 16 floats (D >= 12),
+  // and the density rows take the buffers from VB to xb0
+  L.VA = take(sizeof(float) * Ppad * 16);
   L.QB = take(sizeof(float) * Ppad * KK * 4);
+  L.VB = take(sizeof(float) * Ppad * 16);
   L.KA = take(sizeof(float) * Ppad * KK * 4);
-  L.VB = take(sizeof(float) * Ppad * vw);
+  L.t1 = take(sizeof(float) * Ppad * D);
+  L.xb0 = take(sizeof(float) * p.P * D);
   L.part = take(sizeof(float) * (size_t)kMaxSplits * Ppad * 16);
   L.xc = take(sizeof(float) * Ppad * D);
-  L.t1 = take(sizeof(float) * Ppad * D);
   L.S = take(sizeof(float) * Ppad);
   L.wv = take(sizeof(float) * Ppad);
   L.meanp = take(sizeof(double) * nblk * 16);
@@ -180,7 +182,6 @@ Layout make_layout(const vds_problem &p) {
   L.KH = take(sizeof(uint16_t) * Ppad * 32 * f16_slices(D));
   L.RN = take(sizeof(float) * Ppad);
   L.hist = take(sizeof(unsigned long long) * 2 * kHistBins);
-  L.xb0 = take(sizeof(float) * p.P * D);
   L.xb1 = take(sizeof(float) * p.P * D);
   L.xpred = take(sizeof(float) * p.P * D);
   L.total = off;
@@ -209,7 +210,6 @@ void fill_params(vds_ctx c) {
   e.log_norm = (float)(0.5 * e.D * std::log(2.0 * M_PI * p.h * p.h));
   e.KQ = f16_slices(e.D);
   e.cs = (float)std::sqrt(2.0 * 1.4426950408889634 / (2.0 * p.h * p.h));
-  e.KP = mfma32_kslots(e.D);
   c->nblk = (int)((p.P + kRedBlock - 1) / kRedBlock);
   c->nblk_comb = (int)((p.P * 16 + kRedBlock - 1) / kRedBlock);
   apply_tuning(c, c->tune);  // operand formats of the default implementation
@@ -709,11 +709,12 @@ vds_status vds_density_at(vds_ctx c, const float *q, const float *w, const float
   // foreign rows go through the Q-operand buffer in blocks of Ppad rows
   for (int64_t r0 = 0; r0 < ny; r0 += e.Ppad) {
     const int64_t nr = std::min<int64_t>(e.Ppad, ny - r0);
-    launch_density_rows(e, y + r0 * e.D, nr, c->meanp, c->nblk, c->QB, &c->f16, c->stream);
+    float *rows = e.bf3 ? c->VB : c->QB;
+    launch_density_rows(e, y + r0 * e.D, nr, c->meanp, c->nblk, rows, &c->f16, c->stream);
     const int64_t nrb = round_up(nr, kRowAlign) / 16;
     timed(c, VDS_TIMER_PAIR, (double)nr * (double)c->prob.P, [&] {
       launch_pair_pass(c->tune, e.KK, e.D, c->QB, nrb, c->KA, c->VA, ncol_chunks(c), e.Ppad, c->xc, false,
-                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream, c->QB);
+                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream, rows);
     });
     launch_density_out(e, c->part, pair_split_map(c->tune, e.D, nrb, ncol_chunks(c)), nr, norm, f + r0, c->stream);
   }

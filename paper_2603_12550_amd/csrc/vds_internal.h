@@ -63,9 +63,8 @@ struct EvalParams {
   int qhalf;          // FP16 distance operands QH/KH and row norms RN written too (VDS_PAIR_MFMA_F16X2_ALL)
   int KQ;             // FP16 distance slices of 32 products: f16_slices(D)
   float cs;           // sqrt(2 kappa): the distance operands are cs x
-  int bf3;            // operands of VDS_PAIR_MFMA32: BF16 thirds K3 and V3 (see bf3_index, v3_index) and KC;
+  int bf3;            // operands of VDS_PAIR_MFMA32: BF16 thirds K3 and V3 (see bf3_index, v3_index);
                       // QB/KA in the 16-row layout are then not written
-  int KP;             // K slots of KC (the kernel-GEMM's distance product): D + 2 rounded up to even
 };
 
 // Operands of VDS_PAIR_MFMA32 (see pair_kernels.hip), every number as three
@@ -83,9 +82,6 @@ struct EvalParams {
 //       bf3_tiles(D) tiles of 16 columns, 32 rows J each, at v3_index (in 16-bit
 //       units).  Ppad * bf3_tiles(D) * 32 bytes, in VA or VB and, for D >= 12,
 //       the first part of the buffer behind (QB or KA).
-//   KC: slot k < KP of column J at [((J / 32) * KP + k) * 32 + J % 32], FP32 (the
-//       kernel-GEMM of the reduced model): slot k < D holds 2 kappa x_J[k], slot
-//       D the column norm term -kappa |x_J|^2, slot D + 1 one, zero beyond.
 __host__ __device__ constexpr int bf3_slices(int D) { return (6 * D + 6 + 31) / 32; }
 __host__ __device__ constexpr int bf3_tiles(int D) { return (3 * (D + 1) + 15) / 16; }
 __host__ __device__ inline int64_t bf3_index(int64_t J, int dd, int NQ) {
@@ -94,8 +90,6 @@ __host__ __device__ inline int64_t bf3_index(int64_t J, int dd, int NQ) {
 __host__ __device__ inline int64_t v3_index(int64_t J, int c, int NT) {
   return (((J >> 5) * NT + (c >> 4)) * 64 + (c & 15) + 16 * ((J & 15) >> 2)) * 8 + 4 * ((J >> 4) & 1) + (J & 3);
 }
-__host__ __device__ constexpr int mfma32_kslots(int D) { return (D + 3) & ~1; }
-__host__ __device__ inline int64_t kc_index(int64_t J, int k, int KP) { return ((J >> 5) * KP + k) * 32 + (J & 31); }
 
 // FP16 MFMA slices (32 products each) of the split distance product: three
 // per configuration component and two for the column norm.
