@@ -77,7 +77,7 @@ MlpLayout mlp_layout(int nin, int w, int nout, int B) {
   L.ysc = take(sizeof(float) * nout);
   L.xin = take(sizeof(float) * Bp * nin);
   L.tin = take(sizeof(float) * Bp * nout);
-  const int64_t g1 = (int64_t)gemm_splits(w, nin, Bp) * w * nin, g3 = (int64_t)gemm_splits(nout, w, Bp) * nout * w;
+  const int64_t g1 = (int64_t)gemm_splits_small(w, nin, Bp, 1024) * w * nin, g3 = (int64_t)gemm_splits_small(nout, w, Bp, 1024) * nout * w;
   const int64_t g0 = (int64_t)Bp * std::max(nout, std::max(w, nin)) * 2;
   L.part = take(sizeof(float) * std::max(std::max(g1, g3), g0));
   L.lossp = take(sizeof(double) * ((int64_t)(Bp * nout + 255) / 256 + 2));
@@ -565,7 +565,7 @@ void dense(vds_mlp m, const float *A, int n, int K, const float *B, int N, float
   g.ldb = K;
   g.C = C;
   g.ldc = N;
-  launch_gemm(g, m->part, m->s);
+  launch_gemm_small(g, m->part, m->s);
 }
 
 void forward_fp32(vds_mlp m, const float *X, int n) {
@@ -591,8 +591,8 @@ void weight_grad(vds_mlp m, const float *dZ, int n, int N, const float *A, int K
   g.b_mn = true;
   g.C = dW;
   g.ldc = K;
-  g.splits = gemm_splits(N, K, n, 512);
-  launch_gemm(g, m->part, m->s);
+  g.splits = gemm_splits_small(N, K, n, 512);
+  launch_gemm_small(g, m->part, m->s);
 }
 
 // dA (n x K) = dZ W with dZ: n x N, W: N x K
@@ -608,7 +608,7 @@ void input_grad(vds_mlp m, const float *dZ, int n, int N, const float *W, int K,
   g.b_mn = true;
   g.C = dA;
   g.ldc = K;
-  launch_gemm(g, m->part, m->s);
+  launch_gemm_small(g, m->part, m->s);
 }
 
 void backward_fp32(vds_mlp m, const float *X, const float *T, int n) {

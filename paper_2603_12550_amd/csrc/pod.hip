@@ -153,7 +153,7 @@ PodLayout pod_layout(int64_t m, int32_t n, int32_t R) {
   L.GU64 = take(sizeof(double) * R * R);
   L.Linv = take(sizeof(float) * R * R);
   L.work64 = take(sizeof(double) * R * R);
-  const int sg = gemm_splits(n, n, m, 1024, true), su = gemm_splits(R, R, m);
+  const int sg = gemm_splits(n, n, m, 1, true), su = gemm_splits(R, R, m);
   const size_t part = std::max({sizeof(float) * (size_t)sg * n * n, sizeof(float) * (size_t)su * R * R,
                                 sizeof(float) * (size_t)m * R});
   L.part = take(part);
@@ -184,7 +184,7 @@ vds_status gram_into(vds_ctx c, const float *X, int64_t m, int n, float *gram, f
   g.C = gram;
   g.ldc = n;
   g.symmetric = true;
-  g.splits = gemm_splits(n, n, m, 1024, true);
+  g.splits = gemm_splits(n, n, m, 1, true);
   // the symmetric product's own work: n (n + 1) / 2 entries of 2 m FLOP
   timed(c, VDS_TIMER_GEMM, (double)n * (n + 1) * (double)m, [&] { launch_gemm(g, part, c->stream); });
   return hip_check(c, hipGetLastError(), "gram");
@@ -319,7 +319,7 @@ vds_status vds_pod_basis(vds_ctx c, const float *X, int64_t m, int32_t n, int32_
 size_t vds_pod_map_workspace_bytes(const vds_problem *prob, int32_t R) {
   if (prob == nullptr || prob->P < 1 || prob->nb < 1 || R < 1) return 0;
   const int64_t m = 3 * prob->P;
-  const size_t a = sizeof(float) * (size_t)gemm_splits(prob->nb, R, m, 2048) * prob->nb * R;
+  const size_t a = sizeof(float) * (size_t)gemm_splits_small(prob->nb, R, m, 2048) * prob->nb * R;
   const size_t b = sizeof(float) * (size_t)m * prob->nb;
   const size_t c = sizeof(float) * (size_t)kProjChunks * prob->nb * R;
   return (std::max(std::max(a, b), c) + 255) / 256 * 256;

@@ -108,7 +108,7 @@ RomLayout rom_layout(const vds_problem &p, int R) {
   const int64_t m = 3 * P;
   // (the GEMMs' split partials, or the kernel-GEMM's continuation tiles: one per run)
   const size_t part = std::max({sizeof(float) * (size_t)gemm_splits(3 * R, 3 * R, P) * 9 * R * R,
-                                sizeof(float) * (size_t)gemm_splits(R, R, P) * R * R,
+                                sizeof(float) * (size_t)gemm_splits(R, R, P, 3) * R * R,
                                 sizeof(float) * (size_t)m * p.nb,
                                 sizeof(float) * (size_t)L.kg.G * kgemm_tile(L.kg.NB)});
   L.part = take(part);
@@ -1089,7 +1089,7 @@ vds_status operators_bf3(vds_rom r) {
   g.scale = r->invS;
   g.C = W;
   g.ldc = R;
-  g.splits = gemm_splits(R, R, P);
+  g.splits = gemm_splits(R, R, P, 3);
   rom_gemm(r, g, 2.0 * 3 * RR * P);
   g.B = r->Ude;  // G2 = sum_a U_a^T diag(T) U_a
   g.ldb = P;
@@ -1186,7 +1186,7 @@ vds_status freeze(vds_rom r, const float *p) {
     g.C = r->XB1;
     g.ldc = R;
     g.accumulate = true;
-    g.splits = gemm_splits(R, R, P);
+    g.splits = gemm_splits(R, R, P, 3);
     rom_gemm(r, g, 2.0 * 3 * RR * P);
   }
   // X^B2 = -(1/h^2) sum_a U_a^T diag(T) U_a + (1/h^2) sum_a U_a^T Y2_a
@@ -1206,7 +1206,7 @@ vds_status freeze(vds_rom r, const float *p) {
     g.alpha = -ih2;
     g.C = r->XB2;
     g.ldc = R;
-    g.splits = gemm_splits(R, R, P);
+    g.splits = gemm_splits(R, R, P, 3);
     rom_gemm(r, g, 2.0 * 3 * RR * P);
     g.B = r->Y + 3 * R;
     g.ldb = L.ldy;

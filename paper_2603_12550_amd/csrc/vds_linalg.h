@@ -35,19 +35,39 @@ struct GemmShape {
   bool symmetric = false;
 };
 
-size_t gemm_part_bytes(const GemmShape &g);
+// Large products: BF16 matrix cores, three BF16 parts per FP32 factor.  Sums
+// within a split in FP32, over the splits in FP64.
 void launch_gemm(const GemmShape &g, float *part, hipStream_t s);
+// Small products: FP32 matrix cores, one workgroup per 64 x 64 tile and split.
+void launch_gemm_small(const GemmShape &g, float *part, hipStream_t s);
 void launch_cholesky(double *A, int n, double shift, int *info, hipStream_t s);
 void launch_tri_inverse(const double *L, int n, double *work, float *Linv, hipStream_t s);
 void launch_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);
 
-// Split count giving roughly `target` workgroups for an M x N output.
-inline int gemm_splits(int M, int N, int64_t K, int target = 1024, bool symmetric = false) {
-  const int64_t tm = (M + 63) / 64, tn = (N + 63) / 64;
+constexpr int kGemmTile = 96;  // output tile edge of launch_gemm
+constexpr int kGemmSlab = 32;  // k-depth of one round
+
+// Splits of launch_gemm's K (all batches end to end, in rounds of 32): two
+// workgroups per compute unit, at least four rounds each, a multiple of eight
+// from eight on (a split's tiles then share an XCD), and at most 64 so that the
+// sum over the splits stays small.
+inline int gemm_splits(int M, int N, int64_t K, int nbatch = 1, bool symmetric = false) {
+  const int64_t tm = (M + kGemmTile - 1) / kGemmTile, tn = (N + kGemmTile - 1) / kGemmTile;
   // a symmetric product runs only the tiles on and above the diagonal
   const int64_t tiles = symmetric ? tm * (tm + 1) / 2 : tm * tn;
+  const int64_t rounds = (K + kGemmSlab - 1) / kGemmSlab * nbatch;
+  int64_t s = 512 / tiles;
+  if (s > rounds / 4) s = rounds / 4;
+  if (s > 64) s = 64;
+  if (s >= 8) s -= s % 8;
+  return (int)(s < 1 ? 1 : s);
+}
+
+// Splits of launch_gemm_small: roughly `target` workgroups, at least 256 k each.
+inline int gemm_splits_small(int M, int N, int64_t K, int target) {
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
   int64_t s = (target + tiles - 1) / tiles;
-  const int64_t kmax = (K + 255) / 256;  // keep >= 256 k per split
+  const int64_t kmax = (K + 255) / 256;
   if (s > kmax) s = kmax;
   if (s < 1) s = 1;
   if (s > 64) s = 64;

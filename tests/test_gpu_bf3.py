@@ -48,3 +48,38 @@ def test_pair_sums_tile_edges(lib, P, nb, rb):
         ctx.set_tuning(rows_per_wave=rb, col_splits=sp)
         S, t1, t2 = (t.cpu().numpy().astype(np.float64) for t in ctx.pair_sums(_dev(q), _dev(w)))
         _check_rows(t1 + t2, ovds.bond_major(t1_o + t2_o, nb), S, S_o, f"P={P} nb={nb} rb={rb} sp={sp}")
+
+
+# tile (96), round (32 k) and split edges, rows that do and do not start on 16 bytes
+@pytest.mark.parametrize("m,n", [(3, 2), (31, 96), (33, 97), (129, 1), (600, 95), (1999, 193), (6001, 40), (20000, 300)])
+def test_gram_tile_edges(lib, m, n):
+    import torch
+    g = torch.Generator().manual_seed(m + n)
+    X = torch.randn((n, m), generator=g) * torch.logspace(-3, 3, n)[:, None]
+    ctx = lib.Context(1, max(1, m // 3), 1.0)
+    G = ctx.pod_gram(X.cuda()).cpu().double()
+    Xd = X.double()
+    ref = Xd @ Xd.T
+    # FP32 accumulation against the entry's own scale |x_i| |x_j|: a few 2^-24 per round of 32 within a split
+    scale = Xd.norm(dim=1)[:, None] * Xd.norm(dim=1)[None, :]
+    err = ((G - ref).abs() / scale).max().item()
+    print(f"m={m} n={n} err {err:.2e}", flush=True)
+    assert err <= 1e-6 and torch.equal(G, G.T)
+
+
+def test_gram_of_infinite_snapshots(lib):
+    """Entries with an infinite factor are what FP32 arithmetic makes of them."""
+    import torch
+    g = torch.Generator().manual_seed(1)
+    X = torch.randn((5, 200), generator=g)
+    X[1, 7] = float("inf")
+    X[3, 9] = float("-inf")
+    X[4, 11] = 3.4e38
+    G = lib.Context(1, 66, 1.0).pod_gram(X.cuda()).cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = np.zeros((5, 5), np.float32)
+        for k in range(200):
+            ref += np.outer(X[:, k].numpy(), X[:, k].numpy())
+    assert (np.isnan(G) == np.isnan(ref)).all() and (G[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+    ok = np.isfinite(ref)
+    assert np.allclose(G[ok], ref[ok], rtol=1e-5, atol=1e-4)
