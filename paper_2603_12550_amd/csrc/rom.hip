@@ -411,12 +411,23 @@ __global__ __launch_bounds__(kKgWaves * 64) __attribute__((amdgpu_waves_per_eu(2
       bf16x8 bv[3];
 #pragma unroll
       for (int p = 0; p < 3; ++p) bv[p] = as_bf8(bb[(T * 3 + p) * 64 + lane]);
-      constexpr int pe[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+      // the small products of the chunk among themselves first: added to the
+      // sum over all of Z one by one, what is below half a unit of it would be
+      // lost, and Z's lower parts are all positive
+      constexpr int pe[5] = {2, 0, 1, 1, 0}, pb[5] = {0, 2, 1, 0, 1};
+      floatx4 low[2];
 #pragma unroll
-      for (int x = 0; x < 6; ++x)
+      for (int r = 0; r < 2; ++r) low[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int x = 0; x < 5; ++x)
 #pragma unroll
         for (int r = 0; r < 2; ++r)
-          acc[r][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep[r][pe[x]], bv[pb[x]], acc[r][T], 0, 0, 0);
+          low[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep[r][pe[x]], bv[pb[x]], low[r], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        acc[r][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep[r][0], bv[0], acc[r][T], 0, 0, 0);
+        acc[r][T] += low[r];
+      }
     };
     distances(K3 + (int64_t)c0 * KP * 64);
     self_pairs(c0);
