@@ -2,6 +2,8 @@
 // (operand layouts: vds_internal.h; the method: pair_kernels.hip).
 #pragma once
 
+#include <type_traits>
+
 #include "vds_internal.h"
 
 namespace vds {
@@ -99,11 +101,85 @@ __device__ __forceinline__ void minus_identity(int lane, bf16x8 (&neg)[2]) {
     for (int i = 0; i < 8; ++i) neg[b][i] = (d >= 0 && d < 4 && i == 4 * b + d) ? (__bf16)-1.f : (__bf16)0.f;
 }
 
+// Lane i of each row of 16 gets lane (i + R) % 16 of its row.
+template <int R>
+__device__ __forceinline__ float row_rotate(float v) {
+  if constexpr (R % 16 == 0) return v;
+  else
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + (16 - R % 16), 0xf, 0xf, true));
+}
+
+constexpr int kFlush3 = 8;  // 32-column chunks per FP32 accumulation group of the pair sums
+
+// The three parts of every sum (columns p (D + 1) + n of the tiles) added up in
+// lane n of each row of 16, into FP64; clears the FP32 sums.
+template <int D>
+__device__ __forceinline__ void bf3_flush(floatx4 (&acc)[bf3_tiles(D)], int lane, double (&tot)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float v = 0.f;
+    auto part = [&](auto pc) {
+      constexpr int s = decltype(pc)::value * (D + 1);
+      float u = row_rotate<s % 16>(acc[s / 16][i]);
+      if constexpr (s % 16 + D + 1 > 16) {
+        const float u2 = row_rotate<s % 16>(acc[s / 16 + 1][i]);
+        u = (lane & 15) < 16 - s % 16 ? u : u2;
+      }
+      v += u;
+    };
+    part(std::integral_constant<int, 2>{});
+    part(std::integral_constant<int, 1>{});
+    part(std::integral_constant<int, 0>{});
+    tot[i] += (double)v;
+  }
+#pragma unroll
+  for (int T = 0; T < bf3_tiles(D); ++T) acc[T] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+
+// The sums of one 16-row block over a 32-column chunk from its exponents
+// (t in e): e = 2^t cut into three parts, each with V's columns (see
+// pair_kernels.hip).  With `self`, block b1 of the chunk holds the rows' self
+// pairs, which are left out.
+template <int D>
+__device__ __forceinline__ void bf3_accumulate(floatx4 (&e)[2], const bf16x8 (&va)[bf3_tiles(D)], const bf16x8 (&neg)[2],
+                                               bool self, int b1, int diag_i, floatx4 (&acc)[bf3_tiles(D)]) {
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      e[b][i] = __builtin_amdgcn_exp2f(e[b][i]);
+      e[b][i] = self && b == b1 && diag_i == i ? 0.f : e[b][i];
+    }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const int nt = ((3 - p) * (D + 1) + 15) / 16;
+    const bf16x8 ep = upper_halves(e[0], e[1]);
+    if (p < 2) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) e[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(neg[b], ep, e[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int T = 0; T < nt; ++T) acc[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ep, va[T], acc[T], 0, 0, 0);
+  }
+}
+
 // One piece of 64 x 16 bytes straight from memory to LDS (asynchronous: the
 // wave waits on vmcnt before it meets the barrier that publishes the piece).
 __device__ __forceinline__ void piece_to_lds(const uint4 *src, uint4 *dst, int lane) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + lane),
                                    (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+
+// f(std::integral_constant<int, D>) for the configuration dimension D.
+template <class F>
+void by_dimension(int D, F &&f) {
+  switch (D) {
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 9: f(std::integral_constant<int, 9>{}); break;
+    case 12: f(std::integral_constant<int, 12>{}); break;
+    default: f(std::integral_constant<int, 15>{}); break;
+  }
 }
 
 }  // namespace vds

@@ -9,12 +9,15 @@
 
 namespace vds {
 
-// Fixed-order tree sum over the 256 threads of a block for NS values each.
+// Fixed-order tree sum over the first 256 threads of a block for NS values each
+// (every thread of the block calls it).
 template <int NS>
 __device__ void block_sum(double (&v)[NS], double (*sm)[kRedBlock]) {
   const int t = threadIdx.x;
+  if (t < kRedBlock) {
 #pragma unroll
-  for (int s = 0; s < NS; ++s) sm[s][t] = v[s];
+    for (int s = 0; s < NS; ++s) sm[s][t] = v[s];
+  }
   __syncthreads();
   for (int stride = kRedBlock / 2; stride > 0; stride >>= 1) {
     if (t < stride) {
@@ -187,14 +190,15 @@ __device__ bool picard_converged(const PicardCheck &chk, const float *__restrict
   __shared__ float sr[kRedBlock / 64], sx[kRedBlock / 64];
   __shared__ int conv;
   __shared__ float rr;
-  const int nt = strided_count(threadIdx.x, nblk, kRedBlock);
+  // (blocks of more threads: the first 256 take the maxima)
+  const int nt = threadIdx.x < kRedBlock ? strided_count(threadIdx.x, nblk, kRedBlock) : 0;
   float r = strided_max(blockmax + 2 * threadIdx.x, nt, 2 * kRedBlock, 0.f);
   float x = strided_max(blockmax + 2 * threadIdx.x + 1, nt, 2 * kRedBlock, 0.f);
   for (int off = 32; off > 0; off >>= 1) {
     r = fmaxf(r, __shfl_xor(r, off));
     x = fmaxf(x, __shfl_xor(x, off));
   }
-  if ((threadIdx.x & 63) == 0) {
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < kRedBlock) {
     sr[threadIdx.x >> 6] = r;
     sx[threadIdx.x >> 6] = x;
   }
@@ -349,19 +353,16 @@ __device__ inline double sum_splits(const EvalParams &p, const float *__restrict
 
 // Pass-A finalisation: S_I = w_I + sum_{J != I} w_J e_IJ,
 // term1_I = -(1/h^2) sum_J w_J e_IJ (x_I - x_J) / S_I, and the pass-B operand
-// with weights w_J / S_J.
-__device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__restrict__ partial, const SplitMap &splits,
-                                const float *__restrict__ xc, const float *__restrict__ wv, float *__restrict__ S,
-                                float *__restrict__ t1, float *__restrict__ VB) {
-  const int64_t I = group_particle(lb);
-  const int n = group_lane();
-  if (I >= p.Ppad) return;
+// with weights w_J / S_J.  o is lane n's sum of particle I: the difference sum's
+// component n < D, the weighted kernel sum at n = D.
+__device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, const float *__restrict__ xc,
+                               const float *__restrict__ wv, float *__restrict__ S, float *__restrict__ t1,
+                               float *__restrict__ VB) {
   if (I >= p.P) {  // padding columns carry zero weight in pass B too
     if (p.bf3) store_v3(p, VB, I, n, 0.0);
     else store_v(p, VB, I, n, 0.f);
     return;
   }
-  const double o = n <= p.D ? sum_splits(p, partial, splits, I, n) : 0.0;
   const double wI = (double)wv[I];
   const double Si = gshfl(o, p.D) + wI;  // the pass left out the self term w_I e_II = w_I
   const float wb = (float)(wI / Si);
@@ -381,6 +382,16 @@ __device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__
   store_v(p, VB, I, n, v);  // wb <= 1, so the FP16 form needs no normalisation
 }
 
+__device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__restrict__ partial, const SplitMap &splits,
+                                const float *__restrict__ xc, const float *__restrict__ wv, float *__restrict__ S,
+                                float *__restrict__ t1, float *__restrict__ VB) {
+  const int64_t I = group_particle(lb);
+  const int n = group_lane();
+  if (I >= p.Ppad) return;
+  const double o = I < p.P && n <= p.D ? sum_splits(p, partial, splits, I, n) : 0.0;
+  finalize_a_row(p, I, n, o, xc, wv, S, t1, VB);
+}
+
 __global__ __launch_bounds__(kRedBlock) void k_finalize_a(EvalParams p, const float *__restrict__ partial, SplitMap splits,
                                                           const float *__restrict__ xc, const float *__restrict__ wv,
                                                           float *__restrict__ S, float *__restrict__ t1,
@@ -397,15 +408,17 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize_a(EvalParams p, const fl
 // (fixed-point or explicit mode) it packs the new iterate's or state's pair
 // operands as the prep kernel would: the same lanes hold the same coordinates
 // there.
-__device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs, const float *__restrict__ partial,
-                             const SplitMap &splits, const float *xc, const float *__restrict__ t1,
-                             const float *__restrict__ S, const float *wv, const float *qin,
-                             const float *__restrict__ qs, float *out, float *out2, double *__restrict__ redp,
-                             float *__restrict__ blockmax, const PackOps &pack, int *fene_out) {
+// The block's first 256 threads hold its particles (act), all threads call it;
+// o is lane n's pass-B sum of particle I, as in finalize_a_row.
+__device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs, bool act, double o, const float *xc,
+                             const float *__restrict__ t1, const float *__restrict__ S, const float *wv,
+                             const float *qin, const float *__restrict__ qs, float *out, float *out2,
+                             double *__restrict__ redp, float *__restrict__ blockmax, const PackOps &pack,
+                             int *fene_out) {
   __shared__ double sm[12][kRedBlock];
   const int64_t I = group_particle(lb);
   const int n = group_lane();
-  const bool real = I < p.P;          // uniform over the 16 lanes of a particle
+  const bool real = act && I < p.P;   // uniform over the 16 lanes of a particle
   const bool comp = real && n < p.D;  // this lane owns a component
   const int k = n / 3, al = n % 3, base = 3 * k;
   const int64_t idx = ((int64_t)k * p.P + I) * 3 + al;
@@ -414,8 +427,7 @@ __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs,
   for (int s = 0; s < 12; ++s) red[s] = 0.0;
   float resid = 0.f, xmax = 0.f, xnew = 0.f;
 
-  const double o = comp ? sum_splits(p, partial, splits, I, n) : 0.0;
-  const float t2v = (float)(-(double)p.inv_h2 * o);
+  const float t2v = comp ? (float)(-(double)p.inv_h2 * o) : 0.f;
   const float t1v = comp ? t1[I * p.D + n] : 0.f;
   const float b = t1v + t2v;
   if (mode == MODE_TERMS) {
@@ -468,7 +480,7 @@ __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs,
         xnew = xn;
       }
     }
-    if ((mode == MODE_PICARD || mode == MODE_EXPLICIT) && pack.VA != nullptr) {
+    if (act && (mode == MODE_PICARD || mode == MODE_EXPLICIT) && pack.VA != nullptr) {
       // the prep kernel's work for the new iterate or state: wv already holds
       // the weights (zero past the particles)
       const float x = comp ? xnew - pack.cmean[n] : 0.f;
@@ -492,7 +504,7 @@ __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs,
   }
   if (obs) {
     block_sum<12>(red, sm);
-    if (threadIdx.x < 12) redp[lb * 16 + threadIdx.x] = red[threadIdx.x];
+    if (threadIdx.x < 12 && lb * 16 < p.P) redp[lb * 16 + threadIdx.x] = red[threadIdx.x];
   }
   if (mode == MODE_PICARD) {
     // block maxima of |dx| and |x| into per-block slots; the check kernel
@@ -502,12 +514,12 @@ __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs,
       resid = fmaxf(resid, __shfl_xor(resid, off));
       xmax = fmaxf(xmax, __shfl_xor(xmax, off));
     }
-    if ((threadIdx.x & 63) == 0) {
+    if (act && (threadIdx.x & 63) == 0) {
       smax[0][threadIdx.x >> 6] = resid;
       smax[1][threadIdx.x >> 6] = xmax;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && lb * 16 < p.P) {
       float r = 0.f, x = 0.f;
       for (int i = 0; i < kRedBlock / 64; ++i) {
         r = fmaxf(r, smax[0][i]);
@@ -517,6 +529,16 @@ __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs,
       blockmax[2 * lb + 1] = x;
     }
   }
+}
+
+__device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs, const float *__restrict__ partial,
+                             const SplitMap &splits, const float *xc, const float *__restrict__ t1,
+                             const float *__restrict__ S, const float *wv, const float *qin,
+                             const float *__restrict__ qs, float *out, float *out2, double *__restrict__ redp,
+                             float *__restrict__ blockmax, const PackOps &pack, int *fene_out) {
+  const int64_t I = group_particle(lb);
+  const double o = I < p.P && group_lane() < p.D ? sum_splits(p, partial, splits, I, group_lane()) : 0.0;
+  combine_rows(p, lb, mode, obs, true, o, xc, t1, S, wv, qin, qs, out, out2, redp, blockmax, pack, fene_out);
 }
 
 __global__ __launch_bounds__(kRedBlock) void k_combine(EvalParams p, int mode, int obs,
@@ -815,6 +837,150 @@ __global__ void k_batch_stress_sum(const EnsDesc *__restrict__ ens, const double
   tau[(int64_t)blockIdx.x * 9 + s] = acc;
 }
 
+// ---- small problems: a pass and what follows it in one launch ----------------
+//
+// Below kRowsMaxP particles a pass is a few microseconds of work and the launch
+// that sums its partials costs as much again, most of it a chain of dependent
+// loads.  Here a workgroup of sixteen waves owns 16 rows: wave w takes the
+// 32-column chunks w, w + 16, ... (operands straight from memory, the next
+// chunk's in flight), the waves' FP64 sums meet in LDS in wave order, and the
+// first 256 threads, sixteen lanes per particle as everywhere, finish the rows:
+// pass A with S, term1 and the pass-B operand, pass B with drift, update and the
+// next state's operands.  Those go to a second K3 buffer, since other
+// workgroups still read this one.
+// Bound: latency (launch, row operand, first chunk, sums).  Above about 2000
+// particles every workgroup's reading of all columns through L2 (P^2 / 16 x 6 KB
+// per 32 columns) outweighs the launch it saves.  Measured per explicit step of
+// the 4-bead chain at P = 1000: 36 us in four launches, 15 in two; five implicit
+// steps of the dumbbell at P = 2000: 0.71 against 0.37 ms.
+
+constexpr int kRowsWaves = 16;
+
+template <int D>
+struct RowsLds {
+  double red[kRowsWaves][16][16];
+};
+
+// Sum of lane (particle 16 blockIdx.x + t / 16, n = t % 16) for the first 256
+// threads: the difference sum's component n < D, the kernel sum at n = D.
+template <int D>
+__device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restrict__ V3, const float *__restrict__ xc,
+                            int nch, RowsLds<D> &lds) {
+  constexpr int NQ = bf3_slices(D), NT = bf3_tiles(D);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb = (int)blockIdx.x;
+  const int diag_i = (lane & 15) - 4 * (lane >> 4);
+  bf16x8 neg[2], q[NQ];
+  minus_identity(lane, neg);
+  bf3_row_operand<D>(K3, rb, lane, q);
+  uint4 kv[2 * NQ], vv[NT];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < 2 * NQ; ++i) kv[i] = K3[((int64_t)c * 2 * NQ + i) * 64 + lane];
+#pragma unroll
+    for (int T = 0; T < NT; ++T) vv[T] = V3[((int64_t)c * NT + T) * 64 + lane];
+  };
+  if (wave < nch) load(wave);
+  floatx4 acc[NT];
+#pragma unroll
+  for (int T = 0; T < NT; ++T) acc[T] = floatx4{0.f, 0.f, 0.f, 0.f};
+  double tot[4] = {0.0, 0.0, 0.0, 0.0};
+  int done = 0;
+  for (int c = wave; c < nch; c += kRowsWaves) {
+    floatx4 e[2];
+    bf16x8 va[NT];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      e[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < NQ; ++m)
+        e[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(kv[b * NQ + m]), q[m], e[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int T = 0; T < NT; ++T) va[T] = as_bf8(vv[T]);
+    if (c + kRowsWaves < nch) load(c + kRowsWaves);
+    bf3_accumulate<D>(e, va, neg, c == rb >> 1, rb & 1, diag_i, acc);
+    if (++done % kFlush3 == 0) bf3_flush<D>(acc, lane, tot);
+  }
+  bf3_flush<D>(acc, lane, tot);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) lds.red[wave][4 * (lane >> 4) + i][lane & 15] = tot[i];
+  __syncthreads();
+  double o = 0.0;
+  if (threadIdx.x < kRedBlock) {
+    const int r = threadIdx.x >> 4, n = threadIdx.x & 15;
+    for (int w = 0; w < kRowsWaves; ++w) o += lds.red[w][r][n];
+    const double s = gshfl(o, D);
+    const int64_t I = (int64_t)rb * 16 + r;
+    if (n < D) o = (double)xc[I * D + n] * s - o;
+  }
+  return o;
+}
+
+// Pass A, S, term1 and the pass-B operand.  With chk.ctrl the launch first tests
+// the fixed-point iteration before it (k_picard_check's work): every workgroup
+// takes the test from the same block maxima, the first one records it.
+template <int D>
+__global__ __launch_bounds__(kRowsWaves * 64) void k_rows_a(EvalParams p, const uint4 *__restrict__ K3,
+                                                            const uint4 *__restrict__ VA, const float *__restrict__ xc,
+                                                            const float *__restrict__ wv, float *__restrict__ S,
+                                                            float *__restrict__ t1, float *__restrict__ VB, int nch,
+                                                            const int *__restrict__ done, PicardCheck chk,
+                                                            const float *__restrict__ blockmax, int nblk_chk) {
+  __shared__ RowsLds<D> lds;
+  __shared__ int stop;
+  if (chk.ctrl != nullptr) {
+    // the flag once per block: the first block may set it during this launch
+    if (threadIdx.x == 0) stop = *done;
+    float r;
+    const bool conv = picard_converged(chk, blockmax, nblk_chk, &r);  // (holds barriers)
+    const bool was = stop != 0;
+    if (!was && blockIdx.x == 0 && threadIdx.x == 0) {
+      chk.ctrl->last_resid = r;
+      chk.ctrl->checked = chk.iter + 1;
+      if (conv) {
+        chk.ctrl->conv_iter = chk.iter;
+        chk.ctrl->done = 1;
+      }
+    }
+    if (was || conv) return;
+  } else if (done != nullptr && *done) {
+    return;
+  }
+  const double o = rows_pass<D>(K3, VA, xc, nch, lds);
+  if (threadIdx.x < kRedBlock)
+    finalize_a_row(p, group_particle(blockIdx.x), group_lane(), o, xc, wv, S, t1, VB);
+}
+
+// Pass B and the combination (modes of k_combine), or with MODE_SUMS the row
+// scalars of the reduced model: out = sum_K (w_K / S_K) e_IK (K = I included),
+// out2 = 1 / S_I.
+template <int D>
+__global__ __launch_bounds__(kRowsWaves * 64) void k_rows_b(EvalParams p, int mode, int obs,
+                                                            const uint4 *__restrict__ K3, const uint4 *__restrict__ VB,
+                                                            int nch, const float *xc, const float *__restrict__ t1,
+                                                            const float *__restrict__ S, const float *wv,
+                                                            const float *qin, const float *__restrict__ qs, float *out,
+                                                            float *out2, double *__restrict__ redp,
+                                                            float *__restrict__ blockmax, const int *__restrict__ done,
+                                                            PackOps pack, int *fene_out) {
+  __shared__ RowsLds<D> lds;
+  if (done != nullptr && *done) return;
+  const double o = rows_pass<D>(K3, VB, xc, nch, lds);
+  if (mode == MODE_SUMS) {
+    const int64_t I = group_particle(blockIdx.x);
+    if (threadIdx.x < kRedBlock && I < p.P && group_lane() == D) {
+      const double Si = (double)S[I];
+      out[I] = (float)(o + (double)wv[I] / Si);
+      out2[I] = (float)(1.0 / Si);
+    }
+    return;
+  }
+  combine_rows(p, blockIdx.x, mode, obs, threadIdx.x < kRedBlock, o, xc, t1, S, wv, qin, qs, out, out2, redp, blockmax,
+               pack, fene_out);
+}
+
 // ---- launchers ----
 
 static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kRedBlock - 1) / kRedBlock); }
@@ -841,6 +1007,33 @@ void launch_combine(const EvalParams &p, int mode, bool obs, const float *partia
   const PackOps pk = pack != nullptr ? *pack : PackOps{};
   k_combine<<<nblocks(p.P * 16), kRedBlock, 0, s>>>(p, mode, obs ? 1 : 0, partial, splits, xc, t1, S, wv, qin, q0,
                                                     out, out2, redp, blockmax, done, pk, fene_out);
+}
+// (particles up to the last chunk's end: their operands are written as zeros)
+static unsigned rows_grid(const EvalParams &p) { return (unsigned)(round_up(p.P, 32) / 16); }
+void launch_rows_a(const EvalParams &p, const void *K3, const float *VA, const float *xc, const float *wv, float *S,
+                   float *t1, float *VB, const int *done, const PicardCheck *chk, const float *blockmax, int nblk_chk,
+                   hipStream_t s) {
+  const PicardCheck ck = chk != nullptr ? *chk : PicardCheck{nullptr, 0.f, 0};
+  const int nch = (int)((p.P + 31) / 32);
+  auto go = [&](auto d) {
+    k_rows_a<decltype(d)::value><<<rows_grid(p), kRowsWaves * 64, 0, s>>>(
+        p, static_cast<const uint4 *>(K3), reinterpret_cast<const uint4 *>(VA), xc, wv, S, t1, VB, nch, done, ck,
+        blockmax, nblk_chk);
+  };
+  by_dimension(p.D, go);
+}
+void launch_rows_b(const EvalParams &p, int mode, bool obs, const void *K3, const float *VB, const float *xc,
+                   const float *t1, const float *S, const float *wv, const float *qin, const float *q0, float *out,
+                   float *out2, double *redp, float *blockmax, const int *done, hipStream_t s, const PackOps *pack,
+                   int *fene_out) {
+  const PackOps pk = pack != nullptr ? *pack : PackOps{};
+  const int nch = (int)((p.P + 31) / 32);
+  auto go = [&](auto d) {
+    k_rows_b<decltype(d)::value><<<rows_grid(p), kRowsWaves * 64, 0, s>>>(
+        p, mode, obs ? 1 : 0, static_cast<const uint4 *>(K3), reinterpret_cast<const uint4 *>(VB), nch, xc, t1, S, wv,
+        qin, q0, out, out2, redp, blockmax, done, pk, fene_out);
+  };
+  by_dimension(p.D, go);
 }
 void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, const int *done, hipStream_t s) {
   k_reduce_final<<<1, 1024, 0, s>>>(redp, nblk, nslots, out, done);

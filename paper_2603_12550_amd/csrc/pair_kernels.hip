@@ -216,7 +216,6 @@ __global__ __launch_bounds__(256) void k_pair_mfma(const float *__restrict__ QB,
 
 constexpr int kWaves3 = 8;   // waves per workgroup
 constexpr int kStage3 = 2;   // 32-column chunks staged in LDS per barrier
-constexpr int kFlush3 = 8;   // chunks per FP32 accumulation group (a multiple of kStage3)
 
 // Row blocks of 16 per wave: rows_per_wave of the tuning, 1 or 2.  From D = 12
 // on, two would not leave four waves a SIMD's registers (D = 15, P = 30000: 368
@@ -240,14 +239,6 @@ struct Bf3Lds {
   uint4 buf[2][kStage3 * Bf3Shape<D>::PC * 64];
   double tot[kWaves3][4 * kMaxRB3][64];
 };
-
-// Lane i of each row of 16 gets lane (i + R) % 16 of its row.
-template <int R>
-__device__ __forceinline__ float row_rotate(float v) {
-  if constexpr (R % 16 == 0) return v;
-  else
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + (16 - R % 16), 0xf, 0xf, true));
-}
 
 // One segment: wave w of the workgroup takes the 16-row blocks
 // (kWaves3 rg + w) RB .. + RB - 1 against the columns of chunks [c0, c1) and
@@ -300,32 +291,16 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
 #pragma unroll
     for (int T = 0; T < NT; ++T) acc[r][T] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  // the three parts of every sum (columns p (D + 1) + n of the tiles) added up
-  // in lane n of each row of 16, into FP64
   auto flush = [&] {
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
+    for (int r = 0; r < RB; ++r) {
+      double t[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float v = 0.f;
-        auto part = [&](auto pc) {
-          constexpr int s = decltype(pc)::value * (D + 1);
-          float u = row_rotate<s % 16>(acc[r][s / 16][i]);
-          if constexpr (s % 16 + D + 1 > 16) {
-            const float u2 = row_rotate<s % 16>(acc[r][s / 16 + 1][i]);
-            u = (lane & 15) < 16 - s % 16 ? u : u2;
-          }
-          v += u;
-        };
-        part(std::integral_constant<int, 2>{});
-        part(std::integral_constant<int, 1>{});
-        part(std::integral_constant<int, 0>{});
-        tl[4 * r + i][lane] += (double)v;
-      }
+      for (int i = 0; i < 4; ++i) t[i] = tl[4 * r + i][lane];
+      bf3_flush<D>(acc[r], lane, t);
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
-#pragma unroll
-      for (int T = 0; T < NT; ++T) acc[r][T] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < 4; ++i) tl[4 * r + i][lane] = t[i];
+    }
   };
   // one chunk of 32 columns; kDiag: it holds the wave's self pairs
   auto chunk = [&](int c, const uint4 *cb, auto diag) {

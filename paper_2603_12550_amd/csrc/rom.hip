@@ -1122,9 +1122,12 @@ vds_status freeze(vds_rom r, const float *p) {
   reconstruct_qt(r, p);
   // S and T at q~ (uniform weights), Q/K operands for Z
   eval_pass_a(c, r->qt, nullptr, nullptr);
-  eval_pass_b(c, nullptr);
-  k_rom_scalars<<<nblk256(Ppad), 256, 0, s>>>(c->part, c->smap, Ppad, P, c->ep.D, c->S, c->wv, r->T,
-                                              r->invS);
+  if (rows_path(c)) {
+    pass_b(c, MODE_SUMS, false, nullptr, nullptr, r->T, r->invS, nullptr, 0, nullptr, nullptr);
+  } else {
+    eval_pass_b(c, nullptr);
+    k_rom_scalars<<<nblk256(Ppad), 256, 0, s>>>(c->part, c->smap, Ppad, P, c->ep.D, c->S, c->wv, r->T, r->invS);
+  }
   if (c->ep.bf3) return operators_bf3(r);
   r->b3_ready = false;  // the forms below lay their weighted columns out in Bsw
   // Y = Z B, in the FP16-split form when the context's pair kernels use it

@@ -102,12 +102,54 @@ void apply_tuning(vds_ctx c, const vds_tuning &t) {
   c->ep.bf3 = t.impl == VDS_PAIR_MFMA32 ? 1 : 0;
 }
 
+bool rows_path(vds_ctx c) { return c->ep.bf3 && c->prob.P <= kRowsMaxP; }
+
+// The K3 buffer of packing parity `par`: 0 is the one the prep kernel writes, 1
+// (small problems only) sits in the partial-sum buffer, which that path leaves
+// unused.
+void *k3_buffer(vds_ctx c, int par) { return par == 0 ? c->f16.QH : static_cast<void *>(c->part); }
+
+// Pass A and its finalisation on the packed operands of parity `par`; with chk
+// (small problems) the test of the iteration before.
+void pass_a(vds_ctx c, const int *done, int par, const PicardCheck *chk) {
+  if (rows_path(c)) {
+    timed(c, VDS_TIMER_PAIR, (double)c->prob.P * (double)c->prob.P, [&] {
+      launch_rows_a(c->ep, k3_buffer(c, par), c->VA, c->xc, c->wv, c->S, c->t1, c->VB, done, chk, c->blockmax,
+                    c->nblk_comb, c->stream);
+    });
+    return;
+  }
+  pair_pass(c, c->VA, c->wscale, done);
+  launch_finalize_a(c->ep, c->part, c->smap, c->xc, c->wv, c->S, c->t1, c->VB, done, c->stream);
+}
+
+// Pass B and the combination in `mode` (arguments as launch_combine).
+void pass_b(vds_ctx c, int mode, bool obs, const float *qin, const float *q0, float *out, float *out2,
+            const int *done, int par, const PackOps *pack, int *fene_out) {
+  if (rows_path(c)) {
+    timed(c, VDS_TIMER_PAIR, (double)c->prob.P * (double)c->prob.P, [&] {
+      launch_rows_b(c->ep, mode, obs, k3_buffer(c, par), c->VB, c->xc, c->t1, c->S, c->wv, qin, q0, out, out2, c->redp,
+                    c->blockmax, done, c->stream, pack, fene_out);
+    });
+    return;
+  }
+  pair_pass(c, c->VB, nullptr, done);
+  launch_combine(c->ep, mode, obs, c->part, c->smap, c->xc, c->t1, c->S, c->wv, qin, q0, out, out2, c->redp,
+                 c->blockmax, done, c->stream, pack, fene_out);
+}
+
+// What a combine kernel packs the next state into: parity `par`'s K3 buffer.
+PackOps pack_ops(vds_ctx c, int par) {
+  PackOps pk{c->xc, c->wv, c->QB, c->KA, c->VA, c->f16, c->cmean};
+  if (rows_path(c)) pk.f16.QH = k3_buffer(c, par);
+  return pk;
+}
+
 void eval_pass_a(vds_ctx c, const float *q, const float *w, const int *done, bool centre) {
   const EvalParams &e = c->ep;
   if (centre) launch_mean_partials(e, q, w, c->meanp, done, nullptr, c->stream);
   launch_prep(e, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, done, c->stream);
-  pair_pass(c, c->VA, c->wscale, done);
-  launch_finalize_a(e, c->part, c->smap, c->xc, c->wv, c->S, c->t1, c->VB, done, c->stream);
+  pass_a(c, done, 0, nullptr);
 }
 
 void eval_pass_b(vds_ctx c, const int *done) { pair_pass(c, c->VB, nullptr, done); }
@@ -238,11 +280,8 @@ void drain_timers(vds_ctx c) {
 // differences, so any centre near the particles gives the same result).
 void evaluate(vds_ctx c, const float *q, const float *w, int mode, bool obs, const float *q0, float *out,
               float *out2, const int *done, bool centre = true) {
-  const EvalParams &e = c->ep;
   eval_pass_a(c, q, w, done, centre);
-  eval_pass_b(c, done);
-  launch_combine(e, mode, obs, c->part, c->smap, c->xc, c->t1, c->S, c->wv, q, q0, out, out2, c->redp,
-                 c->blockmax, done, c->stream, nullptr, fene_flag(c));
+  pass_b(c, mode, obs, q, q0, out, out2, done, 0, nullptr, fene_flag(c));
   if (obs) launch_reduce_final(c->redp, c->nblk_comb, 12, c->redout, done, c->stream);
 }
 
@@ -496,19 +535,17 @@ constexpr int kQueueSteps = 64;
 // packs the next step's operands centred where the last prep centred (the
 // sums are differences, so a centre near the particles serves).
 void explicit_steps(vds_ctx c, float *q, const float *w, int nsteps) {
-  const PackOps pk{c->xc, c->wv, c->QB, c->KA, c->VA, c->f16, c->cmean};
   for (int s = 0; s < nsteps; ++s) {
+    const int par = s % kQueueSteps & 1;
     if (s % kQueueSteps == 0) {
       launch_mean_partials(c->ep, q, w, c->meanp, nullptr, nullptr, c->stream);
       launch_prep(c->ep, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, nullptr,
                   c->stream, c->cmean);
     }
-    pair_pass(c, c->VA, c->wscale, nullptr);
-    launch_finalize_a(c->ep, c->part, c->smap, c->xc, c->wv, c->S, c->t1, c->VB, nullptr, c->stream);
-    eval_pass_b(c, nullptr);
+    pass_a(c, nullptr, par, nullptr);
     const bool pack = s + 1 < nsteps && (s + 1) % kQueueSteps != 0;
-    launch_combine(c->ep, MODE_EXPLICIT, false, c->part, c->smap, c->xc, c->t1, c->S, c->wv, q, nullptr,
-                   q, nullptr, c->redp, c->blockmax, nullptr, c->stream, pack ? &pk : nullptr, fene_flag(c));
+    const PackOps pk = pack_ops(c, par ^ 1);
+    pass_b(c, MODE_EXPLICIT, false, q, nullptr, q, nullptr, nullptr, par, pack ? &pk : nullptr, fene_flag(c));
   }
 }
 
@@ -592,19 +629,15 @@ vds_status implicit_steps(vds_ctx c, float *q, const float *w, int nsteps, StepC
         if (m == 0) {
           launch_prep(c->ep, x0, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16,
                       j == 0 ? done : nullptr, c->stream, c->cmean, j > 0 ? c->ctrl : nullptr);
-        } else {
-          // the previous combine packed this iterate's operands; one block
-          // tests the previous iteration
-          launch_picard_check(PicardCheck{c->ctrl, (float)p.picard_rtol, m - 1}, c->blockmax, c->nblk_comb,
-                              c->stream);
         }
-        pair_pass(c, c->VA, c->wscale, done);
-        launch_finalize_a(c->ep, c->part, c->smap, c->xc, c->wv, c->S, c->t1, c->VB, done, c->stream);
-        eval_pass_b(c, done);
-        const PackOps pk{c->xc, c->wv, c->QB, c->KA, c->VA, c->f16, c->cmean};
-        launch_combine(c->ep, MODE_PICARD, false, c->part, c->smap, c->xc, c->t1, c->S, c->wv, xin, q,
-                       c->xb[m & 1], nullptr, c->redp, c->blockmax, done, c->stream, m + 1 < batch ? &pk : nullptr,
-                       fene_flag(c));
+        // the previous combine packed this iterate's operands; the previous
+        // iteration is tested by one block, or in pass A of a small problem
+        const PicardCheck chk{c->ctrl, (float)p.picard_rtol, m - 1};
+        if (m > 0 && !rows_path(c)) launch_picard_check(chk, c->blockmax, c->nblk_comb, c->stream);
+        pass_a(c, done, m & 1, m > 0 ? &chk : nullptr);
+        const PackOps pk = pack_ops(c, (m + 1) & 1);
+        pass_b(c, MODE_PICARD, false, xin, q, c->xb[m & 1], nullptr, done, m & 1, m + 1 < batch ? &pk : nullptr,
+               fene_flag(c));
       }
       launch_step_end(c->ep, c->ctrl, PicardCheck{c->ctrl, (float)p.picard_rtol, batch - 1}, c->blockmax,
                       c->nblk_comb, c->xb[0], c->xb[1], q, p.picard_predictor ? c->xpred : nullptr, w,

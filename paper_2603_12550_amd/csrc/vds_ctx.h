@@ -83,5 +83,11 @@ void timed(vds_ctx c, int which, double work, F &&fn) {
 void eval_pass_a(vds_ctx c, const float *q, const float *w, const int *done, bool centre = true);
 // Pass B with the operand eval_pass_a left; partial sums stay in c->part.
 void eval_pass_b(vds_ctx c, const int *done);
+// Whether the context's evaluations take the one-launch-per-pass path of small
+// problems (launch_rows_a, launch_rows_b), and its pass B with what follows
+// (mode and arrays as launch_combine) on the operands eval_pass_a left.
+bool rows_path(vds_ctx c);
+void pass_b(vds_ctx c, int mode, bool obs, const float *qin, const float *q0, float *out, float *out2,
+            const int *done, int par, const PackOps *pack, int *fene_out);
 
 }  // namespace vds

@@ -188,7 +188,7 @@ struct PackOps {
 };
 
 // Modes of the combine kernel.
-enum CombineMode { MODE_TERMS = 0, MODE_VELOCITY = 1, MODE_EXPLICIT = 2, MODE_PICARD = 3, MODE_OBS_ONLY = 4 };
+enum CombineMode { MODE_TERMS = 0, MODE_VELOCITY = 1, MODE_EXPLICIT = 2, MODE_PICARD = 3, MODE_OBS_ONLY = 4, MODE_SUMS = 5 };
 
 // ---- launchers (pair_kernels.hip) ----
 // Writes partial[slot][row][0..D) = sum_J e wh (x_row - x_J) and [D] = sum_J e wh
@@ -250,6 +250,18 @@ void launch_combine(const EvalParams &p, int mode, bool obs, const float *partia
                     const float *t1, const float *S, const float *wv, const float *qin, const float *q0,
                     float *out, float *out2, double *redp, float *blockmax, const int *done, hipStream_t s,
                     const PackOps *pack = nullptr, int *fene_out = nullptr);
+// Small problems (P <= kRowsMaxP, VDS_PAIR_MFMA32): a pass with what follows it in one
+// launch.  launch_rows_a is pass A with launch_finalize_a, and with chk launch_picard_check
+// before it; launch_rows_b pass B with launch_combine (pack then names another K3 buffer than
+// K3), or with MODE_SUMS the reduced model's row scalars.
+constexpr int64_t kRowsMaxP = 2048;
+void launch_rows_a(const EvalParams &p, const void *K3, const float *VA, const float *xc, const float *wv, float *S,
+                   float *t1, float *VB, const int *done, const PicardCheck *chk, const float *blockmax, int nblk_chk,
+                   hipStream_t s);
+void launch_rows_b(const EvalParams &p, int mode, bool obs, const void *K3, const float *VB, const float *xc,
+                   const float *t1, const float *S, const float *wv, const float *qin, const float *q0, float *out,
+                   float *out2, double *redp, float *blockmax, const int *done, hipStream_t s,
+                   const PackOps *pack = nullptr, int *fene_out = nullptr);
 void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, const int *done, hipStream_t s);
 void launch_ctrl_reset(Ctrl *ctrl, hipStream_t s);
 // Closes a queued implicit step whose last queued iteration is chk.iter: tests
