@@ -30,6 +30,16 @@ __device__ void block_sum(double (&v)[NS], double (*sm)[kRedBlock]) {
   for (int s = 0; s < NS; ++s) v[s] = sm[s][0];
 }
 
+// The dimension known at compile time, so that the per-particle bodies' index
+// arithmetic folds (assumed, not stored: a changed copy of the parameters would
+// put their arrays, which are indexed per lane, into scratch memory).
+template <int D>
+__device__ __forceinline__ void assume_dimension(const EvalParams &p) {
+  __builtin_assume(p.D == D);
+  __builtin_assume(p.nb == D / 3);
+  __builtin_assume(p.KK == (D + 5) / 4);
+}
+
 __device__ inline float load_weight(const float *w, int64_t I, float uniform_w) {
   return w != nullptr ? w[I] : uniform_w;
 }
@@ -323,6 +333,7 @@ __device__ void prep_body(const EvalParams &p, int64_t lb, const float *__restri
   prep_write(p, I, n, x, wi, mean_sh, xc, wv, QB, KA, VA, f16);
 }
 
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_prep(EvalParams p, const float *__restrict__ q,
                                                     const float *__restrict__ w, const double *__restrict__ meanp,
                                                     int nmeanp, float *__restrict__ xc, float *__restrict__ wv,
@@ -342,6 +353,7 @@ __global__ __launch_bounds__(kRedBlock) void k_prep(EvalParams p, const float *_
   } else if (done != nullptr && *done) {
     return;
   }
+  assume_dimension<D>(p);
   prep_body(p, blockIdx.x, q, w, meanp, nmeanp, xc, wv, QB, KA, VA, wscale, f16, cmean);
 }
 
@@ -355,28 +367,29 @@ __device__ inline double sum_splits(const EvalParams &p, const float *__restrict
 // term1_I = -(1/h^2) sum_J w_J e_IJ (x_I - x_J) / S_I, and the pass-B operand
 // with weights w_J / S_J.  o is lane n's sum of particle I: the difference sum's
 // component n < D, the weighted kernel sum at n = D.
-__device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, const float *__restrict__ xc,
-                               const float *__restrict__ wv, float *__restrict__ S, float *__restrict__ t1,
-                               float *__restrict__ VB) {
+// x and w are lane n's centred coordinate and the particle's weight, loaded
+// ahead of the sums.
+__device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, float x, float w,
+                               float *__restrict__ S, float *__restrict__ t1, float *__restrict__ VB) {
   if (I >= p.P) {  // padding columns carry zero weight in pass B too
     if (p.bf3) store_v3(p, VB, I, n, 0.0);
     else store_v(p, VB, I, n, 0.f);
     return;
   }
-  const double wI = (double)wv[I];
+  const double wI = (double)w;
   const double Si = gshfl(o, p.D) + wI;  // the pass left out the self term w_I e_II = w_I
   const float wb = (float)(wI / Si);
   float v = 0.f;
   if (n < p.D) {
     t1[I * p.D + n] = (float)(-(double)p.inv_h2 * o / Si);
-    v = wb * xc[I * p.D + n];
+    v = wb * x;
   } else if (n == p.D) {
     S[I] = (float)Si;
     v = wb;
   }
   if (p.bf3) {
     const double wd = wI / Si;
-    store_v3(p, VB, I, n, n < p.D ? wd * (double)xc[I * p.D + n] : wd);
+    store_v3(p, VB, I, n, n < p.D ? wd * (double)x : wd);
     return;
   }
   store_v(p, VB, I, n, v);  // wb <= 1, so the FP16 form needs no normalisation
@@ -388,15 +401,18 @@ __device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__
   const int64_t I = group_particle(lb);
   const int n = group_lane();
   if (I >= p.Ppad) return;
+  const float x = n < p.D ? xc[I * p.D + n] : 0.f, w = wv[I];
   const double o = I < p.P && n <= p.D ? sum_splits(p, partial, splits, I, n) : 0.0;
-  finalize_a_row(p, I, n, o, xc, wv, S, t1, VB);
+  finalize_a_row(p, I, n, o, x, w, S, t1, VB);
 }
 
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_finalize_a(EvalParams p, const float *__restrict__ partial, SplitMap splits,
                                                           const float *__restrict__ xc, const float *__restrict__ wv,
                                                           float *__restrict__ S, float *__restrict__ t1,
                                                           float *__restrict__ VB, const int *__restrict__ done) {
   if (done != nullptr && *done) return;
+  assume_dimension<D>(p);
   finalize_a_body(p, blockIdx.x, partial, splits, xc, wv, S, t1, VB);
 }
 
@@ -408,13 +424,32 @@ __global__ __launch_bounds__(kRedBlock) void k_finalize_a(EvalParams p, const fl
 // (fixed-point or explicit mode) it packs the new iterate's or state's pair
 // operands as the prep kernel would: the same lanes hold the same coordinates
 // there.
+// Lane n's inputs of particle I beside the pass-B sum, loaded ahead of it.
+struct CombineIn {
+  float t1, q, qs, w, S;
+};
+__device__ inline CombineIn combine_load(const EvalParams &p, int64_t lb, int mode, int obs, bool act,
+                                         const float *__restrict__ t1, const float *__restrict__ S, const float *wv,
+                                         const float *qin, const float *__restrict__ qs) {
+  const int64_t I = group_particle(lb);
+  const int n = group_lane();
+  const bool real = act && I < p.P, comp = real && n < p.D;
+  const int64_t idx = ((int64_t)(n / 3) * p.P + I) * 3 + n % 3;
+  CombineIn c;
+  c.t1 = comp ? t1[I * p.D + n] : 0.f;
+  c.q = comp && mode != MODE_TERMS ? qin[idx] : 0.f;
+  c.qs = comp && mode == MODE_PICARD ? qs[idx] : 0.f;
+  c.w = real ? wv[I] : 0.f;
+  c.S = real && obs ? S[I] : 1.f;
+  return c;
+}
+
 // The block's first 256 threads hold its particles (act), all threads call it;
-// o is lane n's pass-B sum of particle I, as in finalize_a_row.
-__device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs, bool act, double o, const float *xc,
-                             const float *__restrict__ t1, const float *__restrict__ S, const float *wv,
-                             const float *qin, const float *__restrict__ qs, float *out, float *out2,
-                             double *__restrict__ redp, float *__restrict__ blockmax, const PackOps &pack,
-                             int *fene_out) {
+// o is lane n's pass-B sum of particle I, as in finalize_a_row, and in its other
+// inputs (combine_load).
+__device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs, bool act, double o,
+                             const CombineIn &in, float *out, float *out2, double *__restrict__ redp,
+                             float *__restrict__ blockmax, const PackOps &pack, int *fene_out) {
   __shared__ double sm[12][kRedBlock];
   const int64_t I = group_particle(lb);
   const int n = group_lane();
@@ -428,7 +463,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
   float resid = 0.f, xmax = 0.f, xnew = 0.f;
 
   const float t2v = comp ? (float)(-(double)p.inv_h2 * o) : 0.f;
-  const float t1v = comp ? t1[I * p.D + n] : 0.f;
+  const float t1v = in.t1;
   const float b = t1v + t2v;
   if (mode == MODE_TERMS) {
     if (comp) {
@@ -436,11 +471,17 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
       out2[idx] = t2v;
     }
   } else {
-    const float qv = comp ? qin[idx] : 0.f;
+    const float qv = in.q;
     // the three components of this lane's bond
     const float q0 = gshfl(qv, base), q1 = gshfl(qv, base + 1), q2 = gshfl(qv, base + 2);
     const float r2 = q0 * q0 + q1 * q1 + q2 * q2;
-    const float H = k < p.nb ? p.H[k < kMaxNb ? k : 0] : 0.f;
+    // this lane's spring constant and row of G, by selects of uniform values: an
+    // index that differs per lane would read the kernel arguments as vector loads
+    float H = 0.f, G0 = p.G[6], G1 = p.G[7], G2 = p.G[8];
+#pragma unroll
+    for (int j = 0; j < kMaxNb; ++j) H = j == k && j < p.nb ? p.H[j] : H;
+    if (al == 0) G0 = p.G[0], G1 = p.G[1], G2 = p.G[2];
+    if (al == 1) G0 = p.G[3], G1 = p.G[4], G2 = p.G[5];
     float fac = H, psi = 0.f;
     if (p.potential == VDS_FENE) {
       const float sb = 1.f - r2 / p.b_max;
@@ -458,12 +499,12 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
     float Ag = 2.f * g;
     if (k > 0) Ag -= gm;
     if (k + 1 < p.nb) Ag -= gpl;
-    const float flow = p.G[3 * (al % 3)] * q0 + p.G[3 * (al % 3) + 1] * q1 + p.G[3 * (al % 3) + 2] * q2;
+    const float flow = G0 * q0 + G1 * q1 + G2 * q2;
     float qstart = 0.f, flow0 = 0.f;
     if (mode == MODE_PICARD) {
-      qstart = comp ? qs[idx] : 0.f;
+      qstart = in.qs;
       const float s0 = gshfl(qstart, base), s1 = gshfl(qstart, base + 1), s2 = gshfl(qstart, base + 2);
-      flow0 = p.G[3 * (al % 3)] * s0 + p.G[3 * (al % 3) + 1] * s1 + p.G[3 * (al % 3) + 2] * s2;
+      flow0 = G0 * s0 + G1 * s1 + G2 * s2;
     }
     const float u = -p.inv_zeta * Ag;
     if (comp) {
@@ -484,21 +525,21 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
       // the prep kernel's work for the new iterate or state: wv already holds
       // the weights (zero past the particles)
       const float x = comp ? xnew - pack.cmean[n] : 0.f;
-      const float wi = real ? wv[I] : 0.f;
+      const float wi = in.w;
       prep_write(p, I, n, x, wi, pack.cmean, pack.xc, pack.wv, pack.QB, pack.KA, pack.VA, pack.f16);
     }
     if (obs) {
       // stress column beta needs grad Psi of this bond's component beta
       const float gp0 = gshfl(gp, base), gp1 = gshfl(gp, base + 1), gp2 = gshfl(gp, base + 2);
       if (comp) {
-        const double wi = (double)wv[I];
+        const double wi = (double)in.w;
         red[RED_DISS] = wi * (double)g * (double)Ag * (double)p.inv_zeta;
         red[RED_WORK] = wi * (double)g * (double)flow;
         red[RED_TAU + 3 * al + 0] = (double)p.n * wi * (double)qv * (double)gp0;
         red[RED_TAU + 3 * al + 1] = (double)p.n * wi * (double)qv * (double)gp1;
         red[RED_TAU + 3 * al + 2] = (double)p.n * wi * (double)qv * (double)gp2;
         red[RED_F] = wi * (double)psi;
-        if (n == 0) red[RED_F] += wi * (double)p.kT * (log((double)S[I]) - (double)p.log_norm);
+        if (n == 0) red[RED_F] += wi * (double)p.kT * (log((double)in.S) - (double)p.log_norm);
       }
     }
   }
@@ -532,15 +573,17 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
 }
 
 __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs, const float *__restrict__ partial,
-                             const SplitMap &splits, const float *xc, const float *__restrict__ t1,
-                             const float *__restrict__ S, const float *wv, const float *qin,
-                             const float *__restrict__ qs, float *out, float *out2, double *__restrict__ redp,
-                             float *__restrict__ blockmax, const PackOps &pack, int *fene_out) {
+                             const SplitMap &splits, const float *__restrict__ t1, const float *__restrict__ S,
+                             const float *wv, const float *qin, const float *__restrict__ qs, float *out, float *out2,
+                             double *__restrict__ redp, float *__restrict__ blockmax, const PackOps &pack,
+                             int *fene_out) {
   const int64_t I = group_particle(lb);
+  const CombineIn in = combine_load(p, lb, mode, obs, true, t1, S, wv, qin, qs);
   const double o = I < p.P && group_lane() < p.D ? sum_splits(p, partial, splits, I, group_lane()) : 0.0;
-  combine_rows(p, lb, mode, obs, true, o, xc, t1, S, wv, qin, qs, out, out2, redp, blockmax, pack, fene_out);
+  combine_rows(p, lb, mode, obs, true, o, in, out, out2, redp, blockmax, pack, fene_out);
 }
 
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_combine(EvalParams p, int mode, int obs,
                                                        const float *__restrict__ partial, SplitMap splits,
                                                        const float *xc, const float *__restrict__ t1,
@@ -550,7 +593,8 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(EvalParams p, int mode, i
                                                        float *__restrict__ blockmax, const int *__restrict__ done,
                                                        PackOps pack, int *fene_out) {
   if (done != nullptr && *done) return;
-  combine_body(p, blockIdx.x, mode, obs, partial, splits, xc, t1, S, wv, qin, qs, out, out2, redp, blockmax, pack,
+  assume_dimension<D>(p);
+  combine_body(p, blockIdx.x, mode, obs, partial, splits, t1, S, wv, qin, qs, out, out2, redp, blockmax, pack,
                fene_out);
 }
 
@@ -816,7 +860,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const
                                                               const float *__restrict__ wv, float *q) {
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
-  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + o * 16, SplitMap{}, xc + o * b.D, t1 + o * b.D, S + o,
+  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + o * 16, SplitMap{}, t1 + o * b.D, S + o,
                wv + o, q + d.q_off, nullptr, q + d.q_off, nullptr, nullptr, nullptr, PackOps{}, nullptr);
 }
 
@@ -864,16 +908,14 @@ struct RowsLds {
 // Sum of lane (particle 16 blockIdx.x + t / 16, n = t % 16) for the first 256
 // threads: the difference sum's component n < D, the kernel sum at n = D.
 template <int D>
-__device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restrict__ V3, const float *__restrict__ xc,
-                            int nch, RowsLds<D> &lds) {
+__device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restrict__ V3, float x, int nch,
+                            const int *__restrict__ done, RowsLds<D> &lds, bool &stopped) {
   constexpr int NQ = bf3_slices(D), NT = bf3_tiles(D);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rb = (int)blockIdx.x;
   const int diag_i = (lane & 15) - 4 * (lane >> 4);
   bf16x8 neg[2], q[NQ];
-  minus_identity(lane, neg);
-  bf3_row_operand<D>(K3, rb, lane, q);
   uint4 kv[2 * NQ], vv[NT];
   auto load = [&](int c) {
 #pragma unroll
@@ -881,12 +923,20 @@ __device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restric
 #pragma unroll
     for (int T = 0; T < NT; ++T) vv[T] = V3[((int64_t)c * NT + T) * 64 + lane];
   };
-  if (wave < nch) load(wave);
+  // the flag, the row operand and the first chunk travel together (waves past
+  // the chunks load chunk 0)
+  const int dn = done != nullptr ? *done : 0;
+  load(wave < nch ? wave : 0);
+  bf3_row_operand<D>(K3, rb, lane, q);
+  asm volatile("" : "+v"(kv[0].x), "+v"(vv[0].x));  // keeps the loads ahead of the test
+  stopped = dn != 0;
+  if (stopped) return 0.0;
+  minus_identity(lane, neg);
   floatx4 acc[NT];
 #pragma unroll
   for (int T = 0; T < NT; ++T) acc[T] = floatx4{0.f, 0.f, 0.f, 0.f};
   double tot[4] = {0.0, 0.0, 0.0, 0.0};
-  int done = 0;
+  int count = 0;
   for (int c = wave; c < nch; c += kRowsWaves) {
     floatx4 e[2];
     bf16x8 va[NT];
@@ -901,7 +951,7 @@ __device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restric
     for (int T = 0; T < NT; ++T) va[T] = as_bf8(vv[T]);
     if (c + kRowsWaves < nch) load(c + kRowsWaves);
     bf3_accumulate<D>(e, va, neg, c == rb >> 1, rb & 1, diag_i, acc);
-    if (++done % kFlush3 == 0) bf3_flush<D>(acc, lane, tot);
+    if (++count % kFlush3 == 0) bf3_flush<D>(acc, lane, tot);
   }
   bf3_flush<D>(acc, lane, tot);
 #pragma unroll
@@ -912,8 +962,7 @@ __device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restric
     const int r = threadIdx.x >> 4, n = threadIdx.x & 15;
     for (int w = 0; w < kRowsWaves; ++w) o += lds.red[w][r][n];
     const double s = gshfl(o, D);
-    const int64_t I = (int64_t)rb * 16 + r;
-    if (n < D) o = (double)xc[I * D + n] * s - o;
+    if (n < D) o = (double)x * s - o;
   }
   return o;
 }
@@ -930,6 +979,12 @@ __global__ __launch_bounds__(kRowsWaves * 64) void k_rows_a(EvalParams p, const 
                                                             const float *__restrict__ blockmax, int nblk_chk) {
   __shared__ RowsLds<D> lds;
   __shared__ int stop;
+  assume_dimension<D>(p);
+  __builtin_assume(p.bf3 == 1 && p.vhalf == 0 && p.qhalf == 0);
+  const int64_t I = group_particle(blockIdx.x);
+  const int n = group_lane();
+  const bool act = threadIdx.x < kRedBlock;
+  const float x = act && n < D ? xc[I * D + n] : 0.f, w = act ? wv[I] : 0.f;
   if (chk.ctrl != nullptr) {
     // the flag once per block: the first block may set it during this launch
     if (threadIdx.x == 0) stop = *done;
@@ -945,12 +1000,10 @@ __global__ __launch_bounds__(kRowsWaves * 64) void k_rows_a(EvalParams p, const 
       }
     }
     if (was || conv) return;
-  } else if (done != nullptr && *done) {
-    return;
   }
-  const double o = rows_pass<D>(K3, VA, xc, nch, lds);
-  if (threadIdx.x < kRedBlock)
-    finalize_a_row(p, group_particle(blockIdx.x), group_lane(), o, xc, wv, S, t1, VB);
+  bool stopped;
+  const double o = rows_pass<D>(K3, VA, x, nch, chk.ctrl != nullptr ? nullptr : done, lds, stopped);
+  if (!stopped && act) finalize_a_row(p, I, n, o, x, w, S, t1, VB);
 }
 
 // Pass B and the combination (modes of k_combine), or with MODE_SUMS the row
@@ -966,19 +1019,30 @@ __global__ __launch_bounds__(kRowsWaves * 64) void k_rows_b(EvalParams p, int mo
                                                             float *__restrict__ blockmax, const int *__restrict__ done,
                                                             PackOps pack, int *fene_out) {
   __shared__ RowsLds<D> lds;
-  if (done != nullptr && *done) return;
-  const double o = rows_pass<D>(K3, VB, xc, nch, lds);
+  assume_dimension<D>(p);
+  __builtin_assume(p.bf3 == 1 && p.vhalf == 0 && p.qhalf == 0);
+  const int64_t I = group_particle(blockIdx.x);
+  const int n = group_lane();
+  const bool act = threadIdx.x < kRedBlock;
+  const float x = act && n < D ? xc[I * D + n] : 0.f;
+  CombineIn in{};
   if (mode == MODE_SUMS) {
-    const int64_t I = group_particle(blockIdx.x);
-    if (threadIdx.x < kRedBlock && I < p.P && group_lane() == D) {
-      const double Si = (double)S[I];
-      out[I] = (float)(o + (double)wv[I] / Si);
+    if (act && I < p.P) in.S = S[I], in.w = wv[I];
+  } else {
+    in = combine_load(p, blockIdx.x, mode, obs, act, t1, S, wv, qin, qs);
+  }
+  bool stopped;
+  const double o = rows_pass<D>(K3, VB, x, nch, done, lds, stopped);
+  if (stopped) return;
+  if (mode == MODE_SUMS) {
+    if (act && I < p.P && n == D) {
+      const double Si = (double)in.S;
+      out[I] = (float)(o + (double)in.w / Si);
       out2[I] = (float)(1.0 / Si);
     }
     return;
   }
-  combine_rows(p, blockIdx.x, mode, obs, threadIdx.x < kRedBlock, o, xc, t1, S, wv, qin, qs, out, out2, redp, blockmax,
-               pack, fene_out);
+  combine_rows(p, blockIdx.x, mode, obs, act, o, in, out, out2, redp, blockmax, pack, fene_out);
 }
 
 // ---- launchers ----
@@ -993,20 +1057,28 @@ void launch_prep(const EvalParams &p, const float *q, const float *w, const doub
                  float *wv, float *QB, float *KA, float *VA, float *wscale, const F16Operands *f16, const int *done,
                  hipStream_t s, float *cmean, Ctrl *begin) {
   const F16Operands ops = f16 != nullptr ? *f16 : F16Operands{nullptr, nullptr, nullptr};
-  k_prep<<<nblocks(p.Ppad * 16), kRedBlock, 0, s>>>(p, q, w, meanp, nmeanp, xc, wv, QB, KA, VA, wscale, ops, done,
-                                                    cmean, begin);
+  by_dimension(p.D, [&](auto d) {
+    k_prep<decltype(d)::value><<<nblocks(p.Ppad * 16), kRedBlock, 0, s>>>(p, q, w, meanp, nmeanp, xc, wv, QB, KA, VA,
+                                                                          wscale, ops, done, cmean, begin);
+  });
 }
 void launch_finalize_a(const EvalParams &p, const float *partial, const SplitMap &splits, const float *xc, const float *wv,
                        float *S, float *t1, float *VB, const int *done, hipStream_t s) {
-  k_finalize_a<<<nblocks(p.Ppad * 16), kRedBlock, 0, s>>>(p, partial, splits, xc, wv, S, t1, VB, done);
+  by_dimension(p.D, [&](auto d) {
+    k_finalize_a<decltype(d)::value>
+        <<<nblocks(p.Ppad * 16), kRedBlock, 0, s>>>(p, partial, splits, xc, wv, S, t1, VB, done);
+  });
 }
 void launch_combine(const EvalParams &p, int mode, bool obs, const float *partial, const SplitMap &splits, const float *xc,
                     const float *t1, const float *S, const float *wv, const float *qin, const float *q0,
                     float *out, float *out2, double *redp, float *blockmax, const int *done, hipStream_t s,
                     const PackOps *pack, int *fene_out) {
   const PackOps pk = pack != nullptr ? *pack : PackOps{};
-  k_combine<<<nblocks(p.P * 16), kRedBlock, 0, s>>>(p, mode, obs ? 1 : 0, partial, splits, xc, t1, S, wv, qin, q0,
-                                                    out, out2, redp, blockmax, done, pk, fene_out);
+  by_dimension(p.D, [&](auto d) {
+    k_combine<decltype(d)::value><<<nblocks(p.P * 16), kRedBlock, 0, s>>>(p, mode, obs ? 1 : 0, partial, splits, xc, t1,
+                                                                          S, wv, qin, q0, out, out2, redp, blockmax,
+                                                                          done, pk, fene_out);
+  });
 }
 // (particles up to the last chunk's end: their operands are written as zeros)
 static unsigned rows_grid(const EvalParams &p) { return (unsigned)(round_up(p.P, 32) / 16); }

@@ -940,13 +940,15 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
   // kWaves3 waves of RB 16-row blocks per row group (whole groups: the rows are
   // a multiple of 256); columns in chunks of 32
   const int rb = bf3_rb(D, t.rows_per_wave);
-  m.rows_per_group = kWaves3 * rb * 16;
+  m.group_shift = rb == 2 ? 8 : 7;  // kWaves3 rb 16 rows
+  static_assert(kWaves3 * 16 == 128, "row groups of 128 or 256 rows");
   m.n_rg = (nrow_blocks + kWaves3 * rb - 1) / (kWaves3 * rb);
   m.nch = (ncol_chunks + 1) / 2;
   m.splits = kMaxSplits;
   // col_splits / 2 workgroups of eight waves per compute unit; runs of at least
   // qmin units, so that at most kMaxSplits runs meet in one row group
   const int64_t U = m.units();
+  m.inv_units = 1.0 / (double)U;
   const int64_t qmin = (m.nch + kMaxSplits - 2) / (kMaxSplits - 1);
   int64_t G = std::min<int64_t>(std::max<int64_t>(1, (int64_t)t.col_splits * device_cu_count() / 2), U / qmin);
   if (G >= 8) G -= G % 8;

@@ -163,16 +163,24 @@ struct SplitMap {
   int width = 16;          // floats per row of a slot: 16, or D + 1 for the compact layout
   int splits = 1;          // fixed splits; with G > 0, a bound on count()
   int G = 0;               // runs (workgroups) of the balanced grid, 0 for fixed splits
-  int rows_per_group = 0;  // rows of one row group
+  int group_shift = 0;     // log2 of the rows of one row group
   int64_t nch = 0;         // column chunks per row group
   int64_t n_rg = 0;        // row groups
+  double inv_units = 0.0;  // 1 / units(): a 64-bit division is some hundred instructions on the GPU
   __host__ __device__ int64_t units() const { return n_rg * nch; }
-  // first unit of run L, and the run holding unit u
+  // first unit of run L, and the run holding unit u (units() G stays below 2^53)
   __host__ __device__ int64_t run_start(int64_t L) const { return L * units() / G; }
-  __host__ __device__ int64_t run_of(int64_t u) const { return ((u + 1) * G - 1) / units(); }
+  __host__ __device__ int64_t run_of(int64_t u) const {
+    const int64_t a = (u + 1) * G - 1, b = units();
+    int64_t q = (int64_t)((double)a * inv_units);
+    const int64_t r = a - q * b;
+    if (r < 0) --q;
+    else if (r >= b) ++q;
+    return q;
+  }
   __host__ __device__ int count(int64_t row) const {
     if (G == 0) return splits;
-    const int64_t rg = row / rows_per_group;
+    const int64_t rg = row >> group_shift;
     return (int)(run_of((rg + 1) * nch - 1) - run_of(rg * nch) + 1);
   }
 };
