@@ -79,7 +79,8 @@ MlpLayout mlp_layout(int nin, int w, int nout, int B) {
   L.tin = take(sizeof(float) * Bp * nout);
   const int64_t g1 = (int64_t)gemm_splits_small(w, nin, Bp, 1024) * w * nin, g3 = (int64_t)gemm_splits_small(nout, w, Bp, 1024) * nout * w;
   const int64_t g0 = (int64_t)Bp * std::max(nout, std::max(w, nin)) * 2;
-  L.part = take(sizeof(float) * std::max(std::max(g1, g3), g0));
+  const int64_t g2 = (int64_t)gemm_splits_small(w, w, Bp, 1024) * w * w;
+  L.part = take(sizeof(float) * std::max(std::max(g1, g2), std::max(g3, g0)));
   L.lossp = take(sizeof(double) * ((int64_t)(Bp * nout + 255) / 256 + 2));
   L.total = off;
   return L;
