@@ -9,7 +9,6 @@
 #include <vector>
 
 #include "vds_ctx.h"
-#include "vds_linalg.h"
 #include "vds_mlp.h"
 #include "vds_pod.h"
 
@@ -23,8 +22,7 @@ typedef short shortx4 __attribute__((ext_vector_type(4)));
 thread_local std::string g_mlp_create_error;
 
 struct MlpLayout {
-  size_t params, grads, adam_m, adam_v, wbf, wpk, Z1, A1, Z2, A2, Y, dY, dA, dZ, xs, xsc, ys, ysc, xin, tin, part, lossp,
-      total;
+  size_t params, grads, adam_m, adam_v, wbf, wpk, Z1, A1, Z2, A2, Y, dY, dZ1, dZ2, xs, xsc, ys, ysc, xin, tin, lossp, total;
 };
 
 // Resident learned steps (k_learned_steps_reg): one workgroup of 1024 threads
@@ -47,6 +45,11 @@ int64_t nparams(int nin, int w, int nout) {
   return (int64_t)w * nin + w + (int64_t)w * w + w + (int64_t)nout * w + nout;
 }
 
+// Output tiles of tb x tb blocks of 16 x 16.
+__host__ __device__ constexpr int64_t mlp_tiles(int64_t M, int64_t N, int tb) {
+  return ((M + 16 * tb - 1) / (16 * tb)) * ((N + 16 * tb - 1) / (16 * tb));
+}
+
 MlpLayout mlp_layout(int nin, int w, int nout, int B) {
   MlpLayout L{};
   size_t off = 0;
@@ -56,7 +59,7 @@ MlpLayout mlp_layout(int nin, int w, int nout, int B) {
     return o;
   };
   const int64_t np = nparams(nin, w, nout);
-  const int Bp = (B + 15) / 16 * 16;
+  const int64_t Bp = (B + 15) / 16 * 16;
   L.params = take(sizeof(float) * np);
   L.grads = take(sizeof(float) * np);
   L.adam_m = take(sizeof(float) * np);
@@ -69,19 +72,15 @@ MlpLayout mlp_layout(int nin, int w, int nout, int B) {
   L.A2 = take(sizeof(float) * Bp * w);
   L.Y = take(sizeof(float) * Bp * nout);
   L.dY = take(sizeof(float) * Bp * nout);
-  L.dA = take(sizeof(float) * Bp * w);
-  L.dZ = take(sizeof(float) * Bp * w);
+  L.dZ1 = take(sizeof(float) * Bp * w);
+  L.dZ2 = take(sizeof(float) * Bp * w);
   L.xs = take(sizeof(float) * nin);
   L.xsc = take(sizeof(float) * nin);
   L.ys = take(sizeof(float) * nout);
   L.ysc = take(sizeof(float) * nout);
   L.xin = take(sizeof(float) * Bp * nin);
   L.tin = take(sizeof(float) * Bp * nout);
-  const int64_t g1 = (int64_t)gemm_splits_small(w, nin, Bp, 1024) * w * nin, g3 = (int64_t)gemm_splits_small(nout, w, Bp, 1024) * nout * w;
-  const int64_t g0 = (int64_t)Bp * std::max(nout, std::max(w, nin)) * 2;
-  const int64_t g2 = (int64_t)gemm_splits_small(w, w, Bp, 1024) * w * w;
-  L.part = take(sizeof(float) * std::max(std::max(g1, g2), std::max(g3, g0)));
-  L.lossp = take(sizeof(double) * ((int64_t)(Bp * nout + 255) / 256 + 2));
+  L.lossp = take(sizeof(double) * (mlp_tiles(B, nout, 1) + 2));
   L.total = off;
   return L;
 }
@@ -101,56 +100,243 @@ __global__ void k_to_bf16(const float *__restrict__ a, short *__restrict__ b, in
   if (i < n) b[i] = f2bf(a[i]);
 }
 
-// Z[i][j] += bias[j]; A = silu(Z) (act) or A = Z.
-__global__ void k_bias_act(float *__restrict__ Z, const float *__restrict__ bias, int n, int m, int act,
-                           float *__restrict__ A) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (int64_t)n * m) return;
-  const float z = Z[t] + bias[t % m];
-  Z[t] = z;
-  if (A) A[t] = act ? silu(z) : z;
+// ---- training products ----
+//
+// A minibatch is six launches, one per link of the chain
+//   Z1 -> Z2 -> Y, loss -> {dZ2, dW3, db3} -> {dZ1, dW2, db2} -> {dW1, db1, loss}
+// with bias, SiLU, the loss gradient and SiLU's derivative in the products'
+// epilogues.  At the learned step's own shape (541-128-128-540, 64 rows: 62
+// MFLOP, 1 MB) only latency counts, so an output tile is one 16 x 16 block, K
+// goes over the eight waves of a workgroup (the block's wave sums meet in LDS)
+// and the operands come straight from memory, four rounds of 16 in flight per
+// wave.
+// Bound: the chain of launches (3.3 to 4.9 us each, one or two memory latencies
+// and the wave sum; 24 us together, 41 with the loss on the host).  25 launches
+// of 64 x 64-tile products (each with its own sum over K splits), elementwise
+// passes and one-thread column sums took 250 and 270 us.
+enum MlpEpi { kEpiHidden, kEpiOutput, kEpiInputGrad, kEpiWeightGrad };
+
+// C (M x N) = A B^T over K, FP32 MFMA.
+struct MlpOp {
+  int M, N, K;
+  int epi;
+  int64_t tiles;           // of the launch's tile edge
+  const float *A, *B;
+  int64_t lda, ldb;
+  const float *aux;        // bias; in kEpiInputGrad Z of the layer below
+  const float *T;          // kEpiOutput: targets, or null for the forward pass alone
+  float *C;                // Z or Y; dZ; dW
+  float *C2;               // hidden: A = silu(Z); output: dY
+  double *lossp;           // output: one partial sum of (Y - T)^2 per tile
+};
+
+// db[j] = sum_i dZ[i][j] (N columns, n rows), in FP64.
+struct MlpColsum {
+  const float *dZ;
+  int64_t n;
+  int N;
+  float *db;
+};
+
+// *out = (add ? *out : 0) + scale * sum of np partial sums.
+struct MlpLoss {
+  const double *lossp;
+  int64_t np;
+  double scale;
+  int add;
+  double *out;
+};
+
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// k indices k .. k+3 of one row (MN: of one column at stride ld) of an operand.
+template <bool MN>
+__device__ inline floatx4 mlp_load(const float *__restrict__ p, int64_t ld, int k) {
+  if constexpr (MN) {
+    const float *q = p + k * ld;
+    return floatx4{q[0], q[ld], q[2 * ld], q[3 * ld]};
+  } else {
+    return *reinterpret_cast<const float4u *>(p + k);
+  }
 }
 
-// dY = 2 (Y - T) / (n m), per-block FP64 partial sums of (Y - T)^2.
-__global__ void k_mse(const float *__restrict__ Y, const float *__restrict__ T, int n, int m, float *__restrict__ dY,
-                      double *__restrict__ lossp) {
-  __shared__ double sm[256];
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double e2 = 0.0;
-  if (t < (int64_t)n * m) {
-    const float d = Y[t] - T[t];
-    dY[t] = 2.f * d / ((float)n * (float)m);
-    e2 = (double)d * (double)d;
+// The same at the end of K: what lies beyond counts as zero.
+template <bool MN>
+__device__ inline floatx4 mlp_load_tail(const float *__restrict__ p, int64_t ld, int k, int K) {
+  floatx4 v;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int64_t kk = min(k + t, K - 1);
+    const float x = p[MN ? kk * ld : kk];
+    v[t] = k + t < K ? x : 0.f;
   }
-  sm[threadIdx.x] = e2;
+  return v;
+}
+
+constexpr int kMlpWaves = 8;
+
+// This wave's share of tile (ti, tj): rounds of 16 k, wave, wave + 8, ...  Lane
+// l holds k 4 (l / 16) .. + 3 of a round in row l % 16 of each block, one step
+// of the matrix unit taking one k from each group of four.
+template <int TB, bool A_MN, bool B_MN>
+__device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int lane, int wave,
+                                   floatx4 (&acc)[TB][TB]) {
+  constexpr int U = TB == 1 ? 4 : 1;
+  const int m = lane & 15, k0 = (lane >> 4) * 4;
+  const float *pa[TB], *pb[TB];
+#pragma unroll
+  for (int a = 0; a < TB; ++a) {
+    const int64_t ra = min(ti * (16 * TB) + 16 * a + m, (int64_t)o.M - 1);
+    const int64_t rb = min(tj * (16 * TB) + 16 * a + m, (int64_t)o.N - 1);
+    pa[a] = o.A + (A_MN ? ra : ra * o.lda);
+    pb[a] = o.B + (B_MN ? rb : rb * o.ldb);
+  }
+  auto products = [&](const floatx4(&va)[TB], const floatx4(&vb)[TB]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int a = 0; a < TB; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(va[a][t], vb[b][t], acc[a][b], 0, 0, 0);
+  };
+  const int full = o.K / 16;
+  int r = wave;
+  for (; r + (U - 1) * kMlpWaves < full; r += U * kMlpWaves) {
+    floatx4 va[U][TB], vb[U][TB];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int a = 0; a < TB; ++a) {
+        const int k = 16 * (r + u * kMlpWaves) + k0;
+        va[u][a] = mlp_load<A_MN>(pa[a], o.lda, k);
+        vb[u][a] = mlp_load<B_MN>(pb[a], o.ldb, k);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) products(va[u], vb[u]);
+  }
+  for (; r <= full; r += kMlpWaves) {
+    if (r == full && o.K % 16 == 0) break;
+    floatx4 va[TB], vb[TB];
+    const int k = 16 * r + k0;
+#pragma unroll
+    for (int a = 0; a < TB; ++a) {
+      va[a] = r < full ? mlp_load<A_MN>(pa[a], o.lda, k) : mlp_load_tail<A_MN>(pa[a], o.lda, k, o.K);
+      vb[a] = r < full ? mlp_load<B_MN>(pb[a], o.ldb, k) : mlp_load_tail<B_MN>(pb[a], o.ldb, k, o.K);
+    }
+    products(va, vb);
+  }
+}
+
+// Sum of v over the workgroup's 512 threads, in thread 0, fixed order.
+__device__ inline double mlp_block_sum(double v, int tid) {
+  __shared__ double wsum[kMlpWaves];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_down(v, d);
+  if ((tid & 63) == 0) wsum[tid >> 6] = v;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sm[threadIdx.x] += sm[threadIdx.x + s];
-    __syncthreads();
+  double s = 0.0;
+  if (tid == 0)
+    for (int i = 0; i < kMlpWaves; ++i) s += wsum[i];
+  return s;
+}
+
+template <int TB>
+__device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int tid) {
+  constexpr int E = 16 * TB, NE = E * E;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int64_t tm = (o.M + E - 1) / E, ti = tile % tm, tj = tile / tm;
+  floatx4 acc[TB][TB];
+#pragma unroll
+  for (int a = 0; a < TB; ++a)
+#pragma unroll
+    for (int b = 0; b < TB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (o.epi == kEpiInputGrad)
+    mlp_product<TB, false, true>(o, ti, tj, lane, wave, acc);
+  else if (o.epi == kEpiWeightGrad)
+    mlp_product<TB, true, true>(o, ti, tj, lane, wave, acc);
+  else
+    mlp_product<TB, false, false>(o, ti, tj, lane, wave, acc);
+#pragma unroll
+  for (int a = 0; a < TB; ++a)
+#pragma unroll
+    for (int b = 0; b < TB; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        red[wave * NE + (16 * a + 4 * (lane >> 4) + t) * E + 16 * b + (lane & 15)] = acc[a][b][t];
+  __syncthreads();
+  double e2 = 0.0;
+  for (int e = tid; e < NE; e += kMlpWaves * 64) {
+    const int64_t i = ti * E + e / E;
+    const int j = (int)(tj * E) + e % E;
+    if (i >= o.M || j >= o.N) continue;
+    float c = 0.f;
+#pragma unroll
+    for (int v = 0; v < kMlpWaves; ++v) c += red[v * NE + e];
+    const int64_t at = i * o.N + j;
+    if (o.epi == kEpiHidden) {
+      const float z = c + o.aux[j];
+      o.C[at] = z;
+      o.C2[at] = silu(z);
+    } else if (o.epi == kEpiOutput) {
+      const float y = c + o.aux[j];
+      o.C[at] = y;
+      if (o.T) {
+        const float d = y - o.T[at];
+        o.C2[at] = 2.f * d / ((float)o.M * (float)o.N);
+        e2 += (double)d * (double)d;
+      }
+    } else if (o.epi == kEpiInputGrad) {
+      o.C[at] = c * silu_grad(o.aux[at]);
+    } else {
+      o.C[at] = c;
+    }
   }
-  if (threadIdx.x == 0) lossp[blockIdx.x] = sm[0];
+  if (o.epi == kEpiOutput && o.T) {
+    e2 = mlp_block_sum(e2, tid);
+    if (tid == 0) o.lossp[tile] = e2;
+  }
 }
 
-__global__ void k_sum_loss(const double *__restrict__ lossp, int nb, double scale, double *__restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// One launch: the tiles of two products, then 64 columns of a column sum per
+// workgroup (eight groups of rows), then the loss.
+template <int TB>
+__global__ __launch_bounds__(kMlpWaves * 64) void k_mlp(MlpOp o0, MlpOp o1, MlpColsum cs, MlpLoss ls) {
+  __shared__ float red[kMlpWaves * 256 * TB * TB];
+  const int tid = threadIdx.x;
+  int64_t b = blockIdx.x;
+  if (b < o0.tiles) return mlp_tile<TB>(o0, b, red, tid);
+  b -= o0.tiles;
+  if (b < o1.tiles) return mlp_tile<TB>(o1, b, red, tid);
+  b -= o1.tiles;
+  if (b < (cs.N + 63) / 64) {
+    double *sums = reinterpret_cast<double *>(red);
+    const int64_t j = b * 64 + (tid & 63);
+    double s = 0.0;
+    if (j < cs.N) {
+      const float *p = cs.dZ + j;
+      int64_t i = tid >> 6;
+      for (; i + 7 * kMlpWaves < cs.n; i += 8 * kMlpWaves) {  // eight rows in flight
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(i + u * kMlpWaves) * cs.N];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += (double)v[u];
+      }
+      for (; i < cs.n; i += kMlpWaves) s += (double)p[i * cs.N];
+    }
+    sums[tid] = s;
+    __syncthreads();
+    if (tid < 64 && j < cs.N) {
+      for (int v = 1; v < kMlpWaves; ++v) s += sums[v * 64 + tid];
+      cs.db[j] = (float)s;
+    }
+    return;
+  }
   double s = 0.0;
-  for (int i = 0; i < nb; ++i) s += lossp[i];
-  *out = s * scale;
-}
-
-__global__ void k_silu_back(const float *__restrict__ dA, const float *__restrict__ Z, int64_t n,
-                            float *__restrict__ dZ) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < n) dZ[t] = dA[t] * silu_grad(Z[t]);
-}
-
-// db[j] = sum_i dZ[i][j], fixed order.
-__global__ void k_colsum(const float *__restrict__ dZ, int n, int m, float *__restrict__ db) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= m) return;
-  double s = 0.0;
-  for (int i = 0; i < n; ++i) s += (double)dZ[(int64_t)i * m + j];
-  db[j] = (float)s;
+  for (int64_t i = tid; i < ls.np; i += kMlpWaves * 64) s += ls.lossp[i];
+  s = mlp_block_sum(s, tid);
+  if (tid == 0) *ls.out = (ls.add ? *ls.out : 0.0) + s * ls.scale;
 }
 
 __global__ void k_adam(float *__restrict__ th, const float *__restrict__ g, float *__restrict__ m1,
@@ -525,10 +711,10 @@ struct vds_mlp_s {
   hipStream_t s = nullptr;
   MlpLayout L{};
   char *ws = nullptr;
-  float *params, *grads, *am, *av, *Z1, *A1, *Z2, *A2, *Y, *dY, *dA, *dZ, *xs, *xsc, *ys, *ysc, *xin, *tin, *part;
+  float *params, *grads, *am, *av, *Z1, *A1, *Z2, *A2, *Y, *dY, *dZ1, *dZ2, *xs, *xsc, *ys, *ysc, *xin, *tin;
   short *wbf, *wpk;
   double *lossp;
-  double *loss_out;  // one slot after the per-block partials
+  double *loss_out;  // one slot after the per-tile partials
   int t = 0;
   bool bf_stale = true;
   float noise = 0.f;          // training input noise (vds_mlp_set_input_noise)
@@ -554,80 +740,97 @@ vds_status mhip(vds_mlp m, hipError_t e, const char *what) {
   return merr(m, VDS_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// C = A B^T (row-major), A: n x K, B: N x K, both K-contiguous.
-void dense(vds_mlp m, const float *A, int n, int K, const float *B, int N, float *C) {
-  GemmShape g;
-  g.M = n;
-  g.N = N;
-  g.K = K;
-  g.A = A;
-  g.lda = K;
-  g.B = B;
-  g.ldb = K;
-  g.C = C;
-  g.ldc = N;
-  launch_gemm_small(g, m->part, m->s);
+// Tile edge of a launch in blocks of 16: wider tiles read less, but each product
+// needs enough of them, since a tile's K is not split further than over its
+// workgroup.  32 wide from 512 tiles on (two workgroups per compute unit): a
+// minibatch of 2048 at 541-128-128-540 takes 112 us so and 121 with 16; 64 wide
+// from 1024 on: 2049-2048-2048-2048 with 2048 rows 1.72 ms, 2.08 with 32 and
+// 3.29 with 16.  By the smaller of the two products: 16384 rows at
+// 541-128-128-540 take 0.78 ms with 16 and 1.19 when the many rows of one
+// product choose 64 for both.
+int mlp_edge(const MlpOp &a, const MlpOp &b) {
+  auto tiles = [&](int tb) {
+    const int64_t ta = mlp_tiles(a.M, a.N, tb);
+    return b.M ? std::min(ta, mlp_tiles(b.M, b.N, tb)) : ta;
+  };
+  return tiles(4) >= 1024 ? 4 : tiles(2) >= 512 ? 2 : 1;
 }
 
-void forward_fp32(vds_mlp m, const float *X, int n) {
-  dense(m, X, n, m->nin, m->W1(), m->w, m->Z1);
-  k_bias_act<<<nb256((int64_t)n * m->w), 256, 0, m->s>>>(m->Z1, m->b1(), n, m->w, 1, m->A1);
-  dense(m, m->A1, n, m->w, m->W2(), m->w, m->Z2);
-  k_bias_act<<<nb256((int64_t)n * m->w), 256, 0, m->s>>>(m->Z2, m->b2(), n, m->w, 1, m->A2);
-  dense(m, m->A2, n, m->w, m->W3(), m->nout, m->Y);
-  k_bias_act<<<nb256((int64_t)n * m->nout), 256, 0, m->s>>>(m->Y, m->b3(), n, m->nout, 0, nullptr);
+// Returns the tiles of the first product.
+int64_t launch_mlp(vds_mlp m, MlpOp a, MlpOp b = MlpOp{}, const MlpColsum &cs = MlpColsum{},
+                   const MlpLoss &ls = MlpLoss{}) {
+  const int tb = mlp_edge(a, b);
+  a.tiles = mlp_tiles(a.M, a.N, tb);
+  b.tiles = mlp_tiles(b.M, b.N, tb);
+  const unsigned grid = (unsigned)(a.tiles + b.tiles + (cs.N + 63) / 64 + (ls.out ? 1 : 0));
+  if (tb == 4)
+    k_mlp<4><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+  else if (tb == 2)
+    k_mlp<2><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+  else
+    k_mlp<1><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+  return a.tiles;
 }
 
-// dW (N x K) = dZ^T A with dZ: n x N, A: n x K (both row-major)
-void weight_grad(vds_mlp m, const float *dZ, int n, int N, const float *A, int K, float *dW) {
-  GemmShape g;
-  g.M = N;
-  g.N = K;
-  g.K = n;
-  g.A = dZ;
-  g.lda = N;
-  g.a_mn = true;
-  g.B = A;
-  g.ldb = K;
-  g.b_mn = true;
-  g.C = dW;
-  g.ldc = K;
-  g.splits = gemm_splits_small(N, K, n, 512);
-  launch_gemm_small(g, m->part, m->s);
+// Z (n x N) = X W^T + bias, X: n x K, W: N x K, and A = silu(Z); in the last
+// layer (A null) with targets T also dY and the loss partials.
+MlpOp dense(const float *X, int n, int K, const float *W, const float *bias, int N, float *Z, float *A) {
+  MlpOp o{};
+  o.M = n, o.N = N, o.K = K;
+  o.epi = A ? kEpiHidden : kEpiOutput;
+  o.A = X, o.lda = K;
+  o.B = W, o.ldb = K;
+  o.aux = bias;
+  o.C = Z, o.C2 = A;
+  return o;
 }
 
-// dA (n x K) = dZ W with dZ: n x N, W: N x K
-void input_grad(vds_mlp m, const float *dZ, int n, int N, const float *W, int K, float *dA) {
-  GemmShape g;
-  g.M = n;
-  g.N = K;
-  g.K = N;
-  g.A = dZ;
-  g.lda = N;
-  g.B = W;
-  g.ldb = K;
-  g.b_mn = true;
-  g.C = dA;
-  g.ldc = K;
-  launch_gemm_small(g, m->part, m->s);
+// dZ of the layer below (n x K) = (dZ W) silu'(Z), dZ: n x N, W: N x K
+MlpOp input_grad(const float *dZ, int n, int N, const float *W, int K, const float *Z, float *out) {
+  MlpOp o{};
+  o.M = n, o.N = K, o.K = N;
+  o.epi = kEpiInputGrad;
+  o.A = dZ, o.lda = N;
+  o.B = W, o.ldb = K;
+  o.aux = Z;
+  o.C = out;
+  return o;
 }
 
-void backward_fp32(vds_mlp m, const float *X, const float *T, int n) {
+// dW (N x K) = dZ^T A, dZ: n x N, A: n x K
+MlpOp weight_grad(const float *dZ, int n, int N, const float *A, int K, float *dW) {
+  MlpOp o{};
+  o.M = N, o.N = K, o.K = n;
+  o.epi = kEpiWeightGrad;
+  o.A = dZ, o.lda = N;
+  o.B = A, o.ldb = K;
+  o.C = dW;
+  return o;
+}
+
+// Y (n x nout); with targets T also dY, the loss partials and their number.
+int64_t forward_fp32(vds_mlp m, const float *X, int n, float *Y, const float *T = nullptr) {
+  launch_mlp(m, dense(X, n, m->nin, m->W1(), m->b1(), m->w, m->Z1, m->A1));
+  launch_mlp(m, dense(m->A1, n, m->w, m->W2(), m->b2(), m->w, m->Z2, m->A2));
+  MlpOp out = dense(m->A2, n, m->w, m->W3(), m->b3(), m->nout, Y, nullptr);
+  out.T = T;
+  out.C2 = m->dY;
+  out.lossp = m->lossp;
+  return launch_mlp(m, out);
+}
+
+// Gradients and loss of one minibatch; the loss is added to *loss_out or put there.
+void loss_grad_fp32(vds_mlp m, const float *X, const float *T, int n, bool add_loss) {
   const int w = m->w, nin = m->nin, nout = m->nout;
   float *gW1 = m->grads, *gb1 = gW1 + (int64_t)w * nin, *gW2 = gb1 + w, *gb2 = gW2 + (int64_t)w * w,
         *gW3 = gb2 + w, *gb3 = gW3 + (int64_t)nout * w;
-  const int64_t ny = (int64_t)n * nout;
-  k_mse<<<nb256(ny), 256, 0, m->s>>>(m->Y, T, n, nout, m->dY, m->lossp);
-  weight_grad(m, m->dY, n, nout, m->A2, w, gW3);
-  k_colsum<<<nb256(nout), 256, 0, m->s>>>(m->dY, n, nout, gb3);
-  input_grad(m, m->dY, n, nout, m->W3(), w, m->dA);
-  k_silu_back<<<nb256((int64_t)n * w), 256, 0, m->s>>>(m->dA, m->Z2, (int64_t)n * w, m->dZ);
-  weight_grad(m, m->dZ, n, w, m->A1, w, gW2);
-  k_colsum<<<nb256(w), 256, 0, m->s>>>(m->dZ, n, w, gb2);
-  input_grad(m, m->dZ, n, w, m->W2(), w, m->dA);
-  k_silu_back<<<nb256((int64_t)n * w), 256, 0, m->s>>>(m->dA, m->Z1, (int64_t)n * w, m->dZ);
-  weight_grad(m, m->dZ, n, w, X, nin, gW1);
-  k_colsum<<<nb256(w), 256, 0, m->s>>>(m->dZ, n, w, gb1);
+  const int64_t np = forward_fp32(m, X, n, m->Y, T);
+  launch_mlp(m, input_grad(m->dY, n, nout, m->W3(), w, m->Z2, m->dZ2), weight_grad(m->dY, n, nout, m->A2, w, gW3),
+             MlpColsum{m->dY, n, nout, gb3});
+  launch_mlp(m, input_grad(m->dZ2, n, w, m->W2(), w, m->Z1, m->dZ1), weight_grad(m->dZ2, n, w, m->A1, w, gW2),
+             MlpColsum{m->dZ2, n, w, gb2});
+  launch_mlp(m, weight_grad(m->dZ1, n, w, X, nin, gW1), MlpOp{}, MlpColsum{m->dZ1, n, w, gb1},
+             MlpLoss{m->lossp, np, 1.0 / ((double)n * nout), add_loss, m->loss_out});
 }
 
 void refresh_bf16(vds_mlp m) {
@@ -735,17 +938,16 @@ vds_status vds_mlp_bind_workspace(vds_mlp m, void *ws, size_t bytes) {
   m->A2 = f(L.A2);
   m->Y = f(L.Y);
   m->dY = f(L.dY);
-  m->dA = f(L.dA);
-  m->dZ = f(L.dZ);
+  m->dZ1 = f(L.dZ1);
+  m->dZ2 = f(L.dZ2);
   m->xs = f(L.xs);
   m->xsc = f(L.xsc);
   m->ys = f(L.ys);
   m->ysc = f(L.ysc);
   m->xin = f(L.xin);
   m->tin = f(L.tin);
-  m->part = f(L.part);
   m->lossp = reinterpret_cast<double *>(m->ws + L.lossp);
-  m->loss_out = m->lossp + ((int64_t)((m->B + 15) / 16 * 16) * m->nout + 255) / 256 + 1;
+  m->loss_out = m->lossp + mlp_tiles(m->B, m->nout, 1);
   // identity scaling until set
   std::vector<float> zx(m->nin, 0.f), ox(m->nin, 1.f), zy(m->nout, 0.f), oy(m->nout, 1.f);
   vds_status st = mhip(m, hipMemcpyAsync(m->xs, zx.data(), 4 * m->nin, hipMemcpyHostToDevice, m->s), "init");
@@ -790,9 +992,7 @@ vds_status vds_mlp_forward(vds_mlp m, const float *X, int32_t n, float *Y, int32
   if (bf16) {
     forward_bf16(m, X, n, Y);
   } else {
-    forward_fp32(m, X, n);
-    vds_status st = mhip(m, hipMemcpyAsync(Y, m->Y, 4 * (size_t)n * m->nout, hipMemcpyDeviceToDevice, m->s), "copy");
-    if (st != VDS_OK) return st;
+    forward_fp32(m, X, n, Y);
   }
   return mhip(m, hipGetLastError(), "forward");
 }
@@ -820,14 +1020,10 @@ vds_status vds_mlp_loss_grad(vds_mlp m, const float *X, const float *T, int32_t 
   if (!m || !X || !T) return VDS_ERR_ARG;
   if (!m->ws) return merr(m, VDS_ERR_STATE, "no workspace bound");
   if (n < 1 || n > m->B) return merr(m, VDS_ERR_ARG, "batch size out of range");
-  forward_fp32(m, X, n);
-  backward_fp32(m, X, T, n);
+  loss_grad_fp32(m, X, T, n, false);
   vds_status st = mhip(m, hipGetLastError(), "loss_grad");
   if (st != VDS_OK || loss == nullptr) return st;
-  const int nblk = (int)nb256((int64_t)n * m->nout);
-  double *dev = m->loss_out;
-  k_sum_loss<<<1, 64, 0, m->s>>>(m->lossp, nblk, 1.0 / ((double)n * m->nout), dev);
-  st = mhip(m, hipMemcpyAsync(loss, dev, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy loss");
+  st = mhip(m, hipMemcpyAsync(loss, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy loss");
   if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
   return st;
 }
@@ -854,21 +1050,15 @@ vds_status vds_mlp_train_epoch(vds_mlp m, const float *X, const float *T, int32_
         X, T, order, bi * batch, batch, m->nin, m->nout, m->xs, m->xsc, m->ys, m->ysc, m->xin, m->tin, m->noise,
         m->noise_seed, m->noise_draws);
     m->noise_draws += (uint64_t)batch * m->nin;
-    forward_fp32(m, m->xin, batch);
-    backward_fp32(m, m->xin, m->tin, batch);
+    loss_grad_fp32(m, m->xin, m->tin, batch, bi > 0);
     vds_mlp_adam_step(m, lr, 0.9f, 0.999f, 1e-8f);
-    if (loss) {
-      const int nblk = (int)nb256((int64_t)batch * m->nout);
-      k_sum_loss<<<1, 64, 0, m->s>>>(m->lossp, nblk, 1.0 / ((double)batch * m->nout), m->loss_out);
-      double l = 0.0;
-      vds_status st = mhip(m, hipMemcpyAsync(&l, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy");
-      if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
-      if (st != VDS_OK) return st;
-      acc += l;
-    }
   }
-  if (loss) *loss = acc / nbatch;
-  return mhip(m, hipStreamSynchronize(m->s), "synchronise");
+  vds_status st = mhip(m, hipGetLastError(), "train epoch");
+  if (st == VDS_OK && loss)
+    st = mhip(m, hipMemcpyAsync(&acc, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy");
+  if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
+  if (st == VDS_OK && loss) *loss = acc / nbatch;
+  return st;
 }
 
 vds_status vds_mlp_fit_scaling(vds_mlp m, const float *X, const float *T, int32_t n) {

@@ -35,11 +35,9 @@ struct GemmShape {
   bool symmetric = false;
 };
 
-// Large products: BF16 matrix cores, three BF16 parts per FP32 factor.  Sums
+// BF16 matrix cores, three BF16 parts per FP32 factor.  Sums
 // within a split in FP32, over the splits in FP64.
 void launch_gemm(const GemmShape &g, float *part, hipStream_t s);
-// Small products: FP32 matrix cores, one workgroup per 64 x 64 tile and split.
-void launch_gemm_small(const GemmShape &g, float *part, hipStream_t s);
 void launch_cholesky(double *A, int n, double shift, int *info, hipStream_t s);
 void launch_tri_inverse(const double *L, int n, double *work, float *Linv, hipStream_t s);
 void launch_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);

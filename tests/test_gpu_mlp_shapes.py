@@ -1,11 +1,11 @@
 """Loss and gradients of the learned step's training over network and batch
-shapes: fewer inputs and outputs than hidden units, remainders of the 16-wide
-matrix tiles, one row, and a batch smaller than the one laid out for.
+shapes: fewer inputs and outputs than hidden units, remainders of the 16-, 32-
+and 64-wide tiles, one row, and a batch smaller than the one laid out for.
 
-Tolerances: every value is an FP32 sum of at most K = 541 products with
-relative error below K 2^-24 = 3.2e-5 even if all errors add up: loss relative
-1e-5 (an FP64 mean over many elements), gradients relative Frobenius 1e-4 per
-tensor (three products in a chain)."""
+Tolerances: a value is an FP32 sum of up to K = 2100 products, whose rounding
+errors of varying sign come to about sqrt(K) 2^-24 = 2.7e-6 of its terms: loss
+relative 1e-5 (an FP64 mean over many elements), gradients relative Frobenius
+1e-4 per tensor (three such products in a chain, and sums that cancel)."""
 import numpy as np
 import pytest
 
@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     (16, 16, 16, 16, 16),
     (130, 65, 129, 100, 100),
     (541, 128, 540, 128, 65),
+    (37, 1100, 1090, 520, 520),    # 32-wide tiles
+    (70, 2050, 2060, 2049, 2049),  # 64-wide tiles
 ])
 def test_loss_and_gradients(nin, w, nout, batch, n):
     import torch
