@@ -227,10 +227,9 @@ __device__ bool picard_converged(const PicardCheck &chk, const float *__restrict
 }
 
 // Column operand K3 of particle I from its centred coordinate x (lane n;
-// zeros past the particles): see vds_internal.h.
-__device__ inline void store_k3(const EvalParams &p, uint32_t *__restrict__ K3, int64_t I, int n, float x) {
+// zeros past the particles, when not real): see vds_internal.h.
+__device__ inline void store_k3(const EvalParams &p, bool real, uint32_t *__restrict__ K3, int64_t I, int n, float x) {
   const int NQ = bf3_slices(p.D);
-  const bool real = I < p.P;
   const Bf3 y = split_bf3(n < p.D ? p.cs * (double)x : 0.0);
   const double ys = bf16_value(y.h) + bf16_value(y.m) + bf16_value(y.l);
   double nrm = ys * ys;
@@ -269,7 +268,7 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
   if (n == 0) wv[I] = wi;
   if (n < p.D) xc[I * p.D + n] = x;
   // the FP32 distance operands are read only by the FP32-distance pair forms
-  if (p.bf3) store_k3(p, reinterpret_cast<uint32_t *>(f16.QH), I, n, x);
+  if (p.bf3) store_k3(p, real, reinterpret_cast<uint32_t *>(f16.QH), I, n, x);
   for (int k = n; k < ((p.qhalf || p.bf3) ? 0 : 4 * p.KK); k += 16) {
     float qa = 0.f, ka = 0.f;
     if (real) {
@@ -791,20 +790,6 @@ __global__ __launch_bounds__(kRedBlock) void k_density_rows(EvalParams p, const 
   }
 }
 
-// The same for VDS_PAIR_MFMA32: the rows in K3's layout, sixteen lanes per row.
-__global__ __launch_bounds__(kRedBlock) void k_density_rows_bf3(EvalParams p, const float *__restrict__ y, int64_t ny,
-                                                                const double *__restrict__ meanp, int nmeanp,
-                                                                uint32_t *__restrict__ R3, int64_t nrows_pad) {
-  __shared__ float mean_sh[16];
-  load_mean(p, meanp, nmeanp, mean_sh);
-  const int64_t I = group_particle(blockIdx.x);
-  const int n = group_lane();
-  if (I >= nrows_pad) return;
-  EvalParams pr = p;
-  pr.P = ny;  // rows past ny are zeros
-  store_k3(pr, R3, I, n, I < ny && n < p.D ? y[I * p.D + n] - mean_sh[n] : 0.f);
-}
-
 __global__ __launch_bounds__(kRedBlock) void k_density_out(const float *__restrict__ partial, SplitMap splits,
                                                            int64_t stride_rows, int64_t ny, int D, float norm,
                                                            float *__restrict__ f) {
@@ -1045,6 +1030,123 @@ __global__ __launch_bounds__(kRowsWaves * 64) void k_rows_b(EvalParams p, int mo
   combine_rows(p, blockIdx.x, mode, obs, act, o, in, out, out2, redp, blockmax, pack, fene_out);
 }
 
+// ---- density at given points, VDS_PAIR_MFMA32 ---------------------------------
+//
+// f(y_I) = norm sum_J w_J e_IJ: no difference sums, so a pair is its exponent
+// (matrix cores), one exp2 and one FP32 FMA with the weight, and only 16 RB row
+// sums leave a workgroup.  It packs its rows' operands itself (into LDS), its
+// eight waves take the 32-column chunks c, c + 8, ... of the workgroup's columns
+// with the next chunk's operands in flight, FP32 sums of at most 16 terms go to
+// FP64 in fixed order.
+// Bound: exp2 (a quarter of the vector rate) and the columns' operands through
+// L2, 4 KB per chunk at D = 9 for 16 RB rows.  Measured, D = 9, P = 5000, 19683
+// points: 23 us (the same in blocks of P rows through the pair pass: 27 + 5.3 +
+// 5.5 us in each of four blocks).
+constexpr int kDensityWaves = 8;
+
+template <int D, int RB>
+__global__ __launch_bounds__(kDensityWaves * 64) void k_density_bf3(EvalParams p, const float *__restrict__ y,
+                                                                    int64_t ny, const float *__restrict__ cmean,
+                                                                    const uint4 *__restrict__ K3,
+                                                                    const float *__restrict__ wv, int nch, float norm,
+                                                                    float *__restrict__ f, double *__restrict__ part) {
+  constexpr int NQ = bf3_slices(D);
+  __shared__ uint4 rows[RB * NQ * 64];
+  __shared__ double red[kDensityWaves][16 * RB];
+  assume_dimension<D>(p);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)blockIdx.x * (16 * RB);
+  const int cps = (nch + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int c0 = (int)blockIdx.y * cps, c1 = min(nch, c0 + cps);
+  uint4 kv[2 * NQ];
+  float4 wj[2];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < 2 * NQ; ++i) kv[i] = K3[((int64_t)c * 2 * NQ + i) * 64 + lane];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      wj[b] = *reinterpret_cast<const float4 *>(wv + (int64_t)c * 32 + 16 * b + 4 * (lane >> 4));
+  };
+  if (c0 + wave < c1) load(c0 + wave);
+  for (int t = threadIdx.x; t < 256 * RB; t += kDensityWaves * 64) {
+    const int r = t >> 4, n = t & 15;
+    const bool real = i0 + r < ny;
+    store_k3(p, real, reinterpret_cast<uint32_t *>(rows), r, n, real && n < D ? y[(i0 + r) * D + n] - cmean[n] : 0.f);
+  }
+  __syncthreads();
+  bf16x8 q[RB][NQ];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) bf3_row_operand<D>(rows, r, lane, q[r]);
+  float acc[RB][4];
+  double tot[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    tot[r] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[r][i] = 0.f;
+  }
+  auto flush = [&] {
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      tot[r] += ((double)acc[r][0] + (double)acc[r][1]) + ((double)acc[r][2] + (double)acc[r][3]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[r][i] = 0.f;
+    }
+  };
+  int count = 0;
+  for (int c = c0 + wave; c < c1; c += kDensityWaves) {
+    floatx4 e[RB][2];
+    const float4 wc[2] = {wj[0], wj[1]};
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) e[r][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < NQ; ++m)
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          e[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(kv[b * NQ + m]), q[r][m], e[r][b], 0, 0, 0);
+    if (c + kDensityWaves < c1) load(c + kDensityWaves);
+    // lane: columns 4 (lane / 16) + i of block b, row lane % 16
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float wb[4] = {wc[b].x, wc[b].y, wc[b].z, wc[b].w};
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[r][i] = fmaf(wb[i], __builtin_amdgcn_exp2f(e[r][b][i]), acc[r][i]);
+    }
+    if (++count % kFlush3 == 0) flush();
+  }
+  flush();
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    double t = tot[r];
+    t += __shfl_xor(t, 16);
+    t += __shfl_xor(t, 32);
+    if (lane < 16) red[wave][16 * r + lane] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < 16 * RB && i0 + threadIdx.x < ny) {
+    double t = 0.0;
+    for (int v = 0; v < kDensityWaves; ++v) t += red[v][threadIdx.x];
+    if (part != nullptr) part[(int64_t)blockIdx.y * ny + i0 + threadIdx.x] = t;
+    else f[i0 + threadIdx.x] = (float)t * norm;
+  }
+}
+
+__global__ __launch_bounds__(kRedBlock) void k_density_sum(const double *__restrict__ part, int splits, int64_t ny,
+                                                           float norm, float *__restrict__ f) {
+  const int64_t I = (int64_t)blockIdx.x * kRedBlock + threadIdx.x;
+  if (I >= ny) return;
+  double t = 0.0;
+  for (int s = 0; s < splits; ++s) t += part[s * ny + I];
+  f[I] = (float)t * norm;
+}
+
 // ---- launchers ----
 
 static inline unsigned nblocks(int64_t n) { return (unsigned)((n + kRedBlock - 1) / kRedBlock); }
@@ -1127,16 +1229,58 @@ void launch_density_rows(const EvalParams &p, const float *y, int64_t ny, const 
   const F16Operands ops = f16 != nullptr ? *f16 : F16Operands{nullptr, nullptr, nullptr};
   // rows are padded to a multiple of 256 within the Ppad-row operand buffer
   const int64_t nrows_pad = round_up(ny, kRowAlign);
-  if (p.bf3) {
-    k_density_rows_bf3<<<nblocks(nrows_pad * 16), kRedBlock, 0, s>>>(p, y, ny, meanp, nmeanp,
-                                                                     reinterpret_cast<uint32_t *>(QB), nrows_pad);
-    return;
-  }
   k_density_rows<<<nblocks(nrows_pad), kRedBlock, 0, s>>>(p, y, ny, meanp, nmeanp, QB, ops, nrows_pad);
 }
 void launch_density_out(const EvalParams &p, const float *partial, const SplitMap &splits, int64_t ny, float norm, float *f,
                         hipStream_t s) {
   k_density_out<<<nblocks(ny), kRedBlock, 0, s>>>(partial, splits, p.Ppad, ny, p.D, norm, f);
+}
+
+// Row blocks per wave.  A compute unit takes ceil(workgroups / 256) of them one
+// after the other (or at once, at a share of its speed), each a time of about
+// RB + 1 (RB blocks of arithmetic, one of operand traffic).  P = 10000, D = 9,
+// 19683 points: RB 1 to 5 take 93, 68, 58, 75, 52 us for the whole call (model
+// 10, 9, 8, 10, 6); 40000 points at P = 20000: 280, 168, 165, 178, 146 (20, 15,
+// 16, 15, 12); 8192 points: 77, 72, 74, 80, 84 (4, 3, 4, 5, 6).
+static int density_row_blocks(int64_t ny) {
+  int best = 1;
+  int64_t cost = INT64_MAX;
+  for (int rb = 1; rb <= 5; ++rb) {
+    const int64_t wgs = (ny + 16 * rb - 1) / (16 * rb), cu = device_cu_count();
+    const int64_t t = (wgs + cu - 1) / cu * (rb + 1);
+    if (t < cost) best = rb, cost = t;
+  }
+  return best;
+}
+// With at most 256 workgroups of 16 rows the columns are split too, but only into
+// parts of at least 8 chunks a wave, about what the second launch costs
+// (P = 20000, one point: 25 us for the call; 37 unsplit, 64 by the general pair
+// pass).
+int density_splits(int64_t P, int64_t ny) {
+  const int64_t groups = (ny + 15) / 16, nch = (P + 31) / 32;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(512 / groups, nch / (8 * kDensityWaves)));
+}
+void launch_density(const EvalParams &p, const float *y, int64_t ny, const float *cmean, const void *K3,
+                    const float *wv, float norm, float *f, void *part, hipStream_t s) {
+  const int splits = density_splits(p.P, ny), nch = (int)((p.P + 31) / 32);
+  double *pt = splits > 1 ? static_cast<double *>(part) : nullptr;
+  const uint4 *k3 = static_cast<const uint4 *>(K3);
+  by_dimension(p.D, [&](auto d) {
+    constexpr int D = decltype(d)::value;
+    auto go = [&](auto rc) {
+      constexpr int RB = decltype(rc)::value;
+      const dim3 grid((unsigned)((ny + 16 * RB - 1) / (16 * RB)), (unsigned)splits);
+      k_density_bf3<D, RB><<<grid, kDensityWaves * 64, 0, s>>>(p, y, ny, cmean, k3, wv, nch, norm, f, pt);
+    };
+    switch (density_row_blocks(ny)) {
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      case 4: go(std::integral_constant<int, 4>{}); break;
+      default: go(std::integral_constant<int, 5>{}); break;
+    }
+  });
+  if (splits > 1) k_density_sum<<<nblocks(ny), kRedBlock, 0, s>>>(pt, splits, ny, norm, f);
 }
 
 void launch_batch_mean(const BatchView &b, const float *q, double *meanp, hipStream_t s) {

@@ -242,16 +242,15 @@ struct Bf3Lds {
 
 // One segment: wave w of the workgroup takes the 16-row blocks
 // (kWaves3 rg + w) RB .. + RB - 1 against the columns of chunks [c0, c1) and
-// writes partial sums for its rows to out[row][W] (W >= D + 1).  R3 holds the
-// rows in the column-operand layout (K3 itself when the rows are the
-// particles).  Every thread of the workgroup calls it with the same arguments
-// (it holds barriers).  With run_len > 0 the segment is part of a run of
+// writes partial sums for its rows to out[row][W] (W >= D + 1), self pairs left
+// out.  Every thread of the workgroup calls it with the same arguments (it holds
+// barriers).  With run_len > 0 the segment is part of a run of
 // run_len chunk units of which done0 came before it, and every stage sets the
 // waves' issue priority by the share of the run still to do (see k_pair_bf3).
 template <int D, int RB, int W>
-__device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const uint4 *__restrict__ K3,
-                                            const uint4 *__restrict__ V3, const float *__restrict__ xr, int rg, int c0,
-                                            int c1, int exclude_self, float *__restrict__ out, Bf3Lds<D> &lds,
+__device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ K3, const uint4 *__restrict__ V3,
+                                            const float *__restrict__ xr, int rg, int c0,
+                                            int c1, float *__restrict__ out, Bf3Lds<D> &lds,
                                             int64_t done0 = 0, int64_t run_len = 0) {
   using S = Bf3Shape<D>;
   constexpr int NQ = S::NQ, NT = S::NT, PC = S::PC;
@@ -281,7 +280,7 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
 
   bf16x8 q[RB][NQ];
 #pragma unroll
-  for (int r = 0; r < RB; ++r) bf3_row_operand<D>(R3, rb0 + r, lane, q[r]);
+  for (int r = 0; r < RB; ++r) bf3_row_operand<D>(K3, rb0 + r, lane, q[r]);
   double (*tl)[64] = lds.tot[wave];
   floatx4 acc[RB][NT];
 #pragma unroll
@@ -371,7 +370,7 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
     if (c + kStage3 < c1) stage(c + kStage3, buf ^ 1);
     const uint4 *cb = lds.buf[buf];
     for (int cc = 0; cc < kStage3 && c + cc < c1; ++cc) {
-      if (exclude_self && c + cc == rb0 >> 1)  // scalar branch
+      if (c + cc == rb0 >> 1)  // scalar branch
         chunk(c + cc, cb + cc * PC * 64, std::true_type{});
       else
         chunk(c + cc, cb + cc * PC * 64, std::false_type{});
@@ -398,8 +397,7 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ R3, const 
 
 template <int D, int RB>
 __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_pair_bf3(
-    const uint4 *__restrict__ R3, const uint4 *__restrict__ K3, const uint4 *__restrict__ V3,
-    const float *__restrict__ xr, SplitMap map, int exclude_self, float *__restrict__ partial,
+    const uint4 *__restrict__ K3, const uint4 *__restrict__ V3, const float *__restrict__ xr, SplitMap map, float *__restrict__ partial,
     int64_t part_stride_rows, const int *__restrict__ done) {
   __shared__ Bf3Lds<D> lds;
   if (done != nullptr && *done) return;  // the whole grid returns: no barrier is left waiting
@@ -423,7 +421,7 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
     const int slot = (int)(L - map.run_of(rg * nch));
     u = rg * nch + c1;
     // slots in the compact layout: D + 1 floats per row
-    bf3_segment<D, RB, D + 1>(R3, K3, V3, xr, (int)rg, c0, c1, exclude_self,
+    bf3_segment<D, RB, D + 1>(K3, V3, xr, (int)rg, c0, c1,
                               partial + (int64_t)slot * part_stride_rows * (D + 1), lds, rg * nch + c0 - u_beg,
                               u_end - u_beg);
   }
@@ -447,7 +445,7 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
     const int64_t off = ens[item.x].pad_off;
     const int nc = (int)((ens[item.x].p.P + 31) / 32);
     const uint4 *k3 = K3 + off / 16 * S::NQ * 64;
-    bf3_segment<D, RB, 16>(k3, k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y, 0, nc, 1, partial + off * 16, lds,
+    bf3_segment<D, RB, 16>(k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y, 0, nc, partial + off * 16, lds,
                            done, total);
     done += nc;
   }
@@ -904,15 +902,14 @@ static void launch_mfma16_k(int rb, dim3 grid, const PairF16Ops &ops, int nrb, i
 }
 
 template <int D>
-static void launch_bf3_d(int rb, const void *R3, const void *K3, const float *V3, const float *xr, const SplitMap &map,
-                         int ex, float *partial, int64_t stride, const int *done, hipStream_t s) {
-  const uint4 *r3 = reinterpret_cast<const uint4 *>(R3), *k3 = reinterpret_cast<const uint4 *>(K3),
-              *v3 = reinterpret_cast<const uint4 *>(V3);
+static void launch_bf3_d(int rb, const void *K3, const float *V3, const float *xr, const SplitMap &map,
+                         float *partial, int64_t stride, const int *done, hipStream_t s) {
+  const uint4 *k3 = reinterpret_cast<const uint4 *>(K3), *v3 = reinterpret_cast<const uint4 *>(V3);
   const dim3 grid((unsigned)map.G), block(kWaves3 * 64);
   if (bf3_rb(D, rb) == 1)
-    k_pair_bf3<D, 1><<<grid, block, 0, s>>>(r3, k3, v3, xr, map, ex, partial, stride, done);
+    k_pair_bf3<D, 1><<<grid, block, 0, s>>>(k3, v3, xr, map, partial, stride, done);
   else
-    k_pair_bf3<D, bf3_rb(D, 2)><<<grid, block, 0, s>>>(r3, k3, v3, xr, map, ex, partial, stride, done);
+    k_pair_bf3<D, bf3_rb(D, 2)><<<grid, block, 0, s>>>(k3, v3, xr, map, partial, stride, done);
 }
 
 // Compute units of the current device (256 on MI355X), looked up once per
@@ -959,7 +956,7 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
 void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64_t nrow_blocks, const float *KA,
                       const float *VB, int64_t ncol_chunks, int64_t ncol_pad, const float *xc, bool exclude_self,
                       const float *wscale, const F16Operands &f16, float *partial, int64_t part_stride_rows,
-                      const int *done, hipStream_t s, const void *rows3) {
+                      const int *done, hipStream_t s) {
   const int ex = exclude_self ? 1 : 0;
   const int splits = t.col_splits;
   const int64_t cps = (ncol_chunks + splits - 1) / splits;
@@ -970,11 +967,11 @@ void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64
     const SplitMap map = pair_split_map(t, D, nrow_blocks, ncol_chunks);
     const int rb = t.rows_per_wave;
     switch (D) {
-      case 3: launch_bf3_d<3>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
-      case 6: launch_bf3_d<6>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
-      case 9: launch_bf3_d<9>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
-      case 12: launch_bf3_d<12>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
-      default: launch_bf3_d<15>(rb, rows3, f16.QH, VB, xc, map, ex, partial, part_stride_rows, done, s); break;
+      case 3: launch_bf3_d<3>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
+      case 6: launch_bf3_d<6>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
+      case 9: launch_bf3_d<9>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
+      case 12: launch_bf3_d<12>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
+      default: launch_bf3_d<15>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
     }
     return;
   }

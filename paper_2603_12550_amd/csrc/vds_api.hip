@@ -88,7 +88,7 @@ void pair_pass(vds_ctx c, const float *V, const float *wscale, const int *done) 
   const double pairs = (double)c->prob.P * (double)c->prob.P;
   timed(c, VDS_TIMER_PAIR, pairs, [&] {
     launch_pair_pass(c->tune, c->ep.KK, c->ep.D, c->QB, nrb, c->KA, V, ncol_chunks(c), c->ep.Ppad, c->xc, true,
-                     wscale, c->f16, c->part, c->ep.Ppad, done, c->stream, c->f16.QH);
+                     wscale, c->f16, c->part, c->ep.Ppad, done, c->stream);
   });
 }
 
@@ -200,8 +200,7 @@ Layout make_layout(const vds_problem &p) {
     return o;
   };
   // VDS_PAIR_MFMA32 does not use QB and KA: its V operands run from VA on into
-  // QB and from VB on into KA where they need more than 16 floats (D >= 12),
-  // and the density rows take the buffers from VB to xb0
+  // QB and from VB on into KA where they need more than 16 floats (D >= 12)
   L.VA = take(sizeof(float) * Ppad * 16);
   L.QB = take(sizeof(float) * Ppad * KK * 4);
   L.VB = take(sizeof(float) * Ppad * 16);
@@ -737,17 +736,22 @@ vds_status vds_density_at(vds_ctx c, const float *q, const float *w, const float
   if (ny == 0) return VDS_OK;
   const EvalParams &e = c->ep;
   launch_mean_partials(e, q, w, c->meanp, nullptr, nullptr, c->stream);
-  launch_prep(e, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, nullptr, c->stream);
+  launch_prep(e, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, nullptr, c->stream,
+              c->cmean);
   const float norm = (float)std::pow(2.0 * M_PI * c->prob.h * c->prob.h, -0.5 * e.D);
+  if (e.bf3) {
+    timed(c, VDS_TIMER_PAIR, (double)ny * (double)c->prob.P,
+          [&] { launch_density(e, y, ny, c->cmean, c->f16.QH, c->wv, norm, f, c->part, c->stream); });
+    return hip_check(c, hipGetLastError(), "launch");
+  }
   // foreign rows go through the Q-operand buffer in blocks of Ppad rows
   for (int64_t r0 = 0; r0 < ny; r0 += e.Ppad) {
     const int64_t nr = std::min<int64_t>(e.Ppad, ny - r0);
-    float *rows = e.bf3 ? c->VB : c->QB;
-    launch_density_rows(e, y + r0 * e.D, nr, c->meanp, c->nblk, rows, &c->f16, c->stream);
+    launch_density_rows(e, y + r0 * e.D, nr, c->meanp, c->nblk, c->QB, &c->f16, c->stream);
     const int64_t nrb = round_up(nr, kRowAlign) / 16;
     timed(c, VDS_TIMER_PAIR, (double)nr * (double)c->prob.P, [&] {
       launch_pair_pass(c->tune, e.KK, e.D, c->QB, nrb, c->KA, c->VA, ncol_chunks(c), e.Ppad, c->xc, false,
-                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream, rows);
+                       c->wscale, c->f16, c->part, e.Ppad, nullptr, c->stream);
     });
     launch_density_out(e, c->part, pair_split_map(c->tune, e.D, nrb, ncol_chunks(c)), nr, norm, f + r0, c->stream);
   }

@@ -207,12 +207,11 @@ enum CombineMode { MODE_TERMS = 0, MODE_VELOCITY = 1, MODE_EXPLICIT = 2, MODE_PI
 // the padded column count the V operand was written for.  With the FP16-split
 // implementation the V weights were divided by *wscale (NULL: by one), which
 // the pass multiplies back.
-// VDS_PAIR_MFMA32 reads K3 from f16.QH, V3 from VB and its rows from rows3, in K3's layout
-// (K3 itself when the rows are the particles).
+// VDS_PAIR_MFMA32 (rows are the particles) reads K3 from f16.QH and V3 from VB.
 void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64_t nrow_blocks,
                       const float *KA, const float *VB, int64_t ncol_chunks, int64_t ncol_pad, const float *xc,
                       bool exclude_self, const float *wscale, const F16Operands &f16, float *partial,
-                      int64_t part_stride_rows, const int *done, hipStream_t s, const void *rows3 = nullptr);
+                      int64_t part_stride_rows, const int *done, hipStream_t s);
 bool pair_shape_ok(const vds_tuning &t, int D);
 // Rows a workgroup of the matrix-core implementation impl takes (rb as rows_per_wave of
 // vds_tuning).
@@ -285,11 +284,16 @@ void launch_step_end(const EvalParams &p, Ctrl *ctrl, const PicardCheck &chk, co
 // packing combine; host-driven iterations).
 void launch_picard_check(const PicardCheck &chk, const float *blockmax, int nblk_chk, hipStream_t s);
 void launch_stress(const EvalParams &p, const float *q, const float *w, double *redp, hipStream_t s);
-// With p.bf3 the centred rows go to QB in K3's layout (VDS_PAIR_MFMA32).
+// Density at ny points y by the general pair pass (rows to operands, then the pass, then out).
 void launch_density_rows(const EvalParams &p, const float *y, int64_t ny, const double *meanp, int nmeanp,
                          float *QB, const F16Operands *f16, hipStream_t s);
 void launch_density_out(const EvalParams &p, const float *partial, const SplitMap &splits, int64_t ny, float norm,
                         float *f, hipStream_t s);
+// The same for VDS_PAIR_MFMA32 in one pass, points centred at cmean; part takes density_splits
+// sums of ny doubles when that is more than one (512 workgroups of 16 points at most).
+int density_splits(int64_t P, int64_t ny);
+void launch_density(const EvalParams &p, const float *y, int64_t ny, const float *cmean, const void *K3,
+                    const float *wv, float norm, float *f, void *part, hipStream_t s);
 void launch_copy(const float *src, float *dst, int64_t n, const int *done_flag_or_null, hipStream_t s);
 // q[k][i] = sum_r U[r][i] p[k][r] for i < m, k < nb (U is m x R column-major; pod.hip).
 void launch_pod_reconstruct(const float *U, int64_t m, int R, int nb, const float *p, float *q, hipStream_t s);
