@@ -10,8 +10,10 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
+#include "bf3.h"
 #include "vds_ctx.h"
 #include "vds_linalg.h"
 #include "vds_pod.h"
@@ -20,111 +22,156 @@ using namespace vds;
 
 namespace {
 
-// q_k = U p_k for the nb bonds k: thread i sums over r in order, reading U
-// column by column (coalesced over i; sixteen columns in flight), so U is read
-// once.
-constexpr int kReconThreads = 256;
+// Both maps read U once from memory and little else, so what counts is enough
+// loads in flight: 43 MB at P = 20000, R = 180.
+
+// f(std::integral_constant<int, NB>) for the number of bonds.
+template <class F>
+void by_bonds(int nb, F &&f) {
+  switch (nb) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    default: f(std::integral_constant<int, 5>{}); break;
+  }
+}
+
+// q_k = U p_k for the bonds k.  A workgroup owns 64 positions; its four waves
+// take a quarter of the columns each, sixteen in flight, and add up in LDS
+// (one position per thread over all columns left one wave per SIMD waiting).
+// Bound: reading U.  Measured, P = 20000, R = 180: 10.4 us (4.2 TB/s, a copy
+// reaches 4.9), 16.7 with one wave per SIMD.
+constexpr int kReconWaves = 4;
 constexpr int kReconInFlight = 16;
 
-__global__ __launch_bounds__(kReconThreads) void k_pod_reconstruct(const float *__restrict__ U, int64_t m, int R,
-                                                                   int nb, const float *__restrict__ p,
-                                                                   float *__restrict__ q) {
-  const int64_t i = (int64_t)blockIdx.x * kReconThreads + threadIdx.x;
-  if (i >= m) return;
-  float acc[kMaxNb];
+template <int NB>
+__global__ __launch_bounds__(kReconWaves * 64) void k_pod_reconstruct(const float *__restrict__ U, int64_t m, int R,
+                                                                      const float *__restrict__ p,
+                                                                      float *__restrict__ q) {
+  __shared__ float red[kReconWaves][NB][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const int per = (R + kReconWaves - 1) / kReconWaves;
+  const int r0 = wave * per, r1 = min(R, r0 + per);
+  const float *u = U + min(i, m - 1);
+  float acc[NB];
 #pragma unroll
-  for (int k = 0; k < kMaxNb; ++k) acc[k] = 0.f;
-  const float *u = U + i;
-  int r = 0;
-  for (; r + kReconInFlight <= R; r += kReconInFlight) {
+  for (int k = 0; k < NB; ++k) acc[k] = 0.f;
+  for (int r = r0; r < r1; r += kReconInFlight) {
     float uv[kReconInFlight];
 #pragma unroll
-    for (int j = 0; j < kReconInFlight; ++j) uv[j] = u[(int64_t)(r + j) * m];
+    for (int j = 0; j < kReconInFlight; ++j) uv[j] = u[(int64_t)min(r + j, r1 - 1) * m];
 #pragma unroll
-    for (int k = 0; k < kMaxNb; ++k)
-      if (k < nb) {
-        const float *pk = p + (int64_t)k * R + r;
+    for (int j = 0; j < kReconInFlight; ++j)
+      if (r + j < r1) {  // scalar
 #pragma unroll
-        for (int j = 0; j < kReconInFlight; ++j) acc[k] = fmaf(uv[j], pk[j], acc[k]);
+        for (int k = 0; k < NB; ++k) acc[k] = fmaf(uv[j], p[(int64_t)k * R + r + j], acc[k]);
       }
   }
-  for (; r < R; ++r) {
-    const float u0 = u[(int64_t)r * m];
 #pragma unroll
-    for (int k = 0; k < kMaxNb; ++k)
-      if (k < nb) acc[k] = fmaf(u0, p[(int64_t)k * R + r], acc[k]);
-  }
+  for (int k = 0; k < NB; ++k) red[wave][k][lane] = acc[k];
+  __syncthreads();
+  for (int k = wave; k < NB; k += kReconWaves)
+    if (i < m) {
+      float v = 0.f;
 #pragma unroll
-  for (int k = 0; k < kMaxNb; ++k)
-    if (k < nb) q[(int64_t)k * m + i] = acc[k];
+      for (int w = 0; w < kReconWaves; ++w) v += red[w][k][lane];
+      q[(int64_t)k * m + i] = v;
+    }
 }
 
 constexpr int kProjThreads = 256;
-constexpr int kProjChunks = 32;
+constexpr int kProjChunks = 32;  // the workspace holds at least this many partial sums per coefficient
 constexpr int kProjRows = 8;
 
 // First stage of p_k[r] = U_r . q_k: block (g, c) takes the rows
 // r = 8 g .. 8 g + 7 of U against chunk c of the positions; a thread reads
-// q_k[i] once for all eight rows (thirteen loads in flight per position), so U
-// is read once and q once per eight rows.  Then a fixed-order block reduction
-// per (row, bond) into part[c][k][r].
-__global__ __launch_bounds__(kProjThreads) void k_pod_project(const float *__restrict__ U, int64_t m, int R, int nb,
-                                                              const float *__restrict__ q, float *__restrict__ part) {
-  __shared__ float red[kProjRows * kMaxNb][kProjThreads / 64];
+// q_k[i] once for all eight rows and two positions at a time, so U is read once
+// and q once per eight rows.  Then sums over rows of 16 lanes by DPP and over
+// the block in LDS, in fixed order, into part[k R + r][c].
+// Bound: reading U.  Measured, P = 20000, R = 180: 9.9 us (4.4 TB/s); 18 with one
+// position at a time and cross-lane sums of all five possible bonds.
+template <int NB>
+__global__ __launch_bounds__(kProjThreads) void k_pod_project(const float *__restrict__ U, int64_t m, int R,
+                                                              int64_t len, const float *__restrict__ q,
+                                                              float *__restrict__ part) {
+  constexpr int kGroups = kProjThreads / 16;
+  __shared__ float red[kProjRows * NB][kGroups + 1];
   const int r0 = (int)blockIdx.x * kProjRows, c = (int)blockIdx.y;
   const int nr = min(kProjRows, R - r0);
-  const int64_t len = (m + kProjChunks - 1) / kProjChunks, i0 = c * len, i1 = min(m, i0 + len);
-  float acc[kProjRows][kMaxNb];
+  const int64_t i0 = c * len, i1 = min(m, i0 + len);
+  float acc[kProjRows][NB];
 #pragma unroll
   for (int j = 0; j < kProjRows; ++j)
 #pragma unroll
-    for (int k = 0; k < kMaxNb; ++k) acc[j][k] = 0.f;
-  for (int64_t i = i0 + threadIdx.x; i < i1; i += kProjThreads) {
-    float qv[kMaxNb];
+    for (int k = 0; k < NB; ++k) acc[j][k] = 0.f;
+  const float *u[kProjRows];
 #pragma unroll
-    for (int k = 0; k < kMaxNb; ++k) qv[k] = k < nb ? q[(int64_t)k * m + i] : 0.f;
+  for (int j = 0; j < kProjRows; ++j) u[j] = U + (int64_t)(r0 + min(j, nr - 1)) * m;  // rows past R repeat the last
+  auto body = [&](auto nc, int64_t i) {
+    constexpr int N = decltype(nc)::value;
+    float qv[N][NB], uv[N][kProjRows];
 #pragma unroll
-    for (int j = 0; j < kProjRows; ++j) {
-      const float u = j < nr ? U[(int64_t)(r0 + j) * m + i] : 0.f;
+    for (int t = 0; t < N; ++t) {
 #pragma unroll
-      for (int k = 0; k < kMaxNb; ++k) acc[j][k] = fmaf(u, qv[k], acc[j][k]);
+      for (int k = 0; k < NB; ++k) qv[t][k] = q[(int64_t)k * m + i + t * kProjThreads];
+#pragma unroll
+      for (int j = 0; j < kProjRows; ++j) uv[t][j] = u[j][i + t * kProjThreads];
     }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < N; ++t)
+#pragma unroll
+      for (int j = 0; j < kProjRows; ++j)
+#pragma unroll
+        for (int k = 0; k < NB; ++k) acc[j][k] = fmaf(uv[t][j], qv[t][k], acc[j][k]);
+  };
+  int64_t i = i0 + threadIdx.x;
+  for (; i + kProjThreads < i1; i += 2 * kProjThreads) body(std::integral_constant<int, 2>{}, i);
+  if (i < i1) body(std::integral_constant<int, 1>{}, i);
 #pragma unroll
   for (int j = 0; j < kProjRows; ++j)
 #pragma unroll
-    for (int k = 0; k < kMaxNb; ++k) {
+    for (int k = 0; k < NB; ++k) {
       float v = acc[j][k];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      if (lane == 0) red[j * kMaxNb + k][wave] = v;
+      v += row_rotate<8>(v);
+      v += row_rotate<4>(v);
+      v += row_rotate<2>(v);
+      v += row_rotate<1>(v);
+      if ((threadIdx.x & 15) == 0) red[j * NB + k][threadIdx.x >> 4] = v;
     }
   __syncthreads();
   const int t = threadIdx.x;
-  if (t < kProjRows * kMaxNb) {
-    const int j = t / kMaxNb, k = t % kMaxNb;
-    if (j < nr && k < nb) {
+  if (t < kProjRows * NB) {
+    const int j = t / NB, k = t % NB;
+    if (j < nr) {
       float v = 0.f;
-      for (int w = 0; w < kProjThreads / 64; ++w) v += red[t][w];
-      part[((int64_t)c * nb + k) * R + r0 + j] = v;
+      for (int w = 0; w < kGroups; ++w) v += red[t][w];
+      part[((int64_t)k * R + r0 + j) * gridDim.y + c] = v;
     }
   }
 }
 
-// Second stage: p[k][r] = sum over the chunks in order.
-__global__ void k_pod_project_sum(const float *__restrict__ part, int R, int nb, float *__restrict__ p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= nb * R) return;
-  float v = 0.f;
-  for (int c = 0; c < kProjChunks; ++c) v += part[(int64_t)c * nb * R + e];
-  p[e] = v;
+// Second stage: p[k R + r] = sum over the chunks, a wave per coefficient, FP64.
+__global__ __launch_bounds__(256) void k_pod_project_sum(const float *__restrict__ part, int n, int nch,
+                                                         float *__restrict__ p) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (e >= n) return;
+  double v = 0.0;
+  for (int c = lane; c < nch; c += 64) v += (double)part[(int64_t)e * nch + c];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  if (lane == 0) p[e] = (float)v;
 }
 
 }  // namespace
 
 namespace vds {
 void launch_pod_reconstruct(const float *U, int64_t m, int R, int nb, const float *p, float *q, hipStream_t s) {
-  k_pod_reconstruct<<<(unsigned)((m + kReconThreads - 1) / kReconThreads), kReconThreads, 0, s>>>(U, m, R, nb, p, q);
+  by_bonds(nb, [&](auto n) {
+    k_pod_reconstruct<decltype(n)::value><<<(unsigned)((m + 63) / 64), kReconWaves * 64, 0, s>>>(U, m, R, p, q);
+  });
 }
 }  // namespace vds
 
@@ -319,10 +366,11 @@ vds_status vds_pod_basis(vds_ctx c, const float *X, int64_t m, int32_t n, int32_
 size_t vds_pod_map_workspace_bytes(const vds_problem *prob, int32_t R) {
   if (prob == nullptr || prob->P < 1 || prob->nb < 1 || R < 1) return 0;
   const int64_t m = 3 * prob->P;
-  const size_t a = sizeof(float) * (size_t)gemm_splits_small(prob->nb, R, m, 2048) * prob->nb * R;
-  const size_t b = sizeof(float) * (size_t)m * prob->nb;
-  const size_t c = sizeof(float) * (size_t)kProjChunks * prob->nb * R;
-  return (std::max(std::max(a, b), c) + 255) / 256 * 256;
+  // partial sums of the projection; never less than the positions of all bonds
+  const int64_t tiles = (R + 63) / 64;
+  const int64_t chunks = std::max<int64_t>(kProjChunks, std::min<int64_t>({64, (m + 255) / 256,
+                                                                             (2048 + tiles - 1) / tiles}));
+  return (sizeof(float) * (size_t)prob->nb * (size_t)std::max<int64_t>(chunks * R, m) + 255) / 256 * 256;
 }
 
 vds_status vds_pod_project(vds_ctx c, const float *U, int32_t R, const float *q, float *p, void *ws, size_t bytes) {
@@ -332,10 +380,19 @@ vds_status vds_pod_project(vds_ctx c, const float *U, int32_t R, const float *q,
   const int64_t m = 3 * c->prob.P;
   const int nb = c->prob.nb;
   float *part = static_cast<float *>(ws);
+  // about four workgroups per compute unit over the groups of rows and the
+  // chunks of positions (at least 256 each), as far as the workspace holds their
+  // partial sums
+  const int64_t groups = (R + kProjRows - 1) / kProjRows;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>({1024 / groups, (m + 255) / 256,
+                                                              std::max<int64_t>(kProjChunks, m / R)}));
+  const int64_t len = round_up((m + want - 1) / want, 64), nch = (m + len - 1) / len;
   timed(c, VDS_TIMER_PROJ, 4.0 * m * R, [&] {
-    k_pod_project<<<dim3((unsigned)((R + kProjRows - 1) / kProjRows), kProjChunks), kProjThreads, 0, c->stream>>>(
-        U, m, R, nb, q, part);
-    k_pod_project_sum<<<(nb * R + 255) / 256, 256, 0, c->stream>>>(part, R, nb, p);
+    by_bonds(nb, [&](auto n) {
+      k_pod_project<decltype(n)::value>
+          <<<dim3((unsigned)groups, (unsigned)nch), kProjThreads, 0, c->stream>>>(U, m, R, len, q, part);
+    });
+    k_pod_project_sum<<<(nb * R + 3) / 4, 256, 0, c->stream>>>(part, nb * R, (int)nch, p);
   });
   return hip_check(c, hipGetLastError(), "project");
 }

@@ -61,15 +61,4 @@ inline int gemm_splits(int M, int N, int64_t K, int nbatch = 1, bool symmetric =
   return (int)(s < 1 ? 1 : s);
 }
 
-// Splits of launch_gemm_small: roughly `target` workgroups, at least 256 k each.
-inline int gemm_splits_small(int M, int N, int64_t K, int target) {
-  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  int64_t s = (target + tiles - 1) / tiles;
-  const int64_t kmax = (K + 255) / 256;
-  if (s > kmax) s = kmax;
-  if (s < 1) s = 1;
-  if (s > 64) s = 64;
-  return (int)s;
-}
-
 }  // namespace vds
