@@ -794,6 +794,12 @@ __global__ void k_extrapolate(float *__restrict__ p, const float *__restrict__ p
   if (t < n) p[t] = fmaf(a, p[t] - prev[t], p[t]);
 }
 
+// Lanes of each four exchanged by a DPP quad_perm control.
+template <int kPerm>
+__device__ __forceinline__ float quad_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kPerm, 0xf, 0xf, true));
+}
+
 // Explicit Euler on the reduced state p[k][s] (eq. model_DymReduced):
 // dp_k/dt = X^H p_k - (kT/zeta) sum_j A_kj X^B p_j - (1/zeta) sum_j A_kj H_j p_j.
 // One workgroup; p in LDS; each wavefront takes whole rows of X^H / X^B.
@@ -856,102 +862,115 @@ __global__ __launch_bounds__(1024) void k_rom_steps(const float *__restrict__ XH
 }
 
 // The same steps with both operators held in registers for the whole window:
-// thread t works on matrix row t / 2 (the rows of X^H, then those of X^B) over
-// half t % 2 of its columns (halves aligned to four columns), so a step reads
-// only the state, as float4 broadcasts from LDS, and combines the two halves
-// with one shuffle.  The state is double-buffered: two barriers per step.
-// 768 threads (three waves per SIMD leave room for the matrix slice);
-// R <= 2 kHalf, NB = nb bonds known at compile time (no per-bond branches
-// between the loads and their uses).
-constexpr int kRegThreads = 768;
-template <int kHalf, int NB>
-__global__ __launch_bounds__(kRegThreads) void k_rom_steps_reg(const float *__restrict__ XH,
-                                                               const float *__restrict__ XB, float *__restrict__ p,
-                                                               int R, int nsteps, EvalParams ep) {
-  static_assert(kHalf % 4 == 0, "halves are read as float4");
-  constexpr int W = 2 * kHalf;
-  constexpr int kPer = (NB * W + kRegThreads - 1) / kRegThreads;  // state entries per thread
-  __shared__ float4 ps4[2][NB][W / 4];
-  __shared__ float y[NB][W];
-  __shared__ float z[NB][W];
-  float *ps0 = reinterpret_cast<float *>(&ps4[0][0][0]);
+// four lanes per matrix row s, each with the float4 column groups g, g + 4, ...
+// of X^H and of X^B, so a step reads only the state, as float4 broadcasts from
+// LDS.  The sums over the four lanes (DPP) give a row's y_k and z_k for every
+// bond in the same lanes, which also keep the row's own state: the update needs
+// no exchange, and with the state double-buffered in LDS a step is one barrier.
+// Only as many waves as the rows need.  kQ: columns per lane (R <= 4 kQ, kQ a
+// multiple of 4), NB = nb bonds known at compile time.
+// Bound: one wave's chain of 2 NB kQ FMAs, the sums, the LDS read and the
+// barrier; the register budget of exactly the waves there are lets the state's
+// loads go out together (R = 64: 407 against 651 ns).  Measured per step, NB = 3:
+// R = 16 0.20, 40 0.34, 64 0.41, 128 0.73, 180 1.3 us; two lanes per row of
+// [X^H; X^B], 768 threads and an exchange through LDS took 0.65, 0.90, 0.91,
+// 2.4, 2.1.
+constexpr int kRegMaxR = 192;
+template <int kQ, int NB>
+__global__ __launch_bounds__(16 * kQ) __attribute__((amdgpu_waves_per_eu((kQ + 15) / 16, (kQ + 15) / 16))) void
+k_rom_steps_reg(const float *__restrict__ XH, const float *__restrict__ XB, float *__restrict__ p, int R, int nsteps,
+                EvalParams ep) {
+  static_assert(kQ % 4 == 0 && 4 * kQ <= kRegMaxR, "columns are read as float4");
+  constexpr int W = 4 * kQ, C4 = kQ / 4;
+  __shared__ float4 ps[2][NB][W / 4];
   const int tid = threadIdx.x;
-  const int row = tid >> 1, half = tid & 1;
-  const int hl = (((R + 1) / 2) + 3) & ~3;  // <= kHalf
-  const int u0 = half * hl;
-  const int len = min(hl, R - u0);
-  const bool active = row < 2 * R;
-  const float *M = row < R ? XH + (int64_t)row * R : XB + (int64_t)(row - R) * R;
-  float m[kHalf];
+  const int row = tid >> 2, g = tid & 3;
+  const bool active = row < R;
+  float mh[kQ], mb[kQ];
 #pragma unroll
-  for (int j = 0; j < kHalf; ++j) m[j] = (active && j < len) ? M[u0 + j] : 0.f;
-  for (int t = tid; t < 2 * NB * W; t += kRegThreads) {  // zero padding: the unused m[j] meet zeros
+  for (int j = 0; j < kQ; ++j) {
+    const int u = 16 * (j / 4) + 4 * g + j % 4;
+    const bool in = active && u < R;
+    mh[j] = in ? XH[(int64_t)row * R + u] : 0.f;
+    mb[j] = in ? XB[(int64_t)row * R + u] : 0.f;
+  }
+  float *ps0 = reinterpret_cast<float *>(&ps[0][0][0]);
+  for (int t = tid; t < 2 * NB * W; t += blockDim.x) {  // zero padding: the unused columns meet zeros
     const int b = t / (NB * W), k = (t / W) % NB, s = t % W;
     ps0[t] = (b == 0 && s < R) ? p[k * R + s] : 0.f;
   }
+  float own[NB], H[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    own[k] = active ? p[k * R + row] : 0.f;
+    H[k] = ep.H[k];
+  }
+  const float ktz = ep.kT * ep.inv_zeta, inv_zeta = ep.inv_zeta, dt = ep.dt;
   __syncthreads();
-  const float ktz = ep.kT * ep.inv_zeta;
   int cur = 0;
   for (int step = 0; step < nsteps; ++step) {
-    float acc[NB];
+    float y[NB], z[NB];
 #pragma unroll
-    for (int k = 0; k < NB; ++k) acc[k] = 0.f;
+    for (int k = 0; k < NB; ++k) y[k] = z[k] = 0.f;
 #pragma unroll
-    for (int j4 = 0; j4 < kHalf / 4; ++j4) {
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        const float4 v = ps4[cur][k][(u0 >> 2) + j4];
-        acc[k] = fmaf(m[4 * j4], v.x, acc[k]);
-        acc[k] = fmaf(m[4 * j4 + 1], v.y, acc[k]);
-        acc[k] = fmaf(m[4 * j4 + 2], v.z, acc[k]);
-        acc[k] = fmaf(m[4 * j4 + 3], v.w, acc[k]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) acc[k] += __shfl_xor(acc[k], 1);
-    if (active && half == 0) {
+    for (int c = 0; c < C4; ++c)
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
-        if (row < R) y[k][row] = acc[k];
-        else z[k][row - R] = acc[k];
+        const float4 v = ps[cur][k][4 * c + g];
+        y[k] = fmaf(mh[4 * c], v.x, y[k]);
+        z[k] = fmaf(mb[4 * c], v.x, z[k]);
+        y[k] = fmaf(mh[4 * c + 1], v.y, y[k]);
+        z[k] = fmaf(mb[4 * c + 1], v.y, z[k]);
+        y[k] = fmaf(mh[4 * c + 2], v.z, y[k]);
+        z[k] = fmaf(mb[4 * c + 2], v.z, z[k]);
+        y[k] = fmaf(mh[4 * c + 3], v.w, y[k]);
+        z[k] = fmaf(mb[4 * c + 3], v.w, z[k]);
       }
-    }
-    __syncthreads();
-    const float *pc = reinterpret_cast<const float *>(&ps4[cur][0][0]);
-    float *pn = reinterpret_cast<float *>(&ps4[cur ^ 1][0][0]);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int t = tid + i * kRegThreads;
-      if (t < NB * R) {
-        const int k = t / R, s = t % R;
-        float az = 2.f * z[k][s], ah = 2.f * ep.H[k] * pc[k * W + s];
-        if (k > 0) {
-          az -= z[k - 1][s];
-          ah -= ep.H[k - 1] * pc[(k - 1) * W + s];
-        }
-        if (k + 1 < NB) {
-          az -= z[k + 1][s];
-          ah -= ep.H[k + 1] * pc[(k + 1) * W + s];
-        }
-        pn[k * W + s] = pc[k * W + s] + ep.dt * (y[k][s] - ktz * az - ep.inv_zeta * ah);
+    for (int k = 0; k < NB; ++k) {
+      y[k] += quad_swap<0x4e>(y[k]);  // lanes 2, 3, 0, 1 of each four
+      z[k] += quad_swap<0x4e>(z[k]);
+      y[k] += quad_swap<0xb1>(y[k]);  // lanes 1, 0, 3, 2
+      z[k] += quad_swap<0xb1>(z[k]);
+    }
+    float nw[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      float az = 2.f * z[k], ah = 2.f * H[k] * own[k];
+      if (k > 0) {
+        az -= z[k - 1];
+        ah -= H[k - 1] * own[k - 1];
       }
+      if (k + 1 < NB) {
+        az -= z[k + 1];
+        ah -= H[k + 1] * own[k + 1];
+      }
+      nw[k] = own[k] + dt * (y[k] - ktz * az - inv_zeta * ah);
+    }
+    float *pn = reinterpret_cast<float *>(&ps[cur ^ 1][0][0]);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      own[k] = nw[k];
+      if (active && g == k % 4) pn[k * W + row] = nw[k];
     }
     __syncthreads();
     cur ^= 1;
   }
-  const float *pf = reinterpret_cast<const float *>(&ps4[cur][0][0]);
-  for (int t = tid; t < NB * R; t += kRegThreads) p[t] = pf[(t / R) * W + t % R];
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+    if (active && g == k % 4) p[k * R + row] = own[k];
 }
 
-template <int kHalf>
+template <int kQ>
 void launch_steps_reg(int nb, const float *XH, const float *XB, float *p, int R, int n, const EvalParams &ep,
                       hipStream_t s) {
+  const int threads = (4 * R + 63) / 64 * 64;
   switch (nb) {
-    case 1: k_rom_steps_reg<kHalf, 1><<<1, kRegThreads, 0, s>>>(XH, XB, p, R, n, ep); break;
-    case 2: k_rom_steps_reg<kHalf, 2><<<1, kRegThreads, 0, s>>>(XH, XB, p, R, n, ep); break;
-    case 3: k_rom_steps_reg<kHalf, 3><<<1, kRegThreads, 0, s>>>(XH, XB, p, R, n, ep); break;
-    case 4: k_rom_steps_reg<kHalf, 4><<<1, kRegThreads, 0, s>>>(XH, XB, p, R, n, ep); break;
-    default: k_rom_steps_reg<kHalf, 5><<<1, kRegThreads, 0, s>>>(XH, XB, p, R, n, ep); break;
+    case 1: k_rom_steps_reg<kQ, 1><<<1, threads, 0, s>>>(XH, XB, p, R, n, ep); break;
+    case 2: k_rom_steps_reg<kQ, 2><<<1, threads, 0, s>>>(XH, XB, p, R, n, ep); break;
+    case 3: k_rom_steps_reg<kQ, 3><<<1, threads, 0, s>>>(XH, XB, p, R, n, ep); break;
+    case 4: k_rom_steps_reg<kQ, 4><<<1, threads, 0, s>>>(XH, XB, p, R, n, ep); break;
+    default: k_rom_steps_reg<kQ, 5><<<1, threads, 0, s>>>(XH, XB, p, R, n, ep); break;
   }
 }
 
@@ -1468,14 +1487,14 @@ namespace {
 void rom_steps(vds_rom r, float *p, int n) {
   vds_ctx c = r->ctx;
   const int nb = c->prob.nb, R = r->R;
-  if (R <= 32)
-    launch_steps_reg<16>(nb, r->XH, r->XB, p, R, n, c->ep, c->stream);
-  else if (R <= 64)
-    launch_steps_reg<32>(nb, r->XH, r->XB, p, R, n, c->ep, c->stream);
-  else if (R <= 128)
-    launch_steps_reg<64>(nb, r->XH, r->XB, p, R, n, c->ep, c->stream);
-  else if (R <= 192)
-    launch_steps_reg<96>(nb, r->XH, r->XB, p, R, n, c->ep, c->stream);
+  auto reg = [&](auto q) { launch_steps_reg<decltype(q)::value>(nb, r->XH, r->XB, p, R, n, c->ep, c->stream); };
+  if (R <= 16) reg(std::integral_constant<int, 4>{});
+  else if (R <= 32) reg(std::integral_constant<int, 8>{});
+  else if (R <= 48) reg(std::integral_constant<int, 12>{});
+  else if (R <= 64) reg(std::integral_constant<int, 16>{});
+  else if (R <= 96) reg(std::integral_constant<int, 24>{});
+  else if (R <= 128) reg(std::integral_constant<int, 32>{});
+  else if (R <= kRegMaxR) reg(std::integral_constant<int, 48>{});
   else
     k_rom_steps<<<1, 1024, 0, c->stream>>>(r->XH, r->XB, p, nb, R, n, c->ep);
 }
