@@ -172,21 +172,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
 }
 
-// Entry (i, j) in FP32, term by term: for entries that are not numbers in the
-// three-part product (an infinite factor, or one past the BF16 range, has no
-// parts), so that they are what FP32 arithmetic makes of the inputs.
-__device__ float gemm_entry_fp32(const GemmShape &g, int i, int j) {
-  float s = 0.f;
-  for (int b = 0; b < g.nbatch; ++b)
-    for (int64_t k = 0; k < g.K; ++k) {
-      const float x = g.A[b * g.sA + (g.a_mn ? k * g.lda + i : (int64_t)i * g.lda + k)];
-      float y = g.B[b * g.sB + (g.b_mn ? k * g.ldb + j : (int64_t)j * g.ldb + k)];
-      if (g.scale != nullptr) y *= g.scale[b * g.sS + k];
-      s = fmaf(x, y, s);
-    }
-  return s;
-}
-
 // C = alpha * sum_splits part (+ C if accumulate), fixed summation order.  A
 // symmetric product takes the entries below the diagonal from their mirror
 // images (inside a diagonal tile the two differ in the order of their parts).
@@ -207,7 +192,7 @@ static void launch_reduce(const GemmShape &g, const float *part, hipStream_t s) 
   k_gemm_reduce<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(g, part);
 }
 
-void launch_gemm(const GemmShape &g, float *part, hipStream_t s) {
+void launch_gemm_parts(const GemmShape &g, float *part, hipStream_t s) {
   const int tm = (g.M + kGemmTile - 1) / kGemmTile, tn = (g.N + kGemmTile - 1) / kGemmTile;
   const int ntile = g.symmetric ? tm * (tm + 1) / 2 : tm * tn;
   // 16-byte loads where every row starts on 16 bytes
@@ -234,6 +219,10 @@ void launch_gemm(const GemmShape &g, float *part, hipStream_t s) {
   else if (g.a_mn && !g.b_mn) go(std::true_type{}, std::false_type{});
   else if (!g.a_mn && g.b_mn) go(std::false_type{}, std::true_type{});
   else go(std::true_type{}, std::true_type{});
+}
+
+void launch_gemm(const GemmShape &g, float *part, hipStream_t s) {
+  launch_gemm_parts(g, part, s);
   launch_reduce(g, part, s);
 }
 

@@ -36,9 +36,20 @@ constexpr int kgemm_tile(int NB) { return kKgRows * 16 * NB; }
 struct KgMap {
   int NB;       // column tiles of 16 per item: 4, 8 or 12
   int NCG, n_rg, nch, G;
+  double inv_G, inv_units;  // a 64-bit division is some hundred instructions on the GPU
   __host__ __device__ int64_t items() const { return (int64_t)NCG * n_rg; }
   __host__ __device__ int64_t units() const { return items() * nch; }
-  __host__ __device__ int64_t run_start(int64_t L) const { return L * units() / G; }
+  // floor(a / b) for a below 2^53, with inv = 1 / b
+  __host__ __device__ static int64_t quotient(int64_t a, int64_t b, double inv) {
+    int64_t q = (int64_t)((double)a * inv);
+    const int64_t r = a - q * b;
+    if (r < 0) --q;
+    else if (r >= b) ++q;
+    return q;
+  }
+  // first unit of run L, and the first run that starts after unit u
+  __host__ __device__ int64_t run_start(int64_t L) const { return quotient(L * units(), G, inv_G); }
+  __host__ __device__ int64_t run_after(int64_t u) const { return quotient((u + 1) * G - 1, units(), inv_units) + 1; }
 };
 
 // One workgroup per compute unit (its eight waves take a SIMD's registers two
@@ -63,6 +74,8 @@ KgMap kgemm_map(int64_t P, int ncols) {
   int64_t G = std::min<int64_t>(device_cu_count(), m.units() / 2);
   if (G >= 8) G -= G % 8;
   m.G = (int)std::max<int64_t>(G, 1);
+  m.inv_G = 1.0 / (double)m.G;
+  m.inv_units = 1.0 / (double)m.units();
   return m;
 }
 
@@ -72,7 +85,7 @@ int64_t rom_ldy3(int R) { return (3 * (int64_t)R + 15) / 16 * 16; }
 struct RomLayout {
   size_t Ude, Mbig, XH, I1, XB1, XB2, XB, Bsw, Y, qt, T, invS, part, red, psave, pprev, total;
   int NB16;
-  int64_t ldy;
+  int64_t ldy, part_floats;
   KgMap kg;     // grid of the default kernel-GEMM (its continuation slots are sized for its runs)
 };
 
@@ -100,8 +113,7 @@ RomLayout rom_layout(const vds_problem &p, int R) {
   L.kg = kgemm_map(P, 3 * R);
   L.Bsw = take(std::max(sizeof(float) * (size_t)Ppad * L.ldy,
                         sizeof(uint16_t) * 3 * (size_t)Ppad * 16 * L.kg.NB * L.kg.NCG));
-  // Y of 6 R columns, or of 3 R (then W, R x R, sits behind it)
-  L.Y = take(sizeof(float) * std::max((size_t)Ppad * L.ldy, (size_t)Ppad * rom_ldy3(R) + (size_t)R * R));
+  L.Y = take(sizeof(float) * (size_t)Ppad * L.ldy);  // Y of 6 R columns, or of 3 R
   L.qt = take(sizeof(float) * (size_t)p.nb * P * 3);
   L.T = take(sizeof(float) * Ppad);
   L.invS = take(sizeof(float) * Ppad);
@@ -112,11 +124,23 @@ RomLayout rom_layout(const vds_problem &p, int R) {
                                 sizeof(float) * (size_t)m * p.nb,
                                 sizeof(float) * (size_t)L.kg.G * kgemm_tile(L.kg.NB)});
   L.part = take(part);
+  L.part_floats = (int64_t)(part / sizeof(float));
   L.red = take(sizeof(double) * 16);
   L.psave = take(sizeof(float) * (size_t)p.nb * R);
   L.pprev = take(sizeof(float) * (size_t)p.nb * R);
   L.total = off;
   return L;
+}
+
+// Splits of the two R x R x 3 P products of a reduced operator build: two
+// workgroups per compute unit (one leaves each waiting for its own loads: 62 and
+// 77 us at R = 180, P = 20000; with two 44 and 51), at least four rounds each, as many
+// as the partial-sum buffer holds for both.
+int rom_splits(const RomLayout &L, int R, int64_t P) {
+  const int64_t t = (R + kGemmTile - 1) / kGemmTile, rounds = (P + kGemmSlab - 1) / kGemmSlab * 3;
+  int64_t s = std::min<int64_t>({512 / (t * t), rounds / 4, L.part_floats / (2 * (int64_t)R * R)});
+  if (s >= 8) s -= s % 8;
+  return (int)std::max<int64_t>(s, 1);
 }
 
 // Ude[a][s][I] = U[s m + 3 I + a]: the mode blocks U_a, K-contiguous over I.
@@ -471,21 +495,25 @@ __global__ __launch_bounds__(kKgWaves * 64) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // Y += the slots of the runs that continue item blockIdx.y, in run order
-// (block x: elements x 256 .. of its tile).
-__global__ __launch_bounds__(256) void k_kgemm_fixup(const float *__restrict__ slots, KgMap map, int ncols,
-                                                     float *__restrict__ Y, int64_t ldy) {
-  const int64_t item = blockIdx.y;
-  const int64_t u0 = item * map.nch, u1 = u0 + map.nch;
-  int64_t L = (u0 * map.G) / map.units();  // a run that starts at or before u0
-  while (L < map.G && map.run_start(L) <= u0) ++L;
-  if (L >= map.G || map.run_start(L) >= u1) return;
-  const int e = (int)blockIdx.x * 256 + threadIdx.x;
-  const int W = 16 * map.NB, r = e / W, cc = e % W;
-  const int col = (int)(item / map.n_rg) * W + cc;
-  if (col >= ncols) return;
-  float *y = Y + ((item % map.n_rg) * kKgRows + r) * ldy + col;
-  float v = *y;
-  for (; L < map.G && map.run_start(L) < u1; ++L) v += slots[L * kgemm_tile(map.NB) + e];
+// (block x: elements x 1024 .. of its tile, four per thread).
+// Bound: memory (Y twice, the slots once).  P = 20000, R = 180: 21 us, 72 with
+// one element per thread and 64-bit divisions for the runs.
+__global__ __launch_bounds__(256) void k_kgemm_fixup(const float *__restrict__ slots, KgMap map, float *__restrict__ Y,
+                                                     int64_t ldy) {
+  const int item = (int)blockIdx.y;
+  const int64_t u0 = (int64_t)item * map.nch, u1 = u0 + map.nch;
+  const int64_t La = map.run_after(u0), Lb = min((int64_t)map.G, map.run_after(u1 - 1));
+  if (La >= Lb) return;
+  const int e = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;
+  const int W = 16 * map.NB, r = e / W;
+  const int col = item / map.n_rg * W + e % W;
+  if (col >= ldy) return;
+  float4 *y = reinterpret_cast<float4 *>(Y + ((int64_t)(item % map.n_rg) * kKgRows + r) * ldy + col);
+  float4 v = *y;
+  for (int64_t L = La; L < Lb; ++L) {
+    const float4 c = *reinterpret_cast<const float4 *>(slots + L * kgemm_tile(map.NB) + e);
+    v.x += c.x, v.y += c.y, v.z += c.z, v.w += c.w;
+  }
   *y = v;
 }
 
@@ -500,13 +528,61 @@ void launch_kgemm_bf3(const KgMap &m, const uint4 *K3, const uint4 *Bk, int ncol
   }
 }
 
-// X^B1 = (w W - I1) / h^2, X^B2 = (w W^T - G2) / h^2 (XB2 holds G2 on entry), X^B their sum.
-__global__ void k_rom_assemble(const float *__restrict__ W, const float *__restrict__ I1, int R, float w, float ih2,
-                               float *__restrict__ XB1, float *__restrict__ XB2, float *__restrict__ XB) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (int64_t)R * R) return;
-  const int i = (int)(t / R), j = (int)(t % R);
-  const float a = ih2 * (w * W[t] - I1[t]), b = ih2 * (w * W[(int64_t)j * R + i] - XB2[t]);
+// X^B1 = (w W - I1) / h^2, X^B2 = (w W^T - G2) / h^2 and X^B their sum, straight
+// from the split partials of W and of the symmetric G2 (whose entries below the
+// diagonal are those above it).  A workgroup owns a 16 x 16 tile; its four groups
+// of 256 threads take every fourth split of W's tile, of its mirror image and of
+// G2's, FP64, fixed order.
+// Bound: the latency of splits / 4 loads, then the partials' bytes.  P = 20000,
+// R = 180: 18 us for 128 splits; two sums over 64 splits, one thread per entry, and
+// an elementwise launch took 17 + 17 + 3.
+__global__ __launch_bounds__(1024) void k_rom_assemble(GemmShape gw, GemmShape gg, const float *__restrict__ partW,
+                                                       const float *__restrict__ partG, int splits,
+                                                       const float *__restrict__ I1, int R, float w, float ih2,
+                                                       float *__restrict__ XB1, float *__restrict__ XB2,
+                                                       float *__restrict__ XB) {
+  __shared__ double red[3][4][256];
+  __shared__ float tot[3][16][17];
+  const int ti = blockIdx.x, tj = blockIdx.y;
+  const int sg = threadIdx.x >> 8, e = threadIdx.x & 255, r = e >> 4, c = e & 15;
+  const int64_t RR = (int64_t)R * R;
+  // tile (a, b) of the three matrices: W's (ti, tj) and (tj, ti), G2's on or above the diagonal
+  const int ta[3] = {ti, tj, min(ti, tj)}, tb[3] = {tj, ti, max(ti, tj)};
+  const float *src[3];
+  bool in[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int i = 16 * ta[q] + r, j = 16 * tb[q] + c;
+    in[q] = i < R && j < R;
+    src[q] = (q < 2 ? partW : partG) + (in[q] ? (int64_t)i * R + j : 0);
+  }
+  double s3[3] = {0.0, 0.0, 0.0};
+  for (int k0 = sg; k0 < splits; k0 += 32) {
+    float v[3][8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) v[q][u] = src[q][min(k0 + 4 * u, splits - 1) * RR];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s3[q] += k0 + 4 * u < splits ? (double)v[q][u] : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) red[q][sg][e] = in[q] ? s3[q] : 0.0;
+  __syncthreads();
+  if (sg < 3) {
+    const int i = 16 * ta[sg] + r, j = 16 * tb[sg] + c;
+    double s = (red[sg][0][e] + red[sg][1][e]) + (red[sg][2][e] + red[sg][3][e]);
+    if (s != s) s = (double)gemm_entry_fp32(sg < 2 ? gw : gg, i, j);
+    tot[sg][r][c] = (float)s;
+  }
+  __syncthreads();
+  const int i = 16 * ti + r, j = 16 * tj + c;
+  if (sg != 0 || i >= R || j >= R) return;
+  const int64_t t = (int64_t)i * R + j;
+  const float g2 = i > j ? tot[2][c][r] : tot[2][r][c];
+  const float a = ih2 * (w * tot[0][r][c] - I1[t]), b = ih2 * (w * tot[1][c][r] - g2);
   XB1[t] = a;
   XB2[t] = b;
   XB[t] = a + b;
@@ -1017,26 +1093,34 @@ __global__ void k_f64_to_f32(const double *__restrict__ a, int64_t n, float *__r
   if (t < n) b[t] = (float)a[t];
 }
 
-// tau_ab = (n / P) sum_k H_k p_k^T M_ab p_k (uniform weights), FP64 sums.
-__global__ __launch_bounds__(256) void k_rom_stress(const float *__restrict__ Mbig, const float *__restrict__ p, int nb,
-                                                    int R, EvalParams ep, double *__restrict__ out) {
-  __shared__ double sm[256];
+// tau_ab = (n / P) sum_k H_k p_k^T M_ab p_k (uniform weights), FP64 sums: a
+// workgroup per ab, its waves over the rows, lanes over the columns.
+__global__ __launch_bounds__(1024) void k_rom_stress(const float *__restrict__ Mbig, const float *__restrict__ p, int nb,
+                                                     int R, EvalParams ep, double *__restrict__ out) {
+  __shared__ double sm[16];
   const int ab = blockIdx.x;  // 0..8
-  const int a = ab / 3, b = ab % 3;
+  const int a = ab / 3, b = ab % 3, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ld = 3 * (int64_t)R;
+  const float *M = Mbig + (int64_t)a * R * ld + (int64_t)b * R;
   double acc = 0.0;
-  for (int64_t t = threadIdx.x; t < (int64_t)R * R; t += 256) {
-    const int s = (int)(t / R), u = (int)(t % R);
-    const double m = Mbig[(a * (int64_t)R + s) * ld + b * R + u];
-    for (int k = 0; k < nb; ++k) acc += (double)ep.H[k] * (double)p[k * R + s] * m * (double)p[k * R + u];
-  }
-  sm[threadIdx.x] = acc;
+  for (int u = lane; u < R; u += 64)
+    for (int s = wave; s < R; s += 16) {
+      const double m = M[s * ld + u];
+      double pp = 0.0;
+#pragma unroll
+      for (int k = 0; k < kMaxNb; ++k)
+        if (k < nb) pp += (double)ep.H[k] * (double)p[k * R + s] * (double)p[k * R + u];
+      acc += m * pp;
+    }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
+  if (lane == 0) sm[wave] = acc;
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) sm[threadIdx.x] += sm[threadIdx.x + st];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int v = 0; v < 16; ++v) t += sm[v];
+    out[ab] = t * (double)ep.n / (double)ep.P;
   }
-  if (threadIdx.x == 0) out[ab] = sm[0] * (double)ep.n / (double)ep.P;
 }
 
 inline unsigned nblk256(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -1091,7 +1175,6 @@ vds_status operators_bf3(vds_rom r) {
   if (!r->b3_ready) prepare_b3(r);
   const int ncols = 3 * R;
   const int64_t ldy = rom_ldy3(R);
-  float *W = r->Y + c->ep.Ppad * ldy;
   timed(c, VDS_TIMER_KGEMM, 2.0 * (double)P * P * ncols, [&] {
     const uint4 *k3 = static_cast<const uint4 *>(c->f16.QH), *bk = reinterpret_cast<const uint4 *>(r->Bsw);
     switch (c->ep.D) {
@@ -1101,8 +1184,8 @@ vds_status operators_bf3(vds_rom r) {
       case 12: launch_kgemm_bf3<12>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
       default: launch_kgemm_bf3<15>(L.kg, k3, bk, ncols, r->Y, ldy, r->part, s); break;
     }
-    k_kgemm_fixup<<<dim3((unsigned)(kgemm_tile(L.kg.NB) / 256), (unsigned)L.kg.items()), 256, 0, s>>>(
-        r->part, L.kg, ncols, r->Y, ldy);
+    k_kgemm_fixup<<<dim3((unsigned)(kgemm_tile(L.kg.NB) / 1024), (unsigned)L.kg.items()), 256, 0, s>>>(r->part, L.kg,
+                                                                                                       r->Y, ldy);
   });
   GemmShape g;
   g.M = R;
@@ -1117,18 +1200,22 @@ vds_status operators_bf3(vds_rom r) {
   g.sB = R;
   g.b_mn = true;
   g.scale = r->invS;
-  g.C = W;
-  g.ldc = R;
-  g.splits = gemm_splits(R, R, P, 3);
-  rom_gemm(r, g, 2.0 * 3 * RR * P);
-  g.B = r->Ude;  // G2 = sum_a U_a^T diag(T) U_a
-  g.ldb = P;
-  g.sB = (int64_t)R * P;
-  g.b_mn = false;
-  g.scale = r->T;
-  g.C = r->XB2;
-  rom_gemm(r, g, 2.0 * 3 * RR * P);
-  k_rom_assemble<<<nblk256(RR), 256, 0, s>>>(W, r->I1, R, c->ep.uniform_w, c->ep.inv_h2, r->XB1, r->XB2, r->XB);
+  g.splits = rom_splits(L, R, P);
+  float *partG = r->part + (int64_t)g.splits * RR;
+  timed(c, VDS_TIMER_GEMM, 2.0 * 3 * RR * P, [&] { launch_gemm_parts(g, r->part, s); });
+  GemmShape g2 = g;
+  g2.B = r->Ude;  // G2 = sum_a U_a^T diag(T) U_a
+  g2.ldb = P;
+  g2.sB = (int64_t)R * P;
+  g2.b_mn = false;
+  g2.scale = r->T;
+  g2.symmetric = true;
+  timed(c, VDS_TIMER_GEMM, 2.0 * 3 * RR * P, [&] {
+    launch_gemm_parts(g2, partG, s);
+    const unsigned t16 = (unsigned)((R + 15) / 16);
+    k_rom_assemble<<<dim3(t16, t16), 1024, 0, s>>>(g, g2, r->part, partG, g.splits, r->I1, R, c->ep.uniform_w,
+                                                   c->ep.inv_h2, r->XB1, r->XB2, r->XB);
+  });
   return hip_check(c, hipGetLastError(), "reduced operators");
 }
 
@@ -1341,7 +1428,7 @@ vds_status vds_rom_stress(vds_rom r, const float *p, double *tau) {
   if (r == nullptr) return VDS_ERR_ARG;
   vds_ctx c = r->ctx;
   if (!p || !tau) return set_err(c, VDS_ERR_ARG, "null argument");
-  k_rom_stress<<<9, 256, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
+  k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
   vds_status st = hip_check(c, hipMemcpyAsync(tau, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream), "copy");
   if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
   return st;
@@ -1514,7 +1601,7 @@ enum FreezeAt { FREEZE_START = 0, FREEZE_MIDPOINT = 1, FREEZE_EXTRAPOLATED = 2 }
 // stream order (the caller synchronises before reading it).
 vds_status rom_stress_async(vds_rom r, const float *p, double *tau_host) {
   vds_ctx c = r->ctx;
-  k_rom_stress<<<9, 256, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
+  k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
   return hip_check(c, hipMemcpyAsync(tau_host, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream),
                    "copy stress");
 }

@@ -38,6 +38,25 @@ struct GemmShape {
 // BF16 matrix cores, three BF16 parts per FP32 factor.  Sums
 // within a split in FP32, over the splits in FP64.
 void launch_gemm(const GemmShape &g, float *part, hipStream_t s);
+// The same without the sum: part[split][i][j], M x N per split (symmetric: the
+// entries of tiles on and above the diagonal).
+void launch_gemm_parts(const GemmShape &g, float *part, hipStream_t s);
+
+// Entry (i, j) in FP32, term by term: for entries that are not numbers in the
+// three-part product (an infinite factor, or one past the BF16 range, has no
+// parts), so that they are what FP32 arithmetic makes of the inputs.
+__device__ inline float gemm_entry_fp32(const GemmShape &g, int i, int j) {
+  float s = 0.f;
+  for (int b = 0; b < g.nbatch; ++b)
+    for (int64_t k = 0; k < g.K; ++k) {
+      const float x = g.A[b * g.sA + (g.a_mn ? k * g.lda + i : (int64_t)i * g.lda + k)];
+      float y = g.B[b * g.sB + (g.b_mn ? k * g.ldb + j : (int64_t)j * g.ldb + k)];
+      if (g.scale != nullptr) y *= g.scale[b * g.sS + k];
+      s = fmaf(x, y, s);
+    }
+  return s;
+}
+
 void launch_cholesky(double *A, int n, double shift, int *info, hipStream_t s);
 void launch_tri_inverse(const double *L, int n, double *work, float *Linv, hipStream_t s);
 void launch_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);
