@@ -601,9 +601,10 @@ __global__ __launch_bounds__(kRedBlock) void k_combine(EvalParams p, int mode, i
 // lane l folds blocks l, l + 64, ... in order, then a fixed butterfly over the
 // wave (deterministic; the latency is that of nblk / 64 loads, not nblk).
 __global__ __launch_bounds__(1024) void k_reduce_final(const double *__restrict__ redp, int nblk, int nslots,
-                                                       double *__restrict__ out, const int *__restrict__ done) {
-  if (done != nullptr && *done) return;
+                                                       double *__restrict__ out, const Ctrl *__restrict__ ctrl,
+                                                       Ctrl *__restrict__ ctrl_out) {
   const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (ctrl_out != nullptr && threadIdx.x == 1023) *ctrl_out = *ctrl;
   if (s >= nslots) return;
   double a0 = 0.0, a1 = 0.0;
   int b = lane;
@@ -855,15 +856,18 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_stress(BatchView b, const f
   stress_body(d.p, blockIdx.x - d.blk256, q + d.q_off, nullptr, redp + (int64_t)d.blk256 * 16);
 }
 
-__global__ void k_batch_stress_sum(const EnsDesc *__restrict__ ens, const double *__restrict__ redp,
-                                   double *__restrict__ tau) {
+// A workgroup per ensemble, a wave per component: lane l folds blocks l, l + 64,
+// ..., then the wave (one thread per component took 18 us at 63 blocks).
+__global__ __launch_bounds__(576) void k_batch_stress_sum(const EnsDesc *__restrict__ ens,
+                                                          const double *__restrict__ redp, double *__restrict__ tau) {
   const EnsDesc &d = ens[blockIdx.x];
-  const int s = threadIdx.x;
-  if (s >= 9) return;
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nb = (int)(d.p.Ppad / kRedBlock);
   double acc = 0.0;
-  for (int i = 0; i < nb; ++i) acc += redp[((int64_t)d.blk256 + i) * 16 + s];
-  tau[(int64_t)blockIdx.x * 9 + s] = acc;
+  for (int i = lane; i < nb; i += 64) acc += redp[((int64_t)d.blk256 + i) * 16 + s];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if (lane == 0) tau[(int64_t)blockIdx.x * 9 + s] = acc;
 }
 
 // ---- small problems: a pass and what follows it in one launch ----------------
@@ -1209,8 +1213,9 @@ void launch_rows_b(const EvalParams &p, int mode, bool obs, const void *K3, cons
   };
   by_dimension(p.D, go);
 }
-void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, const int *done, hipStream_t s) {
-  k_reduce_final<<<1, 1024, 0, s>>>(redp, nblk, nslots, out, done);
+void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, hipStream_t s, const Ctrl *ctrl,
+                         Ctrl *ctrl_out) {
+  k_reduce_final<<<1, 1024, 0, s>>>(redp, nblk, nslots, out, ctrl, ctrl_out);
 }
 void launch_ctrl_reset(Ctrl *ctrl, hipStream_t s) { k_ctrl_reset<<<1, 64, 0, s>>>(ctrl); }
 void launch_step_end(const EvalParams &p, Ctrl *ctrl, const PicardCheck &chk, const float *blockmax, int nblk_chk,
@@ -1302,7 +1307,7 @@ void launch_batch_stress(const BatchView &b, const float *q, double *redp, hipSt
   k_batch_stress<<<b.nblk256, kRedBlock, 0, s>>>(b, q, redp);
 }
 void launch_batch_stress_sum(const EnsDesc *ens, int nens, const double *redp, double *tau, hipStream_t s) {
-  k_batch_stress_sum<<<nens, 64, 0, s>>>(ens, redp, tau);
+  k_batch_stress_sum<<<nens, 576, 0, s>>>(ens, redp, tau);
 }
 
 __global__ void k_copy(const float *__restrict__ src, float *__restrict__ dst, int64_t n) {

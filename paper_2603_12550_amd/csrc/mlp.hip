@@ -715,6 +715,7 @@ struct vds_mlp_s {
   short *wbf, *wpk;
   double *lossp;
   double *loss_out;  // one slot after the per-tile partials
+  double *host_loss = nullptr;  // pinned (see vds::pinned_slot)
   int t = 0;
   bool bf_stale = true;
   float noise = 0.f;          // training input noise (vds_mlp_set_input_noise)
@@ -819,8 +820,8 @@ int64_t forward_fp32(vds_mlp m, const float *X, int n, float *Y, const float *T 
   return launch_mlp(m, out);
 }
 
-// Gradients and loss of one minibatch; the loss is added to *loss_out or put there.
-void loss_grad_fp32(vds_mlp m, const float *X, const float *T, int n, bool add_loss) {
+// Gradients and loss of one minibatch; the loss is added to *loss or put there.
+void loss_grad_fp32(vds_mlp m, const float *X, const float *T, int n, double *loss, bool add_loss) {
   const int w = m->w, nin = m->nin, nout = m->nout;
   float *gW1 = m->grads, *gb1 = gW1 + (int64_t)w * nin, *gW2 = gb1 + w, *gb2 = gW2 + (int64_t)w * w,
         *gW3 = gb2 + w, *gb3 = gW3 + (int64_t)nout * w;
@@ -830,7 +831,7 @@ void loss_grad_fp32(vds_mlp m, const float *X, const float *T, int n, bool add_l
   launch_mlp(m, input_grad(m->dZ2, n, w, m->W2(), w, m->Z1, m->dZ1), weight_grad(m->dZ2, n, w, m->A1, w, gW2),
              MlpColsum{m->dZ2, n, w, gb2});
   launch_mlp(m, weight_grad(m->dZ1, n, w, X, nin, gW1), MlpOp{}, MlpColsum{m->dZ1, n, w, gb1},
-             MlpLoss{m->lossp, np, 1.0 / ((double)n * nout), add_loss, m->loss_out});
+             MlpLoss{m->lossp, np, 1.0 / ((double)n * nout), add_loss, loss});
 }
 
 void refresh_bf16(vds_mlp m) {
@@ -958,7 +959,10 @@ vds_status vds_mlp_bind_workspace(vds_mlp m, void *ws, size_t bytes) {
   return st;
 }
 
-void vds_mlp_destroy(vds_mlp m) { delete m; }
+void vds_mlp_destroy(vds_mlp m) {
+  if (m != nullptr && m->host_loss != nullptr) (void)hipHostFree(m->host_loss);
+  delete m;
+}
 const char *vds_mlp_last_error(vds_mlp m) { return m ? m->err.c_str() : g_mlp_create_error.c_str(); }
 int64_t vds_mlp_param_count(vds_mlp m) { return m ? m->np : -1; }
 
@@ -1020,11 +1024,14 @@ vds_status vds_mlp_loss_grad(vds_mlp m, const float *X, const float *T, int32_t 
   if (!m || !X || !T) return VDS_ERR_ARG;
   if (!m->ws) return merr(m, VDS_ERR_STATE, "no workspace bound");
   if (n < 1 || n > m->B) return merr(m, VDS_ERR_ARG, "batch size out of range");
-  loss_grad_fp32(m, X, T, n, false);
+  double *host = loss != nullptr ? pinned_slot(m->host_loss, sizeof(double)) : nullptr;
+  loss_grad_fp32(m, X, T, n, host != nullptr ? host : m->loss_out, false);
   vds_status st = mhip(m, hipGetLastError(), "loss_grad");
   if (st != VDS_OK || loss == nullptr) return st;
-  st = mhip(m, hipMemcpyAsync(loss, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy loss");
+  if (host == nullptr)
+    st = mhip(m, hipMemcpyAsync(loss, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy loss");
   if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
+  if (st == VDS_OK && host != nullptr) *loss = *host;
   return st;
 }
 
@@ -1050,7 +1057,7 @@ vds_status vds_mlp_train_epoch(vds_mlp m, const float *X, const float *T, int32_
         X, T, order, bi * batch, batch, m->nin, m->nout, m->xs, m->xsc, m->ys, m->ysc, m->xin, m->tin, m->noise,
         m->noise_seed, m->noise_draws);
     m->noise_draws += (uint64_t)batch * m->nin;
-    loss_grad_fp32(m, m->xin, m->tin, batch, bi > 0);
+    loss_grad_fp32(m, m->xin, m->tin, batch, m->loss_out, bi > 0);
     vds_mlp_adam_step(m, lr, 0.9f, 0.999f, 1e-8f);
   }
   vds_status st = mhip(m, hipGetLastError(), "train epoch");

@@ -8,6 +8,7 @@
 // freeze per window, at the state half a window on.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -1136,16 +1137,45 @@ struct vds_rom_s {
   bool b3_ready = false;  // Bsw holds the basis as the default kernel-GEMM reads it
   float *Ude, *Mbig, *XH, *I1, *XB1, *XB2, *XB, *Bsw, *Y, *qt, *T, *invS, *part, *psave, *pprev;
   double *red;
+  double *host_tau = nullptr;  // pinned (see vds::pinned_slot): kHostTau stresses
 };
 
 namespace {
+
+constexpr int kHostTau = 64;
 
 vds_status rom_gemm(vds_rom r, GemmShape g, double flops) {
   timed(r->ctx, VDS_TIMER_GEMM, flops, [&] { launch_gemm(g, r->part, r->ctx->stream); });
   return VDS_OK;
 }
 
-// X^B1, X^B2 (and X^B = X^B1 + X^B2) at q~ = U p.
+// Stresses of reduced states (from the M_ab), in stream order into tau[9],
+// tau[9] + 9, ...: the kernel writes them to pinned memory, which is emptied
+// when it is full and at the end.
+struct StressOut {
+  vds_rom r;
+  double *tau;
+  int queued = 0;
+  vds_status add(const float *p) {
+    vds_ctx c = r->ctx;
+    double *host = pinned_slot(r->host_tau, sizeof(double) * 9 * kHostTau);
+    k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, host ? host + 9 * queued : r->red);
+    if (host != nullptr) return ++queued == kHostTau ? finish() : VDS_OK;
+    vds_status st = hip_check(c, hipMemcpyAsync(tau, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream),
+                              "copy stress");
+    tau += 9;
+    return st;
+  }
+  vds_status finish() {  // synchronises
+    vds_status st = hip_check(r->ctx, hipStreamSynchronize(r->ctx->stream), "synchronise");
+    if (st != VDS_OK) return st;
+    if (queued > 0) std::memcpy(tau, r->host_tau, sizeof(double) * 9 * queued);
+    tau += 9 * queued;
+    queued = 0;
+    return VDS_OK;
+  }
+};
+
 // q~ = U p into r->qt.
 void reconstruct_qt(vds_rom r, const float *p) {
   vds_ctx c = r->ctx;
@@ -1409,7 +1439,10 @@ vds_status vds_rom_create(vds_ctx c, const float *U, int32_t R, void *ws, size_t
   return VDS_OK;
 }
 
-void vds_rom_destroy(vds_rom r) { delete r; }
+void vds_rom_destroy(vds_rom r) {
+  if (r != nullptr && r->host_tau != nullptr) (void)hipHostFree(r->host_tau);
+  delete r;
+}
 
 vds_status vds_rom_operators(vds_rom r, const float *p, float *XH, float *XB1, float *XB2) {
   if (r == nullptr) return VDS_ERR_ARG;
@@ -1428,10 +1461,9 @@ vds_status vds_rom_stress(vds_rom r, const float *p, double *tau) {
   if (r == nullptr) return VDS_ERR_ARG;
   vds_ctx c = r->ctx;
   if (!p || !tau) return set_err(c, VDS_ERR_ARG, "null argument");
-  k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
-  vds_status st = hip_check(c, hipMemcpyAsync(tau, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream), "copy");
-  if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
-  return st;
+  StressOut out{r, tau};
+  vds_status st = out.add(p);
+  return st == VDS_OK ? out.finish() : st;
 }
 
 size_t vds_rom_exact_workspace_bytes(const vds_problem *prob, int32_t R) {
@@ -1597,22 +1629,13 @@ void rom_steps(vds_rom r, float *p, int n) {
 // frozen operators are O(L^2) from those at the true midpoint.
 enum FreezeAt { FREEZE_START = 0, FREEZE_MIDPOINT = 1, FREEZE_EXTRAPOLATED = 2 };
 
-// Stress of the reduced state p from the M_ab, copied into tau_host[9] in
-// stream order (the caller synchronises before reading it).
-vds_status rom_stress_async(vds_rom r, const float *p, double *tau_host) {
-  vds_ctx c = r->ctx;
-  k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, r->red);
-  return hip_check(c, hipMemcpyAsync(tau_host, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream),
-                   "copy stress");
-}
-
 // With output_every >= 1 the stress after steps output_every, 2 output_every,
 // ... and after the last step goes to tau[9 i ...]; with output_every == 0 only
 // the stress after the last step (tau may be NULL).
 vds_status rom_windows(vds_rom r, float *p, int nsteps, int freeze_every, FreezeAt at, double *tau,
                        int output_every = 0) {
   vds_ctx c = r->ctx;
-  int nout = 0;
+  StressOut out{r, tau};
   // steps [k, k + n) of the run, split at the output steps
   auto steps_out = [&](int k, int n) -> vds_status {
     while (n > 0) {
@@ -1621,7 +1644,7 @@ vds_status rom_windows(vds_rom r, float *p, int nsteps, int freeze_every, Freeze
       k += m;
       n -= m;
       if (tau != nullptr && ((output_every > 0 && k % output_every == 0) || k == nsteps)) {
-        vds_status st = rom_stress_async(r, p, tau + 9 * nout++);
+        vds_status st = out.add(p);
         if (st != VDS_OK) return st;
       }
     }
@@ -1667,9 +1690,8 @@ vds_status rom_windows(vds_rom r, float *p, int nsteps, int freeze_every, Freeze
   }
   vds_status st = hip_check(c, hipGetLastError(), "reduced steps");
   if (st != VDS_OK) return st;
-  if (tau != nullptr && nsteps == 0) st = rom_stress_async(r, p, tau);
-  if (st != VDS_OK) return st;
-  return hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
+  if (tau != nullptr && nsteps == 0) st = out.add(p);
+  return st == VDS_OK ? out.finish() : st;
 }
 
 }  // namespace

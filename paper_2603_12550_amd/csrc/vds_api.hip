@@ -273,6 +273,28 @@ void drain_timers(vds_ctx c) {
   }
 }
 
+// Sums the first nslots slots of the block partials for read_back, with the
+// control block.
+void reduce_out(vds_ctx c, int nblk, int nslots) {
+  HostOut *h = pinned_slot(c->host, sizeof(HostOut));
+  launch_reduce_final(c->redp, nblk, nslots, h ? h->red : c->redout, c->stream, c->ctrl, h ? &h->ctrl : nullptr);
+}
+
+// What the last reduce_out left (synchronises).
+vds_status read_back(vds_ctx c, HostOut &out) {
+  vds_status st = VDS_OK;
+  if (c->host == nullptr) {
+    st = hip_check(c, hipMemcpyAsync(out.red, c->redout, sizeof(out.red), hipMemcpyDeviceToHost, c->stream),
+                   "copy sums");
+    if (st == VDS_OK)
+      st = hip_check(c, hipMemcpyAsync(&out.ctrl, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream),
+                     "copy ctrl");
+  }
+  if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
+  if (st == VDS_OK && c->host != nullptr) out = *c->host;
+  return st;
+}
+
 // Prep + pass A + finalize A + pass B + combine(mode).  Without `centre` the
 // centring partials already in the workspace are used (the fixed-point
 // iterations of a step all centre at the step's start state: the sums are
@@ -281,48 +303,27 @@ void evaluate(vds_ctx c, const float *q, const float *w, int mode, bool obs, con
               float *out2, const int *done, bool centre = true) {
   eval_pass_a(c, q, w, done, centre);
   pass_b(c, mode, obs, q, q0, out, out2, done, 0, nullptr, fene_flag(c));
-  if (obs) launch_reduce_final(c->redp, c->nblk_comb, 12, c->redout, done, c->stream);
+  if (obs) reduce_out(c, c->nblk_comb, 12);
 }
 
-// Reads and clears the FENE domain flag (FENE problems only; synchronises).
-vds_status fene_domain_check(vds_ctx c) {
-  if (c->prob.potential != VDS_FENE) return VDS_OK;
-  int out = 0;
-  vds_status st = hip_check(c, hipMemcpyAsync(&out, fene_flag(c), sizeof(int), hipMemcpyDeviceToHost, c->stream),
-                            "copy flag");
-  if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
-  if (st != VDS_OK) return st;
-  if (out == 0) return VDS_OK;
+// The FENE domain flag of a finished evaluation or step (FENE problems only).
+vds_status fene_domain_check(vds_ctx c, const HostOut &h) {
+  if (c->prob.potential != VDS_FENE || h.ctrl.fene_out == 0) return VDS_OK;
   launch_ctrl_reset(c->ctrl, c->stream);
   return set_err(c, VDS_ERR_ARG, "a FENE bond reached |q|^2 >= b_max (outside the spring's domain) or is not finite");
 }
 
-vds_status fetch_obs(vds_ctx c, vds_diag *d) {
-  double r[16];
-  vds_status st = hip_check(c, hipMemcpyAsync(r, c->redout, sizeof(double) * 12, hipMemcpyDeviceToHost, c->stream),
-                            "copy observables");
-  if (st != VDS_OK) return st;
-  st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
-  if (st != VDS_OK) return st;
-  d->F = r[RED_F];
-  d->dissipation = r[RED_DISS];
-  d->work = r[RED_WORK];
-  for (int i = 0; i < 9; ++i) d->tau[i] = r[RED_TAU + i];
-  d->energy_valid = 1;
-  return VDS_OK;
+void queue_stress(vds_ctx c, const float *q, const float *w) {
+  launch_stress(c->ep, q, w, c->redp, c->stream);
+  reduce_out(c, c->nblk, 9);
 }
 
 vds_status stress_into(vds_ctx c, const float *q, const float *w, double *tau) {
-  launch_stress(c->ep, q, w, c->redp, c->stream);
-  launch_reduce_final(c->redp, c->nblk, 9, c->redout, nullptr, c->stream);
-  double r[9];
-  vds_status st =
-      hip_check(c, hipMemcpyAsync(r, c->redout, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream), "copy stress");
-  if (st != VDS_OK) return st;
-  st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
-  if (st != VDS_OK) return st;
-  std::memcpy(tau, r, sizeof(r));
-  return VDS_OK;
+  queue_stress(c, q, w);
+  HostOut h;
+  vds_status st = read_back(c, h);
+  if (st == VDS_OK) std::memcpy(tau, h.red, 9 * sizeof(double));
+  return st;
 }
 
 }  // namespace
@@ -377,6 +378,7 @@ void vds_destroy(vds_ctx c) {
     }
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   if (c->blas != nullptr) rocblas_destroy_handle(static_cast<rocblas_handle>(c->blas));
+  if (c->host != nullptr) (void)hipHostFree(c->host);
   delete c;
 }
 
@@ -509,17 +511,41 @@ vds_status vds_pair_sums_noalloc(vds_ctx c, const float *q, const float *w, floa
   return st;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Ends an evaluation: the FENE domain flag, and with d (evaluated with its
+// observables) the observables.
+vds_status observables(vds_ctx c, vds_diag *d) {
+  vds_status st = hip_check(c, hipGetLastError(), "launch");
+  const bool fene = c->prob.potential == VDS_FENE;
+  if (st != VDS_OK || (!fene && d == nullptr)) return st;
+  if (d == nullptr) reduce_out(c, 0, 0);
+  HostOut h;
+  st = read_back(c, h);
+  if (st == VDS_OK) st = fene_domain_check(c, h);
+  if (st != VDS_OK || d == nullptr) return st;
+  std::memset(d, 0, sizeof(*d));
+  d->F = h.red[RED_F];
+  d->dissipation = h.red[RED_DISS];
+  d->work = h.red[RED_WORK];
+  for (int i = 0; i < 9; ++i) d->tau[i] = h.red[RED_TAU + i];
+  d->energy_valid = 1;
+  return VDS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 vds_status vds_velocity(vds_ctx c, const float *q, const float *w, float *v, vds_diag *d) {
   vds_status st = ready(c);
   if (st != VDS_OK) return st;
   if (!q || !v) return set_err(c, VDS_ERR_ARG, "null array");
   if (c->prob.potential == VDS_FENE) launch_ctrl_reset(c->ctrl, c->stream);
   evaluate(c, q, w, MODE_VELOCITY, d != nullptr, nullptr, v, nullptr, nullptr);
-  st = hip_check(c, hipGetLastError(), "launch");
-  if (st == VDS_OK) st = fene_domain_check(c);
-  if (st != VDS_OK || d == nullptr) return st;
-  std::memset(d, 0, sizeof(*d));
-  return fetch_obs(c, d);
+  return observables(c, d);
 }
 
 }  // extern "C"
@@ -606,8 +632,11 @@ vds_status finish_step(vds_ctx c, float *q, const float *w, int m0, StepCounts &
 // step-end kernel writes the converged iterate back.  A step
 // that has not converged after its queued iterations halts the queue (every
 // later kernel returns at once); the host then finishes that step and queues
-// the rest.  The host synchronises once per kQueueSteps steps.
-vds_status implicit_steps(vds_ctx c, float *q, const float *w, int nsteps, StepCounts &n, int &steps_taken) {
+// the rest.  The host synchronises once per kQueueSteps steps.  With `tau` the
+// last queue ends with the stress of the final state, which is then in tau
+// unless that queue halted (returned in have_tau).
+vds_status implicit_steps(vds_ctx c, float *q, const float *w, int nsteps, StepCounts &n, int &steps_taken, double *tau,
+                          bool &have_tau) {
   const vds_problem &p = c->prob;
   const int batch = std::min(p.picard_batch, p.picard_max);
   const int *done = &c->ctrl->done;
@@ -642,13 +671,19 @@ vds_status implicit_steps(vds_ctx c, float *q, const float *w, int nsteps, StepC
                       c->nblk_comb, c->xb[0], c->xb[1], q, p.picard_predictor ? c->xpred : nullptr, w,
                       j + 1 < chunk ? c->meanp : nullptr, c->stream);
     }
-    Ctrl h{};
-    vds_status st = hip_check(c, hipMemcpyAsync(&h, c->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, c->stream),
-                              "copy ctrl");
-    if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
+    const bool with_tau = tau != nullptr && steps_taken + chunk == nsteps;
+    if (with_tau) queue_stress(c, q, w);
+    else reduce_out(c, 0, 0);
+    HostOut out;
+    vds_status st = read_back(c, out);
     if (st != VDS_OK) return st;
+    const Ctrl &h = out.ctrl;
     if (h.fene_out)
       return set_err(c, VDS_ERR_ARG, "a FENE bond reached |q|^2 >= b_max (outside the spring's domain) or is not finite");
+    if (with_tau && !h.halted) {
+      std::memcpy(tau, out.red, 9 * sizeof(double));
+      have_tau = true;
+    }
     n.total_iters += (int)h.total_iters;
     if (h.steps_done > 0) n.last_iters = h.last_iters;
     n.last_resid = h.last_resid;  // of the last iteration checked
@@ -675,14 +710,25 @@ vds_status vds_step(vds_ctx c, float *q, const float *w, int32_t nsteps, vds_dia
   if (nsteps < 0) return set_err(c, VDS_ERR_ARG, "nsteps < 0");
   const vds_problem &p = c->prob;
   StepCounts n;
+  double tau[9];
+  bool have_tau = false;
   if (p.scheme == VDS_EXPLICIT) {
-    if (p.potential == VDS_FENE && nsteps > 0) launch_ctrl_reset(c->ctrl, c->stream);
+    const bool flag = p.potential == VDS_FENE && nsteps > 0;
+    if (flag) launch_ctrl_reset(c->ctrl, c->stream);
     explicit_steps(c, q, w, nsteps);
-    if (nsteps > 0) st = fene_domain_check(c);
-    if (st != VDS_OK) return st;
+    if (flag || d != nullptr) {
+      if (d != nullptr) queue_stress(c, q, w);
+      else reduce_out(c, 0, 0);
+      HostOut h;
+      st = read_back(c, h);
+      if (st == VDS_OK && flag) st = fene_domain_check(c, h);
+      if (st != VDS_OK) return st;
+      std::memcpy(tau, h.red, sizeof(tau));
+      have_tau = true;
+    }
   } else if (nsteps > 0) {
     int taken = 0;
-    st = implicit_steps(c, q, w, nsteps, n, taken);
+    st = implicit_steps(c, q, w, nsteps, n, taken, d != nullptr ? tau : nullptr, have_tau);
     if (st == VDS_ERR_NOT_CONVERGED && d != nullptr) {
       std::memset(d, 0, sizeof(*d));
       d->steps = taken;
@@ -693,15 +739,14 @@ vds_status vds_step(vds_ctx c, float *q, const float *w, int32_t nsteps, vds_dia
     if (st != VDS_OK) return st;
   }
   st = hip_check(c, hipGetLastError(), "launch");
-  if (st != VDS_OK) return st;
-  if (d != nullptr) {
-    std::memset(d, 0, sizeof(*d));
-    d->steps = nsteps;
-    d->iters = n.total_iters;
-    d->last_iters = n.last_iters;
-    d->resid = n.last_resid;
-    return stress_into(c, q, w, d->tau);
-  }
+  if (st != VDS_OK || d == nullptr) return st;
+  std::memset(d, 0, sizeof(*d));
+  d->steps = nsteps;
+  d->iters = n.total_iters;
+  d->last_iters = n.last_iters;
+  d->resid = n.last_resid;
+  if (!have_tau) return stress_into(c, q, w, d->tau);
+  std::memcpy(d->tau, tau, sizeof(tau));
   return VDS_OK;
 }
 
@@ -718,10 +763,8 @@ vds_status vds_energy(vds_ctx c, const float *q, const float *w, double *F, doub
   if (!q) return set_err(c, VDS_ERR_ARG, "null state");
   if (c->prob.potential == VDS_FENE) launch_ctrl_reset(c->ctrl, c->stream);
   evaluate(c, q, w, MODE_OBS_ONLY, true, nullptr, nullptr, nullptr, nullptr);
-  st = fene_domain_check(c);
-  if (st != VDS_OK) return st;
   vds_diag d{};
-  st = fetch_obs(c, &d);
+  st = observables(c, &d);
   if (st != VDS_OK) return st;
   if (F) *F = d.F;
   if (diss) *diss = d.dissipation;

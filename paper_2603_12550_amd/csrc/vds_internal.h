@@ -37,6 +37,29 @@ struct Ctrl {
   int fene_out;           // a combine kernel saw a FENE bond with |q|^2 >= b_max (or not finite)
 };
 
+// What a call reads back: kernels write it straight into pinned host memory (see
+// pinned_slot), which the host reads after synchronising the stream.
+struct HostOut {
+  double red[16];
+  Ctrl ctrl;
+};
+
+// An object's pinned host memory, made on the first call that reads back (such a
+// call synchronises, so it is never part of a capture) and freed with the
+// object; null if there is none.  A result written there by the last kernel and
+// read after the synchronisation takes 11 us from launch to host, a copy to
+// pageable memory 23.
+template <class T>
+T *pinned_slot(T *&slot, size_t bytes) {
+  if (slot == nullptr &&
+      hipHostMalloc(reinterpret_cast<void **>(&slot), bytes, hipHostMallocPortable | hipHostMallocCoherent) !=
+          hipSuccess) {
+    slot = nullptr;
+    (void)hipGetLastError();
+  }
+  return slot;
+}
+
 // Convergence test of one fixed-point iteration, taken from the combine
 // kernel's block maxima by the next kernel in stream order.
 struct PicardCheck {
@@ -269,7 +292,9 @@ void launch_rows_b(const EvalParams &p, int mode, bool obs, const void *K3, cons
                    const float *t1, const float *S, const float *wv, const float *qin, const float *q0, float *out,
                    float *out2, double *redp, float *blockmax, const int *done, hipStream_t s,
                    const PackOps *pack = nullptr, int *fene_out = nullptr);
-void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, const int *done, hipStream_t s);
+// out[s] = the sum of slot s over the blocks (s < nslots); with ctrl_out also *ctrl there.
+void launch_reduce_final(const double *redp, int nblk, int nslots, double *out, hipStream_t s,
+                         const Ctrl *ctrl = nullptr, Ctrl *ctrl_out = nullptr);
 void launch_ctrl_reset(Ctrl *ctrl, hipStream_t s);
 // Closes a queued implicit step whose last queued iteration is chk.iter: tests
 // it unless an earlier test converged, then copies the converged iterate
