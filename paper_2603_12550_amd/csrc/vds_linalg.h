@@ -64,19 +64,17 @@ void launch_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);
 constexpr int kGemmTile = 96;  // output tile edge of launch_gemm
 constexpr int kGemmSlab = 32;  // k-depth of one round
 
-// Splits of launch_gemm's K (all batches end to end, in rounds of 32): two
-// workgroups per compute unit, at least four rounds each, a multiple of eight
-// from eight on (a split's tiles then share an XCD), and at most 64 so that the
-// sum over the splits stays small.
+// Splits of launch_gemm's K (all batches end to end, in rounds of 32): up to three
+// workgroups per compute unit, at least four rounds each, and at most 64 so that
+// the sum over the splits stays small.
 inline int gemm_splits(int M, int N, int64_t K, int nbatch = 1, bool symmetric = false) {
   const int64_t tm = (M + kGemmTile - 1) / kGemmTile, tn = (N + kGemmTile - 1) / kGemmTile;
   // a symmetric product runs only the tiles on and above the diagonal
   const int64_t tiles = symmetric ? tm * (tm + 1) / 2 : tm * tn;
   const int64_t rounds = (K + kGemmSlab - 1) / kGemmSlab * nbatch;
-  int64_t s = 512 / tiles;
+  int64_t s = 768 / tiles;
   if (s > rounds / 4) s = rounds / 4;
   if (s > 64) s = 64;
-  if (s >= 8) s -= s % 8;
   return (int)(s < 1 ? 1 : s);
 }
 
