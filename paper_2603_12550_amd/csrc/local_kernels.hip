@@ -183,7 +183,47 @@ __device__ void load_mean(const EvalParams &p, const double *meanp, int nmeanp, 
 __device__ inline int64_t group_particle(int64_t lb) { return (lb * kRedBlock + threadIdx.x) >> 4; }
 __device__ inline int group_lane() { return threadIdx.x & 15; }
 __device__ inline float gshfl(float v, int n) { return __shfl(v, n, 16); }
-__device__ inline double gshfl(double v, int n) { return __shfl(v, n, 16); }
+// Lane movements inside a row of 16 as data-parallel-primitive controls: a few
+// cycles each, where a shuffle goes through the LDS crossbar and back (some hundred
+// in a chain).  0x100 + i: from lane n + i, 0x110 + i: from lane n - i (zeros from
+// outside the row), 0x120 + i: rotated, 0x150 + i: lane i to all.
+template <int kCtrl>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+template <int kCtrl>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Lane D of the row to all its lanes.
+__device__ __forceinline__ double row_lane_d(int D, double v) {
+  switch (D) {
+    case 3: return row_move<0x150 + 3>(v);
+    case 6: return row_move<0x150 + 6>(v);
+    case 9: return row_move<0x150 + 9>(v);
+    case 12: return row_move<0x150 + 12>(v);
+    default: return row_move<0x150 + 15>(v);
+  }
+}
+// The three components of this lane's bond (al = lane % 3).
+struct Bond {
+  float c0, c1, c2;
+};
+__device__ __forceinline__ Bond row_bond(float v, int al) {
+  const float l1 = row_move<0x111>(v), l2 = row_move<0x112>(v), r1 = row_move<0x101>(v), r2 = row_move<0x102>(v);
+  return Bond{al == 0 ? v : al == 1 ? l1 : l2, al == 0 ? r1 : al == 1 ? v : l1, al == 0 ? r2 : al == 1 ? r1 : v};
+}
+// The largest value of the wave, in every lane.
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, row_move<0x128>(v));
+  v = fmaxf(v, row_move<0x124>(v));
+  v = fmaxf(v, row_move<0x122>(v));
+  v = fmaxf(v, row_move<0x121>(v));
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
 __device__ inline float gsum(float v) {
 #pragma unroll
   for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
@@ -204,10 +244,8 @@ __device__ bool picard_converged(const PicardCheck &chk, const float *__restrict
   const int nt = threadIdx.x < kRedBlock ? strided_count(threadIdx.x, nblk, kRedBlock) : 0;
   float r = strided_max(blockmax + 2 * threadIdx.x, nt, 2 * kRedBlock, 0.f);
   float x = strided_max(blockmax + 2 * threadIdx.x + 1, nt, 2 * kRedBlock, 0.f);
-  for (int off = 32; off > 0; off >>= 1) {
-    r = fmaxf(r, __shfl_xor(r, off));
-    x = fmaxf(x, __shfl_xor(x, off));
-  }
+  r = wave_max(r);
+  x = wave_max(x);
   if ((threadIdx.x & 63) == 0 && threadIdx.x < kRedBlock) {
     sr[threadIdx.x >> 6] = r;
     sx[threadIdx.x >> 6] = x;
@@ -233,8 +271,10 @@ __device__ inline void store_k3(const EvalParams &p, bool real, uint32_t *__rest
   const Bf3 y = split_bf3(n < p.D ? p.cs * (double)x : 0.0);
   const double ys = bf16_value(y.h) + bf16_value(y.m) + bf16_value(y.l);
   double nrm = ys * ys;
-#pragma unroll
-  for (int off = 8; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 16);
+  nrm += row_move<0x128>(nrm);
+  nrm += row_move<0x124>(nrm);
+  nrm += row_move<0x122>(nrm);
+  nrm += row_move<0x121>(nrm);
   // lane n holds dwords 3n .. 3n + 2: component n, the norm (n = D) or zeros
   uint32_t d[3] = {0u, 0u, 0u};
   if (real && n < p.D) {
@@ -376,18 +416,18 @@ __device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, 
     return;
   }
   const double wI = (double)w;
-  const double Si = gshfl(o, p.D) + wI;  // the pass left out the self term w_I e_II = w_I
-  const float wb = (float)(wI / Si);
+  const double Si = row_lane_d(p.D, o) + wI;  // the pass left out the self term w_I e_II = w_I
+  const double rS = 1.0 / Si, wd = wI * rS;
+  const float wb = (float)wd;
   float v = 0.f;
   if (n < p.D) {
-    t1[I * p.D + n] = (float)(-(double)p.inv_h2 * o / Si);
+    t1[I * p.D + n] = (float)(-(double)p.inv_h2 * o * rS);
     v = wb * x;
   } else if (n == p.D) {
     S[I] = (float)Si;
     v = wb;
   }
   if (p.bf3) {
-    const double wd = wI / Si;
     store_v3(p, VB, I, n, n < p.D ? wd * (double)x : wd);
     return;
   }
@@ -454,7 +494,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
   const int n = group_lane();
   const bool real = act && I < p.P;   // uniform over the 16 lanes of a particle
   const bool comp = real && n < p.D;  // this lane owns a component
-  const int k = n / 3, al = n % 3, base = 3 * k;
+  const int k = n / 3, al = n % 3;
   const int64_t idx = ((int64_t)k * p.P + I) * 3 + al;
   double red[12];
 #pragma unroll
@@ -472,7 +512,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
   } else {
     const float qv = in.q;
     // the three components of this lane's bond
-    const float q0 = gshfl(qv, base), q1 = gshfl(qv, base + 1), q2 = gshfl(qv, base + 2);
+    const auto [q0, q1, q2] = row_bond(qv, al);
     const float r2 = q0 * q0 + q1 * q1 + q2 * q2;
     // this lane's spring constant and row of G, by selects of uniform values: an
     // index that differs per lane would read the kernel arguments as vector loads
@@ -494,7 +534,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
     const float gp = comp ? fac * qv : 0.f;
     const float g = comp ? p.kT * b + gp : 0.f;
     // (A (x) I) g with A = tridiag(-1, 2, -1) over bonds
-    const float gm = gshfl(g, n >= 3 ? n - 3 : n), gpl = gshfl(g, n + 3 < 16 ? n + 3 : n);
+    const float gm = row_move<0x113>(g), gpl = row_move<0x103>(g);
     float Ag = 2.f * g;
     if (k > 0) Ag -= gm;
     if (k + 1 < p.nb) Ag -= gpl;
@@ -502,7 +542,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
     float qstart = 0.f, flow0 = 0.f;
     if (mode == MODE_PICARD) {
       qstart = in.qs;
-      const float s0 = gshfl(qstart, base), s1 = gshfl(qstart, base + 1), s2 = gshfl(qstart, base + 2);
+      const auto [s0, s1, s2] = row_bond(qstart, al);
       flow0 = G0 * s0 + G1 * s1 + G2 * s2;
     }
     const float u = -p.inv_zeta * Ag;
@@ -529,7 +569,7 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
     }
     if (obs) {
       // stress column beta needs grad Psi of this bond's component beta
-      const float gp0 = gshfl(gp, base), gp1 = gshfl(gp, base + 1), gp2 = gshfl(gp, base + 2);
+      const auto [gp0, gp1, gp2] = row_bond(gp, al);
       if (comp) {
         const double wi = (double)in.w;
         red[RED_DISS] = wi * (double)g * (double)Ag * (double)p.inv_zeta;
@@ -550,10 +590,8 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
     // block maxima of |dx| and |x| into per-block slots; the check kernel
     // takes the max over blocks (no contended atomics)
     __shared__ float smax[2][kRedBlock / 64];
-    for (int off = 32; off > 0; off >>= 1) {
-      resid = fmaxf(resid, __shfl_xor(resid, off));
-      xmax = fmaxf(xmax, __shfl_xor(xmax, off));
-    }
+    resid = wave_max(resid);
+    xmax = wave_max(xmax);
     if (act && (threadIdx.x & 63) == 0) {
       smax[0][threadIdx.x >> 6] = resid;
       smax[1][threadIdx.x >> 6] = xmax;
@@ -950,7 +988,7 @@ __device__ double rows_pass(const uint4 *__restrict__ K3, const uint4 *__restric
   if (threadIdx.x < kRedBlock) {
     const int r = threadIdx.x >> 4, n = threadIdx.x & 15;
     for (int w = 0; w < kRowsWaves; ++w) o += lds.red[w][r][n];
-    const double s = gshfl(o, D);
+    const double s = row_move<0x150 + D>(o);
     if (n < D) o = (double)x * s - o;
   }
   return o;
