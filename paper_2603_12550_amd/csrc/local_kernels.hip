@@ -9,25 +9,41 @@
 
 namespace vds {
 
+// Lane movements inside a row of 16 as data-parallel-primitive controls: a few
+// cycles each, where a shuffle goes through the LDS crossbar and back (some hundred
+// in a chain).  0x100 + i: from lane n + i, 0x110 + i: from lane n - i (zeros from
+// outside the row), 0x120 + i: rotated, 0x150 + i: lane i to all.
+template <int kCtrl>
+__device__ __forceinline__ float row_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+template <int kCtrl>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
 // Fixed-order tree sum over the first 256 threads of a block for NS values each
 // (every thread of the block calls it).
 template <int NS>
-__device__ void block_sum(double (&v)[NS], double (*sm)[kRedBlock]) {
+__device__ void block_sum(double (&v)[NS], double (*sm)[kRedBlock / 64]) {
   const int t = threadIdx.x;
   if (t < kRedBlock) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) sm[s][t] = v[s];
+    for (int s = 0; s < NS; ++s) {
+      double x = v[s];
+      x += row_move<0x128>(x);
+      x += row_move<0x124>(x);
+      x += row_move<0x122>(x);
+      x += row_move<0x121>(x);
+      x += __shfl_xor(x, 16);
+      x += __shfl_xor(x, 32);
+      if ((t & 63) == 0) sm[s][t >> 6] = x;
+    }
   }
   __syncthreads();
-  for (int stride = kRedBlock / 2; stride > 0; stride >>= 1) {
-    if (t < stride) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) sm[s][t] += sm[s][t + stride];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int s = 0; s < NS; ++s) v[s] = sm[s][0];
+  for (int s = 0; s < NS; ++s) v[s] = (sm[s][0] + sm[s][1]) + (sm[s][2] + sm[s][3]);
 }
 
 // The dimension known at compile time, so that the per-particle bodies' index
@@ -109,31 +125,32 @@ __device__ inline void store_v3(const EvalParams &p, float *V, int64_t J, int n,
   V3[v3_index(J, 2 * (p.D + 1) + n, NT)] = s.l;
 }
 
-// Partial sums of w_I x_I (FP64) per block, for the weighted centring.
+// Partial sums of w_I x_I (FP64) per block of 256 particles, for the weighted
+// centring, and in slot 15 the block's largest weight: lane n of group r of 16
+// takes component n of particles r, r + 16, ... (all loads in flight), then the
+// sixteen groups in order.
 // Bodies take the block index `lb` within the problem (one ensemble) so that
 // the batched step can run them per ensemble.
 __device__ void mean_partials_body(const EvalParams &p, int64_t lb, const float *__restrict__ q,
                                    const float *__restrict__ w, double *__restrict__ meanp) {
-  __shared__ double sm[kMaxD][kRedBlock];
-  const int64_t I = lb * kRedBlock + threadIdx.x;
-  double v[kMaxD];
-  const double wi = I < p.P ? (double)load_weight(w, I, p.uniform_w) : 0.0;
+  __shared__ double part[16][17];
+  const int r = threadIdx.x >> 4, n = threadIdx.x & 15;
+  double v = 0.0;
+  float m = 0.f;
 #pragma unroll
-  for (int a = 0; a < kMaxD; ++a) {
-    const int k = a / 3, al = a % 3;
-    v[a] = (I < p.P && a < p.D) ? wi * (double)q[((int64_t)k * p.P + I) * 3 + al] : 0.0;
+  for (int i = 0; i < kRedBlock / 16; ++i) {
+    const int64_t I = lb * kRedBlock + 16 * i + r;
+    const float wi = I < p.P ? load_weight(w, I, p.uniform_w) : 0.f;
+    const float x = I < p.P && n < p.D ? q[((int64_t)(n / 3) * p.P + I) * 3 + n % 3] : 0.f;
+    v += (double)wi * (double)x;
+    m = fmaxf(m, wi);
   }
-  block_sum<kMaxD>(v, sm);
-  if (threadIdx.x < kMaxD) meanp[lb * 16 + threadIdx.x] = v[threadIdx.x];
-  // slot 15: the block's largest weight
-  __shared__ float wm[kRedBlock / 64];
-  float m = I < p.P ? load_weight(w, I, p.uniform_w) : 0.f;
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  part[r][n] = n == 15 ? (double)m : v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < kRedBlock / 64; ++i) m = fmaxf(m, wm[i]);
-    meanp[lb * 16 + 15] = (double)m;
+  if (threadIdx.x < 16) {
+    double o = part[0][n];
+    for (int i = 1; i < 16; ++i) o = n == 15 ? fmax(o, part[i][n]) : o + part[i][n];
+    meanp[lb * 16 + n] = o;
   }
 }
 
@@ -183,20 +200,6 @@ __device__ void load_mean(const EvalParams &p, const double *meanp, int nmeanp, 
 __device__ inline int64_t group_particle(int64_t lb) { return (lb * kRedBlock + threadIdx.x) >> 4; }
 __device__ inline int group_lane() { return threadIdx.x & 15; }
 __device__ inline float gshfl(float v, int n) { return __shfl(v, n, 16); }
-// Lane movements inside a row of 16 as data-parallel-primitive controls: a few
-// cycles each, where a shuffle goes through the LDS crossbar and back (some hundred
-// in a chain).  0x100 + i: from lane n + i, 0x110 + i: from lane n - i (zeros from
-// outside the row), 0x120 + i: rotated, 0x150 + i: lane i to all.
-template <int kCtrl>
-__device__ __forceinline__ float row_move(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kCtrl, 0xf, 0xf, true));
-}
-template <int kCtrl>
-__device__ __forceinline__ double row_move(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
 // Lane D of the row to all its lanes.
 __device__ __forceinline__ double row_lane_d(int D, double v) {
   switch (D) {
@@ -355,21 +358,28 @@ __device__ void prep_write(const EvalParams &p, int64_t I, int n, float x, float
   store_v(p, VA, I, n, v);
 }
 
+// kGroups groups of 16 particles per block.
+template <int kGroups>
 __device__ void prep_body(const EvalParams &p, int64_t lb, const float *__restrict__ q, const float *__restrict__ w,
                           const double *__restrict__ meanp, int nmeanp, float *__restrict__ xc,
                           float *__restrict__ wv, float *__restrict__ QB, float *__restrict__ KA,
                           float *__restrict__ VA, float *__restrict__ wscale, F16Operands f16,
                           float *__restrict__ cmean = nullptr) {
   __shared__ float mean_sh[16];
+  const int n = group_lane();
+  float x[kGroups];
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) x[g] = prep_coord(p, q, group_particle(lb * kGroups + g), n);
   load_mean(p, meanp, nmeanp, mean_sh);
   if (p.vhalf && wscale != nullptr && lb == 0 && threadIdx.x == 0) *wscale = mean_sh[15];
   if (cmean != nullptr && lb == 0 && threadIdx.x < 16) cmean[threadIdx.x] = mean_sh[threadIdx.x];
-  const int64_t I = group_particle(lb);
-  const int n = group_lane();
-  if (I >= p.Ppad) return;
-  const float x = I < p.P && n < p.D ? prep_coord(p, q, I, n) - mean_sh[n] : 0.f;
-  const float wi = I < p.P ? load_weight(w, I, p.uniform_w) : 0.f;
-  prep_write(p, I, n, x, wi, mean_sh, xc, wv, QB, KA, VA, f16);
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const int64_t I = group_particle(lb * kGroups + g);
+    if (I >= p.Ppad) return;
+    const float wi = I < p.P ? load_weight(w, I, p.uniform_w) : 0.f;
+    prep_write(p, I, n, I < p.P && n < p.D ? x[g] - mean_sh[n] : 0.f, wi, mean_sh, xc, wv, QB, KA, VA, f16);
+  }
 }
 
 template <int D>
@@ -393,7 +403,7 @@ __global__ __launch_bounds__(kRedBlock) void k_prep(EvalParams p, const float *_
     return;
   }
   assume_dimension<D>(p);
-  prep_body(p, blockIdx.x, q, w, meanp, nmeanp, xc, wv, QB, KA, VA, wscale, f16, cmean);
+  prep_body<1>(p, blockIdx.x, q, w, meanp, nmeanp, xc, wv, QB, KA, VA, wscale, f16, cmean);
 }
 
 // Component n of row I summed over its partial-sum slots in slot order, in FP64.
@@ -410,28 +420,21 @@ __device__ inline double sum_splits(const EvalParams &p, const float *__restrict
 // ahead of the sums.
 __device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, float x, float w,
                                float *__restrict__ S, float *__restrict__ t1, float *__restrict__ VB) {
-  if (I >= p.P) {  // padding columns carry zero weight in pass B too
-    if (p.bf3) store_v3(p, VB, I, n, 0.0);
-    else store_v(p, VB, I, n, 0.f);
-    return;
-  }
+  const bool real = I < p.P;  // padding columns carry zero weight in pass B too
   const double wI = (double)w;
   const double Si = row_lane_d(p.D, o) + wI;  // the pass left out the self term w_I e_II = w_I
-  const double rS = 1.0 / Si, wd = wI * rS;
+  const double rS = 1.0 / Si, wd = real ? wI * rS : 0.0;
   const float wb = (float)wd;
   float v = 0.f;
   if (n < p.D) {
-    t1[I * p.D + n] = (float)(-(double)p.inv_h2 * o * rS);
+    if (real) t1[I * p.D + n] = (float)(-(double)p.inv_h2 * o * rS);
     v = wb * x;
   } else if (n == p.D) {
-    S[I] = (float)Si;
+    if (real) S[I] = (float)Si;
     v = wb;
   }
-  if (p.bf3) {
-    store_v3(p, VB, I, n, n < p.D ? wd * (double)x : wd);
-    return;
-  }
-  store_v(p, VB, I, n, v);  // wb <= 1, so the FP16 form needs no normalisation
+  if (p.bf3) store_v3(p, VB, I, n, !real ? 0.0 : n < p.D ? wd * (double)x : wd);
+  else store_v(p, VB, I, n, real ? v : 0.f);  // wb <= 1, so the FP16 form needs no normalisation
 }
 
 __device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__restrict__ partial, const SplitMap &splits,
@@ -489,7 +492,7 @@ __device__ inline CombineIn combine_load(const EvalParams &p, int64_t lb, int mo
 __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs, bool act, double o,
                              const CombineIn &in, float *out, float *out2, double *__restrict__ redp,
                              float *__restrict__ blockmax, const PackOps &pack, int *fene_out) {
-  __shared__ double sm[12][kRedBlock];
+  __shared__ double sm[12][kRedBlock / 64];
   const int64_t I = group_particle(lb);
   const int n = group_lane();
   const bool real = act && I < p.P;   // uniform over the 16 lanes of a particle
@@ -756,8 +759,11 @@ __global__ __launch_bounds__(kRedBlock) void k_step_end(EvalParams p, Ctrl *ctrl
     }
   }
   // the next step's centring partials from the new state, as k_mean_partials
-  // computes them (each thread reads back what it wrote)
-  if (meanp != nullptr) mean_partials_body(p, blockIdx.x, q, w, meanp);
+  // computes them (of the block's own particles, written above)
+  if (meanp != nullptr) {
+    __syncthreads();
+    mean_partials_body(p, blockIdx.x, q, w, meanp);
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctrl->steps_done += 1;
     ctrl->last_iters = it + 1;
@@ -767,7 +773,7 @@ __global__ __launch_bounds__(kRedBlock) void k_step_end(EvalParams p, Ctrl *ctrl
 
 __device__ void stress_body(const EvalParams &p, int64_t lb, const float *__restrict__ q, const float *__restrict__ w,
                             double *__restrict__ redp) {
-  __shared__ double sm[9][kRedBlock];
+  __shared__ double sm[9][kRedBlock / 64];
   const int64_t I = lb * kRedBlock + threadIdx.x;
   double t[9];
 #pragma unroll
@@ -856,27 +862,36 @@ __device__ inline F16Operands batch_f16(const BatchView &b, const EnsDesc &d) {
                      b.f16.RN + d.pad_off};
 }
 
+// Four groups of 16 particles per block (an ensemble is padded to 256): every block
+// sums its ensemble's centring partials.  Bound: the operands' FP64 splits.  Measured over
+// 269000 particles, D = 9: 54 us, 70 with one group (and D not known at compile time).
+constexpr int kBatchGroups = 4;
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_batch_prep(BatchView b, const float *__restrict__ q,
                                                           const double *__restrict__ meanp, float *__restrict__ xc,
                                                           float *__restrict__ wv, float *__restrict__ QB,
                                                           float *__restrict__ KA, float *__restrict__ VA) {
-  const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
+  const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x * kBatchGroups]];
   const int64_t o = d.pad_off;
-  prep_body(d.p, blockIdx.x - d.blk16, q + d.q_off, nullptr, meanp + (int64_t)d.blk256 * 16,
-            (int)(d.p.Ppad / kRedBlock), xc + o * b.D, wv + o, QB + o * b.KK * 4, KA + o * b.KK * 4, VA + o * b.vw,
-            nullptr, batch_f16(b, d));
+  assume_dimension<D>(d.p);
+  prep_body<kBatchGroups>(d.p, blockIdx.x - d.blk16 / kBatchGroups, q + d.q_off, nullptr,
+                          meanp + (int64_t)d.blk256 * 16, (int)(d.p.Ppad / kRedBlock), xc + o * b.D, wv + o,
+                          QB + o * b.KK * 4, KA + o * b.KK * 4, VA + o * b.vw, nullptr, batch_f16(b, d));
 }
 
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_batch_finalize_a(BatchView b, const float *__restrict__ partial,
                                                                 const float *__restrict__ xc,
                                                                 const float *__restrict__ wv, float *__restrict__ S,
                                                                 float *__restrict__ t1, float *__restrict__ VB) {
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
+  assume_dimension<D>(d.p);
   finalize_a_body(d.p, blockIdx.x - d.blk16, partial + o * 16, SplitMap{}, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
                   VB + o * b.vw);
 }
 
+template <int D>
 __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const float *__restrict__ partial,
                                                               const float *__restrict__ xc,
                                                               const float *__restrict__ t1,
@@ -884,6 +899,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const
                                                               const float *__restrict__ wv, float *q) {
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
+  assume_dimension<D>(d.p);
   combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + o * 16, SplitMap{}, t1 + o * b.D, S + o,
                wv + o, q + d.q_off, nullptr, q + d.q_off, nullptr, nullptr, nullptr, PackOps{}, nullptr);
 }
@@ -1331,15 +1347,22 @@ void launch_batch_mean(const BatchView &b, const float *q, double *meanp, hipStr
 }
 void launch_batch_prep(const BatchView &b, const float *q, const double *meanp, float *xc, float *wv, float *QB,
                        float *KA, float *VA, hipStream_t s) {
-  k_batch_prep<<<b.nblk16, kRedBlock, 0, s>>>(b, q, meanp, xc, wv, QB, KA, VA);
+  by_dimension(b.D, [&](auto d) {
+    k_batch_prep<decltype(d)::value>
+        <<<b.nblk16 / kBatchGroups, kRedBlock, 0, s>>>(b, q, meanp, xc, wv, QB, KA, VA);
+  });
 }
 void launch_batch_finalize_a(const BatchView &b, const float *partial, const float *xc, const float *wv, float *S,
                              float *t1, float *VB, hipStream_t s) {
-  k_batch_finalize_a<<<b.nblk16, kRedBlock, 0, s>>>(b, partial, xc, wv, S, t1, VB);
+  by_dimension(b.D, [&](auto d) {
+    k_batch_finalize_a<decltype(d)::value><<<b.nblk16, kRedBlock, 0, s>>>(b, partial, xc, wv, S, t1, VB);
+  });
 }
 void launch_batch_explicit(const BatchView &b, const float *partial, const float *xc, const float *t1,
                            const float *S, const float *wv, float *q, hipStream_t s) {
-  k_batch_explicit<<<b.nblk16, kRedBlock, 0, s>>>(b, partial, xc, t1, S, wv, q);
+  by_dimension(b.D, [&](auto d) {
+    k_batch_explicit<decltype(d)::value><<<b.nblk16, kRedBlock, 0, s>>>(b, partial, xc, t1, S, wv, q);
+  });
 }
 void launch_batch_stress(const BatchView &b, const float *q, double *redp, hipStream_t s) {
   k_batch_stress<<<b.nblk256, kRedBlock, 0, s>>>(b, q, redp);
