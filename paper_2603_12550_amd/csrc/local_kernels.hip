@@ -135,15 +135,23 @@ __device__ void mean_partials_body(const EvalParams &p, int64_t lb, const float 
                                    const float *__restrict__ w, double *__restrict__ meanp) {
   __shared__ double part[16][17];
   const int r = threadIdx.x >> 4, n = threadIdx.x & 15;
+  constexpr int N = kRedBlock / 16;
+  // (past the particles or the components: the last one's values, not counted)
+  const float *src = q + (int64_t)(min(n, p.D - 1) / 3) * p.P * 3 + min(n, p.D - 1) % 3;
+  float x[N], wi[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int64_t I = min(lb * kRedBlock + 16 * i + r, p.P - 1);
+    x[i] = src[3 * I];
+    wi[i] = load_weight(w, I, p.uniform_w);
+  }
   double v = 0.0;
   float m = 0.f;
 #pragma unroll
-  for (int i = 0; i < kRedBlock / 16; ++i) {
-    const int64_t I = lb * kRedBlock + 16 * i + r;
-    const float wi = I < p.P ? load_weight(w, I, p.uniform_w) : 0.f;
-    const float x = I < p.P && n < p.D ? q[((int64_t)(n / 3) * p.P + I) * 3 + n % 3] : 0.f;
-    v += (double)wi * (double)x;
-    m = fmaxf(m, wi);
+  for (int i = 0; i < N; ++i) {
+    const bool real = lb * kRedBlock + 16 * i + r < p.P;
+    v += real && n < p.D ? (double)wi[i] * (double)x[i] : 0.0;
+    m = fmaxf(m, real ? wi[i] : 0.f);
   }
   part[r][n] = n == 15 ? (double)m : v;
   __syncthreads();

@@ -139,7 +139,7 @@ RomLayout rom_layout(const vds_problem &p, int R) {
 // as the partial-sum buffer holds for both.
 int rom_splits(const RomLayout &L, int R, int64_t P) {
   const int64_t t = (R + kGemmTile - 1) / kGemmTile, rounds = (P + kGemmSlab - 1) / kGemmSlab * 3;
-  int64_t s = std::min<int64_t>({512 / (t * t), rounds / 4, L.part_floats / (2 * (int64_t)R * R)});
+  int64_t s = std::min<int64_t>({512 / (t * t), rounds / 2, L.part_floats / (2 * (int64_t)R * R)});
   if (s >= 8) s -= s % 8;
   return (int)std::max<int64_t>(s, 1);
 }
@@ -1105,6 +1105,7 @@ __global__ __launch_bounds__(1024) void k_rom_stress(const float *__restrict__ M
   const float *M = Mbig + (int64_t)a * R * ld + (int64_t)b * R;
   double acc = 0.0;
   for (int u = lane; u < R; u += 64)
+#pragma unroll 4
     for (int s = wave; s < R; s += 16) {
       const double m = M[s * ld + u];
       double pp = 0.0;
