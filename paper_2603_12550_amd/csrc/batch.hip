@@ -49,7 +49,7 @@ struct vds_batch_s {
   float *QB, *KA, *VA, *VB, *xc, *t1, *S, *wv, *part;
   F16Operands f16{};
   double *meanp, *redp, *tau;
-  double *host_tau = nullptr;  // pinned (see vds::pinned_slot), 9 per ensemble
+  HostSlot host;  // stresses, 9 per ensemble
 };
 
 namespace {
@@ -344,7 +344,6 @@ void vds_batch_destroy(vds_batch b) {
   if (b->ev_in) (void)hipEventDestroy(b->ev_in);
   if (b->ev_out) (void)hipEventDestroy(b->ev_out);
   if (b->priv) (void)hipStreamDestroy(b->priv);
-  if (b->host_tau) (void)hipHostFree(b->host_tau);
   delete b;
 }
 
@@ -451,7 +450,7 @@ vds_status vds_batch_step(vds_batch b, float *q, int32_t nsteps, double *tau_hos
   }
   if (st != VDS_OK) return st;
   const size_t tau_bytes = sizeof(double) * 9 * b->nens;
-  double *host = tau_host ? pinned_slot(b->host_tau, tau_bytes) : nullptr;
+  double *host = tau_host ? static_cast<double *>(b->host.take(tau_bytes)) : nullptr;
   if (tau_host) {
     launch_batch_stress(view(b), q, b->redp, b->priv);
     launch_batch_stress_sum(b->d_ens, b->nens, b->redp, host ? host : b->tau, b->priv);
@@ -460,7 +459,10 @@ vds_status vds_batch_step(vds_batch b, float *q, int32_t nsteps, double *tau_hos
   if (st == VDS_OK) st = bhip(b, hipEventRecord(b->ev_out, b->priv), "event");
   if (st == VDS_OK) st = bhip(b, hipStreamWaitEvent(b->user, b->ev_out, 0), "wait");
   if (st == VDS_OK && tau_host) st = bhip(b, hipStreamSynchronize(b->priv), "synchronise");
-  if (st == VDS_OK && host != nullptr) std::memcpy(tau_host, host, tau_bytes);
+  if (st == VDS_OK && host != nullptr) {
+    std::memcpy(tau_host, host, tau_bytes);
+    b->host.read();
+  }
   return st;
 }
 

@@ -715,7 +715,7 @@ struct vds_mlp_s {
   short *wbf, *wpk;
   double *lossp;
   double *loss_out;  // one slot after the per-tile partials
-  double *host_loss = nullptr;  // pinned (see vds::pinned_slot)
+  HostSlot host;  // a loss
   int t = 0;
   bool bf_stale = true;
   float noise = 0.f;          // training input noise (vds_mlp_set_input_noise)
@@ -959,10 +959,7 @@ vds_status vds_mlp_bind_workspace(vds_mlp m, void *ws, size_t bytes) {
   return st;
 }
 
-void vds_mlp_destroy(vds_mlp m) {
-  if (m != nullptr && m->host_loss != nullptr) (void)hipHostFree(m->host_loss);
-  delete m;
-}
+void vds_mlp_destroy(vds_mlp m) { delete m; }
 const char *vds_mlp_last_error(vds_mlp m) { return m ? m->err.c_str() : g_mlp_create_error.c_str(); }
 int64_t vds_mlp_param_count(vds_mlp m) { return m ? m->np : -1; }
 
@@ -1024,14 +1021,17 @@ vds_status vds_mlp_loss_grad(vds_mlp m, const float *X, const float *T, int32_t 
   if (!m || !X || !T) return VDS_ERR_ARG;
   if (!m->ws) return merr(m, VDS_ERR_STATE, "no workspace bound");
   if (n < 1 || n > m->B) return merr(m, VDS_ERR_ARG, "batch size out of range");
-  double *host = loss != nullptr ? pinned_slot(m->host_loss, sizeof(double)) : nullptr;
+  double *host = loss != nullptr ? static_cast<double *>(m->host.take(sizeof(double))) : nullptr;
   loss_grad_fp32(m, X, T, n, host != nullptr ? host : m->loss_out, false);
   vds_status st = mhip(m, hipGetLastError(), "loss_grad");
   if (st != VDS_OK || loss == nullptr) return st;
   if (host == nullptr)
     st = mhip(m, hipMemcpyAsync(loss, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy loss");
   if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
-  if (st == VDS_OK && host != nullptr) *loss = *host;
+  if (st == VDS_OK && host != nullptr) {
+    *loss = *host;
+    m->host.read();
+  }
   return st;
 }
 

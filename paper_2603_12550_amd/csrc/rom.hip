@@ -1138,12 +1138,12 @@ struct vds_rom_s {
   bool b3_ready = false;  // Bsw holds the basis as the default kernel-GEMM reads it
   float *Ude, *Mbig, *XH, *I1, *XB1, *XB2, *XB, *Bsw, *Y, *qt, *T, *invS, *part, *psave, *pprev;
   double *red;
-  double *host_tau = nullptr;  // pinned (see vds::pinned_slot): kHostTau stresses
+  HostSlot host;  // kHostTau stresses
 };
 
 namespace {
 
-constexpr int kHostTau = 64;
+constexpr int kHostTau = 56;  // 72 bytes each in one block
 
 vds_status rom_gemm(vds_rom r, GemmShape g, double flops) {
   timed(r->ctx, VDS_TIMER_GEMM, flops, [&] { launch_gemm(g, r->part, r->ctx->stream); });
@@ -1159,7 +1159,7 @@ struct StressOut {
   int queued = 0;
   vds_status add(const float *p) {
     vds_ctx c = r->ctx;
-    double *host = pinned_slot(r->host_tau, sizeof(double) * 9 * kHostTau);
+    double *host = static_cast<double *>(r->host.take(sizeof(double) * 9 * kHostTau));
     k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, host ? host + 9 * queued : r->red);
     if (host != nullptr) return ++queued == kHostTau ? finish() : VDS_OK;
     vds_status st = hip_check(c, hipMemcpyAsync(tau, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream),
@@ -1170,7 +1170,8 @@ struct StressOut {
   vds_status finish() {  // synchronises
     vds_status st = hip_check(r->ctx, hipStreamSynchronize(r->ctx->stream), "synchronise");
     if (st != VDS_OK) return st;
-    if (queued > 0) std::memcpy(tau, r->host_tau, sizeof(double) * 9 * queued);
+    if (queued > 0) std::memcpy(tau, r->host.p, sizeof(double) * 9 * queued);
+    r->host.read();
     tau += 9 * queued;
     queued = 0;
     return VDS_OK;
@@ -1440,10 +1441,7 @@ vds_status vds_rom_create(vds_ctx c, const float *U, int32_t R, void *ws, size_t
   return VDS_OK;
 }
 
-void vds_rom_destroy(vds_rom r) {
-  if (r != nullptr && r->host_tau != nullptr) (void)hipHostFree(r->host_tau);
-  delete r;
-}
+void vds_rom_destroy(vds_rom r) { delete r; }
 
 vds_status vds_rom_operators(vds_rom r, const float *p, float *XH, float *XB1, float *XB2) {
   if (r == nullptr) return VDS_ERR_ARG;

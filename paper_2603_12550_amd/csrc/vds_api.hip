@@ -30,6 +30,46 @@ char *g_scratch_dev[kMaxDevices] = {};  // address of `scratch` on each device, 
 
 namespace vds {
 
+namespace {
+constexpr size_t kHostBlock = 4096;
+constexpr int kHostIdle = 8;
+std::mutex g_host_mu;
+void *g_host_idle[kHostIdle];
+int g_host_nidle = 0;
+}  // namespace
+
+void *HostSlot::take(size_t n) {
+  if (p == nullptr) {
+    bytes = n <= kHostBlock ? kHostBlock : n;
+    if (bytes == kHostBlock) {
+      std::lock_guard<std::mutex> lock(g_host_mu);
+      if (g_host_nidle > 0) p = g_host_idle[--g_host_nidle];
+    }
+    if (p == nullptr && hipHostMalloc(&p, bytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  if (p != nullptr) in_flight = true;
+  return p;
+}
+
+HostSlot::~HostSlot() {
+  if (p == nullptr) return;
+  if (bytes == kHostBlock && !in_flight) {
+    std::lock_guard<std::mutex> lock(g_host_mu);
+    if (g_host_nidle < kHostIdle) {
+      g_host_idle[g_host_nidle++] = p;
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
+}  // namespace vds
+
+namespace vds {
+
 vds_status set_err(vds_ctx c, vds_status st, const std::string &m) {
   if (c) c->err = m;
   return st;
@@ -276,14 +316,14 @@ void drain_timers(vds_ctx c) {
 // Sums the first nslots slots of the block partials for read_back, with the
 // control block.
 void reduce_out(vds_ctx c, int nblk, int nslots) {
-  HostOut *h = pinned_slot(c->host, sizeof(HostOut));
+  HostOut *h = static_cast<HostOut *>(c->host.take(sizeof(HostOut)));
   launch_reduce_final(c->redp, nblk, nslots, h ? h->red : c->redout, c->stream, c->ctrl, h ? &h->ctrl : nullptr);
 }
 
 // What the last reduce_out left (synchronises).
 vds_status read_back(vds_ctx c, HostOut &out) {
   vds_status st = VDS_OK;
-  if (c->host == nullptr) {
+  if (c->host.p == nullptr) {
     st = hip_check(c, hipMemcpyAsync(out.red, c->redout, sizeof(out.red), hipMemcpyDeviceToHost, c->stream),
                    "copy sums");
     if (st == VDS_OK)
@@ -291,8 +331,10 @@ vds_status read_back(vds_ctx c, HostOut &out) {
                      "copy ctrl");
   }
   if (st == VDS_OK) st = hip_check(c, hipStreamSynchronize(c->stream), "synchronise");
-  if (st == VDS_OK && c->host != nullptr) out = *c->host;
-  return st;
+  if (st != VDS_OK) return st;
+  if (c->host.p != nullptr) out = *static_cast<const HostOut *>(c->host.p);
+  c->host.read();
+  return VDS_OK;
 }
 
 // Prep + pass A + finalize A + pass B + combine(mode).  Without `centre` the
@@ -378,7 +420,6 @@ void vds_destroy(vds_ctx c) {
     }
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   if (c->blas != nullptr) rocblas_destroy_handle(static_cast<rocblas_handle>(c->blas));
-  if (c->host != nullptr) (void)hipHostFree(c->host);
   delete c;
 }
 

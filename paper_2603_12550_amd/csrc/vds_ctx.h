@@ -47,7 +47,7 @@ struct vds_ctx_s {
   unsigned long long *hist;  // median-bandwidth histograms [2][kHistBins]
   double *meanp, *redp, *redout;
   vds::Ctrl *ctrl;
-  vds::HostOut *host = nullptr;  // pinned (see vds::pinned_slot)
+  vds::HostSlot host;  // a HostOut
   int nblk;       // blocks of the one-thread-per-particle kernels
   int nblk_comb;  // blocks of the sixteen-lanes-per-particle combine kernel
   void *blas = nullptr;  // rocblas_handle of the FP64 eigensolve and exact windows, made on first use

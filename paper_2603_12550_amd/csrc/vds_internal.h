@@ -37,28 +37,31 @@ struct Ctrl {
   int fene_out;           // a combine kernel saw a FENE bond with |q|^2 >= b_max (or not finite)
 };
 
-// What a call reads back: kernels write it straight into pinned host memory (see
-// pinned_slot), which the host reads after synchronising the stream.
+// What a call reads back: kernels write it straight into pinned host memory,
+// which the host reads after synchronising the stream.
 struct HostOut {
   double red[16];
   Ctrl ctrl;
 };
 
-// An object's pinned host memory, made on the first call that reads back (such a
-// call synchronises, so it is never part of a capture) and freed with the
-// object; null if there is none.  A result written there by the last kernel and
-// read after the synchronisation takes 11 us from launch to host, a copy to
-// pageable memory 23.
-template <class T>
-T *pinned_slot(T *&slot, size_t bytes) {
-  if (slot == nullptr &&
-      hipHostMalloc(reinterpret_cast<void **>(&slot), bytes, hipHostMallocPortable | hipHostMallocCoherent) !=
-          hipSuccess) {
-    slot = nullptr;
-    (void)hipGetLastError();
-  }
-  return slot;
-}
+// An object's pinned host memory, taken on the first call that reads back (such a
+// call synchronises, so it is never part of a capture) and given back with the
+// object.  A result written there by the last kernel and read after the
+// synchronisation takes 11 us from launch to host, a copy to pageable memory 23.
+// Blocks of up to 4 KB come from a list of at most eight idle ones shared by all
+// objects and threads (making and freeing one costs 25 to 150 us); memory that a
+// kernel may still be writing to when its object goes is freed, which waits.
+struct HostSlot {
+  void *p = nullptr;
+  size_t bytes = 0;
+  bool in_flight = false;  // handed to a kernel, not yet read
+  // At least n bytes for a kernel to write (n the same on every call); null if there are none.
+  void *take(size_t n);
+  void read() { in_flight = false; }  // the stream has been synchronised
+  HostSlot() = default;
+  HostSlot(const HostSlot &) = delete;
+  ~HostSlot();
+};
 
 // Convergence test of one fixed-point iteration, taken from the combine
 // kernel's block maxima by the next kernel in stream order.
