@@ -5,8 +5,8 @@ Hookean chain under shear (P = 20000 particles, D = 9, h = 0.4, dt = 1e-3):
 centring and operand packing, the two O(P^2) kernel passes per fixed-point
 iteration, drift, update and convergence test, and the FP64 stress.  The
 headline value is pair-evaluations per second over the timed steps (one
-pair-evaluation is one ordered (I, J) in one pass), computed in FP32 on the
-FP32 matrix cores.
+pair-evaluation is one ordered (I, J) in one pass), computed with 24-bit
+factors of FP32 range (three BF16 parts each) on the BF16 matrix cores.
 
 Output: one JSON line per extra measurement and one for the FP16-split pair
 form (a separate, labelled arithmetic), then the headline as the LAST line

@@ -6,7 +6,7 @@
  *
  * Conventions of vds.h apply.  Each step is the explicit Euler step of the
  * particle scheme (Appendix A; the scheme of the paper's experiments) applied
- * to every ensemble; a step is five launches captured once into a hipGraph and
+ * to every ensemble; a step is six launches captured once into a hipGraph and
  * replayed, and each kernel pass covers all ensembles (the pair pass is one
  * persistent launch over a work list of (ensemble, row tile) items sorted by
  * decreasing cost).  Weights are uniform within each ensemble.

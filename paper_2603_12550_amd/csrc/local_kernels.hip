@@ -946,8 +946,8 @@ __global__ __launch_bounds__(576) void k_batch_stress_sum(const EnsDesc *__restr
 // Bound: latency (launch, row operand, first chunk, sums).  Above about 2000
 // particles every workgroup's reading of all columns through L2 (P^2 / 16 x 6 KB
 // per 32 columns) outweighs the launch it saves.  Measured per explicit step of
-// the 4-bead chain at P = 1000: 36 us in four launches, 15 in two; five implicit
-// steps of the dumbbell at P = 2000: 0.71 against 0.37 ms.
+// the 4-bead chain at P = 1000: 36 us in four launches, 12.4 in two; five implicit
+// steps of the dumbbell at P = 2000: 0.71 against 0.30 ms.
 
 constexpr int kRowsWaves = 16;
 

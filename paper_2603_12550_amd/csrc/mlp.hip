@@ -1,5 +1,5 @@
 // Learned reduced step (C ABI of include/vds_mlp.h): MLP training kernels
-// (FP32 MFMA GEMMs, SiLU, MSE gradient, Adam), BF16 MFMA inference, and the
+// (FP32 MFMA products with SiLU and MSE epilogues, Adam), BF16 MFMA inference, and the
 // rollout that checks the network against the particle scheme and falls back.
 #include <algorithm>
 #include <cmath>

@@ -1,6 +1,6 @@
 // POD offline phase and POD maps (C ABI of include/vds_pod.h).
 //
-// Gram matrix X^T X by the FP32 MFMA GEMM, symmetric eigensolve in FP64 by
+// Gram matrix X^T X by the three-part GEMM, symmetric eigensolve in FP64 by
 // rocSOLVER (dsyevd), U = X V_R L_R^{-1/2} by the GEMM, then Cholesky-QR
 // re-orthonormalisation (the FP32 Gram resolves eigenvalues only down to
 // ~1e-7 of the largest, so the trailing columns need it).  Projection and
