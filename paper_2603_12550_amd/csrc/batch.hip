@@ -454,7 +454,9 @@ vds_status vds_batch_step(vds_batch b, float *q, int32_t nsteps, double *tau_hos
   if (tau_host) {
     launch_batch_stress(view(b), q, b->redp, b->priv);
     launch_batch_stress_sum(b->d_ens, b->nens, b->redp, host ? host : b->tau, b->priv);
-    if (host == nullptr) st = bhip(b, hipMemcpyAsync(tau_host, b->tau, tau_bytes, hipMemcpyDeviceToHost, b->priv), "copy stress");
+    st = bhip(b, hipGetLastError(), "stress");
+    if (st == VDS_OK && host == nullptr)
+      st = bhip(b, hipMemcpyAsync(tau_host, b->tau, tau_bytes, hipMemcpyDeviceToHost, b->priv), "copy stress");
   }
   if (st == VDS_OK) st = bhip(b, hipEventRecord(b->ev_out, b->priv), "event");
   if (st == VDS_OK) st = bhip(b, hipStreamWaitEvent(b->user, b->ev_out, 0), "wait");

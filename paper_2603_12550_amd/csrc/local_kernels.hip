@@ -1312,8 +1312,9 @@ void launch_density_out(const EvalParams &p, const float *partial, const SplitMa
 static int density_row_blocks(int64_t ny) {
   int best = 1;
   int64_t cost = INT64_MAX;
+  const int64_t cu = device_cu_count();
   for (int rb = 1; rb <= 5; ++rb) {
-    const int64_t wgs = (ny + 16 * rb - 1) / (16 * rb), cu = device_cu_count();
+    const int64_t wgs = (ny + 16 * rb - 1) / (16 * rb);
     const int64_t t = (wgs + cu - 1) / cu * (rb + 1);
     if (t < cost) best = rb, cost = t;
   }

@@ -1161,7 +1161,10 @@ struct StressOut {
     vds_ctx c = r->ctx;
     double *host = static_cast<double *>(r->host.take(sizeof(double) * 9 * kHostTau));
     k_rom_stress<<<9, 1024, 0, c->stream>>>(r->Mbig, p, c->prob.nb, r->R, c->ep, host ? host + 9 * queued : r->red);
-    if (host != nullptr) return ++queued == kHostTau ? finish() : VDS_OK;
+    if (host != nullptr) {
+      vds_status st = hip_check(c, hipGetLastError(), "stress");
+      return st == VDS_OK && ++queued == kHostTau ? finish() : st;
+    }
     vds_status st = hip_check(c, hipMemcpyAsync(tau, r->red, sizeof(double) * 9, hipMemcpyDeviceToHost, c->stream),
                               "copy stress");
     tau += 9;
