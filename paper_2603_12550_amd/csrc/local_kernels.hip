@@ -943,11 +943,12 @@ __global__ __launch_bounds__(576) void k_batch_stress_sum(const EnsDesc *__restr
 // pass A with S, term1 and the pass-B operand, pass B with drift, update and the
 // next state's operands.  Those go to a second K3 buffer, since other
 // workgroups still read this one.
-// Bound: latency (launch, row operand, first chunk, sums).  Above about 2000
-// particles every workgroup's reading of all columns through L2 (P^2 / 16 x 6 KB
-// per 32 columns) outweighs the launch it saves.  Measured per explicit step of
-// the 4-bead chain at P = 1000: 36 us in four launches, 12.4 in two; five implicit
-// steps of the dumbbell at P = 2000: 0.71 against 0.30 ms.
+// Bound: latency (launch, row operand, first chunk, sums), and from some 3000
+// particles on every workgroup's reading of all columns through L2.  The line lies
+// where the workgroups fill the compute units once, 4096 particles: an explicit
+// step of the 4-bead chain takes 12.4 us in two launches (36 in four) at P = 1000,
+// 16.8 (42) at 2500, 23.6 (46) at 4000, but 46 (55) at 5000 and 51 (58) at 6000,
+// and with six beads 29 (41) at 4000 and 59 (50) at 5000.
 
 constexpr int kRowsWaves = 16;
 

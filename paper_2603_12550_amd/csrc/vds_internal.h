@@ -287,7 +287,7 @@ void launch_combine(const EvalParams &p, int mode, bool obs, const float *partia
 // launch.  launch_rows_a is pass A with launch_finalize_a, and with chk launch_picard_check
 // before it; launch_rows_b pass B with launch_combine (pack then names another K3 buffer than
 // K3), or with MODE_SUMS the reduced model's row scalars.
-constexpr int64_t kRowsMaxP = 2048;
+constexpr int64_t kRowsMaxP = 4096;
 void launch_rows_a(const EvalParams &p, const void *K3, const float *VA, const float *xc, const float *wv, float *S,
                    float *t1, float *VB, const int *done, const PicardCheck *chk, const float *blockmax, int nblk_chk,
                    hipStream_t s);

@@ -37,8 +37,8 @@ def _check_rows(b, b_o, S, S_o, label):
 
 
 # chunk (32 columns), stage (64), accumulation group (256) and row group (16; 128, 256) edges, on both sides of
-# the size (2048) up to which a pass and what follows it are one launch
-@pytest.mark.parametrize("P", [31, 32, 33, 65, 257, 513, 2047, 2048, 2049, 2305])
+# the size (4096) up to which a pass and what follows it are one launch
+@pytest.mark.parametrize("P", [31, 32, 33, 65, 257, 513, 2047, 2048, 2049, 2305, 4095, 4096, 4097, 4129, 4353, 4609])
 @pytest.mark.parametrize("nb,rb", [(1, 2), (2, 1), (2, 2), (3, 1), (3, 2), (4, 2), (5, 2)])
 def test_pair_sums_tile_edges(lib, P, nb, rb):
     q = wl.f32_as_f64(wl.to_f32(wl.gaussian_bonds(300 + P, nb, P, 0.5)))
