@@ -165,6 +165,66 @@ __global__ __launch_bounds__(256) void k_pod_project_sum(const float *__restrict
   if (lane == 0) p[e] = (float)v;
 }
 
+// The whole projection in one launch for few and short rows: a workgroup per row of
+// U, a thread takes every 1024th position, eight in flight; sums over rows of 16
+// lanes by DPP and over the block in FP64.
+// Bound: the launch, from some 50000 numbers per workgroup on its loads.  Measured
+// against the two launches, calls in a row / alone: P = 2000, R = 60, nb = 3: 8.2 /
+// 19.1 us, 11.1 / 21.3.
+//
+// The line: a workgroup reads (nb + 1) m numbers, which alone costs more than the
+// launch saved from about 90000 on (P = 6000: nb = 3 20.9 and 21.4 us, nb = 5 22.2
+// and 21.4), and more rows than compute units read q again where the groups of 8
+// rows read it once (nb = 3, P = 6000: R = 256 21.9 and 22.3, R = 300 24.1 and 22.6).
+constexpr int kProjOneThreads = 1024;
+constexpr int kProjOneAhead = 8;
+constexpr int kProjOneRows = 256;
+constexpr int64_t kProjOneReads = 9 * kProjOneAhead * kProjOneThreads;
+
+template <int NB>
+__global__ __launch_bounds__(kProjOneThreads) void k_pod_project_one(const float *__restrict__ U, int64_t m, int R,
+                                                                     const float *__restrict__ q,
+                                                                     float *__restrict__ p) {
+  __shared__ float red[NB][kProjOneThreads / 16];
+  const int r = (int)blockIdx.x;
+  const float *u = U + (int64_t)r * m;
+  float acc[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) acc[k] = 0.f;
+  for (int64_t i = threadIdx.x; i < m; i += kProjOneAhead * kProjOneThreads) {
+    float uv[kProjOneAhead], qv[kProjOneAhead][NB];
+#pragma unroll
+    for (int t = 0; t < kProjOneAhead; ++t) {
+      const int64_t at = min(i + t * kProjOneThreads, m - 1);
+      uv[t] = u[at];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) qv[t][k] = q[(int64_t)k * m + at];
+    }
+#pragma unroll
+    for (int t = 0; t < kProjOneAhead; ++t)
+      if (i + t * kProjOneThreads < m) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) acc[k] = fmaf(uv[t], qv[t][k], acc[k]);
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    float v = acc[k];
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    v += row_rotate<1>(v);
+    if ((threadIdx.x & 15) == 0) red[k][threadIdx.x >> 4] = v;
+  }
+  __syncthreads();
+  const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (k >= NB) return;
+  double v = (double)red[k][lane];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d);
+  if (lane == 0) p[(int64_t)k * R + r] = (float)v;
+}
+
 }  // namespace
 
 namespace vds {
@@ -379,6 +439,14 @@ vds_status vds_pod_project(vds_ctx c, const float *U, int32_t R, const float *q,
   if (bytes < vds_pod_map_workspace_bytes(&c->prob, R)) return set_err(c, VDS_ERR_NOMEM, "workspace too small");
   const int64_t m = 3 * c->prob.P;
   const int nb = c->prob.nb;
+  if (R <= kProjOneRows && (nb + 1) * m <= kProjOneReads) {
+    timed(c, VDS_TIMER_PROJ, 4.0 * m * R, [&] {
+      by_bonds(nb, [&](auto n) {
+        k_pod_project_one<decltype(n)::value><<<(unsigned)R, kProjOneThreads, 0, c->stream>>>(U, m, R, q, p);
+      });
+    });
+    return hip_check(c, hipGetLastError(), "project");
+  }
   float *part = static_cast<float *>(ws);
   // about four workgroups per compute unit over the groups of rows and the
   // chunks of positions (at least 256 each), as far as the workspace holds their
