@@ -116,7 +116,8 @@ typedef struct vds_diag {
 typedef struct vds_tuning {
   int32_t impl;          /* one of the VDS_PAIR_* implementations */
   int32_t rows_per_wave; /* MFMA forms: row blocks per wavefront (16 rows each: 1, 2 or 4;
-                          * VDS_PAIR_MFMA32: 1 or 2; 2 counts as 1 from D = 12 on) */
+                          * VDS_PAIR_MFMA32: 1 or 2; 2 counts as 1 from D = 12 on and
+                          * for at most 9216 particles) */
   int32_t col_splits;    /* 1..32.  Column ranges summed separately, then reduced; for
                           * VDS_PAIR_MFMA32 twice the workgroups (of eight waves) per compute
                           * unit of its balanced grid, whose workgroups take equal runs of

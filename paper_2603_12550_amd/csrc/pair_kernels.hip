@@ -223,6 +223,14 @@ constexpr int kStage3 = 2;   // 32-column chunks staged in LDS per barrier
 constexpr int kMaxRB3 = 2;
 constexpr int bf3_rb(int D, int rows_per_wave) { return D >= 12 ? 1 : rows_per_wave; }
 
+// A single state of at most this many rows takes one as well: with runs of a few
+// units, half the rows are half of what a workgroup loads before its first chunk and
+// sums after its last, and 2048 waves' work divides more evenly.  Explicit step with
+// two and with one, D = 9: P = 4100 49 and 41 us, 7000 67 and 60, 9200 84 and 82,
+// 10240 93 and 93, 12200 116 and 120 (D = 3: 46 and 36, 56 and 49, 67 and 65, 73 and
+// 74, 90 and 94), where each column's operands being read twice as often costs more.
+constexpr int64_t kOneBlockRows3 = 9216;
+
 template <int D>
 struct Bf3Shape {
   static constexpr int NQ = bf3_slices(D);   // instructions of a 16x16 distance tile
@@ -936,7 +944,7 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
   m.width = D + 1;  // the compact layout
   // kWaves3 waves of RB 16-row blocks per row group (whole groups: the rows are
   // a multiple of 256); columns in chunks of 32
-  const int rb = bf3_rb(D, t.rows_per_wave);
+  const int rb = nrow_blocks * 16 <= kOneBlockRows3 ? 1 : bf3_rb(D, t.rows_per_wave);
   m.group_shift = rb == 2 ? 8 : 7;  // kWaves3 rb 16 rows
   static_assert(kWaves3 * 16 == 128, "row groups of 128 or 256 rows");
   m.n_rg = (nrow_blocks + kWaves3 * rb - 1) / (kWaves3 * rb);
@@ -965,7 +973,7 @@ void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64
     // in chunks of 32, the last inside the padding (ncol_pad is a multiple of 256 columns),
     // whose weights are zero
     const SplitMap map = pair_split_map(t, D, nrow_blocks, ncol_chunks);
-    const int rb = t.rows_per_wave;
+    const int rb = (1 << map.group_shift) / (kWaves3 * 16);
     switch (D) {
       case 3: launch_bf3_d<3>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;
       case 6: launch_bf3_d<6>(rb, f16.QH, VB, xc, map, partial, part_stride_rows, done, s); break;

@@ -51,6 +51,12 @@ def test_pair_sums_tile_edges(lib, P, nb, rb):
         _check_rows(t1 + t2, ovds.bond_major(t1_o + t2_o, nb), S, S_o, f"P={P} nb={nb} rb={rb} sp={sp}")
 
 
+# both sides of the size up to which a wave takes one row block whatever the tuning says
+@pytest.mark.parametrize("P", [9216, 9217])
+def test_pair_sums_row_block_line(lib, P):
+    test_pair_sums_tile_edges(lib, P, 3, 2)
+
+
 # tile (96), round (32 k) and split edges, rows that do and do not start on 16 bytes
 @pytest.mark.parametrize("m,n", [(3, 2), (31, 96), (33, 97), (129, 1), (600, 95), (1999, 193), (6001, 40), (20000, 300)])
 def test_gram_tile_edges(lib, m, n):
