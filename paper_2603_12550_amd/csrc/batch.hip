@@ -69,13 +69,47 @@ int64_t pad(int64_t P) { return round_up(P, kRowAlign); }
 // Floats per particle of the V operands in the implementation's format.
 int v_width(int impl, int D) { return impl == VDS_PAIR_MFMA32 ? 8 * bf3_tiles(D) : 16; }
 
+// Column ranges of each ensemble's pair passes under VDS_PAIR_MFMA32, from the sizes
+// alone (sums do not depend on the launch shape).  An item of 256 rows and all columns
+// is a serial chain of P / 32 chunks, and a few small ensembles have fewer of them than
+// the chip holds workgroups (512): ranges of the length that gives some 4096 items of
+// 128 rows, eight per resident workgroup, and at least eight chunks, below which a
+// range's start and its slot cost more than they spread.  With 768 items of 256 rows,
+// one and a half rounds, the order (costliest first) balances them by itself.  A step without and with, nb = 3, sizes drawn
+// between P and 4 P: 3 ensembles, P = 300 87 and 58 us, P = 1000 186 and 79, P = 4000
+// 582 and 299; 16 ensembles, P = 1000 235 and 170, P = 4000 1423 and 1187; 32, P = 1000
+// 276 and 246; one of 12000 1323 and 575.  Above the line 32 ensembles of P = 4000 take
+// 2030 and 2050 (with ranges for 2048 items 2267).
+constexpr int kBatchSplits = 16;
+constexpr int64_t kBatchItems = 4096;
+constexpr int64_t kBatchChunks = 8;
+constexpr int64_t kBatchWholeRows = 768 * 256;
+
+std::vector<int> column_splits(int nens, const int64_t *P) {
+  auto chunks = [&](int e) { return (P[e] + 31) / 32; };
+  int64_t work = 0, rows = 0;
+  for (int e = 0; e < nens; ++e) {
+    work += pad(P[e]) / 128 * chunks(e);
+    rows += pad(P[e]);
+  }
+  if (rows >= kBatchWholeRows) return std::vector<int>(nens, 1);
+  const int64_t len = std::max(kBatchChunks, (work + kBatchItems - 1) / kBatchItems);
+  std::vector<int> splits;
+  for (int e = 0; e < nens; ++e)
+    splits.push_back((int)std::min<int64_t>(kBatchSplits, (chunks(e) + len - 1) / len));
+  return splits;
+}
+
 BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   const int D = 3 * nb, KK = (D + 2 + 3) / 4;
   int64_t Ptot = 0;
-  int64_t items_max = 0;
+  int64_t items_max = 0, slot_rows = 0;
+  const std::vector<int> splits = column_splits(nens, P);
   for (int e = 0; e < nens; ++e) {
     Ptot += pad(P[e]);
-    items_max += pad(P[e]) / 64;  // rows_per_wave = 1: 64 rows per item
+    // rows_per_wave = 1: 64 rows per item, 128 of a column range
+    items_max += std::max(pad(P[e]) / 64, pad(P[e]) / 128 * splits[e]);
+    slot_rows += pad(P[e]) * splits[e];
   }
   BatchLayout L{};
   size_t off = 0;
@@ -101,7 +135,7 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   L.t1 = take(sizeof(float) * Ptot * D);
   L.S = take(sizeof(float) * Ptot);
   L.wv = take(sizeof(float) * Ptot);
-  L.part = take(sizeof(float) * Ptot * 16);
+  L.part = take(sizeof(float) * slot_rows * 16);
   L.meanp = take(sizeof(double) * (Ptot / 256) * 16);
   L.redp = take(sizeof(double) * (Ptot / 256) * 16);
   L.tau = take(sizeof(double) * nens * 9);
@@ -109,7 +143,7 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   return L;
 }
 
-// (ensemble, row tile) items, costliest ensembles first.  A row tile is the
+// (ensemble, row tile, column range) items, costliest ensembles first.  A row tile is the
 // rows a workgroup of the pair implementation takes.
 std::vector<int2> make_items(const vds_batch b, int rb) {
   const int64_t rows = pair_tile_rows(b->impl, rb, b->D);
@@ -119,7 +153,8 @@ std::vector<int2> make_items(const vds_batch b, int rb) {
   std::vector<int2> items;
   for (int e : order) {
     const int64_t tiles = (pad(b->P[e]) + rows - 1) / rows;
-    for (int64_t t = 0; t < tiles; ++t) items.push_back(make_int2(e, (int)t));
+    for (int64_t t = 0; t < tiles; ++t)
+      for (int k = 0; k < b->ens[e].splits; ++k) items.push_back(make_int2(e, (int)t | k << kItemTileBits));
   }
   return items;
 }
@@ -149,7 +184,13 @@ BatchView view(vds_batch b) {
 
 // Operand formats of the ensembles follow the pair implementation.
 void set_formats(vds_batch b) {
-  for (EnsDesc &d : b->ens) {
+  const std::vector<int> splits = column_splits(b->nens, b->P.data());
+  int64_t rows = 0;
+  for (int e = 0; e < b->nens; ++e) {
+    EnsDesc &d = b->ens[e];
+    d.splits = b->impl == VDS_PAIR_MFMA32 ? splits[e] : 1;
+    d.part_off = rows;
+    rows += d.p.Ppad * d.splits;
     d.p.vhalf = (b->impl == VDS_PAIR_MFMA_F16X2 || b->impl == VDS_PAIR_MFMA_F16X2_ALL) ? 1 : 0;
     d.p.qhalf = b->impl == VDS_PAIR_MFMA_F16X2_ALL ? 1 : 0;
     d.p.bf3 = b->impl == VDS_PAIR_MFMA32 ? 1 : 0;  // its BF16-thirds operands

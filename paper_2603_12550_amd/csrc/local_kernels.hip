@@ -895,7 +895,9 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_finalize_a(BatchView b, con
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   assume_dimension<D>(d.p);
-  finalize_a_body(d.p, blockIdx.x - d.blk16, partial + o * 16, SplitMap{}, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
+  SplitMap slots;
+  slots.splits = d.splits;
+  finalize_a_body(d.p, blockIdx.x - d.blk16, partial + d.part_off * 16, slots, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
                   VB + o * b.vw);
 }
 
@@ -908,7 +910,9 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   assume_dimension<D>(d.p);
-  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + o * 16, SplitMap{}, t1 + o * b.D, S + o,
+  SplitMap slots;
+  slots.splits = d.splits;
+  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + d.part_off * 16, slots, t1 + o * b.D, S + o,
                wv + o, q + d.q_off, nullptr, q + d.q_off, nullptr, nullptr, nullptr, PackOps{}, nullptr);
 }
 

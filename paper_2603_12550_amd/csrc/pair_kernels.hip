@@ -435,8 +435,8 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
   }
 }
 
-// Batched form: a persistent grid walks the (ensemble, row group) items; each
-// item takes all columns of its ensemble (one slot of partial sums).
+// Batched form: a persistent grid walks the (ensemble, row group, column range)
+// items, each a slot of partial sums in its rows.
 template <int D, int RB>
 __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_pair_bf3(
     const int2 *__restrict__ items, int nitems, const EnsDesc *__restrict__ ens, const float *__restrict__ xc,
@@ -446,16 +446,27 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
   // this workgroup's chunks over all its items, for the issue priority by
   // progress (see k_pair_bf3)
   int64_t total = 0;
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) total += (ens[items[it].x].p.P + 31) / 32;
+  auto columns = [&](int2 item, int &c0, int &c1) {
+    const EnsDesc &d = ens[item.x];
+    const int nc = (int)((d.p.P + 31) / 32), k = item.y >> kItemTileBits;
+    c0 = (int)((int64_t)k * nc / d.splits);
+    c1 = (int)((int64_t)(k + 1) * nc / d.splits);
+  };
+  int c0, c1;
+  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+    columns(items[it], c0, c1);
+    total += c1 - c0;
+  }
   int64_t done = 0;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
-    const int64_t off = ens[item.x].pad_off;
-    const int nc = (int)((ens[item.x].p.P + 31) / 32);
+    const EnsDesc &d = ens[item.x];
+    const int64_t off = d.pad_off, slot = d.part_off + (item.y >> kItemTileBits) * d.p.Ppad;
+    columns(item, c0, c1);
     const uint4 *k3 = K3 + off / 16 * S::NQ * 64;
-    bf3_segment<D, RB, 16>(k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y, 0, nc, partial + off * 16, lds,
-                           done, total);
-    done += nc;
+    bf3_segment<D, RB, 16>(k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y & ((1 << kItemTileBits) - 1), c0, c1,
+                           partial + slot * 16, lds, done, total);
+    done += c1 - c0;
   }
 }
 

@@ -137,6 +137,8 @@ struct EnsDesc {
   int64_t q_off;    // first float of the ensemble's state [nb][P][3] in the packed state
   int blk16;        // first 16-particle block of the ensemble
   int blk256;       // first 256-particle block of the ensemble
+  int splits;       // column ranges of its pair passes, each with its slot of partial sums
+  int64_t part_off; // first row of its slots (Ppad rows each) in the partial sums
 };
 
 // sum_{k < n} src[k stride], added in the order of k into Acc.  The loads of
@@ -247,7 +249,7 @@ int device_cu_count();
 // The slots a pass of tuning t over nrow_blocks 16-row blocks and ncol_chunks
 // 16-column chunks writes (launch_pair_pass takes its grid from the same map).
 SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t ncol_chunks);
-// Batched pair pass over the (ensemble, row tile) work list `items` with a
+// Batched pair pass over the (ensemble, row tile, column range) work list `items` with a
 // persistent grid of `grid` workgroups; rb = row blocks per wavefront.
 // impl selects the pair implementation (VDS_PAIR_MFMA or one of the FP16-split
 // ones, whose operand formats the ensembles' vhalf / qhalf flags must match);
@@ -328,6 +330,10 @@ void launch_pod_reconstruct(const float *U, int64_t m, int R, int nb, const floa
 
 // ---- batched per-particle kernels (local_kernels.hip) ----
 // Block tables: blk16_ens[b] / blk256_ens[b] = ensemble of 16- / 256-particle block b.
+// A work item of a batched pass is (ensemble, row tile | column range << kItemTileBits)
+// (at most 2^26 particles in tiles of at least 64 rows).
+constexpr int kItemTileBits = 20;
+
 struct BatchView {
   const EnsDesc *ens;
   const int *blk16_ens;
