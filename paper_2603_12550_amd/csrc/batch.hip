@@ -37,6 +37,7 @@ struct vds_batch_s {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   int impl = VDS_PAIR_MFMA32, rb = 2, grid = 1024, use_graph = 1;
   int nitems = 0;
+  int items_rb = 2;  // row blocks per wave the items are made for
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   const float *graph_q = nullptr;  // state pointer the graph was captured for
@@ -159,8 +160,19 @@ std::vector<int2> make_items(const vds_batch b, int rb) {
   return items;
 }
 
+// Fewer items of 256 rows than compute units are made of 128 rows instead: a step of
+// one ensemble of 1000 particles takes 62 us with 256 and 54 with 128, 8 ensembles of
+// 300 to 1200 61 and 54; from 256 items on it is even, then behind (one of 7000: 257
+// and 270).
+constexpr size_t kBatchFewItems = 256;
+
 vds_status upload_items(vds_batch b) {
+  b->items_rb = b->rb;
   std::vector<int2> items = make_items(b, b->rb);
+  if (b->impl == VDS_PAIR_MFMA32 && b->rb == 2 && items.size() < kBatchFewItems) {
+    b->items_rb = 1;
+    items = make_items(b, 1);
+  }
   b->nitems = (int)items.size();
   vds_status st = bhip(b, hipMemcpyAsync(b->d_items, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice,
                                          b->priv), "upload items");
@@ -206,7 +218,7 @@ vds_status upload_ens(vds_batch b) {
 }
 
 void pair_pass(vds_batch b, const float *V, bool pass_a, hipStream_t s) {
-  launch_batch_pair(b->impl, b->rb, b->grid, b->KK, b->D, b->d_items, b->nitems, b->d_ens, b->QB, b->KA, V, b->f16,
+  launch_batch_pair(b->impl, b->items_rb, b->grid, b->KK, b->D, b->d_items, b->nitems, b->d_ens, b->QB, b->KA, V, b->f16,
                     pass_a, b->xc, b->part, s);
 }
 
