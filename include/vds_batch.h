@@ -10,7 +10,8 @@
  * replayed, and each kernel pass covers all ensembles (the pair pass is one
  * persistent launch over a work list of (ensemble, row tile) items sorted by
  * decreasing cost, in column ranges where the batch is small, and in tiles of
- * half the rows whatever rows_per_wave where there would be fewer than 256 items).  Weights are uniform within each ensemble.
+ * half the rows whatever rows_per_wave where there would be fewer than 256 items).
+ * Weights are uniform within each ensemble.
  */
 #ifndef VDS_BATCH_H
 #define VDS_BATCH_H
