@@ -1058,10 +1058,12 @@ vds_status vds_mlp_train_epoch(vds_mlp m, const float *X, const float *T, int32_
         m->noise_seed, m->noise_draws);
     m->noise_draws += (uint64_t)batch * m->nin;
     loss_grad_fp32(m, m->xin, m->tin, batch, m->loss_out, bi > 0);
-    vds_mlp_adam_step(m, lr, 0.9f, 0.999f, 1e-8f);
+    // (takes the launch errors of the whole minibatch)
+    vds_status st = vds_mlp_adam_step(m, lr, 0.9f, 0.999f, 1e-8f);
+    if (st != VDS_OK) return st;
   }
-  vds_status st = mhip(m, hipGetLastError(), "train epoch");
-  if (st == VDS_OK && loss)
+  vds_status st = VDS_OK;
+  if (loss)
     st = mhip(m, hipMemcpyAsync(&acc, m->loss_out, sizeof(double), hipMemcpyDeviceToHost, m->s), "copy");
   if (st == VDS_OK) st = mhip(m, hipStreamSynchronize(m->s), "synchronise");
   if (st == VDS_OK && loss) *loss = acc / nbatch;

@@ -320,10 +320,11 @@ void reduce_out(vds_ctx c, int nblk, int nslots) {
   launch_reduce_final(c->redp, nblk, nslots, h ? h->red : c->redout, c->stream, c->ctrl, h ? &h->ctrl : nullptr);
 }
 
-// What the last reduce_out left (synchronises).
+// What the last reduce_out left (synchronises).  A launch that failed left nothing
+// there: the memory then holds what an earlier call or object read back.
 vds_status read_back(vds_ctx c, HostOut &out) {
-  vds_status st = VDS_OK;
-  if (c->host.p == nullptr) {
+  vds_status st = hip_check(c, hipGetLastError(), "launch");
+  if (st == VDS_OK && c->host.p == nullptr) {
     st = hip_check(c, hipMemcpyAsync(out.red, c->redout, sizeof(out.red), hipMemcpyDeviceToHost, c->stream),
                    "copy sums");
     if (st == VDS_OK)
