@@ -175,6 +175,14 @@ __device__ inline floatx4 mlp_load_tail(const float *__restrict__ p, int64_t ld,
 
 constexpr int kMlpWaves = 8;
 
+// Rounds of 16 k that a wave of a weight gradient, whose K is the batch (up to 2^20),
+// sums in FP32: 256 rows, then to FP64.  Tiles 64 wide keep one FP32 sum, since theirs
+// in FP64 would take 128 registers more than there are.  Relative error of dW1 with one
+// FP32 sum per wave (and of the eight in FP32) and so: 541-128-128-540, 16384 rows 3.3e-7
+// and 1.1e-7, 65536 rows 5.2e-7 and 6.3e-8; 64-16-16-16, 262144 rows 9.8e-7 and 3.2e-8;
+// the time is the same (64 rows 33 us, 16384 649 and 612, 262144 5.07 and 5.09 ms).
+constexpr int kMlpFlush = 16;
+
 // This wave's share of tile (ti, tj): rounds of 16 k, wave, wave + 8, ...  Lane
 // l holds k 4 (l / 16) .. + 3 of a round in row l % 16 of each block, one step
 // of the matrix unit taking one k from each group of four.
@@ -202,19 +210,50 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
   };
   const int full = o.K / 16;
   int r = wave;
-  for (; r + (U - 1) * kMlpWaves < full; r += U * kMlpWaves) {
-    floatx4 va[U][TB], vb[U][TB];
+  auto rounds = [&](int end) {
+    for (; r + (U - 1) * kMlpWaves < end; r += U * kMlpWaves) {
+      floatx4 va[U][TB], vb[U][TB];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int a = 0; a < TB; ++a) {
-        const int k = 16 * (r + u * kMlpWaves) + k0;
-        va[u][a] = mlp_load<A_MN>(pa[a], o.lda, k);
-        vb[u][a] = mlp_load<B_MN>(pb[a], o.ldb, k);
-      }
+        for (int a = 0; a < TB; ++a) {
+          const int k = 16 * (r + u * kMlpWaves) + k0;
+          va[u][a] = mlp_load<A_MN>(pa[a], o.lda, k);
+          vb[u][a] = mlp_load<B_MN>(pb[a], o.ldb, k);
+        }
 #pragma unroll
-    for (int u = 0; u < U; ++u) products(va[u], vb[u]);
+      for (int u = 0; u < U; ++u) products(va[u], vb[u]);
+    }
+  };
+  constexpr bool kLong = A_MN && B_MN && TB <= 2;
+  double tot[kLong ? TB : 1][TB][4];
+  auto flush = [&] {
+    if constexpr (kLong) {
+#pragma unroll
+      for (int a = 0; a < TB; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            tot[a][b][t] += (double)acc[a][b][t];
+            acc[a][b][t] = 0.f;
+          }
+    }
+  };
+  if constexpr (kLong) {
+#pragma unroll
+    for (int a = 0; a < TB; ++a)
+#pragma unroll
+      for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) tot[a][b][t] = 0.0;
+    constexpr int kGroup = kMlpFlush * kMlpWaves;
+    for (int end = kGroup; end < full; end += kGroup) {
+      rounds(end);
+      flush();
+    }
   }
+  rounds(full);
   for (; r <= full; r += kMlpWaves) {
     if (r == full && o.K % 16 == 0) break;
     floatx4 va[TB], vb[TB];
@@ -225,6 +264,15 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
       vb[a] = r < full ? mlp_load<B_MN>(pb[a], o.ldb, k) : mlp_load_tail<B_MN>(pb[a], o.ldb, k, o.K);
     }
     products(va, vb);
+  }
+  if constexpr (kLong) {
+    flush();
+#pragma unroll
+    for (int a = 0; a < TB; ++a)
+#pragma unroll
+      for (int b = 0; b < TB; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[a][b][t] = (float)tot[a][b][t];
   }
 }
 
@@ -270,9 +318,10 @@ __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int ti
     const int64_t i = ti * E + e / E;
     const int j = (int)(tj * E) + e % E;
     if (i >= o.M || j >= o.N) continue;
-    float c = 0.f;
+    double cd = 0.0;
 #pragma unroll
-    for (int v = 0; v < kMlpWaves; ++v) c += red[v * NE + e];
+    for (int v = 0; v < kMlpWaves; ++v) cd += (double)red[v * NE + e];
+    const float c = (float)cd;
     const int64_t at = i * o.N + j;
     if (o.epi == kEpiHidden) {
       const float z = c + o.aux[j];
