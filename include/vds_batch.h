@@ -11,7 +11,8 @@
  * persistent launch over a work list of (ensemble, row tile) items sorted by
  * decreasing cost, in column ranges where the batch is small, and in tiles of
  * half the rows whatever rows_per_wave where there would be fewer than 256 items).
- * Weights are uniform within each ensemble.
+ * Weights are uniform within each ensemble.  A row's sums are added up in FP64; which
+ * other ensembles are in the batch changes only the order of those additions.
  */
 #ifndef VDS_BATCH_H
 #define VDS_BATCH_H

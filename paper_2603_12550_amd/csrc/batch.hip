@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "bf3.h"
 #include "vds_batch.h"
 #include "vds_internal.h"
 
@@ -73,17 +74,21 @@ int v_width(int impl, int D) { return impl == VDS_PAIR_MFMA32 ? 8 * bf3_tiles(D)
 // Column ranges of each ensemble's pair passes under VDS_PAIR_MFMA32, from the sizes
 // alone (sums do not depend on the launch shape).  An item of 256 rows and all columns
 // is a serial chain of P / 32 chunks, and a few small ensembles have fewer of them than
-// the chip holds workgroups (512): ranges of the length that gives some 4096 items of
-// 128 rows, eight per resident workgroup, and at least eight chunks, below which a
-// range's start and its slot cost more than they spread.  With 768 items of 256 rows,
-// one and a half rounds, the order (costliest first) balances them by itself.  A step without and with, nb = 3, sizes drawn
-// between P and 4 P: 3 ensembles, P = 300 87 and 58 us, P = 1000 186 and 79, P = 4000
-// 582 and 299; 16 ensembles, P = 1000 235 and 170, P = 4000 1423 and 1187; 32, P = 1000
-// 276 and 246; one of 12000 1323 and 575.  Above the line 32 ensembles of P = 4000 take
-// 2030 and 2050 (with ranges for 2048 items 2267).
+// the chip holds workgroups (512): ranges of the length that gives some 1536 items of
+// 128 rows, in whole accumulation groups (eight chunks, below which a range's start and
+// its slot cost more than they spread), so that the groups, and with FP64 slots the
+// sums, are those of whole ensembles.  With 768 items of 256 rows, one and a half
+// rounds, the order (costliest first) balances them by itself.
+// A step of whole ensembles, in ranges cut anywhere with FP32 slots (for 4096 items) and
+// in these, nb = 3, sizes drawn between P and 4 P: 3 ensembles, P = 1000 186, 67 and
+// 67 us, P = 4000 582, 290 and 306; 16 ensembles, P = 1000 235, 158 and 142, P = 4000
+// 1423, 1186 and 1224; 32, P = 1000 276, 270 and 246; one of 12000 1323, 147 and 144.
+// Over 18 such batches and nb = 1, 3, 5 these ranges take 0.97 of the time of those cut
+// anywhere (0.84 to 1.08; for 2048 items 0.97, 0.84 to 1.10, for 4096 0.995, 0.88 to
+// 1.13).  Above the line 32 ensembles of P = 4000 take 2030 whole and 2050 in ranges.
 constexpr int kBatchSplits = 16;
-constexpr int64_t kBatchItems = 4096;
-constexpr int64_t kBatchChunks = 8;
+constexpr int64_t kBatchItems = 1536;
+constexpr int64_t kBatchChunks = kFlush3;
 constexpr int64_t kBatchWholeRows = 768 * 256;
 
 std::vector<int> column_splits(int nens, const int64_t *P) {
@@ -94,23 +99,29 @@ std::vector<int> column_splits(int nens, const int64_t *P) {
     rows += pad(P[e]);
   }
   if (rows >= kBatchWholeRows) return std::vector<int>(nens, 1);
-  const int64_t len = std::max(kBatchChunks, (work + kBatchItems - 1) / kBatchItems);
+  // groups per range, to the nearest
+  const int64_t unit = kBatchItems * kBatchChunks, len = std::max<int64_t>(1, (work + unit / 2) / unit);
   std::vector<int> splits;
-  for (int e = 0; e < nens; ++e)
-    splits.push_back((int)std::min<int64_t>(kBatchSplits, (chunks(e) + len - 1) / len));
+  for (int e = 0; e < nens; ++e) {
+    const int64_t groups = (chunks(e) + kBatchChunks - 1) / kBatchChunks;
+    splits.push_back((int)std::min<int64_t>(kBatchSplits, (groups + len - 1) / len));
+  }
   return splits;
 }
+
+// Floats per particle of an ensemble's partial sums: FP64 slots where there are several.
+int64_t slot_floats(int D, int splits) { return splits == 1 ? 16 : 2 * (D + 1) * splits; }
 
 BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   const int D = 3 * nb, KK = (D + 2 + 3) / 4;
   int64_t Ptot = 0;
-  int64_t items_max = 0, slot_rows = 0;
+  int64_t items_max = 0, part = 0;
   const std::vector<int> splits = column_splits(nens, P);
   for (int e = 0; e < nens; ++e) {
     Ptot += pad(P[e]);
     // rows_per_wave = 1: 64 rows per item, 128 of a column range
     items_max += std::max(pad(P[e]) / 64, pad(P[e]) / 128 * splits[e]);
-    slot_rows += pad(P[e]) * splits[e];
+    part += slot_floats(D, splits[e]) * pad(P[e]);
   }
   BatchLayout L{};
   size_t off = 0;
@@ -136,7 +147,7 @@ BatchLayout batch_layout(int nens, const int64_t *P, int nb) {
   L.t1 = take(sizeof(float) * Ptot * D);
   L.S = take(sizeof(float) * Ptot);
   L.wv = take(sizeof(float) * Ptot);
-  L.part = take(sizeof(float) * slot_rows * 16);
+  L.part = take(sizeof(float) * std::max(Ptot * 16, part));
   L.meanp = take(sizeof(double) * (Ptot / 256) * 16);
   L.redp = take(sizeof(double) * (Ptot / 256) * 16);
   L.tau = take(sizeof(double) * nens * 9);
@@ -197,12 +208,12 @@ BatchView view(vds_batch b) {
 // Operand formats of the ensembles follow the pair implementation.
 void set_formats(vds_batch b) {
   const std::vector<int> splits = column_splits(b->nens, b->P.data());
-  int64_t rows = 0;
+  int64_t part = 0;
   for (int e = 0; e < b->nens; ++e) {
     EnsDesc &d = b->ens[e];
     d.splits = b->impl == VDS_PAIR_MFMA32 ? splits[e] : 1;
-    d.part_off = rows;
-    rows += d.p.Ppad * d.splits;
+    d.part_off = part;
+    part += d.p.Ppad * slot_floats(b->D, d.splits);
     d.p.vhalf = (b->impl == VDS_PAIR_MFMA_F16X2 || b->impl == VDS_PAIR_MFMA_F16X2_ALL) ? 1 : 0;
     d.p.qhalf = b->impl == VDS_PAIR_MFMA_F16X2_ALL ? 1 : 0;
     d.p.bf3 = b->impl == VDS_PAIR_MFMA32 ? 1 : 0;  // its BF16-thirds operands

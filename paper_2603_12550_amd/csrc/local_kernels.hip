@@ -419,6 +419,15 @@ __device__ inline double sum_splits(const EvalParams &p, const float *__restrict
                                     int64_t I, int n) {
   return ordered_sum<double>(partial + I * splits.width + n, splits.count(I), p.Ppad * splits.width);
 }
+// The same for an ensemble of a batch.  (FP64 slots of column ranges: rounded once, as
+// the slot of a whole ensemble is.)
+__device__ inline double sum_splits(const EvalParams &p, const float *__restrict__ partial, const EnsDesc &d,
+                                    int64_t I, int n) {
+  const float *part = partial + d.part_off;
+  if (d.splits == 1) return (double)part[I * 16 + n];
+  const int W = p.D + 1;
+  return (double)(float)ordered_sum<double>(reinterpret_cast<const double *>(part) + I * W + n, d.splits, p.Ppad * W);
+}
 
 // Pass-A finalisation: S_I = w_I + sum_{J != I} w_J e_IJ,
 // term1_I = -(1/h^2) sum_J w_J e_IJ (x_I - x_J) / S_I, and the pass-B operand
@@ -445,7 +454,9 @@ __device__ void finalize_a_row(const EvalParams &p, int64_t I, int n, double o, 
   else store_v(p, VB, I, n, real ? v : 0.f);  // wb <= 1, so the FP16 form needs no normalisation
 }
 
-__device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__restrict__ partial, const SplitMap &splits,
+// Slots: the SplitMap of a single state, or the EnsDesc of an ensemble.
+template <class Slots>
+__device__ void finalize_a_body(const EvalParams &p, int64_t lb, const float *__restrict__ partial, const Slots &splits,
                                 const float *__restrict__ xc, const float *__restrict__ wv, float *__restrict__ S,
                                 float *__restrict__ t1, float *__restrict__ VB) {
   const int64_t I = group_particle(lb);
@@ -620,8 +631,9 @@ __device__ void combine_rows(const EvalParams &p, int64_t lb, int mode, int obs,
   }
 }
 
+template <class Slots>
 __device__ void combine_body(const EvalParams &p, int64_t lb, int mode, int obs, const float *__restrict__ partial,
-                             const SplitMap &splits, const float *__restrict__ t1, const float *__restrict__ S,
+                             const Slots &splits, const float *__restrict__ t1, const float *__restrict__ S,
                              const float *wv, const float *qin, const float *__restrict__ qs, float *out, float *out2,
                              double *__restrict__ redp, float *__restrict__ blockmax, const PackOps &pack,
                              int *fene_out) {
@@ -895,9 +907,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_finalize_a(BatchView b, con
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   assume_dimension<D>(d.p);
-  SplitMap slots;
-  slots.splits = d.splits;
-  finalize_a_body(d.p, blockIdx.x - d.blk16, partial + d.part_off * 16, slots, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
+  finalize_a_body(d.p, blockIdx.x - d.blk16, partial, d, xc + o * b.D, wv + o, S + o, t1 + o * b.D,
                   VB + o * b.vw);
 }
 
@@ -910,9 +920,7 @@ __global__ __launch_bounds__(kRedBlock) void k_batch_explicit(BatchView b, const
   const EnsDesc &d = b.ens[b.blk16_ens[blockIdx.x]];
   const int64_t o = d.pad_off;
   assume_dimension<D>(d.p);
-  SplitMap slots;
-  slots.splits = d.splits;
-  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial + d.part_off * 16, slots, t1 + o * b.D, S + o,
+  combine_body(d.p, blockIdx.x - d.blk16, MODE_EXPLICIT, 0, partial, d, t1 + o * b.D, S + o,
                wv + o, q + d.q_off, nullptr, q + d.q_off, nullptr, nullptr, nullptr, PackOps{}, nullptr);
 }
 

@@ -250,15 +250,15 @@ struct Bf3Lds {
 
 // One segment: wave w of the workgroup takes the 16-row blocks
 // (kWaves3 rg + w) RB .. + RB - 1 against the columns of chunks [c0, c1) and
-// writes partial sums for its rows to out[row][W] (W >= D + 1), self pairs left
-// out.  Every thread of the workgroup calls it with the same arguments (it holds
+// hands the partial sums of its rows to put(row, n, sum), self pairs
+// left out.  Every thread of the workgroup calls it with the same arguments (it holds
 // barriers).  With run_len > 0 the segment is part of a run of
 // run_len chunk units of which done0 came before it, and every stage sets the
 // waves' issue priority by the share of the run still to do (see k_pair_bf3).
-template <int D, int RB, int W>
+template <int D, int RB, class Put>
 __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ K3, const uint4 *__restrict__ V3,
                                             const float *__restrict__ xr, int rg, int c0,
-                                            int c1, float *__restrict__ out, Bf3Lds<D> &lds,
+                                            int c1, const Put &put, Bf3Lds<D> &lds,
                                             int64_t done0 = 0, int64_t run_len = 0) {
   using S = Bf3Shape<D>;
   constexpr int NQ = S::NQ, NT = S::NT, PC = S::PC;
@@ -398,8 +398,8 @@ __device__ __forceinline__ void bf3_segment(const uint4 *__restrict__ K3, const 
     for (int i = 0; i < 4; ++i) {
       const double s = tl[4 * r + i][src];
       const int64_t row = (int64_t)(rb0 + r) * 16 + 4 * (lane >> 4) + i;
-      if (n < D) out[row * W + n] = (float)((double)xr[row * D + n] * s - tl[4 * r + i][lane]);
-      else if (n == D) out[row * W + n] = (float)s;
+      if (n < D) put(row, n, (double)xr[row * D + n] * s - tl[4 * r + i][lane]);
+      else if (n == D) put(row, n, s);
     }
 }
 
@@ -428,15 +428,16 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
     const int c1 = (int)min(nch, u_end - rg * nch);
     const int slot = (int)(L - map.run_of(rg * nch));
     u = rg * nch + c1;
-    // slots in the compact layout: D + 1 floats per row
-    bf3_segment<D, RB, D + 1>(K3, V3, xr, (int)rg, c0, c1,
-                              partial + (int64_t)slot * part_stride_rows * (D + 1), lds, rg * nch + c0 - u_beg,
-                              u_end - u_beg);
+    float *out = partial + (int64_t)slot * part_stride_rows * (D + 1);
+    bf3_segment<D, RB>(K3, V3, xr, (int)rg, c0, c1, [out](int64_t row, int n, double v) { out[row * (D + 1) + n] = (float)v; },
+                       lds, rg * nch + c0 - u_beg, u_end - u_beg);
   }
 }
 
 // Batched form: a persistent grid walks the (ensemble, row group, column range)
-// items, each a slot of partial sums in its rows.
+// items, each a slot of partial sums in its rows.  The ranges are whole accumulation
+// groups, their slots FP64 and rounded once when they are added, so that a row's sums
+// are those of a whole ensemble but for the order in which FP64 adds the groups.
 template <int D, int RB>
 __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_pair_bf3(
     const int2 *__restrict__ items, int nitems, const EnsDesc *__restrict__ ens, const float *__restrict__ xc,
@@ -448,9 +449,9 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
   int64_t total = 0;
   auto columns = [&](int2 item, int &c0, int &c1) {
     const EnsDesc &d = ens[item.x];
-    const int nc = (int)((d.p.P + 31) / 32), k = item.y >> kItemTileBits;
-    c0 = (int)((int64_t)k * nc / d.splits);
-    c1 = (int)((int64_t)(k + 1) * nc / d.splits);
+    const int nc = (int)((d.p.P + 31) / 32), ng = (nc + kFlush3 - 1) / kFlush3, k = item.y >> kItemTileBits;
+    c0 = k * ng / d.splits * kFlush3;
+    c1 = min(nc, (k + 1) * ng / d.splits * kFlush3);
   };
   int c0, c1;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
@@ -461,11 +462,21 @@ __global__ __launch_bounds__(kWaves3 * 64) __attribute__((amdgpu_waves_per_eu(4)
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const int2 item = items[it];
     const EnsDesc &d = ens[item.x];
-    const int64_t off = d.pad_off, slot = d.part_off + (item.y >> kItemTileBits) * d.p.Ppad;
+    const int64_t off = d.pad_off, slot = (item.y >> kItemTileBits) * d.p.Ppad;
+    float *out = partial + d.part_off;
     columns(item, c0, c1);
     const uint4 *k3 = K3 + off / 16 * S::NQ * 64;
-    bf3_segment<D, RB, 16>(k3, V3 + off / 32 * S::NT * 64, xc + off * D, item.y & ((1 << kItemTileBits) - 1), c0, c1,
-                           partial + slot * 16, lds, done, total);
+    const uint4 *v3 = V3 + off / 32 * S::NT * 64;
+    const int rg = item.y & ((1 << kItemTileBits) - 1);
+    if (d.splits == 1)
+      bf3_segment<D, RB>(k3, v3, xc + off * D, rg, c0, c1,
+                         [out](int64_t row, int n, double v) { out[row * 16 + n] = (float)v; }, lds, done, total);
+    else
+      bf3_segment<D, RB>(k3, v3, xc + off * D, rg, c0, c1,
+                         [out, slot](int64_t row, int n, double v) {
+                           reinterpret_cast<double *>(out)[(slot + row) * (D + 1) + n] = v;
+                         },
+                         lds, done, total);
     done += c1 - c0;
   }
 }

@@ -138,7 +138,7 @@ struct EnsDesc {
   int blk16;        // first 16-particle block of the ensemble
   int blk256;       // first 256-particle block of the ensemble
   int splits;       // column ranges of its pair passes, each with its slot of partial sums
-  int64_t part_off; // first row of its slots (Ppad rows each) in the partial sums
+  int64_t part_off; // first float of its slots: one of 16 floats a row, or several of D + 1 FP64 numbers
 };
 
 // sum_{k < n} src[k stride], added in the order of k into Acc.  The loads of
