@@ -1135,9 +1135,10 @@ __global__ __launch_bounds__(kDensityWaves * 64) void k_density_bf3(EvalParams p
   assume_dimension<D>(p);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t i0 = (int64_t)blockIdx.x * (16 * RB);
-  const int cps = (nch + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int c0 = (int)blockIdx.y * cps, c1 = min(nch, c0 + cps);
+  const int64_t i0 = long_block() * (16 * RB);
+  if (i0 >= ny) return;
+  const int cps = (nch + (int)gridDim.z - 1) / (int)gridDim.z;
+  const int c0 = (int)blockIdx.z * cps, c1 = min(nch, c0 + cps);
   uint4 kv[2 * NQ];
   float4 wj[2];
   auto load = [&](int c) {
@@ -1212,7 +1213,7 @@ __global__ __launch_bounds__(kDensityWaves * 64) void k_density_bf3(EvalParams p
   if (threadIdx.x < 16 * RB && i0 + threadIdx.x < ny) {
     double t = 0.0;
     for (int v = 0; v < kDensityWaves; ++v) t += red[v][threadIdx.x];
-    if (part != nullptr) part[(int64_t)blockIdx.y * ny + i0 + threadIdx.x] = t;
+    if (part != nullptr) part[(int64_t)blockIdx.z * ny + i0 + threadIdx.x] = t;
     else f[i0 + threadIdx.x] = (float)t * norm;
   }
 }
@@ -1350,7 +1351,8 @@ void launch_density(const EvalParams &p, const float *y, int64_t ny, const float
     constexpr int D = decltype(d)::value;
     auto go = [&](auto rc) {
       constexpr int RB = decltype(rc)::value;
-      const dim3 grid((unsigned)((ny + 16 * RB - 1) / (16 * RB)), (unsigned)splits);
+      dim3 grid = long_grid((ny + 16 * RB - 1) / (16 * RB));
+      grid.z = (unsigned)splits;
       k_density_bf3<D, RB><<<grid, kDensityWaves * 64, 0, s>>>(p, y, ny, cmean, k3, wv, nch, norm, f, pt);
     };
     switch (density_row_blocks(ny)) {

@@ -174,6 +174,15 @@ __device__ inline T strided_max(const T *__restrict__ src, int n, int64_t stride
   return m;
 }
 
+// A grid of n workgroups, and the workgroup's number in it: in two dimensions from 2^20
+// on, since of 2^32 threads and more in one a launch runs only the rest, without an error.
+// (Numbers of n and more occur.)
+inline dim3 long_grid(int64_t n) {
+  const int64_t x = n < (1 << 20) ? n : 1 << 20;
+  return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
+__device__ inline int64_t long_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Terms of a strided loop b = first, first + step, ... < end.
 __host__ __device__ inline int strided_count(int first, int end, int step) {
   return first < end ? (end - first + step - 1) / step : 0;
