@@ -176,19 +176,26 @@ __device__ inline floatx4 mlp_load_tail(const float *__restrict__ p, int64_t ld,
 constexpr int kMlpWaves = 8;
 
 // Rounds of 16 k that a wave of a weight gradient, whose K is the batch (up to 2^20),
-// sums in FP32: 256 rows, then to FP64.  Tiles 64 wide keep one FP32 sum, since theirs
-// in FP64 would take 128 registers more than there are.  Relative error of dW1 with one
+// sums in FP32: 256 rows, then to FP64.  For tiles 64 wide, whose FP64 sums would take
+// 128 registers more than there are, to an FP32 sum in LDS, of at most 512 such groups.
+// Relative error of dW1 with one
 // FP32 sum per wave (and of the eight in FP32) and so: 541-128-128-540, 16384 rows 3.3e-7
 // and 1.1e-7, 65536 rows 5.2e-7 and 6.3e-8; 64-16-16-16, 262144 rows 9.8e-7 and 3.2e-8;
 // the time is the same (64 rows 33 us, 16384 649 and 612, 262144 5.07 and 5.09 ms).
 constexpr int kMlpFlush = 16;
 
+// Where lane and wave keep element t of block (a, b) of a tile in LDS: [wave][row][column].
+template <int TB>
+__device__ inline int mlp_slot(int wave, int lane, int a, int b, int t) {
+  return wave * (256 * TB * TB) + (16 * a + 4 * (lane >> 4) + t) * (16 * TB) + 16 * b + (lane & 15);
+}
+
 // This wave's share of tile (ti, tj): rounds of 16 k, wave, wave + 8, ...  Lane
 // l holds k 4 (l / 16) .. + 3 of a round in row l % 16 of each block, one step
-// of the matrix unit taking one k from each group of four.
+// of the matrix unit taking one k from each group of four.  red: the tile's LDS.
 template <int TB, bool A_MN, bool B_MN>
 __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int lane, int wave,
-                                   floatx4 (&acc)[TB][TB]) {
+                                   floatx4 (&acc)[TB][TB], float *red) {
   constexpr int U = TB == 1 ? 4 : 1;
   const int m = lane & 15, k0 = (lane >> 4) * 4;
   const float *pa[TB], *pb[TB];
@@ -225,32 +232,28 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
       for (int u = 0; u < U; ++u) products(va[u], vb[u]);
     }
   };
-  constexpr bool kLong = A_MN && B_MN && TB <= 2;
-  double tot[kLong ? TB : 1][TB][4];
-  auto flush = [&] {
-    if constexpr (kLong) {
-#pragma unroll
-      for (int a = 0; a < TB; ++a)
-#pragma unroll
-        for (int b = 0; b < TB; ++b)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            tot[a][b][t] += (double)acc[a][b][t];
-            acc[a][b][t] = 0.f;
-          }
-    }
-  };
-  if constexpr (kLong) {
+  constexpr bool kLong = A_MN && B_MN, kInLds = TB > 2;
+  double tot[kLong && !kInLds ? TB : 1][TB][4];
+  auto each = [&](auto &&f) {
 #pragma unroll
     for (int a = 0; a < TB; ++a)
 #pragma unroll
       for (int b = 0; b < TB; ++b)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) tot[a][b][t] = 0.0;
+        for (int t = 0; t < 4; ++t) f(a, b, t);
+  };
+  auto slot = [&](int a, int b, int t) -> float & { return red[mlp_slot<TB>(wave, lane, a, b, t)]; };
+  bool groups = false;  // a group has been taken out of acc
+  if constexpr (kLong) {
     constexpr int kGroup = kMlpFlush * kMlpWaves;
     for (int end = kGroup; end < full; end += kGroup) {
       rounds(end);
-      flush();
+      each([&](int a, int b, int t) {
+        if constexpr (kInLds) slot(a, b, t) = groups ? slot(a, b, t) + acc[a][b][t] : acc[a][b][t];
+        else tot[a][b][t] = groups ? tot[a][b][t] + (double)acc[a][b][t] : (double)acc[a][b][t];
+        acc[a][b][t] = 0.f;
+      });
+      groups = true;
     }
   }
   rounds(full);
@@ -266,13 +269,11 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
     products(va, vb);
   }
   if constexpr (kLong) {
-    flush();
-#pragma unroll
-    for (int a = 0; a < TB; ++a)
-#pragma unroll
-      for (int b = 0; b < TB; ++b)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[a][b][t] = (float)tot[a][b][t];
+    if (groups)
+      each([&](int a, int b, int t) {
+        if constexpr (kInLds) acc[a][b][t] += slot(a, b, t);
+        else acc[a][b][t] = (float)(tot[a][b][t] + (double)acc[a][b][t]);
+      });
   }
 }
 
@@ -300,18 +301,18 @@ __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int ti
 #pragma unroll
     for (int b = 0; b < TB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
   if (o.epi == kEpiInputGrad)
-    mlp_product<TB, false, true>(o, ti, tj, lane, wave, acc);
+    mlp_product<TB, false, true>(o, ti, tj, lane, wave, acc, red);
   else if (o.epi == kEpiWeightGrad)
-    mlp_product<TB, true, true>(o, ti, tj, lane, wave, acc);
+    mlp_product<TB, true, true>(o, ti, tj, lane, wave, acc, red);
   else
-    mlp_product<TB, false, false>(o, ti, tj, lane, wave, acc);
+    mlp_product<TB, false, false>(o, ti, tj, lane, wave, acc, red);
 #pragma unroll
   for (int a = 0; a < TB; ++a)
 #pragma unroll
     for (int b = 0; b < TB; ++b)
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        red[wave * NE + (16 * a + 4 * (lane >> 4) + t) * E + 16 * b + (lane & 15)] = acc[a][b][t];
+        red[mlp_slot<TB>(wave, lane, a, b, t)] = acc[a][b][t];
   __syncthreads();
   double e2 = 0.0;
   for (int e = tid; e < NE; e += kMlpWaves * 64) {

@@ -4,7 +4,8 @@ rows are the longest of the library.
 All terms are made positive, so that no error hides in a sum that cancels.  Tolerance:
 rows go to FP64 in groups of 256 per wave, in FP32 instructions of 4 rows: 64 roundings
 of varying sign, sqrt(64) 2^-25 = 2.4e-7 of the sum; the wave's sum and the result are
-rounded once each (2 x 2^-25 = 6e-8); and every term carries what three layers' SiLU,
+rounded once each (2 x 2^-25 = 6e-8), in 64-wide tiles FP32 adds the 64 groups of 2^17
+rows (sqrt(64) 2^-25 again); and every term carries what three layers' SiLU,
 its derivative and the products round, of which a part (some units of 2^-25) is the same
 in all rows: 8e-7 of each tensor's Frobenius norm in all.  One FP32 sum over a wave's
 rows would round 32768 times at 2^20 rows, some sqrt(32768) 2^-25 = 5e-6."""
@@ -17,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (16, 16, 16, 1 << 20),       # 16-wide tiles
     (20, 24, 40, 300001),        # remainders of tiles, rounds and groups
     (32, 768, 768, 1 << 17),     # 32-wide tiles
+    (24, 2048, 2060, 1 << 17),   # 64-wide tiles
     (64, 16, 16, 2049), (64, 16, 16, 4097),  # one group of rows per wave, and just more
 ])
 def test_weight_gradients_of_many_rows(nin, w, nout, n):
