@@ -354,7 +354,7 @@ template <int TB>
 __global__ __launch_bounds__(kMlpWaves * 64) void k_mlp(MlpOp o0, MlpOp o1, MlpColsum cs, MlpLoss ls) {
   __shared__ float red[kMlpWaves * 256 * TB * TB];
   const int tid = threadIdx.x;
-  int64_t b = blockIdx.x;
+  int64_t b = long_block();
   if (b < o0.tiles) return mlp_tile<TB>(o0, b, red, tid);
   b -= o0.tiles;
   if (b < o1.tiles) return mlp_tile<TB>(o1, b, red, tid);
@@ -383,6 +383,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void k_mlp(MlpOp o0, MlpOp o1, MlpC
     }
     return;
   }
+  if (b > (cs.N + 63) / 64 || ls.out == nullptr) return;
   double s = 0.0;
   for (int64_t i = tid; i < ls.np; i += kMlpWaves * 64) s += ls.lossp[i];
   s = mlp_block_sum(s, tid);
@@ -813,7 +814,7 @@ int64_t launch_mlp(vds_mlp m, MlpOp a, MlpOp b = MlpOp{}, const MlpColsum &cs = 
   const int tb = mlp_edge(a, b);
   a.tiles = mlp_tiles(a.M, a.N, tb);
   b.tiles = mlp_tiles(b.M, b.N, tb);
-  const unsigned grid = (unsigned)(a.tiles + b.tiles + (cs.N + 63) / 64 + (ls.out ? 1 : 0));
+  const dim3 grid = long_grid(a.tiles + b.tiles + (cs.N + 63) / 64 + (ls.out ? 1 : 0));
   if (tb == 4)
     k_mlp<4><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
   else if (tb == 2)
