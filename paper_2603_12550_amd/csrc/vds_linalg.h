@@ -44,16 +44,21 @@ void launch_gemm_parts(const GemmShape &g, float *part, hipStream_t s);
 
 // Entry (i, j) in FP32, term by term: for entries that are not numbers in the
 // three-part product (an infinite factor, or one past the BF16 range, has no
-// parts), so that they are what FP32 arithmetic makes of the inputs.
+// parts), so that they are what FP32 arithmetic makes of the inputs.  No further
+// once the sum is not a number, which it then stays (looked at every 64 terms: at each
+// one, the loads no longer run ahead): a Gram matrix of 60000 x 900 NaN takes 0.45 ms
+// like any other (55 with every entry summed to its end), one with a single infinite
+// factor, whose row of entries runs over all terms, 7.7.
 __device__ inline float gemm_entry_fp32(const GemmShape &g, int i, int j) {
   float s = 0.f;
   for (int b = 0; b < g.nbatch; ++b)
-    for (int64_t k = 0; k < g.K; ++k) {
-      const float x = g.A[b * g.sA + (g.a_mn ? k * g.lda + i : (int64_t)i * g.lda + k)];
-      float y = g.B[b * g.sB + (g.b_mn ? k * g.ldb + j : (int64_t)j * g.ldb + k)];
-      if (g.scale != nullptr) y *= g.scale[b * g.sS + k];
-      s = fmaf(x, y, s);
-    }
+    for (int64_t k0 = 0; k0 < g.K && s == s; k0 += 64)
+      for (int64_t k = k0; k < min(g.K, k0 + 64); ++k) {
+        const float x = g.A[b * g.sA + (g.a_mn ? k * g.lda + i : (int64_t)i * g.lda + k)];
+        float y = g.B[b * g.sB + (g.b_mn ? k * g.ldb + j : (int64_t)j * g.ldb + k)];
+        if (g.scale != nullptr) y *= g.scale[b * g.sS + k];
+        s = fmaf(x, y, s);
+      }
   return s;
 }
 
