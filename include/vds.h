@@ -117,12 +117,13 @@ typedef struct vds_tuning {
   int32_t impl;          /* one of the VDS_PAIR_* implementations */
   int32_t rows_per_wave; /* MFMA forms: row blocks per wavefront (16 rows each: 1, 2 or 4;
                           * VDS_PAIR_MFMA32: 1 or 2; 2 counts as 1 from D = 12 on and
-                          * for at most 9216 particles) */
+                          * for at most 9216 particles, neither counts for at most 4096,
+                          * where a pass and what follows it are one launch) */
   int32_t col_splits;    /* 1..32.  Column ranges summed separately, then reduced; for
                           * VDS_PAIR_MFMA32 twice the workgroups (of eight waves) per compute
                           * unit of its balanced grid, whose workgroups take equal runs of
                           * (row group, column chunk) work and leave one partial sum per row
-                          * group they cover */
+                          * group they cover (without effect for at most 4096 particles) */
   int32_t reserved;
 } vds_tuning;
 
@@ -142,8 +143,9 @@ vds_status vds_bind_workspace(vds_ctx ctx, void *ws_dev, size_t bytes);
 const char *vds_last_error(vds_ctx ctx);
 vds_status vds_set_tuning(vds_ctx ctx, const vds_tuning *t);
 vds_status vds_get_tuning(vds_ctx ctx, vds_tuning *t);
-/* Times every admissible launch shape (row blocks per wave, column splits) of
- * the current implementation on the state q_dev (a pair pass with the
+/* Times every launch shape (row blocks per wave, column splits) that makes a
+ * difference to the current implementation (none for VDS_PAIR_MFMA32 and at most
+ * 4096 particles: the tuning stays) on the state q_dev (a pair pass with the
  * finalisation that sums its column splits) and keeps the fastest; the
  * implementation, and so the arithmetic, is left as set (synchronises). */
 vds_status vds_autotune(vds_ctx ctx, const float *q_dev, const float *w_dev);
@@ -235,7 +237,9 @@ enum { VDS_TIMER_PAIR = 0, VDS_TIMER_GEMM = 1, VDS_TIMER_KGEMM = 2, VDS_TIMER_PR
  * sampled. */
 vds_status vds_timing_enable(vds_ctx ctx, int32_t enable);
 /* Synchronises and returns the summed kernel time (ms), the launch count and
- * the pair-evaluations (pair kernel) or flops (GEMMs) of timer `which`. */
+ * the pair-evaluations (pair kernel) or flops (GEMMs) of timer `which`.  With
+ * VDS_PAIR_MFMA32 and at most 4096 particles a pair launch ends with the finalisation
+ * or the update of its rows, and its time includes that. */
 vds_status vds_timing_read(vds_ctx ctx, int32_t which, double *ms_host, int64_t *launches_host, double *work_host);
 
 #ifdef __cplusplus

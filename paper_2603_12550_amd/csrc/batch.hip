@@ -469,6 +469,9 @@ vds_status vds_batch_autotune(vds_batch b, const float *q) {
       for (int per_cu : {2, 4, 8}) {
         st = vds_batch_set_tuning(b, impl, rb, 256 * per_cu, b->use_graph);
         if (st != VDS_OK) break;
+        // (a launch of 2 row blocks that is that of 1)
+        if (impl == VDS_PAIR_MFMA32 && rb == 2 && pair_tile_rows(impl, b->items_rb, b->D) == pair_tile_rows(impl, 1, b->D))
+          break;
         pair_pass(b, b->VB, false, b->priv);  // warm-up
         (void)hipEventRecord(t0, b->priv);
         pair_pass(b, b->VB, false, b->priv);

@@ -967,8 +967,8 @@ SplitMap pair_split_map(const vds_tuning &t, int D, int64_t nrow_blocks, int64_t
   // kWaves3 waves of RB 16-row blocks per row group (whole groups: the rows are
   // a multiple of 256); columns in chunks of 32
   const int rb = nrow_blocks * 16 <= kOneBlockRows3 ? 1 : bf3_rb(D, t.rows_per_wave);
-  m.group_shift = rb == 2 ? 8 : 7;  // kWaves3 rb 16 rows
-  static_assert(kWaves3 * 16 == 128, "row groups of 128 or 256 rows");
+  m.group_shift = pair_group_shift(rb);  // kWaves3 rb 16 rows
+  static_assert(kWaves3 * 16 == 1 << pair_group_shift(1), "row groups of 128 or 256 rows");
   m.n_rg = (nrow_blocks + kWaves3 * rb - 1) / (kWaves3 * rb);
   m.nch = (ncol_chunks + 1) / 2;
   m.splits = kMaxSplits;

@@ -871,6 +871,8 @@ vds_status vds_autotune(vds_ctx c, const float *q, const float *w) {
   vds_status st = ready(c);
   if (st != VDS_OK) return st;
   if (!q) return set_err(c, VDS_ERR_ARG, "null state");
+  // the one-launch passes of small problems have one shape
+  if (rows_path(c)) return hip_check(c, hipStreamSynchronize(c->stream), "autotune");
   hipEvent_t a = get_event(c), b = get_event(c);
   vds_tuning best = c->tune;
   float best_ms = 1e30f;
@@ -889,6 +891,7 @@ vds_status vds_autotune(vds_ctx c, const float *q, const float *w) {
   for (const vds_tuning &t : cands) {
     if (!pair_shape_ok(t, c->ep.D)) continue;
     apply_tuning(c, t);
+    if (t.impl == VDS_PAIR_MFMA32 && c->smap.group_shift != pair_group_shift(t.rows_per_wave)) continue;  // counts as 1
     if (c->ep.vhalf + 2 * c->ep.qhalf + 4 * c->ep.bf3 != prepared) {  // operand formats follow the implementation
       launch_mean_partials(c->ep, q, w, c->meanp, nullptr, nullptr, c->stream);
       launch_prep(c->ep, q, w, c->meanp, c->nblk, c->xc, c->wv, c->QB, c->KA, c->VA, c->wscale, &c->f16, nullptr,

@@ -253,6 +253,8 @@ bool pair_shape_ok(const vds_tuning &t, int D);
 // Rows a workgroup of the matrix-core implementation impl takes (rb as rows_per_wave of
 // vds_tuning).
 int pair_tile_rows(int impl, int rb, int D);
+// log2 of the rows of a row group of VDS_PAIR_MFMA32 with rb row blocks per wave.
+constexpr int pair_group_shift(int rb) { return rb == 2 ? 8 : 7; }
 // Compute units of the current device (256 on MI355X; 256 if the query fails).
 int device_cu_count();
 // The slots a pass of tuning t over nrow_blocks 16-row blocks and ncol_chunks
