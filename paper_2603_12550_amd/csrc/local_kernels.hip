@@ -292,7 +292,8 @@ __device__ inline void store_k3(const EvalParams &p, bool real, uint32_t *__rest
     d[0] = d[1] = (uint32_t)y.h | ((uint32_t)y.m << 16);
     d[2] = (uint32_t)y.h | ((uint32_t)y.l << 16);
   } else if (real && n == p.D) {
-    const Bf3 r = split_bf3(-0.5 * nrm);
+    // (no less than an FP32 number: a point at 1e19 h and further has density zero)
+    const Bf3 r = split_bf3(fmax(-0.5 * nrm, -1e38));
     d[0] = (uint32_t)r.h | ((uint32_t)r.m << 16);
     d[1] = (uint32_t)r.l | 0x3f800000u;
     d[2] = 0x3f803f80u;
