@@ -36,18 +36,6 @@ __device__ inline bf16x8 as_bf8(uint4 u) {
   __builtin_memcpy(&r, &u, sizeof(r));
   return r;
 }
-// (a, b) = h + m + l, each two BF16 numbers rounded to nearest, exact down to
-// the FP32 subnormals (not for |a| or |b| that round up to infinity).
-__device__ __forceinline__ void split_pair_bf3(float a, float b, uint32_t (&o)[3]) {
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(o[p]) : "v"(a), "v"(b));
-    if (p < 2) {
-      a -= __uint_as_float(o[p] << 16);
-      b -= __uint_as_float(o[p] & 0xffff0000u);
-    }
-  }
-}
 
 // The upper halves of eight values, a BF16 operand (truncation: what is left of
 // a value after two such cuts is again a BF16 number).

@@ -66,7 +66,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(VEC && !A_M
   // staged pieces of 8 rows x 128 bytes of each operand's round
   constexpr int kPiecesA = A_MN ? 0 : kGemmTile / 8, kPiecesB = B_MN ? 0 : kGemmTile / 8;
   constexpr int kLds = (kPiecesA + kPiecesB) * 64;
-  __shared__ float4 lds[2][kLds > 0 ? kLds : 1];
+  static_assert(kLds > 0, "at most one operand is MN-contiguous");
+  __shared__ float4 lds[2][kLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the grid is a multiple of eight: XCD x takes a run of consecutive (split, tile)
@@ -348,14 +349,13 @@ void launch_gemm_parts(const GemmShape &g, float *part, hipStream_t s) {
     if (vec) k_gemm_bf3<A, B, S, true><<<grid, 256, 0, s>>>(g, tn, ntile, part);
     else k_gemm_bf3<A, B, S, false><<<grid, 256, 0, s>>>(g, tn, ntile, part);
   };
-  auto go = [&](auto amn, auto bmn) {
-    if (g.scale != nullptr) run(amn, bmn, std::true_type{});
-    else run(amn, bmn, std::false_type{});
+  auto go = [&](auto bmn) {
+    if (g.scale != nullptr) run(std::false_type{}, bmn, std::true_type{});
+    else run(std::false_type{}, bmn, std::false_type{});
   };
-  if (!g.a_mn && !g.b_mn) go(std::false_type{}, std::false_type{});
-  else if (g.a_mn && !g.b_mn) go(std::true_type{}, std::false_type{});
-  else if (!g.a_mn && g.b_mn) go(std::false_type{}, std::true_type{});
-  else go(std::true_type{}, std::true_type{});
+  if (g.a_mn) run(std::true_type{}, std::false_type{}, std::false_type{});
+  else if (g.b_mn) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 void launch_gemm(const GemmShape &g, float *part, hipStream_t s) {

@@ -1396,12 +1396,4 @@ void launch_batch_stress_sum(const EnsDesc *ens, int nens, const double *redp, d
   k_batch_stress_sum<<<nens, 576, 0, s>>>(ens, redp, tau);
 }
 
-__global__ void k_copy(const float *__restrict__ src, float *__restrict__ dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kRedBlock + threadIdx.x;
-  if (i < n) dst[i] = src[i];
-}
-void launch_copy(const float *src, float *dst, int64_t n, const int *, hipStream_t s) {
-  k_copy<<<nblocks(n), kRedBlock, 0, s>>>(src, dst, n);
-}
-
 }  // namespace vds

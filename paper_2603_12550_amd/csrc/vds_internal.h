@@ -244,7 +244,8 @@ enum CombineMode { MODE_TERMS = 0, MODE_VELOCITY = 1, MODE_EXPLICIT = 2, MODE_PI
 // the padded column count the V operand was written for.  With the FP16-split
 // implementation the V weights were divided by *wscale (NULL: by one), which
 // the pass multiplies back.
-// VDS_PAIR_MFMA32 (rows are the particles) reads K3 from f16.QH and V3 from VB.
+// VDS_PAIR_MFMA32 (rows are the particles and always left out; densities take
+// launch_density) reads K3 from f16.QH and V3 from VB.
 void launch_pair_pass(const vds_tuning &t, int KK, int D, const float *QB, int64_t nrow_blocks,
                       const float *KA, const float *VB, int64_t ncol_chunks, int64_t ncol_pad, const float *xc,
                       bool exclude_self, const float *wscale, const F16Operands &f16, float *partial,
@@ -335,7 +336,6 @@ void launch_density_out(const EvalParams &p, const float *partial, const SplitMa
 int density_splits(int64_t P, int64_t ny);
 void launch_density(const EvalParams &p, const float *y, int64_t ny, const float *cmean, const void *K3,
                     const float *wv, float norm, float *f, void *part, hipStream_t s);
-void launch_copy(const float *src, float *dst, int64_t n, const int *done_flag_or_null, hipStream_t s);
 // q[k][i] = sum_r U[r][i] p[k][r] for i < m, k < nb (U is m x R column-major; pod.hip).
 void launch_pod_reconstruct(const float *U, int64_t m, int R, int nb, const float *p, float *q, hipStream_t s);
 

@@ -9,7 +9,8 @@ namespace vds {
 
 // C = alpha * sum_{b < nbatch} A_b diag(scale_b) B_b^T (+ C when accumulate), where
 // A_b is M x K and B_b is N x K.  Element (i, k) of A_b is A[b*sA + k*lda + i]
-// when a_mn, else A[b*sA + i*lda + k]; likewise B with b_mn.  The output is
+// when a_mn, else A[b*sA + i*lda + k]; likewise B with b_mn.  An MN-contiguous A has
+// a K-contiguous B and no scale beside it (no other form is asked for).  The output is
 // row-major (C[i*ldc + j]) or column-major (C[j*ldc + i]).  K is split over
 // `splits` workgroup layers whose partial tiles are summed in a fixed order.
 struct GemmShape {
