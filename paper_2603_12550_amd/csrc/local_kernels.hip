@@ -958,10 +958,12 @@ __global__ __launch_bounds__(576) void k_batch_stress_sum(const EnsDesc *__restr
 // workgroups still read this one.
 // Bound: latency (launch, row operand, first chunk, sums), and from some 3000
 // particles on every workgroup's reading of all columns through L2.  The line lies
-// where the workgroups fill the compute units once, 4096 particles: an explicit
-// step of the 4-bead chain takes 12.4 us in two launches (36 in four) at P = 1000,
-// 16.8 (42) at 2500, 23.6 (46) at 4000, but 46 (55) at 5000 and 51 (58) at 6000,
-// and with six beads 29 (41) at 4000 and 59 (50) at 5000.
+// where the workgroups fill the compute units once, 4096 particles: beyond it a few
+// units take a second workgroup.  An explicit step in two launches and (in four), in us:
+// D = 9 16.5 (38.0) at P = 2500, 23.0 (37.5) at 4000, 37.9 (40.4) at 4100, 45.1 (43.9) at
+// 5000, 50.7 (50.2) at 6000; D = 15 29.2 (40.4) at 4000, 48.8 (44.9) at 4100, 58.5 (49.0)
+// at 5000; D = 3 17.4 (34.1) at 4000, and above the line still 29.0 (36.0) at 4100 and 47.2
+// (53.0) at 8000: one line serves all dimensions.
 
 constexpr int kRowsWaves = 16;
 

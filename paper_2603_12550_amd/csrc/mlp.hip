@@ -111,7 +111,7 @@ __global__ void k_to_bf16(const float *__restrict__ a, short *__restrict__ b, in
 // and the operands come straight from memory, four rounds of 16 in flight per
 // wave.
 // Bound: the chain of launches (3.3 to 4.9 us each, one or two memory latencies
-// and the wave sum; 24 us together, 41 with the loss on the host).  25 launches
+// and the wave sum; 24 us together, 33 with the loss on the host).  25 launches
 // of 64 x 64-tile products (each with its own sum over K splits), elementwise
 // passes and one-thread column sums took 250 and 270 us.
 enum MlpEpi { kEpiHidden, kEpiOutput, kEpiInputGrad, kEpiWeightGrad };

@@ -2,15 +2,17 @@
 //
 // One pass computes, for every row particle I and a column weight vector wh,
 //   O_I[n] = sum_J e_IJ V_J[n],   V_J = (wh_J x_J, wh_J),
-//   e_IJ   = exp2(min(t_IJ, 0)),  t_IJ = -kappa |x_I - x_J|^2,  kappa = log2(e) / 2h^2,
+//   e_IJ   = exp2(t_IJ),  t_IJ = -kappa |x_I - x_J|^2,  kappa = log2(e) / 2h^2,
 // over all J including J = I (eq. model_DeteParAppr and the two kernel sums of
 // eq. model_DymRepPar).  The squared distance is expanded through augmented
 // vectors so that t_IJ is one dot product:
 //   Q_I = (x_I, -kappa |x_I|^2, 1),  K_J = (2 kappa x_J, 1, -kappa |x_J|^2),
 //   t_IJ = Q_I . K_J.
-// The min(., 0) is the clamp of the expanded |x_I - x_J|^2 at zero.
+// The FP32 forms below clamp e at one, the expanded |x_I - x_J|^2 at zero; the others
+// leave t as it comes, which exceeds zero by its rounding only.
 //
-// Two implementations share the operand arrays the prep kernel writes:
+// Five implementations (vds.h), by the operand arrays that the prep kernel writes.  The
+// default, FP32 by three BF16 parts, is described where it stands; the others:
 //  * MFMA: each wavefront owns RB blocks of 16 rows; per 16-column chunk,
 //    ceil((D+2)/4) v_mfma_f32_16x16x4_f32 form t for a 16x16 pair tile, the
 //    VALU takes exp2, and four more MFMAs accumulate e V.  The accumulator
@@ -35,15 +37,16 @@
 //  * MFMA, FP16-split products throughout: as the previous one, and t too on
 //    v_mfma_f32_16x16x32_f16 from split halves of sqrt(2 kappa) x, with the
 //    squared norms kept in FP32 (layout at pair_rows_f16).
-// Column ranges are split over blockIdx.y; every split writes its own partial
-// sums, reduced later in a fixed order (deterministic, no float atomics).
+// Column ranges are split over blockIdx.y (the default form: over the runs of a balanced
+// grid); every split writes its own partial sums, reduced later in a fixed order
+// (deterministic, no float atomics).
 //
 // Accuracy: the drift needs x_I S_I - M_I, a difference of two sums whose
 // magnitudes can exceed it by an order of magnitude (narrow kernels, isolated
 // particles).  Plain FP32 accumulation over thousands of columns would leave
 // errors of ~1e-6 relative to the sums, amplified by that ratio.  So the FP32
 // accumulators are flushed into FP64 running sums every kFlush chunks (16
-// columns each), and the kernel itself forms, in FP64,
+// columns each; kFlush3 of 32 in the default form), and the kernel itself forms, in FP64,
 //   A_I[n] = x_I[n] O_I[D] - O_I[n]  (n < D),   O_I[D] = sum_J e_IJ wh_J,
 // i.e. it writes sum_J e_IJ wh_J (x_I - x_J) and the weighted kernel sum.
 // With exclude_self the J = I term is left out of both sums: it adds nothing to

@@ -40,8 +40,9 @@ void by_bonds(int nb, F &&f) {
 // q_k = U p_k for the bonds k.  A workgroup owns 64 positions; its four waves
 // take a quarter of the columns each, sixteen in flight, and add up in LDS
 // (one position per thread over all columns left one wave per SIMD waiting).
-// Bound: reading U.  Measured, P = 20000, R = 180: 10.4 us (4.2 TB/s, a copy
-// reaches 4.9), 16.7 with one wave per SIMD.
+// Bound: reading U.  Measured, P = 20000, R = 180, calls in a row: 10.6 us (4.1 TB/s; a
+// large copy reaches 4.9) with the same U, which the last-level cache then holds, 11.9
+// (3.6 TB/s) with sixteen in turn, which it does not; 17.4 and 19.9 with one wave per SIMD.
 constexpr int kReconWaves = 4;
 constexpr int kReconInFlight = 16;
 
@@ -91,7 +92,9 @@ constexpr int kProjRows = 8;
 // q_k[i] once for all eight rows and two positions at a time, so U is read once
 // and q once per eight rows.  Then sums over rows of 16 lanes by DPP and over
 // the block in LDS, in fixed order, into part[k R + r][c].
-// Bound: reading U.  Measured, P = 20000, R = 180: 9.9 us (4.4 TB/s); 18 with one
+// Bound: reading U.  Measured, P = 20000, R = 180, with the sum over chunks, calls in a
+// row: 11.9 us (this kernel alone 9.9, 4.4 TB/s) with the same U, which the last-level
+// cache then holds, 13.4 with sixteen in turn, which it does not; 20.3 and 21.8 with one
 // position at a time and cross-lane sums of all five possible bonds.
 template <int NB>
 __global__ __launch_bounds__(kProjThreads) void k_pod_project(const float *__restrict__ U, int64_t m, int R,

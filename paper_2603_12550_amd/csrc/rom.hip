@@ -135,7 +135,7 @@ RomLayout rom_layout(const vds_problem &p, int R) {
 
 // Splits of the two R x R x 3 P products of a reduced operator build: two
 // workgroups per compute unit (one leaves each waiting for its own loads: 77 and
-// 62 us at R = 180, P = 20000, two took 51 and 44), at least four rounds each, as many
+// 62 us at R = 180, P = 20000, two took 51 and 44), at least two rounds each, as many
 // as the partial-sum buffer holds for both.
 int rom_splits(const RomLayout &L, int R, int64_t P) {
   const int64_t t = (R + kGemmTile - 1) / kGemmTile, rounds = (P + kGemmSlab - 1) / kGemmSlab * 3;
