@@ -276,7 +276,9 @@ __device__ bool picard_converged(const PicardCheck &chk, const float *__restrict
 }
 
 // Column operand K3 of particle I from its centred coordinate x (lane n;
-// zeros past the particles, when not real): see vds_internal.h.
+// zeros past the particles, when not real): see vds_internal.h.  kPoint: x is a point of
+// a density, whose norm stays an FP32 number: at 1e19 h and further the density is zero.
+template <bool kPoint = false>
 __device__ inline void store_k3(const EvalParams &p, bool real, uint32_t *__restrict__ K3, int64_t I, int n, float x) {
   const int NQ = bf3_slices(p.D);
   const Bf3 y = split_bf3(n < p.D ? p.cs * (double)x : 0.0);
@@ -292,8 +294,7 @@ __device__ inline void store_k3(const EvalParams &p, bool real, uint32_t *__rest
     d[0] = d[1] = (uint32_t)y.h | ((uint32_t)y.m << 16);
     d[2] = (uint32_t)y.h | ((uint32_t)y.l << 16);
   } else if (real && n == p.D) {
-    // (no less than an FP32 number: a point at 1e19 h and further has density zero)
-    const Bf3 r = split_bf3(fmax(-0.5 * nrm, -1e38));
+    const Bf3 r = split_bf3(kPoint ? fmax(-0.5 * nrm, -1e38) : -0.5 * nrm);
     d[0] = (uint32_t)r.h | ((uint32_t)r.m << 16);
     d[1] = (uint32_t)r.l | 0x3f800000u;
     d[2] = 0x3f803f80u;
@@ -1155,7 +1156,7 @@ __global__ __launch_bounds__(kDensityWaves * 64) void k_density_bf3(EvalParams p
   for (int t = threadIdx.x; t < 256 * RB; t += kDensityWaves * 64) {
     const int r = t >> 4, n = t & 15;
     const bool real = i0 + r < ny;
-    store_k3(p, real, reinterpret_cast<uint32_t *>(rows), r, n, real && n < D ? y[(i0 + r) * D + n] - cmean[n] : 0.f);
+    store_k3<true>(p, real, reinterpret_cast<uint32_t *>(rows), r, n, real && n < D ? y[(i0 + r) * D + n] - cmean[n] : 0.f);
   }
   __syncthreads();
   bf16x8 q[RB][NQ];
