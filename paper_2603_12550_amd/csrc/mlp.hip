@@ -6,6 +6,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "vds_ctx.h"
@@ -175,14 +176,16 @@ __device__ inline floatx4 mlp_load_tail(const float *__restrict__ p, int64_t ld,
 
 constexpr int kMlpWaves = 8;
 
-// Rounds of 16 k that a wave of a weight gradient, whose K is the batch (up to 2^20),
-// sums in FP32: 256 rows, then to FP64.  For tiles 64 wide, whose FP64 sums would take
-// 128 registers more than there are, to an FP32 sum in LDS, of at most 512 such groups.
-// Relative error of dW1 with one
-// FP32 sum per wave (and of the eight in FP32) and so: 541-128-128-540, 16384 rows 3.3e-7
-// and 1.1e-7, 65536 rows 5.2e-7 and 6.3e-8; 64-16-16-16, 262144 rows 9.8e-7 and 3.2e-8;
-// the time is the same (64 rows 33 us, 16384 649 and 612, 262144 5.07 and 5.09 ms).
-constexpr int kMlpFlush = 16;
+// Rows that a workgroup of a weight gradient, whose K is the batch (up to 2^20), sums in
+// FP32: 256 per wave, 16 rounds of 16 k.  With more (LONG) a wave takes each such group's
+// sum out of the accumulators: to FP64, or for tiles 64 wide, whose FP64 sums would take
+// 128 registers more than there are, to an FP32 sum in LDS, of at most 512 groups.
+// The waves' sums of more than 32 rows are added in FP64.  Relative error of dW1 with one FP32 sum per wave (and
+// of the eight in FP32) and so: 541-128-128-540, 16384 rows 3.3e-7 and 1.1e-7, 65536 rows
+// 5.2e-7 and 6.3e-8; 64-16-16-16, 262144 rows 9.8e-7 and 3.2e-8.  The time: 16384 rows 649
+// and 612 us, 64-16-16-16 5.2 and 5.1 ms; in tiles 64 wide the longer loop holds fewer loads
+// in flight (2049-2048-2048-2048, 4096 rows 3.35 and 3.44 ms).
+constexpr int kMlpGroup = 16 * 16 * kMlpWaves;
 
 // Where lane and wave keep element t of block (a, b) of a tile in LDS: [wave][row][column].
 template <int TB>
@@ -193,7 +196,7 @@ __device__ inline int mlp_slot(int wave, int lane, int a, int b, int t) {
 // This wave's share of tile (ti, tj): rounds of 16 k, wave, wave + 8, ...  Lane
 // l holds k 4 (l / 16) .. + 3 of a round in row l % 16 of each block, one step
 // of the matrix unit taking one k from each group of four.  red: the tile's LDS.
-template <int TB, bool A_MN, bool B_MN>
+template <int TB, bool A_MN, bool B_MN, bool LONG>
 __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int lane, int wave,
                                    floatx4 (&acc)[TB][TB], float *red) {
   constexpr int U = TB == 1 ? 4 : 1;
@@ -232,7 +235,7 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
       for (int u = 0; u < U; ++u) products(va[u], vb[u]);
     }
   };
-  constexpr bool kLong = A_MN && B_MN, kInLds = TB > 2;
+  constexpr bool kLong = LONG && A_MN && B_MN, kInLds = TB > 2;
   double tot[kLong && !kInLds ? TB : 1][TB][4];
   auto each = [&](auto &&f) {
 #pragma unroll
@@ -245,8 +248,7 @@ __device__ inline void mlp_product(const MlpOp &o, int64_t ti, int64_t tj, int l
   auto slot = [&](int a, int b, int t) -> float & { return red[mlp_slot<TB>(wave, lane, a, b, t)]; };
   bool groups = false;  // a group has been taken out of acc
   if constexpr (kLong) {
-    constexpr int kGroup = kMlpFlush * kMlpWaves;
-    for (int end = kGroup; end < full; end += kGroup) {
+    for (int end = kMlpGroup / 16; end < full; end += kMlpGroup / 16) {
       rounds(end);
       each([&](int a, int b, int t) {
         if constexpr (kInLds) slot(a, b, t) = groups ? slot(a, b, t) + acc[a][b][t] : acc[a][b][t];
@@ -290,7 +292,7 @@ __device__ inline double mlp_block_sum(double v, int tid) {
   return s;
 }
 
-template <int TB>
+template <int TB, bool LONG>
 __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int tid) {
   constexpr int E = 16 * TB, NE = E * E;
   const int lane = tid & 63, wave = tid >> 6;
@@ -301,11 +303,11 @@ __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int ti
 #pragma unroll
     for (int b = 0; b < TB; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
   if (o.epi == kEpiInputGrad)
-    mlp_product<TB, false, true>(o, ti, tj, lane, wave, acc, red);
+    mlp_product<TB, false, true, LONG>(o, ti, tj, lane, wave, acc, red);
   else if (o.epi == kEpiWeightGrad)
-    mlp_product<TB, true, true>(o, ti, tj, lane, wave, acc, red);
+    mlp_product<TB, true, true, LONG>(o, ti, tj, lane, wave, acc, red);
   else
-    mlp_product<TB, false, false>(o, ti, tj, lane, wave, acc, red);
+    mlp_product<TB, false, false, LONG>(o, ti, tj, lane, wave, acc, red);
 #pragma unroll
   for (int a = 0; a < TB; ++a)
 #pragma unroll
@@ -319,10 +321,16 @@ __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int ti
     const int64_t i = ti * E + e / E;
     const int j = (int)(tj * E) + e % E;
     if (i >= o.M || j >= o.N) continue;
-    double cd = 0.0;
+    float c = 0.f;
+    if (o.epi == kEpiWeightGrad && o.K > kMlpWaves * 32) {
+      double d = 0.0;
 #pragma unroll
-    for (int v = 0; v < kMlpWaves; ++v) cd += (double)red[v * NE + e];
-    const float c = (float)cd;
+      for (int v = 0; v < kMlpWaves; ++v) d += (double)red[v * NE + e];
+      c = (float)d;
+    } else {
+#pragma unroll
+      for (int v = 0; v < kMlpWaves; ++v) c += red[v * NE + e];
+    }
     const int64_t at = i * o.N + j;
     if (o.epi == kEpiHidden) {
       const float z = c + o.aux[j];
@@ -349,15 +357,16 @@ __device__ inline void mlp_tile(const MlpOp &o, int64_t tile, float *red, int ti
 }
 
 // One launch: the tiles of two products, then 64 columns of a column sum per
-// workgroup (eight groups of rows), then the loss.
-template <int TB>
+// workgroup (eight groups of rows), then the loss.  LONG: batches of more than kMlpGroup
+// rows, and any launch of 2^20 workgroups and more.
+template <int TB, bool LONG>
 __global__ __launch_bounds__(kMlpWaves * 64) void k_mlp(MlpOp o0, MlpOp o1, MlpColsum cs, MlpLoss ls) {
   __shared__ float red[kMlpWaves * 256 * TB * TB];
   const int tid = threadIdx.x;
-  int64_t b = long_block();
-  if (b < o0.tiles) return mlp_tile<TB>(o0, b, red, tid);
+  int64_t b = LONG ? long_block() : blockIdx.x;
+  if (b < o0.tiles) return mlp_tile<TB, LONG>(o0, b, red, tid);
   b -= o0.tiles;
-  if (b < o1.tiles) return mlp_tile<TB>(o1, b, red, tid);
+  if (b < o1.tiles) return mlp_tile<TB, LONG>(o1, b, red, tid);
   b -= o1.tiles;
   if (b < (cs.N + 63) / 64) {
     double *sums = reinterpret_cast<double *>(red);
@@ -383,7 +392,7 @@ __global__ __launch_bounds__(kMlpWaves * 64) void k_mlp(MlpOp o0, MlpOp o1, MlpC
     }
     return;
   }
-  if (b > (cs.N + 63) / 64 || ls.out == nullptr) return;
+  if (LONG && (b > (cs.N + 63) / 64 || ls.out == nullptr)) return;  // past the grid's last
   double s = 0.0;
   for (int64_t i = tid; i < ls.np; i += kMlpWaves * 64) s += ls.lossp[i];
   s = mlp_block_sum(s, tid);
@@ -814,13 +823,17 @@ int64_t launch_mlp(vds_mlp m, MlpOp a, MlpOp b = MlpOp{}, const MlpColsum &cs = 
   const int tb = mlp_edge(a, b);
   a.tiles = mlp_tiles(a.M, a.N, tb);
   b.tiles = mlp_tiles(b.M, b.N, tb);
-  const dim3 grid = long_grid(a.tiles + b.tiles + (cs.N + 63) / 64 + (ls.out ? 1 : 0));
-  if (tb == 4)
-    k_mlp<4><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
-  else if (tb == 2)
-    k_mlp<2><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
-  else
-    k_mlp<1><<<grid, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+  const int64_t n = a.tiles + b.tiles + (cs.N + 63) / 64 + (ls.out ? 1 : 0);
+  const bool lng = (a.epi == kEpiWeightGrad && a.K > kMlpGroup) || (b.epi == kEpiWeightGrad && b.K > kMlpGroup) ||
+                   n >= 1 << 20;
+  auto go = [&](auto edge) {
+    constexpr int TB = decltype(edge)::value;
+    if (lng) k_mlp<TB, true><<<long_grid(n), kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+    else k_mlp<TB, false><<<(unsigned)n, kMlpWaves * 64, 0, m->s>>>(a, b, cs, ls);
+  };
+  if (tb == 4) go(std::integral_constant<int, 4>{});
+  else if (tb == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 1>{});
   return a.tiles;
 }
 
