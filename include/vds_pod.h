@@ -26,7 +26,7 @@ size_t vds_pod_workspace_bytes(int64_t m, int32_t ncols, int32_t R);
  * column-major snapshot matrix X_dev (m rows, leading dimension m): column
  * (l, k) is the bond-k slice q_{k:}(t_l) of snapshot l, so a run of snapshots
  * stored back to back in the state layout [nb][P][3] is X with m = 3P and
- * ncols = snapshots * nb.  products of 24-bit factors (three BF16 parts), fixed-order split-K sums. */
+ * ncols = snapshots * nb.  Products of 24-bit factors (three BF16 parts), fixed-order split-K sums. */
 vds_status vds_pod_gram(vds_ctx ctx, const float *X_dev, int64_t m, int32_t ncols, float *gram_dev,
                         void *ws_dev, size_t ws_bytes);
 
